@@ -400,33 +400,28 @@ ttkv_status check_sel(const ttkv_cache *c, const int32_t *sel_blocks, const int3
   return TTKV_OK;
 }
 
-// Rows were described by `a` (their destination may be a staging view); update the
-// running key sums / mean keys of tier t, whose ring position is taken from its
-// start/len before they are advanced.
-hipError_t run_summary(const ConvArgs &a, const ttkv_cache *c, int t, hipStream_t s, int *nk) {
+// Key sums of tier t, whose ring position is taken from its start/len before they are advanced (the rows described
+// by `a` may go to a staging view).
+void fill_summary(ConvArgs &a, const ttkv_cache *c, int t) {
   const ttkv_tier &T = c->tier[t];
-  if (!T.k_sum) return hipSuccess;
-  ConvArgs u = a;
-  u.dst = make_view(T, make_layout(T, c->n_kv_heads));
-  u.k_sum = T.k_sum;
-  u.k_summary = (uint16_t *)T.k_summary;
-  u.sum_table = T.block_table_dev;
-  u.sum_ring_blocks = (int32_t)T.ring_blocks;
-  u.inv_bt = 1.0f / (float)T.block_tokens;
+  a.k_sum = T.k_sum;
+  a.k_summary = (uint16_t *)T.k_summary;
+  a.sum_table = T.block_table_dev;
+  a.sum_ring_blocks = (int32_t)T.ring_blocks;
+  a.inv_bt = 1.0f / (float)T.block_tokens;
   for (int j = 0; j < a.n_seq; ++j) {
     const int b = a.seq_id[j];
-    u.dst_first_tok[j] = (int32_t)((T.start[b] + T.len[b]) % ring_tokens(T));
-    u.sum_rec_base[j] = (int32_t)((int64_t)b * T.ring_blocks);
+    a.sum_first_block[j] = (int32_t)((T.start[b] + T.len[b]) % ring_tokens(T) / T.block_tokens);
   }
-  return launch_summary(u, s, nk);
 }
 
 void fill_via(ConvArgs &a, const ttkv_cache *c, int tier, bool through) {
   a.n_via = 0;
+  a.via_k = a.via_v = 0;
   if (!through) return;
   for (int u = 1; u < tier; ++u) {
-    a.via_k[a.n_via] = c->tier[u].k_fmt;
-    a.via_v[a.n_via] = c->tier[u].v_fmt;
+    a.via_k |= (uint32_t)c->tier[u].k_fmt << (8 * a.n_via);
+    a.via_v |= (uint32_t)c->tier[u].v_fmt << (8 * a.n_via);
     ++a.n_via;
   }
 }
@@ -511,8 +506,8 @@ ttkv_status append_impl(Handle *h, ttkv_cache *c, int32_t tier, int32_t seq, con
     }
   }
   int nk = 0;
+  fill_summary(a, c, tier);
   TTKV_HIP(h, launch_convert(a, stream, &nk));
-  TTKV_HIP(h, run_summary(a, c, tier, stream, &nk));
   h->stats.kernels += nk;
   if (direct) h->stats.d2h_bytes += (uint64_t)a.n_seq * (uint64_t)n_tokens * (L.kc + L.km + L.vc + L.vm) * c->n_kv_heads;
   if (host_variant && !direct) {
@@ -760,8 +755,8 @@ ttkv_status ttkv_tier_demote(ttkv_handle hh, ttkv_cache *c, int32_t src_tier, in
       }
     }
     int nk = 0;
+    fill_summary(a, c, src_tier + 1);
     TTKV_HIP(h, launch_convert(a, compute, &nk));
-    TTKV_HIP(h, run_summary(a, c, src_tier + 1, compute, &nk));
     h->stats.kernels += nk;
 
     if (to_host) {

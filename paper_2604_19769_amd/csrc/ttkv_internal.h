@@ -178,19 +178,18 @@ struct ConvArgs {
   int32_t seq_id[TTKV_MAX_BATCH];
   int32_t dst_first_tok[TTKV_MAX_BATCH];   // ring token index where the first row lands
   int32_t dst_rec_base[TTKV_MAX_BATCH];
-  int32_t which0;                          // first of {0: K, 1: V} the row kernel converts (1: V only)
   int32_t n_via;                           // intermediate formats a value passes through first
-  int32_t via_k[TTKV_MAX_TIERS], via_v[TTKV_MAX_TIERS];
+  uint32_t via_k, via_v;                   // 8 bits each, the first in the low ones
   // summaries of the destination tier (nullable)
   float *k_sum;
   uint16_t *k_summary;
+  // (their ring is the tier's own, also where the rows themselves go to staging records)
   const int32_t *sum_table;                // device block table of the destination pool for the summaries
-  int32_t sum_rec_base[TTKV_MAX_BATCH];
+  int32_t sum_first_block[TTKV_MAX_BATCH]; // ring block of the first row
   int32_t sum_ring_blocks;
   float inv_bt;
 };
 hipError_t launch_convert(const ConvArgs &a, hipStream_t s, int *n_kernels);
-hipError_t launch_summary(const ConvArgs &a, hipStream_t s, int *n_kernels);
 
 // One launch of the fused attention kernel: up to TTKV_MAX_ENTRIES runs of tokens,
 // each belonging to one (tier, sequence), all passed by value (no per-step upload).

@@ -1,412 +1,708 @@
-// Row conversion kernels: append (Sec. 4.1), Q_8bit / Q_4bit (Sec. 4.2) and the
-// eviction path's decompress -> re-quantize.  Compiled with -ffp-contract=off:
-// every fp32 step below is one IEEE operation (divide and fp16 conversion
-// round to nearest even), so codes, scales and zeros are reproducible bit for bit.
+// Row conversion kernels: append (Sec. 4.1), Q_8bit / Q_4bit (Sec. 4.2), the eviction path's decompress ->
+// re-quantize, and the running key sums behind block identification.  Compiled with -ffp-contract=off: every fp32
+// step of the recipes is one IEEE operation (round to nearest even), so codes, scales and zeros are reproducible
+// bit for bit.
+//
+// Work unit of the row kernel: up to 64 consecutive rows of ONE destination block, one KV head, K or V.  A 16-lane
+// group converts one row at a time (8 channels per lane).  Block and record look-ups, and the division by the block
+// size, happen once per unit on the scalar unit; source and destination formats are compile-time inside the unit;
+// all of a unit's loads are in flight before the first conversion.  Where keys also feed block summaries a unit is a
+// whole destination block (see sum_unit).  Bound: memory for the plain copies (5.3 TB/s of read + write), fp16 -> int8
+// (5.2) and fp16 -> int4 (4.8; a copy of 2 GiB reaches 4.9), vector instructions where a second recipe comes first
+// (int4 through int8 with key sums, 2.7).  The one generic body before -- a 64-bit address and a division by the block
+// size per row, a near-tie branch per element, exchanges through LDS -- reached 3.0 for int4: tiering 2 x 32 heads x
+// 8192 tokens into fp16 + int4 105.6 -> 77.4 us; 8 heads x 32768 tokens into fp16 + K int8 / V int4 channel-major, one
+// launch instead of two, 60 -> 43.5 us.
 #include "ttkv_internal.h"
 
 #include <hip/hip_fp16.h>
+
+#include <algorithm>
 
 namespace ttkv {
 
 namespace {
 
+constexpr int CHUNK = 64;             // rows of a unit; block sizes are multiples of it
+constexpr int SUM_THREADS = 512;      // workgroup of the launches that also keep key sums,
+constexpr int SUM_ROWS = 32;          // and the rows it converts between two barriers
+constexpr int NO_STORE = -1;          // destination "format" of a unit that only feeds the key sums
+
 __device__ __forceinline__ float h2f(uint16_t h) { return __half2float(__ushort_as_half(h)); }
 __device__ __forceinline__ uint16_t f2h(float f) { return __half_as_ushort(__float2half_rn(f)); }
-__device__ __forceinline__ float bf2f(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
 
-// Record index and row of ring token `tok` of sequence `seq`.
-__device__ __forceinline__ uint8_t *head_ptr(const TierView &v, int seq, int rec_base, int tok, int h, int *row) {
-  int r = tok / v.bt;
-  *row = tok - r * v.bt;
-  int64_t rec = v.table ? (int64_t)v.table[(int64_t)seq * v.ring_blocks + r] : (int64_t)rec_base + r;
-  return v.base + rec * v.rec_bytes + (int64_t)h * v.head_bytes;
+// ---------------------------------------------------------------- the recipes, eight channels per lane
+// The codes of Sec. 4.2 are rint(RN(y / s)), one IEEE division per element.  The divisor is an fp16 number common to
+// the group, so its correctly rounded reciprocal r is formed once, and q = y r, q + (y - q s) r (two fused steps) IS
+// the correctly rounded quotient: checked against the division for every fp16 mantissa of s and every fp32 mantissa
+// of y.  Three operations per element where a division takes ten; a rounded product with an exact fallback near
+// half-integers, used here before, cost as much and sent a tenth of the rows through the divisions (keys and scales
+// are both fp16, so exact ties are common).  Adding 1.5 x 2^23 rounds to nearest even and leaves the integer in the
+// low mantissa bits, from where the codes are packed without conversions.
+constexpr float kMagic = 12582912.0f;
+__device__ __forceinline__ float clamped(float t, float lo, float hi) {
+  return __builtin_amdgcn_fmed3f(t, lo, hi);   // NaN: the lower bound, as fmin(fmax(NaN, lo), hi)
 }
 
-__device__ __forceinline__ int wrap(int tok, const TierView &v) {
-  int ring = v.ring_blocks * v.bt;
-  return tok >= ring ? tok - ring : tok;
+// d / D rounded to nearest even, in three operations for a constant D: the product with the rounded reciprocal is
+// within 1 ulp and one residual step corrects it (checked against the division for every fp32 mantissa); the fixup
+// restores infinities and NaN.
+template <int D>
+__device__ __forceinline__ float div_const(float d) {
+  constexpr float c = 1.0f / (float)D;
+  const float y = d * c;
+  const float e = __builtin_fmaf(-(float)D, y, d);
+  return __builtin_amdgcn_div_fixupf(__builtin_fmaf(e, c, y), (float)D, d);
 }
 
-// rint(x / s) as the IEEE division followed by round-to-nearest-even gives it (the recipe of Sec. 4.2's quantizers,
-// one IEEE operation per step), wherever the caller's clamp to [-127, 127] or [0, 15] lets the difference show, for
-// a group's many x against one s: r = 1 / s is divided once; x * r is within 2^-22 |x / s| of the true quotient,
-// i.e. within 5e-5 for |x / s| < 200, so the two rounded integers agree unless the quotient lies within that
-// distance of a half-integer -- ties included -- and there the exact division decides (about one element in a
-// thousand takes it).  Beyond 200 either rounding is clamped to the same bound.
-__device__ __forceinline__ float quot_rint(float x, float s, float r) {
-  const float t = x * r;
-  float q = rintf(t);
-  if (fabsf(t - q) > 0.4995f) q = rintf(x / s);
-  return q;
-}
-
-// ---- in-register quantize / decompress over a group spread across `LANES`
-// consecutive lanes holding N values each.
-
-// Q1 on a 32-element group: returns the fp16 scale bits, codes as ints.
-template <int N, int LANES>
-__device__ __forceinline__ uint16_t q1_group(const float (&x)[N], int (&c)[N]) {
-  float amax = 0.0f;
-#pragma unroll
-  for (int i = 0; i < N; ++i) amax = fmaxf(amax, fabsf(x[i]));
-#pragma unroll
-  for (int m = 1; m < LANES; m <<= 1) amax = fmaxf(amax, __shfl_xor(amax, m));
-  float s32 = amax / 127.0f;
-  uint16_t sh = f2h(s32);
-  float s = h2f(sh);
-  const float r = s != 0.0f ? 1.0f / s : 0.0f;
-#pragma unroll
-  for (int i = 0; i < N; ++i) {
-    float q = 0.0f;
-    if (s != 0.0f) q = fminf(fmaxf(quot_rint(x[i], s, r), -127.0f), 127.0f);
-    c[i] = (int)q;
+// A group's scale as divisor: r = 1 / s rounded to nearest even (the approximate reciprocal is within 1 ulp; one
+// step corrects it, checked for every fp16 mantissa and 1 ulp either way).  A scale of zero or infinity divides
+// everything to zero.
+struct Divisor {
+  float s, r;
+  __device__ __forceinline__ explicit Divisor(float scale) {
+    const float r0 = __builtin_amdgcn_rcpf(scale);
+    const bool none = scale == 0.0f || r0 == 0.0f;
+    s = none ? 0.0f : scale;
+    r = none ? 0.0f : __builtin_fmaf(__builtin_fmaf(-scale, r0, 1.0f), r0, r0);
   }
+  // 1.5 x 2^23 + rint(y / s) clamped to [lo, hi]
+  __device__ __forceinline__ float code(float y, float lo, float hi) const {
+    const float q = y * r;
+    return clamped(__builtin_fmaf(__builtin_fmaf(-q, s, y), r, q), lo, hi) + kMagic;
+  }
+};
+
+template <int CTRL>
+__device__ __forceinline__ uint32_t lanes_max(uint32_t v) {
+  return max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xf, 0xf, true));
+}
+
+// Q1: n[i] = 1.5 x 2^23 + code as a float; the group is 4 lanes.  Returns the fp16 scale bits.
+__device__ __forceinline__ uint16_t q1_codes(const float (&x)[8], float (&n)[8], float *s_out) {
+  float amax = 0.0f;   // a group's NaNs do not count
+#pragma unroll
+  for (int i = 0; i < 8; ++i) amax = fmaxf(amax, fabsf(x[i]));
+  uint32_t bits = __float_as_uint(amax);   // non-negative: ordered like the integers
+  bits = lanes_max<0xB1>(bits);            // quad_perm [1,0,3,2]
+  bits = lanes_max<0x4E>(bits);            // quad_perm [2,3,0,1]
+  const uint16_t sh = f2h(div_const<127>(__uint_as_float(bits)));
+  const float s = h2f(sh);
+  const Divisor d(s);
+#pragma unroll
+  for (int i = 0; i < 8; ++i) n[i] = d.code(x[i], -127.0f, 127.0f);
+  *s_out = s;
   return sh;
 }
 
-// Q2 on a 64-element group: fp16 scale and zero bits, codes 0..15.
-template <int N, int LANES>
-__device__ __forceinline__ void q2_group(const float (&x)[N], int (&c)[N], uint16_t *sh_out, uint16_t *zh_out) {
+__device__ __forceinline__ void q2_range(const float (&x)[8], float *lo_out, float *hi_out) {
   float lo = x[0], hi = x[0];
 #pragma unroll
-  for (int i = 1; i < N; ++i) {
+  for (int i = 1; i < 8; ++i) {
     lo = fminf(lo, x[i]);
     hi = fmaxf(hi, x[i]);
   }
-#pragma unroll
-  for (int m = 1; m < LANES; m <<= 1) {
-    lo = fminf(lo, __shfl_xor(lo, m));
-    hi = fmaxf(hi, __shfl_xor(hi, m));
-  }
+  // over the group's eight lanes; as one block because the compiler would quiet every exchanged value first (18
+  // instructions instead of 6).  A lane exchange reads a register two issue slots after it is written at the earliest.
+  asm("s_nop 1\n\t"
+      "v_min_f32_dpp %0, %0, %0 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+      "v_max_f32_dpp %1, %1, %1 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+      "s_nop 0\n\t"
+      "v_min_f32_dpp %0, %0, %0 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+      "v_max_f32_dpp %1, %1, %1 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+      "s_nop 0\n\t"
+      "v_min_f32_dpp %0, %0, %0 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+      "v_max_f32_dpp %1, %1, %1 row_half_mirror row_mask:0xf bank_mask:0xf"
+      : "+v"(lo), "+v"(hi));
   if (lo == 0.0f) lo = 0.0f;  // a zero minimum is stored as +0 whatever its sign
-  float s32 = (hi - lo) / 15.0f;
-  uint16_t sh = f2h(s32), zh = f2h(lo);
-  float s = h2f(sh), z = h2f(zh);
-  const float r = s != 0.0f ? 1.0f / s : 0.0f;
+  *lo_out = lo;
+  *hi_out = hi;
+}
+// Q2: the same for 4-bit codes; the group is 8 lanes.
+struct Q2Scale {
+  uint32_t word;   // fp16 {scale, zero} as stored
+  float s, z;
+};
+__device__ __forceinline__ Q2Scale q2_codes(const float (&x)[8], float (&n)[8]) {
+  float lo, hi;
+  q2_range(x, &lo, &hi);
+  const uint16_t sh = f2h(div_const<15>(hi - lo)), zh = f2h(lo);
+  const float s = h2f(sh), z = h2f(zh);
+  const Divisor d(s);
 #pragma unroll
-  for (int i = 0; i < N; ++i) {
-    float q = 0.0f;
-    if (s != 0.0f) q = fminf(fmaxf(quot_rint(x[i] - z, s, r), 0.0f), 15.0f);
-    c[i] = (int)q;
-  }
-  *sh_out = sh;
-  *zh_out = zh;
+  for (int i = 0; i < 8; ++i) n[i] = d.code(x[i] - z, 0.0f, 15.0f);
+  return Q2Scale{(uint32_t)sh | ((uint32_t)zh << 16), s, z};
 }
 
-// The values a format decompresses to (a token that passed through a tier).
-template <int N, int L8, int L4>
-__device__ __forceinline__ void roundtrip(int fmt, float (&x)[N]) {
-  int c[N];
-  if (fmt == TTKV_I8_SYM_G32) {
-    uint16_t sh = q1_group<N, L8>(x, c);
-    float s = h2f(sh);
+__device__ __forceinline__ uint32_t pack_bytes(const float *n) {   // low bytes of four codes
+  const uint32_t a = __builtin_amdgcn_perm(__float_as_uint(n[1]), __float_as_uint(n[0]), 0x0c0c0400u);
+  const uint32_t b = __builtin_amdgcn_perm(__float_as_uint(n[3]), __float_as_uint(n[2]), 0x04000c0cu);
+  return a | b;
+}
+__device__ __forceinline__ uint32_t pack_nibbles(const float (&n)[8]) {
+  // every n is 0x4B400000 + code: a chain of shift-adds, less what the constants add up to modulo 2^32
+  uint32_t w = __float_as_uint(n[7]);
 #pragma unroll
-    for (int i = 0; i < N; ++i) x[i] = (float)c[i] * s;
-  } else if (fmt == TTKV_I4_ASYM_G64) {
-    uint16_t sh, zh;
-    q2_group<N, L4>(x, c, &sh, &zh);
-    float s = h2f(sh), z = h2f(zh);
+  for (int i = 6; i >= 0; --i) w = (w << 4) + __float_as_uint(n[i]);
+  uint32_t c = 0x4B400000u;
 #pragma unroll
-    for (int i = 0; i < N; ++i) {
-      float p = (float)c[i] * s;
-      x[i] = p + z;
-    }
-  }
+  for (int i = 6; i >= 0; --i) c = (c << 4) + 0x4B400000u;
+  return w - c;
 }
 
-// ---- loading 8 consecutive elements [8*l16, 8*l16+8) of one row as fp32.
-__device__ __forceinline__ void load8_flat(const void *flat, int fmt, int64_t row, int l16, float (&x)[8]) {
-  if (fmt == TTKV_F32) {
-    const float4 *p = (const float4 *)((const float *)flat + row * 128 + l16 * 8);
-    float4 a = p[0], b = p[1];
-    x[0] = a.x; x[1] = a.y; x[2] = a.z; x[3] = a.w;
-    x[4] = b.x; x[5] = b.y; x[6] = b.z; x[7] = b.w;
+// The values a format decompresses to (a token that passed through a tier).  code x scale is exact in fp32 (at most
+// 7 + 11 bits), so the offset of the codes leaves in the same fused step.
+__device__ __forceinline__ void roundtrip_q1(float (&x)[8]) {
+  float n[8], s;
+  q1_codes(x, n, &s);
+  const float off = -kMagic * s;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) x[i] = __builtin_fmaf(n[i], s, off);
+}
+__device__ __forceinline__ void roundtrip_q2(float (&x)[8]) {
+  float n[8];
+  const Q2Scale q = q2_codes(x, n);
+#pragma unroll
+  for (int i = 0; i < 8; ++i) x[i] = __builtin_fmaf(n[i] - kMagic, q.s, q.z);
+}
+
+// ---------------------------------------------------------------- sources
+// What a lane loads of one row: its eight channels in the source's format, with the group's scale words.
+struct Raw {
+  uint4 a, b;
+};
+// Rows are read once and written once: both with the streaming hint.  Tiering 2 x 32 heads x 8192 tokens into fp16 +
+// int4, the stores' part of it: 83.5 -> 77.2 us; scales and zeros, a few bytes per row, go through the caches.
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint4 ld16(const uint8_t *p) {
+  const u32x4 v = __builtin_nontemporal_load((const u32x4 *)p);
+  return uint4{v.x, v.y, v.z, v.w};
+}
+__device__ __forceinline__ void st_stream(uint8_t *p, const uint4 &v) {
+  __builtin_nontemporal_store(u32x4{v.x, v.y, v.z, v.w}, (u32x4 *)p);
+}
+__device__ __forceinline__ void st_stream(uint8_t *p, const uint2 &v) { __builtin_nontemporal_store(u32x2{v.x, v.y}, (u32x2 *)p); }
+__device__ __forceinline__ void st_stream(uint8_t *p, uint32_t v) { __builtin_nontemporal_store(v, (uint32_t *)p); }
+template <int F>
+__device__ __forceinline__ void load_row(Raw &w, const uint8_t *code, const uint8_t *meta, int l16) {
+  if constexpr (F == TTKV_F32) {
+    w.a = ld16(code + l16 * 32);
+    w.b = ld16(code + l16 * 32 + 16);
+  } else if constexpr (F == TTKV_F16 || F == TTKV_BF16) {
+    w.a = ld16(code + l16 * 16);
+  } else if constexpr (F == TTKV_I8_SYM_G32) {
+    const uint2 c = *(const uint2 *)(code + l16 * 8);
+    w.a.x = c.x;
+    w.a.y = c.y;
+    w.a.z = *(const uint16_t *)(meta + (l16 >> 2) * 2);
   } else {
-    uint4 w = *(const uint4 *)((const uint16_t *)flat + row * 128 + l16 * 8);
-    uint32_t u[4] = {w.x, w.y, w.z, w.w};
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      uint16_t a = (uint16_t)(u[i] & 0xffff), b = (uint16_t)(u[i] >> 16);
-      x[2 * i] = fmt == TTKV_F16 ? h2f(a) : bf2f(a);
-      x[2 * i + 1] = fmt == TTKV_F16 ? h2f(b) : bf2f(b);
-    }
+    w.a.x = *(const uint32_t *)(code + l16 * 4);
+    w.a.y = *(const uint32_t *)(meta + (l16 >> 3) * 4);
   }
 }
-
-__device__ __forceinline__ void load8_tier(const uint8_t *head, int fmt, int code_off, int meta_off, int row, int l16,
-                                           float (&x)[8]) {
-  if (fmt == TTKV_F16 || fmt == TTKV_BF16) {
-    uint4 w = *(const uint4 *)(head + code_off + row * 256 + l16 * 16);
-    uint32_t u[4] = {w.x, w.y, w.z, w.w};
+template <int F>
+__device__ __forceinline__ void expand(const Raw &w, float (&x)[8]) {
+  if constexpr (F == TTKV_F32) {
+    const uint32_t u[8] = {w.a.x, w.a.y, w.a.z, w.a.w, w.b.x, w.b.y, w.b.z, w.b.w};
+#pragma unroll
+    for (int i = 0; i < 8; ++i) x[i] = __uint_as_float(u[i]);
+  } else if constexpr (F == TTKV_F16 || F == TTKV_BF16) {
+    const uint32_t u[4] = {w.a.x, w.a.y, w.a.z, w.a.w};
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      uint16_t a = (uint16_t)(u[i] & 0xffff), b = (uint16_t)(u[i] >> 16);
-      x[2 * i] = fmt == TTKV_F16 ? h2f(a) : bf2f(a);
-      x[2 * i + 1] = fmt == TTKV_F16 ? h2f(b) : bf2f(b);
+      x[2 * i] = F == TTKV_F16 ? h2f((uint16_t)(u[i] & 0xffff)) : __uint_as_float(u[i] << 16);
+      x[2 * i + 1] = F == TTKV_F16 ? h2f((uint16_t)(u[i] >> 16)) : __uint_as_float(u[i] & 0xffff0000u);
     }
-  } else if (fmt == TTKV_I8_SYM_G32) {
-    uint2 w = *(const uint2 *)(head + code_off + row * 128 + l16 * 8);
-    float s = h2f(*(const uint16_t *)(head + meta_off + row * 8 + (l16 >> 2) * 2));
-    uint32_t u[2] = {w.x, w.y};
+  } else if constexpr (F == TTKV_I8_SYM_G32) {
+    const uint32_t u[2] = {w.a.x, w.a.y};
+    const float s = h2f((uint16_t)w.a.z);
 #pragma unroll
     for (int i = 0; i < 8; ++i) x[i] = (float)(int)(int8_t)((u[i >> 2] >> (8 * (i & 3))) & 0xff) * s;
   } else {
-    uint32_t w = *(const uint32_t *)(head + code_off + row * 64 + l16 * 4);
-    uint32_t sz = *(const uint32_t *)(head + meta_off + row * 8 + (l16 >> 3) * 4);
-    float s = h2f((uint16_t)(sz & 0xffff)), z = h2f((uint16_t)(sz >> 16));
+    const float s = h2f((uint16_t)(w.a.y & 0xffff)), z = h2f((uint16_t)(w.a.y >> 16));
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-      float p = (float)(int)((w >> (4 * i)) & 0xf) * s;
+      const float p = (float)(int)((w.a.x >> (4 * i)) & 0xf) * s;
       x[i] = p + z;
     }
   }
 }
+// Bytes of one row's codes in a source format.
+template <int F>
+constexpr int row_bytes() {
+  return F == TTKV_F32 ? 512 : F == TTKV_I8_SYM_G32 ? 128 : F == TTKV_I4_ASYM_G64 ? 64 : 256;
+}
 
-__device__ __forceinline__ void store8_tier(uint8_t *head, int fmt, int code_off, int meta_off, int row, int l16,
-                                            float (&x)[8], bool live) {
-  if (fmt == TTKV_F16 || fmt == TTKV_BF16) {
-    uint32_t u[4];
+__device__ __forceinline__ int wrap(int tok, const TierView &v) {
+  const int ring = v.ring_blocks * v.bt;
+  return tok >= ring ? tok - ring : tok;
+}
+// One KV head of ring block r of sequence seq.
+__device__ __forceinline__ uint8_t *block_head(const TierView &v, int seq, int rec_base, int r, int h) {
+  const int64_t rec = v.table ? (int64_t)v.table[(int64_t)seq * v.ring_blocks + r] : (int64_t)rec_base + r;
+  return v.base + rec * v.rec_bytes + (int64_t)h * v.head_bytes;
+}
+
+// Rows t_first .. of one (entry, KV head, K / V) of the source: a flat array, or rows of a source tier that lie in
+// at most two of its blocks (a unit has at most 64 rows, a block at least 64).
+struct RowSource {
+  const uint8_t *code, *meta;         // first row of the unit
+  const uint8_t *code1, *meta1;       // first row of the block after
+  int split;                          // rows of the unit in the first block
+};
+// The source of one (entry, KV head, K / V), gathered from the launch arguments once per workgroup: everything below
+// works on these scalars (a reference to the arguments, indexed from many places, would put them into scratch).
+struct Source {
+  const uint8_t *flat;                // row 0, or null: the rows of `tier` from ring token `tok`
+  TierView tier;
+  int tok, rec_base, code_off, meta_off, seq, h;
+  int n_via;
+  uint32_t via;                       // formats passed through first, 8 bits each
+};
+__device__ __forceinline__ Source make_source(const ConvArgs &a, int which, int j, int h, int seq) {
+  Source s;
+  s.flat = nullptr;
+  s.tier = a.s.src;
+  if (!a.s.from_tier) {
+    const int64_t rows = ((int64_t)j * a.Hkv + h) * a.n_tokens;
+    const int bytes = a.s.flat_fmt == TTKV_F32 ? 512 : 256;
+    const uint8_t *k = (const uint8_t *)a.s.k_flat, *v = (const uint8_t *)a.s.v_flat;
+    s.flat = (which ? v : k) + rows * bytes;
+  }
+  s.tok = a.s.src_first_tok[j];
+  s.rec_base = a.s.src_rec_base[j];
+  s.code_off = which ? s.tier.v_off : 0;
+  s.meta_off = which ? s.tier.v_meta_off : s.tier.k_meta_off;
+  s.seq = seq;
+  s.h = h;
+  s.n_via = a.n_via;
+  const uint32_t via_k = a.via_k, via_v = a.via_v;
+  s.via = which ? via_v : via_k;
+  return s;
+}
+template <int F>
+__device__ __forceinline__ RowSource row_source(const Source &c, int t_first) {
+  RowSource s;
+  if (c.flat) {
+    s.code = s.code1 = c.flat + (int64_t)t_first * row_bytes<F>();
+    s.meta = s.meta1 = nullptr;
+    s.split = 1 << 30;
+    return s;
+  }
+  const int tok = wrap(c.tok + t_first, c.tier);
+  const int r = tok / c.tier.bt, row = tok - r * c.tier.bt;
+  const uint8_t *h0 = block_head(c.tier, c.seq, c.rec_base, r, c.h);
+  s.code = s.code1 = h0 + c.code_off + row * row_bytes<F>();
+  s.meta = s.meta1 = h0 + c.meta_off + row * 8;
+  s.split = c.tier.bt - row;
+  if (s.split < CHUNK) {
+    const uint8_t *h1 = block_head(c.tier, c.seq, c.rec_base, r + 1 == c.tier.ring_blocks ? 0 : r + 1, c.h);
+    s.code1 = h1 + c.code_off;
+    s.meta1 = h1 + c.meta_off;
+  }
+  return s;
+}
+template <int F>
+__device__ __forceinline__ void load_from(const RowSource &s, int i, int l16, Raw &w) {   // row i of the unit
+  const bool next = i >= s.split;
+  const int o = next ? i - s.split : i;
+  load_row<F>(w, (next ? s.code1 : s.code) + o * row_bytes<F>(), (next ? s.meta1 : s.meta) + o * 8, l16);
+}
+// The formats a token has passed through before this one (Sec. 4.2's recipes, applied and taken back): at most two,
+// the fp formats change nothing.  Written out because a loop over them would copy the eight values in every turn.
+__device__ __forceinline__ void pass_through(const Source &c, float (&x)[8]) {
+  static_assert(TTKV_MAX_TIERS == 4, "tiers 1 and 2 lie above the last one");
+  if (c.n_via > 0) {
+    const uint32_t f = c.via & 0xff;
+    if (f == TTKV_I8_SYM_G32) roundtrip_q1(x);
+    if (f == TTKV_I4_ASYM_G64) roundtrip_q2(x);
+  }
+  if (c.n_via > 1) {
+    const uint32_t f = c.via >> 8;
+    if (f == TTKV_I8_SYM_G32) roundtrip_q1(x);
+    if (f == TTKV_I4_ASYM_G64) roundtrip_q2(x);
+  }
+}
+
+// ---------------------------------------------------------------- one unit
+// Where a unit's rows land: `head` is the KV head's part of the destination block, `row0` the block row of the
+// unit's row 0; rows [lo, hi) of the unit are live and row lo is token t_lo of the call.
+struct Unit {
+  uint8_t *head;
+  int code_off, meta_off, row0;
+  int lo, hi, t_lo;
+};
+
+template <int SRC, int THREADS, int ROWS>
+__device__ __forceinline__ void load_unit(const Source &c, const Unit &u, Raw (&raw)[ROWS * 16 / THREADS]) {
+  const RowSource s = row_source<SRC>(c, u.t_lo);
+  const int l16 = threadIdx.x & 15, r = threadIdx.x >> 4;
+  if (u.lo == 0 && u.hi == ROWS && s.split >= ROWS) {   // every row live and in one block: one base, constant offsets
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      uint32_t a, b;
-      if (fmt == TTKV_F16) {
-        a = f2h(x[2 * i]);
-        b = f2h(x[2 * i + 1]);
-      } else {  // source values are bf16 already: the upper half is exact
-        a = __float_as_uint(x[2 * i]) >> 16;
-        b = __float_as_uint(x[2 * i + 1]) >> 16;
+    for (int p = 0; p < ROWS * 16 / THREADS; ++p) {
+      const uint32_t i = p * (THREADS / 16) + r;
+      load_row<SRC>(raw[p], s.code + i * row_bytes<SRC>(), s.meta + i * 8, l16);
+    }
+  } else {
+#pragma unroll
+    for (int p = 0; p < ROWS * 16 / THREADS; ++p)
+      load_from<SRC>(s, min(max(p * (THREADS / 16) + r, u.lo), u.hi - 1) - u.lo, l16, raw[p]);   // dead rows repeat a live one
+  }
+}
+
+// Row i of the unit from its values x: quantized to DST, stored if live.  Channel-major values leave their codes in
+// s_t32 instead.
+constexpr int kT32Stride = 20;   // words per row of codes: rows 4 apart fall 16 banks apart
+constexpr int kT32Bytes = CHUNK * kT32Stride * 4 + 2 * 2048;
+template <int DST>
+__device__ __forceinline__ void put_row(const Unit &u, int i, int l16, const float (&x)[8], uint32_t *s_t32) {
+  uint8_t *const code = u.head + u.code_off, *const meta = u.head + u.meta_off;
+  const bool live = i >= u.lo && i < u.hi;
+  const uint32_t row = u.row0 + i;
+  float n[8];
+  if constexpr (DST == TTKV_F16 || DST == TTKV_BF16) {
+    uint32_t w[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      uint32_t lo16, hi16;
+      if constexpr (DST == TTKV_F16) {
+        lo16 = f2h(x[2 * k]);
+        hi16 = f2h(x[2 * k + 1]);
+      } else {  // the upper halves (exact for values that come from bf16)
+        lo16 = __float_as_uint(x[2 * k]) >> 16;
+        hi16 = __float_as_uint(x[2 * k + 1]) >> 16;
       }
-      u[i] = a | (b << 16);
+      w[k] = lo16 | (hi16 << 16);
     }
-    if (live) *(uint4 *)(head + code_off + row * 256 + l16 * 16) = make_uint4(u[0], u[1], u[2], u[3]);
-  } else if (fmt == TTKV_I8_SYM_G32) {
-    int c[8];
-    uint16_t sh = q1_group<8, 4>(x, c);
-    uint32_t u[2] = {0, 0};
-#pragma unroll
-    for (int i = 0; i < 8; ++i) u[i >> 2] |= ((uint32_t)c[i] & 0xffu) << (8 * (i & 3));
+    if (live) st_stream(code + row * 256 + l16 * 16, uint4{w[0], w[1], w[2], w[3]});
+  } else if constexpr (DST == TTKV_I8_SYM_G32) {
+    float s;
+    const uint16_t sh = q1_codes(x, n, &s);
+    const bool zero = s == 0.0f;
+    const uint2 w = {zero ? 0u : pack_bytes(n), zero ? 0u : pack_bytes(n + 4)};
     if (live) {
-      *(uint2 *)(head + code_off + row * 128 + l16 * 8) = make_uint2(u[0], u[1]);
-      if ((l16 & 3) == 0) *(uint16_t *)(head + meta_off + row * 8 + (l16 >> 2) * 2) = sh;
+      st_stream(code + row * 128 + l16 * 8, w);
+      if ((l16 & 3) == 0) *(uint16_t *)(meta + row * 8 + (l16 >> 2) * 2) = sh;
     }
-  } else {
-    int c[8];
-    uint16_t sh, zh;
-    q2_group<8, 8>(x, c, &sh, &zh);
-    uint32_t w = 0;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) w |= ((uint32_t)c[i] & 0xfu) << (4 * i);
-    if (live) {
-      *(uint32_t *)(head + code_off + row * 64 + l16 * 4) = w;
-      if ((l16 & 7) == 0) *(uint32_t *)(head + meta_off + row * 8 + (l16 >> 3) * 4) = (uint32_t)sh | ((uint32_t)zh << 16);
-    }
-  }
-}
-
-// One 16-lane group converts one row (one token of one KV head); blockIdx.y
-// picks K (0) or V (1), blockIdx.z the (entry, KV head).
-__global__ __launch_bounds__(256) void convert_rows_kernel(const ConvArgs a) {
-  // grid: (16 tokens per workgroup, K / V, entry x KV head) -- no per-thread division of a 64-bit row number
-  const int which = blockIdx.y + a.which0;
-  const int l16 = threadIdx.x & 15;
-  int t = blockIdx.x * 16 + (threadIdx.x >> 4);
-  const bool live = t < a.n_tokens;
-  if (!live) t = a.n_tokens - 1;
-  const int j = blockIdx.z / a.Hkv, h = blockIdx.z - j * a.Hkv;
-  const int seq = a.seq_id[j];
-
-  float x[8];
-  if (!a.s.from_tier) {
-    load8_flat(which ? a.s.v_flat : a.s.k_flat, a.s.flat_fmt, ((int64_t)j * a.Hkv + h) * a.n_tokens + t, l16, x);
-  } else {
-    int row;
-    const uint8_t *head = head_ptr(a.s.src, seq, a.s.src_rec_base[j], wrap(a.s.src_first_tok[j] + t, a.s.src), h, &row);
-    if (which)
-      load8_tier(head, a.s.src.v_fmt, a.s.src.v_off, a.s.src.v_meta_off, row, l16, x);
-    else
-      load8_tier(head, a.s.src.k_fmt, 0, a.s.src.k_meta_off, row, l16, x);
-  }
-  for (int u = 0; u < a.n_via; ++u) roundtrip<8, 4, 8>(which ? a.via_v[u] : a.via_k[u], x);
-
-  int row;
-  uint8_t *head = head_ptr(a.dst, seq, a.dst_rec_base[j], wrap(a.dst_first_tok[j] + t, a.dst), h, &row);
-  if (which)
-    store8_tier(head, a.dst.v_fmt, a.dst.v_off, a.dst.v_meta_off, row, l16, x, live);
-  else
-    store8_tier(head, a.dst.k_fmt, 0, a.dst.k_meta_off, row, l16, x, live);
-}
-
-// Key value of token t (of this call) of entry j, KV head h, channel i, as it arrives at the destination tier:
-// read from the flat source or from the source tier, then through the formats of the tiers in between.
-// Called by all 128 channel-threads of a head together (the round trips reduce over 32 / 64 lanes).
-__device__ __forceinline__ float arriving_key(const ConvArgs &a, int j, int seq, int h, int t, int i) {
-  float x[1];
-  if (!a.s.from_tier) {
-    int64_t row = ((int64_t)j * a.Hkv + h) * a.n_tokens + t;
-    if (a.s.flat_fmt == TTKV_F32)
-      x[0] = ((const float *)a.s.k_flat)[row * 128 + i];
-    else {
-      uint16_t w = ((const uint16_t *)a.s.k_flat)[row * 128 + i];
-      x[0] = a.s.flat_fmt == TTKV_F16 ? h2f(w) : bf2f(w);
-    }
-  } else {
-    int row;
-    const uint8_t *head = head_ptr(a.s.src, seq, a.s.src_rec_base[j], wrap(a.s.src_first_tok[j] + t, a.s.src), h, &row);
-    const int f = a.s.src.k_fmt;
-    if (f == TTKV_F16 || f == TTKV_BF16) {
-      uint16_t w = *(const uint16_t *)(head + row * 256 + i * 2);
-      x[0] = f == TTKV_F16 ? h2f(w) : bf2f(w);
-    } else if (f == TTKV_I8_SYM_G32) {
-      float s = h2f(*(const uint16_t *)(head + a.s.src.k_meta_off + row * 8 + (i >> 5) * 2));
-      x[0] = (float)(int)(int8_t)head[row * 128 + i] * s;
+  } else if constexpr (DST == TTKV_I4_ASYM_G64 || DST == TTKV_I4_ASYM_G64_T32) {
+    const Q2Scale q = q2_codes(x, n);
+    const uint32_t w = pack_nibbles(n);
+    if constexpr (DST == TTKV_I4_ASYM_G64) {
+      if (live) st_stream(code + row * 64 + l16 * 4, w);
     } else {
-      uint32_t sz = *(const uint32_t *)(head + a.s.src.k_meta_off + row * 8 + (i >> 6) * 4);
-      uint8_t byte = head[row * 64 + (i >> 1)];
-      float p = (float)(int)((i & 1) ? (byte >> 4) : (byte & 0xf)) * h2f((uint16_t)(sz & 0xffff));
-      x[0] = p + h2f((uint16_t)(sz >> 16));
+      s_t32[i * kT32Stride + l16] = w;
     }
+    if (live && (l16 & 7) == 0) *(uint32_t *)(meta + row * 8 + (l16 >> 3) * 4) = q.word;
   }
-  for (int u = 0; u < a.n_via; ++u) roundtrip<1, 32, 64>(a.via_k[u], x);
-  return x[0];
+}
+__device__ __forceinline__ void keep_values(float (*s_x)[128], int i, int l16, const float (&x)[8]) {
+  float4 *o = (float4 *)(s_x[i] + l16 * 8);
+  o[0] = float4{x[0], x[1], x[2], x[3]};
+  o[1] = float4{x[4], x[5], x[6], x[7]};
 }
 
-// Running key sums per destination block, token order, and the fp16 mean key: one thread per channel, one
-// workgroup per (sequence entry, KV head, destination block touched by this call).  A block that was partly
-// filled before continues from its stored sum.
-__global__ __launch_bounds__(128) void summary_kernel(const ConvArgs a) {
-  const int j = blockIdx.x, h = blockIdx.y, z = blockIdx.z, i = threadIdx.x;
-  const int seq = a.seq_id[j];
-  const int r0 = a.dst_first_tok[j] % a.dst.bt;                 // row of the call's first token in its block
-  const int t_lo = max(0, z * a.dst.bt - r0), t_hi = min(a.n_tokens, (z + 1) * a.dst.bt - r0);
-  float sum = 0.0f;
-  for (int t = t_lo; t < t_hi; ++t) {
-    const float x = arriving_key(a, j, seq, h, t, i);
-    const int tok = wrap(a.dst_first_tok[j] + t, a.dst);
-    const int r = tok / a.dst.bt, row = tok - r * a.dst.bt;
-    const int64_t rec = a.sum_table ? (int64_t)a.sum_table[(int64_t)seq * a.sum_ring_blocks + r] : (int64_t)a.sum_rec_base[j] + r;
-    const int64_t o = (rec * a.Hkv + h) * 128 + i;
-    if (row == 0)
-      sum = 0.0f;
-    else if (t == t_lo)
-      sum = a.k_sum[o];
-    sum = sum + x;
-    if (row == a.dst.bt - 1 || t == a.n_tokens - 1) {
-      a.k_sum[o] = sum;
-      a.k_summary[o] = f2h(sum * a.inv_bt);
+// The unit's loaded rows.  SUM: the arriving values also go to s_x.
+template <int SRC, int DST, int THREADS, int ROWS, bool SUM>
+__device__ __forceinline__ void convert_unit(const Source &c, const Unit &u, const Raw (&raw)[ROWS * 16 / THREADS],
+                                             float (*s_x)[128], uint32_t *s_t32) {
+  const int l16 = threadIdx.x & 15;
+#pragma unroll
+  for (int p = 0; p < ROWS * 16 / THREADS; ++p) {
+    const int i = p * (THREADS / 16) + (threadIdx.x >> 4);
+    constexpr bool COPY = SRC == DST && (DST == TTKV_F16 || DST == TTKV_BF16);
+    if (COPY && !SUM && c.n_via == 0) {   // bytes as they are
+      if (i >= u.lo && i < u.hi) st_stream(u.head + u.code_off + (u.row0 + i) * 256 + l16 * 16, raw[p].a);
+      continue;
     }
+    float x[8];
+    expand<SRC>(raw[p], x);
+    pass_through(c, x);
+    if constexpr (SUM) keep_values(s_x, i, l16, x);
+    put_row<DST>(u, i, l16, x, s_t32);
   }
+}
+
+#define TTKV_FOR_SOURCES(DST, CALL)                                       \
+  switch (src_fmt) {                                                      \
+    case TTKV_F16: CALL(TTKV_F16, DST); break;                            \
+    case TTKV_BF16: CALL(TTKV_BF16, DST); break;                          \
+    case TTKV_F32: CALL(TTKV_F32, DST); break;                            \
+    case TTKV_I8_SYM_G32: CALL(TTKV_I8_SYM_G32, DST); break;              \
+    default: CALL(TTKV_I4_ASYM_G64, DST); break;                          \
+  }
+
+// Channel-major values: the unit's two groups of 32 tokens leave as 2 KiB each in the operand order of the
+// matrix-core kernel: piece p = 64 hh + 16 kg + c, word w: channel 16 (4 hh + w) + c, nibble q: token kTok[q] + 4 kg.
+// A thread takes the words of eight such tokens (eight channels each) and turns them by 8 x 8 nibbles in registers --
+// nibbles by masks, then bytes by v_perm, 32 operations for 8 words instead of 24 per word gathered one by one -- and
+// the words meet in LDS in the group's order, pieces permuted inside eights to spread them over the banks.
+template <int THREADS>
+__device__ __forceinline__ void store_t32(const Unit &u, uint32_t *s_t32) {
+  uint4 *const s_out = (uint4 *)(s_t32 + CHUNK * kT32Stride);
+  __syncthreads();
+  if (threadIdx.x < 128) {
+    const int g = threadIdx.x >> 6, kg = (threadIdx.x >> 4) & 3, cw = threadIdx.x & 15;
+    const int kTok[8] = {0, 2, 16, 18, 1, 3, 17, 19};
+    uint32_t in[8], even[4], odd[4];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) in[q] = s_t32[(g * 32 + kTok[q] + 4 * kg) * kT32Stride + cw];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {   // byte k of even (odd): channel 2 k (2 k + 1) of tokens 2 q, 2 q + 1
+      even[q] = (in[2 * q] & 0x0F0F0F0Fu) | ((in[2 * q + 1] << 4) & 0xF0F0F0F0u);
+      odd[q] = ((in[2 * q] >> 4) & 0x0F0F0F0Fu) | (in[2 * q + 1] & 0xF0F0F0F0u);
+    }
+    uint32_t *const out = (uint32_t *)(s_out + g * 128);
+    const int hh = cw >> 3, w = (cw >> 1) & 3, base = 64 * hh + 16 * kg + 8 * (cw & 1), turn = 2 * kg + hh;
+    auto turned = [&](const uint32_t (&m)[4], int odd_channel) {
+      const uint32_t lo01 = __builtin_amdgcn_perm(m[1], m[0], 0x05010400u), lo23 = __builtin_amdgcn_perm(m[3], m[2], 0x05010400u);
+      const uint32_t hi01 = __builtin_amdgcn_perm(m[1], m[0], 0x07030602u), hi23 = __builtin_amdgcn_perm(m[3], m[2], 0x07030602u);
+      const uint32_t t[4] = {__builtin_amdgcn_perm(lo23, lo01, 0x05040100u), __builtin_amdgcn_perm(lo23, lo01, 0x07060302u),
+                             __builtin_amdgcn_perm(hi23, hi01, 0x05040100u), __builtin_amdgcn_perm(hi23, hi01, 0x07060302u)};
+#pragma unroll
+      for (int k = 0; k < 4; ++k) out[4 * ((base + 2 * k + odd_channel) ^ turn) + w] = t[k];
+    };
+    turned(even, 0);
+    turned(odd, 1);
+  }
+  __syncthreads();
+  for (int idx = threadIdx.x; idx < 256; idx += THREADS) {
+    const int g = idx >> 7, p = idx & 127, turn = 2 * ((p >> 4) & 3) + (p >> 6);
+    if (g * 32 >= u.lo && g * 32 < u.hi) st_stream(u.head + u.code_off + (u.row0 + g * 32) * 64 + p * 16, s_out[g * 128 + (p ^ turn)]);
+  }
+}
+
+// Keys of one destination block, converted like any other unit and summed per channel in token order (fp32) for the
+// block's mean key: a block that was partly filled before continues from its stored sum.  The arriving values of 32
+// rows go to LDS, where the two waves whose turn it is add them up (one channel per lane) while the other waves
+// convert the next 32 rows; the running sums pass from turn to turn through LDS.  The order of the additions is the
+// token order, so the sums are reproducible bit for bit; what made the former kernel (one thread per channel,
+// reading and re-quantizing one row after the other from memory) 331 us of the 572 us tiering of 4 x 32768 tokens
+// was the chain of loads, not the additions.
+template <int THREADS>
+__device__ __forceinline__ void sum_unit(const Source &src, Unit u, int src_fmt, int dst_fmt, int rows_lo, int rows_hi, float *k_sum,
+                                         uint16_t *k_summary, float inv_bt, char *s_buf) {
+  // k_sum, k_summary: the block's; rows [rows_lo, rows_hi) of the block arrive, row rows_lo is token u.t_lo
+  float (*s_x)[SUM_ROWS][128] = (float (*)[SUM_ROWS][128])s_buf;            // two buffers
+  float *s_sum = (float *)(s_buf + 2 * SUM_ROWS * 128 * sizeof(float));
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int t0 = u.t_lo;
+  auto place = [&](int row0) {
+    u.row0 = row0;
+    u.lo = max(rows_lo - row0, 0);
+    u.hi = min(rows_hi - row0, SUM_ROWS);
+    u.t_lo = t0 + row0 + u.lo - rows_lo;
+  };
+  Raw raw[SUM_ROWS * 16 / THREADS];
+#define TTKV_LOAD_UNIT(S, D) load_unit<S, THREADS, SUM_ROWS>(src, u, raw)
+  place(rows_lo / SUM_ROWS * SUM_ROWS);
+  TTKV_FOR_SOURCES(0, TTKV_LOAD_UNIT)
+  for (int c = 0;; ++c) {
+#define TTKV_SUM_UNIT(S, D) convert_unit<S, D, THREADS, SUM_ROWS, true>(src, u, raw, s_x[c & 1], nullptr)
+    switch (dst_fmt) {
+      case TTKV_F16: TTKV_SUM_UNIT(TTKV_F16, TTKV_F16); break;
+      case TTKV_BF16: TTKV_SUM_UNIT(TTKV_BF16, TTKV_BF16); break;
+      case TTKV_I8_SYM_G32: TTKV_FOR_SOURCES(TTKV_I8_SYM_G32, TTKV_SUM_UNIT) break;
+      case TTKV_I4_ASYM_G64: TTKV_FOR_SOURCES(TTKV_I4_ASYM_G64, TTKV_SUM_UNIT) break;
+      default: TTKV_FOR_SOURCES(NO_STORE, TTKV_SUM_UNIT) break;
+    }
+#undef TTKV_SUM_UNIT
+    const int lo = u.lo, hi = u.hi, next = u.row0 + SUM_ROWS;
+    const bool more = next < rows_hi;
+    if (more) {
+      place(next);
+      TTKV_FOR_SOURCES(0, TTKV_LOAD_UNIT)
+    }
+    __syncthreads();
+    const int turn = wave - 2 * (c % (THREADS / 128));
+    if (turn == 0 || turn == 1) {
+      const int ch = turn * 64 + lane;
+      float sum = c ? s_sum[ch] : rows_lo ? k_sum[ch] : 0.0f;
+      const float *x = &s_x[c & 1][0][ch];
+      if (lo == 0 && hi == SUM_ROWS) {
+#pragma unroll 16
+        for (int r = 0; r < SUM_ROWS; ++r) sum = sum + x[r * 128];
+      } else {
+        for (int r = lo; r < hi; ++r) sum = sum + x[r * 128];
+      }
+      if (more) {
+        s_sum[ch] = sum;
+      } else {
+        k_sum[ch] = sum;
+        k_summary[ch] = f2h(sum * inv_bt);
+      }
+    }
+    if (!more) break;
+  }
+#undef TTKV_LOAD_UNIT
+}
+
+// Grid: x = K units then V units of one (entry, KV head), y = entry x KV head.  SUM: K units are whole destination
+// blocks and keep the key sums (dst_fmt of K may be NO_STORE: sums only); otherwise every unit is 64 rows.
+template <bool SUM>
+__global__ __launch_bounds__(SUM ? SUM_THREADS : 256, SUM ? 6 : 8) void convert_rows_kernel(const ConvArgs a, int k_units, int k_dst_fmt) {
+  constexpr int THREADS = SUM ? SUM_THREADS : 256;
+  constexpr int SUM_BYTES = 2 * SUM_ROWS * 128 * 4 + 512;
+  __shared__ __align__(16) char s_buf[SUM ? (SUM_BYTES > kT32Bytes ? SUM_BYTES : kT32Bytes) : kT32Bytes];
+  const int j = blockIdx.y / a.Hkv, h = blockIdx.y - j * a.Hkv, seq = a.seq_id[j];
+  const int which = (int)blockIdx.x >= k_units;
+  const int unit = which ? blockIdx.x - k_units : blockIdx.x;
+  const int first = a.dst_first_tok[j];                   // ring token the call's first row lands on
+  const int dst_rec_base = a.dst_rec_base[j], n_tokens = a.n_tokens;
+  const TierView dst = a.dst;
+  const Source src = make_source(a, which, j, h, seq);
+  const int src_fmt = src.flat ? a.s.flat_fmt : which ? src.tier.v_fmt : src.tier.k_fmt;
+  Unit u;
+  u.code_off = which ? dst.v_off : 0;
+  u.meta_off = which ? dst.v_meta_off : dst.k_meta_off;
+
+  if (SUM && !which) {
+    const int r = first / dst.bt, r0 = first - r * dst.bt;
+    const int t_lo = max(0, unit * dst.bt - r0), t_hi = min(n_tokens, (unit + 1) * dst.bt - r0);
+    if (t_lo >= t_hi) return;
+    int rb = r + unit;
+    if (rb >= dst.ring_blocks) rb -= dst.ring_blocks;
+    u.head = k_dst_fmt == NO_STORE ? nullptr : block_head(dst, seq, dst_rec_base, rb, h);
+    int sb = a.sum_first_block[j] + unit;
+    if (sb >= a.sum_ring_blocks) sb -= a.sum_ring_blocks;
+    const int64_t rec = a.sum_table ? (int64_t)a.sum_table[(int64_t)seq * a.sum_ring_blocks + sb] : (int64_t)seq * a.sum_ring_blocks + sb;
+    const int64_t sum_at = (rec * a.Hkv + h) * 128;
+    const int rows_lo = t_lo + r0 - unit * dst.bt, rows_hi = t_hi + r0 - unit * dst.bt;
+    u.t_lo = t_lo;
+    float *const k_sum = a.k_sum + sum_at;
+    uint16_t *const k_summary = a.k_summary + sum_at;
+    const float inv_bt = a.inv_bt;
+    sum_unit<THREADS>(src, u, src_fmt, k_dst_fmt, rows_lo, rows_hi, k_sum, k_summary, inv_bt, s_buf);
+    return;
+  }
+
+  int tok = first / CHUNK * CHUNK + unit * CHUNK;         // ring token of the unit's row 0
+  const int t0 = tok - first;                             // its token of the call (the first unit may start before it)
+  u.lo = max(0, -t0);
+  u.hi = min(CHUNK, n_tokens - t0);
+  u.t_lo = t0 + u.lo;
+  if (u.lo >= u.hi) return;
+  tok = wrap(tok, dst);
+  const int r = tok / dst.bt;
+  u.row0 = tok - r * dst.bt;
+  u.head = block_head(dst, seq, dst_rec_base, r, h);
+  const int dst_fmt = which ? dst.v_fmt : k_dst_fmt;
+  uint32_t *const s_t32 = (uint32_t *)s_buf;
+  Raw raw[CHUNK * 16 / THREADS];
+#define TTKV_ROW_UNIT(S, D) load_unit<S, THREADS, CHUNK>(src, u, raw), convert_unit<S, D, THREADS, CHUNK, false>(src, u, raw, nullptr, s_t32)
+  switch (dst_fmt) {
+    case TTKV_F16: TTKV_ROW_UNIT(TTKV_F16, TTKV_F16); break;
+    case TTKV_BF16: TTKV_ROW_UNIT(TTKV_BF16, TTKV_BF16); break;
+    case TTKV_I8_SYM_G32: TTKV_FOR_SOURCES(TTKV_I8_SYM_G32, TTKV_ROW_UNIT) break;
+    case TTKV_I4_ASYM_G64_T32: TTKV_FOR_SOURCES(TTKV_I4_ASYM_G64_T32, TTKV_ROW_UNIT) break;
+    default: TTKV_FOR_SOURCES(TTKV_I4_ASYM_G64, TTKV_ROW_UNIT) break;
+  }
+#undef TTKV_ROW_UNIT
+  if (dst_fmt == TTKV_I4_ASYM_G64_T32) store_t32<THREADS>(u, s_t32);
 }
 
 // Keys of a tier whose int4 groups run over 128 consecutive tokens of one channel (Q_4bit's arithmetic with the
-// group turned by 90 degrees): one workgroup per (token group, KV head, entry), thread = channel.  Two passes
-// over the group's 128 arriving rows: range, then codes; the two channels of a byte meet by a lane exchange.
-__global__ __launch_bounds__(128) void convert_keys_t128_kernel(const ConvArgs a) {
-  const int g = blockIdx.x, h = blockIdx.y, j = blockIdx.z, i = threadIdx.x;
-  const int seq = a.seq_id[j];
-  float lo = 0.0f, hi = 0.0f;
-  for (int t = 0; t < 128; ++t) {
-    const float x = arriving_key(a, j, seq, h, g * 128 + t, i);
-    lo = t ? fminf(lo, x) : x;
-    hi = t ? fmaxf(hi, x) : x;
-  }
-  if (lo == 0.0f) lo = 0.0f;  // a zero minimum is stored as +0 whatever its sign
-  const float s32 = (hi - lo) / 15.0f;
-  const uint16_t sh = f2h(s32), zh = f2h(lo);
-  const float s = h2f(sh), z = h2f(zh);
-  const float r = s != 0.0f ? 1.0f / s : 0.0f;
-  int row0;
-  uint8_t *head = head_ptr(a.dst, seq, a.dst_rec_base[j], wrap(a.dst_first_tok[j] + g * 128, a.dst), h, &row0);
-  // the group's 128 meta rows of 4 bytes hold {scale, zero} of the 128 channels
-  *(uint32_t *)(head + a.dst.k_meta_off + row0 * 4 + i * 4) = (uint32_t)sh | ((uint32_t)zh << 16);
-  for (int t = 0; t < 128; ++t) {
-    const float x = arriving_key(a, j, seq, h, g * 128 + t, i);
-    float q = 0.0f;
-    if (s != 0.0f) q = fminf(fmaxf(quot_rint(x - z, s, r), 0.0f), 15.0f);
-    const int c = (int)q;
-    const int other = __shfl_xor(c, 1);
-    if (!(i & 1)) head[(row0 + t) * 64 + (i >> 1)] = (uint8_t)(c | (other << 4));
-  }
-}
-
-// Values of a tier that stores Q_4bit codes channel-major per 32 tokens (TTKV_I4_ASYM_G64_T32): one workgroup per
-// (group of 32 arriving tokens, KV head, entry).  Rows are quantized exactly as convert_rows_kernel does (a 16-lane
-// group per row, 8 channels per lane); the meta rows go to their token-major section as usual, the codes meet in LDS
-// and leave as the group's 2 KiB in the operand order of the matrix-core kernel: piece p = 64 hh + 16 kg + c, word w:
-// channel 16 (4 hh + w) + c, nibble j: token kTok[j] + 4 kg.
-__global__ __launch_bounds__(256) void convert_values_t32_kernel(const ConvArgs a) {
-  __shared__ uint8_t s_code[32][128];
-  const int g = blockIdx.x, h = blockIdx.y, j = blockIdx.z;
-  const int seq = a.seq_id[j];
-  const int l16 = threadIdx.x & 15;
-  int row0;
-  uint8_t *head = head_ptr(a.dst, seq, a.dst_rec_base[j], wrap(a.dst_first_tok[j] + g * 32, a.dst), h, &row0);   // row0 % 32 == 0
+// group turned by 90 degrees): one workgroup per (token group, KV head, entry).  The group's 128 arriving rows are
+// read once and stay in registers (a 16-lane group holds rows r, r + 16, ..; 8 channels per lane); the ranges meet
+// over the lanes and waves, one thread per channel forms the scale, and the rows are coded from the registers.
+template <int SRC>
+__device__ __forceinline__ void keys_t128(const Source &src, int g, uint8_t *head, int k_meta_off, int row0, float (*s_lo)[128],
+                                          float (*s_hi)[128], float (*s_q)[128]) {
+  const int l16 = threadIdx.x & 15, wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  float x[8][8];
+  {
+    Raw raw[8];
 #pragma unroll
-  for (int pass = 0; pass < 2; ++pass) {
-    const int r = pass * 16 + (threadIdx.x >> 4), t = g * 32 + r;
-    float x[8];
-    if (!a.s.from_tier) {
-      load8_flat(a.s.v_flat, a.s.flat_fmt, ((int64_t)j * a.Hkv + h) * a.n_tokens + t, l16, x);
-    } else {
-      int row;
-      const uint8_t *src = head_ptr(a.s.src, seq, a.s.src_rec_base[j], wrap(a.s.src_first_tok[j] + t, a.s.src), h, &row);
-      load8_tier(src, a.s.src.v_fmt, a.s.src.v_off, a.s.src.v_meta_off, row, l16, x);
+    for (int half = 0; half < 2; ++half) {
+      const RowSource s = row_source<SRC>(src, g * 128 + half * 64);
+#pragma unroll
+      for (int p = 0; p < 4; ++p) load_from<SRC>(s, p * 16 + (threadIdx.x >> 4), l16, raw[half * 4 + p]);
     }
-    for (int u = 0; u < a.n_via; ++u) roundtrip<8, 4, 8>(a.via_v[u], x);
-    int c[8];
-    uint16_t sh, zh;
-    q2_group<8, 8>(x, c, &sh, &zh);
-    if ((l16 & 7) == 0) *(uint32_t *)(head + a.dst.v_meta_off + (row0 + r) * 8 + (l16 >> 3) * 4) = (uint32_t)sh | ((uint32_t)zh << 16);
 #pragma unroll
-    for (int i = 0; i < 8; ++i) s_code[r][l16 * 8 + i] = (uint8_t)c[i];
+    for (int p = 0; p < 8; ++p) {
+      expand<SRC>(raw[p], x[p]);
+      pass_through(src, x[p]);
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    float lo = x[0][i], hi = x[0][i];
+#pragma unroll
+    for (int p = 1; p < 8; ++p) {
+      lo = fminf(lo, x[p][i]);
+      hi = fmaxf(hi, x[p][i]);
+    }
+    lo = fminf(lo, __shfl_xor(lo, 16));
+    hi = fmaxf(hi, __shfl_xor(hi, 16));
+    lo = fminf(lo, __shfl_xor(lo, 32));
+    hi = fmaxf(hi, __shfl_xor(hi, 32));
+    if (lane < 16) {
+      s_lo[wave][l16 * 8 + i] = lo;
+      s_hi[wave][l16 * 8 + i] = hi;
+    }
   }
   __syncthreads();
-  const int kTok[8] = {0, 2, 16, 18, 1, 3, 17, 19};
-  uint32_t *out = (uint32_t *)(head + a.dst.v_off + row0 * 64);     // the group's 2 KiB: 512 words, two per thread
-#pragma unroll
-  for (int k = 0; k < 2; ++k) {
-    const int d = threadIdx.x + 256 * k;          // word index: piece d / 4, word d % 4
-    const int p = d >> 2, w = d & 3;
-    const int hh = p >> 6, kg = (p >> 4) & 3, c = p & 15;
-    const int ch = 16 * (4 * hh + w) + c;
-    uint32_t v = 0;
-#pragma unroll
-    for (int jn = 0; jn < 8; ++jn) v |= (uint32_t)s_code[kTok[jn] + 4 * kg][ch] << (4 * jn);
-    out[d] = v;
+  if (threadIdx.x < 128) {
+    const int i = threadIdx.x;
+    float lo = fminf(fminf(s_lo[0][i], s_lo[1][i]), fminf(s_lo[2][i], s_lo[3][i]));
+    const float hi = fmaxf(fmaxf(s_hi[0][i], s_hi[1][i]), fmaxf(s_hi[2][i], s_hi[3][i]));
+    if (lo == 0.0f) lo = 0.0f;  // a zero minimum is stored as +0 whatever its sign
+    const uint16_t sh = f2h(div_const<15>(hi - lo)), zh = f2h(lo);
+    s_q[0][i] = h2f(sh);
+    s_q[1][i] = h2f(zh);
+    // the group's 128 meta rows of 4 bytes hold {scale, zero} of the 128 channels
+    *(uint32_t *)(head + k_meta_off + row0 * 4 + i * 4) = (uint32_t)sh | ((uint32_t)zh << 16);
   }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const Divisor d(s_q[0][l16 * 8 + i]);
+    const float z = s_q[1][l16 * 8 + i];
+#pragma unroll
+    for (int p = 0; p < 8; ++p) x[p][i] = d.code(x[p][i] - z, 0.0f, 15.0f);
+  }
+#pragma unroll
+  for (int p = 0; p < 8; ++p)
+    st_stream(head + (row0 + p * 16 + (threadIdx.x >> 4)) * 64 + l16 * 4, pack_nibbles(x[p]));
+}
+__global__ __launch_bounds__(256) void convert_keys_t128_kernel(const ConvArgs a) {
+  __shared__ float s_lo[4][128], s_hi[4][128], s_q[2][128];
+  const int g = blockIdx.x, j = blockIdx.y / a.Hkv, h = blockIdx.y - j * a.Hkv;
+  const int seq = a.seq_id[j], dst_rec_base = a.dst_rec_base[j];
+  const TierView dst = a.dst;
+  const Source src = make_source(a, 0, j, h, seq);
+  const int src_fmt = src.flat ? a.s.flat_fmt : src.tier.k_fmt;
+  const int tok = wrap(a.dst_first_tok[j] + g * 128, dst);
+  const int r = tok / dst.bt, row0 = tok - r * dst.bt;
+  uint8_t *const head = block_head(dst, seq, dst_rec_base, r, h);
+#define TTKV_T128(S, D) keys_t128<S>(src, g, head, dst.k_meta_off, row0, s_lo, s_hi, s_q)
+  TTKV_FOR_SOURCES(0, TTKV_T128)
+#undef TTKV_T128
 }
 
 }  // namespace
 
+// Converts the rows and, where the destination keeps block summaries (a.k_sum), their key sums.
 hipError_t launch_convert(const ConvArgs &a, hipStream_t s, int *n_kernels) {
-  const int64_t total = (int64_t)a.n_seq * a.Hkv * a.n_tokens;
-  if (total <= 0) return hipSuccess;
-  if (a.dst.k_fmt == TTKV_I4_ASYM_T128) {
-    // values row by row, keys by groups of 128 tokens per channel (the caller has checked alignment)
-    ConvArgs v = a;
-    v.which0 = 1;
-    hipLaunchKernelGGL(convert_rows_kernel, dim3((a.n_tokens + 15) / 16, 1, a.n_seq * a.Hkv), dim3(256), 0, s, v);
-    hipLaunchKernelGGL(convert_keys_t128_kernel, dim3(a.n_tokens / 128, a.Hkv, a.n_seq), dim3(128), 0, s, a);
-    *n_kernels += 2;
-    return hipGetLastError();
+  if ((int64_t)a.n_seq * a.Hkv * a.n_tokens <= 0) return hipSuccess;
+  const unsigned y = (unsigned)(a.n_seq * a.Hkv);
+  int chunks = 0, blocks = 0;      // units of the entry that needs most
+  for (int j = 0; j < a.n_seq; ++j) {
+    chunks = std::max(chunks, (a.dst_first_tok[j] % CHUNK + a.n_tokens + CHUNK - 1) / CHUNK);
+    blocks = std::max(blocks, (a.dst_first_tok[j] % a.dst.bt + a.n_tokens + a.dst.bt - 1) / a.dst.bt);
   }
-  if (a.dst.v_fmt == TTKV_I4_ASYM_G64_T32) {
-    // keys row by row, values by groups of 32 tokens (the caller has checked alignment)
-    hipLaunchKernelGGL(convert_rows_kernel, dim3((a.n_tokens + 15) / 16, 1, a.n_seq * a.Hkv), dim3(256), 0, s, a);   // which0 = 0: K only
-    hipLaunchKernelGGL(convert_values_t32_kernel, dim3(a.n_tokens / 32, a.Hkv, a.n_seq), dim3(256), 0, s, a);
-    *n_kernels += 2;
-    return hipGetLastError();
+  const bool t128 = a.dst.k_fmt == TTKV_I4_ASYM_T128;   // whole aligned groups (the caller has checked)
+  if (t128) {
+    hipLaunchKernelGGL(convert_keys_t128_kernel, dim3(a.n_tokens / 128, y), dim3(256), 0, s, a);
+    ++*n_kernels;
   }
-  dim3 grid((a.n_tokens + 15) / 16, 2, a.n_seq * a.Hkv);
-  hipLaunchKernelGGL(convert_rows_kernel, grid, dim3(256), 0, s, a);
-  ++*n_kernels;
-  return hipGetLastError();
-}
-
-// `a.dst` gives the destination ring geometry only (block_tokens, ring_blocks);
-// the kernel writes k_sum / k_summary, never dst.
-hipError_t launch_summary(const ConvArgs &a, hipStream_t s, int *n_kernels) {
-  if (a.n_seq <= 0 || a.n_tokens <= 0 || !a.k_sum) return hipSuccess;
-  hipLaunchKernelGGL(summary_kernel, dim3(a.n_seq, a.Hkv, a.n_tokens / a.dst.bt + 2), dim3(128), 0, s, a);
+  if (a.k_sum) {
+    hipLaunchKernelGGL(convert_rows_kernel<true>, dim3(blocks + chunks, y), dim3(SUM_THREADS), 0, s, a, blocks,
+                       t128 ? NO_STORE : a.dst.k_fmt);
+  } else {
+    const int k_units = t128 ? 0 : chunks;
+    hipLaunchKernelGGL(convert_rows_kernel<false>, dim3(k_units + chunks, y), dim3(256), 0, s, a, k_units, a.dst.k_fmt);
+  }
   ++*n_kernels;
   return hipGetLastError();
 }

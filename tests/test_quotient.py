@@ -1,6 +1,6 @@
-"""The conversion kernels divide once per group and multiply per element (Sec. 4.2's quantizers are fixed as one
-IEEE division per element followed by round-to-nearest-even): rint(x * (1 / s)) with the exact division as fallback
-when x * (1 / s) lies within 5e-4 of a half-integer.  Emulated here in fp32 with numpy, against the plain division,
+"""Dividing once per group and multiplying per element (Sec. 4.2's quantizers are fixed as one IEEE division per
+element followed by round-to-nearest-even): rint(x * (1 / s)) agrees with it but where x * (1 / s) lies within 5e-4
+of a half-integer -- the distance that the conversion kernels' correction step (test_conversion_rules.py) closes.  Emulated here in fp32 with numpy, against the plain division,
 on scales of every fp16 magnitude and quotients placed on, next to and between the half-integers: after the clamp to
 the code range the two must agree everywhere.  (The GPU tests compare the kernels' codes with the oracle's.)"""
 import numpy as np
