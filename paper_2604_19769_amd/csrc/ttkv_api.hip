@@ -106,21 +106,17 @@ int copy_granule(int64_t rec_bytes) {
 }
 
 // Default split-K granularity, in workgroups resident at once on 256 CUs: 2.5 rounds of 4 per CU for the vector
-// kernel (flat between 1 and 3 rounds, measured), exactly one round of 3 per CU for the grouped-query matrix-core
-// kernel (int4: 5.1 TB/s against 4.4-4.7 with two rounds; the other formats are indifferent).
+// kernel (flat between 1 and 3 rounds, measured), exactly one round of the grouped-query matrix-core kernel: 2 per CU
+// with 4-bit tiers, 3 without.  (Two are also the better choice for int8 tiers with many heads: 64 q / 4 kv heads,
+// 4 x 100K tokens, 81.9 us with 512 items, 89.4 with 768.)
 int default_items(const ttkv_cache *c) {
   const int G = c->n_q_heads / c->n_kv_heads;
-  bool special = false;   // K 8-bit / V 4-bit or keys grouped over tokens
+  bool two_per_cu = false;
   for (int t = 0; t < c->n_tiers; ++t) {
-    const ttkv_tier &T = c->tier[t];
-    if (!attn_mfma_fits(T.k_fmt, T.v_fmt, G)) return 2560;
-    special |= T.k_fmt == TTKV_I4_ASYM_T128 || (T.k_fmt == TTKV_I8_SYM_G32 && T.v_fmt != T.k_fmt);
+    if (!attn_mfma_fits(c->tier[t].k_fmt, c->tier[t].v_fmt, G)) return 2560;
+    two_per_cu |= attn_mfma_four_bit(c->tier[t].k_fmt, c->tier[t].v_fmt) || (G > 8 && !is_fp(c->tier[t].k_fmt));
   }
-  if (!attn_mfma_pays(G, special)) return 2560;
-  for (int t = 0; t < c->n_tiers; ++t)
-    if (G > 8 && (c->tier[t].k_fmt == TTKV_I4_ASYM_G64 || c->tier[t].k_fmt == TTKV_I8_SYM_G32))
-      return 512;   // the 16-head cases run 2 workgroups per CU (64 q / 4 kv heads, int8 keys: 6.06 against 5.8 TB/s with 768)
-  return 768;
+  return !attn_mfma_pays(G) ? 2560 : two_per_cu ? 512 : 768;
 }
 
 inline int per_token_bytes(const ttkv_tier &U) {
@@ -155,6 +151,35 @@ int items_for(int64_t len, int per_token, double item_bytes) {
 // target is therefore raised from the kernel's default (default_items) in steps until the items are within 10 % of
 // their mean and the last round is filled (or there are at least three rounds); failing that, the candidate with
 // the smallest estimated loss is taken.  target_items != 0 (ttkv_set_split) is taken as given.
+// Launches with 4-bit tiers on the matrix cores run two workgroups per CU, each at about the rate at which its CU can
+// be fed, so a slot left with one item more than the others costs that item's whole time (512 equal items 82 us, 544
+// of them 110; 8 x 64K tokens, K int8 / V int4).  For them the loss is played through (played_loss).
+
+// The items, largest first as they are launched, go to the slot that is free first; every item costs its bytes and what
+// an idle slot would have streamed in the 6-7 us that an item's start and end take.  Returns the end over the ideal one.
+// The heads of one chunk are alike: slots and items are counted in groups of per_item.
+struct ItemGroup { double bytes; int count; };
+double played_loss(ItemGroup *g, int n, int slots, double ideal) {
+  constexpr double kItemCost = 80e3;
+  double end[512];
+  std::sort(g, g + n, [](const ItemGroup &x, const ItemGroup &y) { return x.bytes > y.bytes; });
+  std::fill(end, end + slots, 0.0);   // a min-heap on the slots' end times
+  double last = 0.0;
+  for (int r = 0; r < n; ++r)
+    for (int k = 0; k < g[r].count; ++k) {
+      const double e = end[0] + g[r].bytes + kItemCost;
+      int at = 0;
+      for (int kid; (kid = 2 * at + 1) < slots; at = kid) {
+        if (kid + 1 < slots && end[kid + 1] < end[kid]) ++kid;
+        if (end[kid] >= e) break;
+        end[at] = end[kid];
+      }
+      end[at] = e;
+      last = std::max(last, e);
+    }
+  return last / (ideal + kItemCost);
+}
+
 double choose_item_bytes(const ttkv_cache *c, const bool *dense, int target_items, const int64_t *last_tokens, SplitMemo *memo) {
   // last_tokens: null, or the tokens of the last tier that are attended, per sequence (its selected blocks)
   // The runs, gathered once: length and bytes per token (at most batch x tiers of them).
@@ -187,6 +212,7 @@ double choose_item_bytes(const ttkv_cache *c, const bool *dense, int target_item
   const float *steps = vector_kernel ? steps_v : steps_m;
 
   struct Fit { double b, largest, sum_b, sum_b2, n_big; bool all_max; };
+  ItemGroup groups[TTKV_MAX_BATCH * TTKV_MAX_TIERS];   // of the latest fit
   // Item size for `want_rounds` rounds.  The item counts come out in steps: if the large items (at least half the
   // largest) overshoot the rounds aimed at, slightly larger items are asked for, up to three times.
   auto fit = [&](double want_rounds) {
@@ -202,6 +228,7 @@ double choose_item_bytes(const ttkv_cache *c, const bool *dense, int target_item
       for (int r = 0; r < n_runs; ++r) {
         count[r] = items_for(runs[r].len, runs[r].per_token, f.b);
         item[r] = (double)even_chunk(runs[r].len, count[r]) * runs[r].per_token;
+        groups[r] = ItemGroup{item[r], count[r]};
         f.sum_b += count[r] * item[r];
         f.sum_b2 += count[r] * item[r] * item[r];
         f.largest = std::max(f.largest, item[r]);
@@ -235,7 +262,11 @@ double choose_item_bytes(const ttkv_cache *c, const bool *dense, int target_item
     const double frac = rounds - std::floor(rounds);
     const double fill = frac == 0.0 ? 1.0 : frac;
     const bool filled = rounds >= 3.0 || fill >= (vector_kernel ? 0.45 : 0.75) || (rounds < 1.0 && (f.all_max || rounds >= 0.75));
-    const double loss = imbalance <= 1.10 && filled ? 0.0 : imbalance * (1.0 + (1.0 - fill) / std::max(1.0, std::ceil(rounds)));
+    double loss = imbalance <= 1.10 && filled ? 0.0 : imbalance * (1.0 + (1.0 - fill) / std::max(1.0, std::ceil(rounds)));
+    if (resident == 512) {
+      loss = played_loss(groups, n_runs, std::max(1, resident / per_item), (double)S * Hkv / resident);
+      if (loss <= 1.03) loss = 0.0;
+    }
     if (loss < best_loss) {
       best_loss = loss;
       best_b = f.b;
@@ -926,6 +957,11 @@ static ttkv_status decode_impl(Handle *h, const ttkv_cache *c, const void *q, in
   for (int pass = 0; pass < 2; ++pass)
     for (const Run &r : P.runs)
       if ((c->tier[r.tier].mem == TTKV_MEM_HOST_PINNED) == (pass == 0)) order.push_back(&r);
+  // among the tiers in HBM the runs with the largest items first (as choose_item_bytes plays them through): what is
+  // left for the last round is then small
+  const auto first_hbm = std::find_if(order.begin(), order.end(), [&](const Run *r) { return c->tier[r->tier].mem != TTKV_MEM_HOST_PINNED; });
+  auto item_bytes = [&](const Run *r) { return (int64_t)(r->len / r->n_chunks) * per_token_bytes(c->tier[r->tier]); };
+  std::stable_sort(first_hbm, order.end(), [&](const Run *x, const Run *y) { return item_bytes(x) > item_bytes(y); });
   // a timed call may issue its launch(es) several times back to back (same arguments, same partials): the event
   // pair's own cost is then spread over them
   const int reps = timed ? std::max(1, h->time_repeat) : 1;

@@ -73,6 +73,15 @@ struct Splice {
   }
 };
 
+// Eight 4-bit codes -> four registers of packed fp16 pairs, offsets 1024 (even registers) and 64 (odd ones) included.
+__device__ __forceinline__ void splice4(uint32_t x, uint32_t *r, const Splice &k) {
+  const uint32_t y = x >> 8;
+  r[0] = (x & k.m0) | k.c0;   // (1024 + n0, 1024 + n4)
+  r[1] = (x & k.m1) | k.c1;   // (  64 + n1,   64 + n5)
+  r[2] = (y & k.m0) | k.c0;   // (1024 + n2, 1024 + n6)
+  r[3] = (y & k.m1) | k.c1;   // (  64 + n3,   64 + n7)
+}
+
 // 16 bytes of a row -> EPL/2 registers of packed 16-bit pairs (fp16, or bf16 for the bf16 tier).
 template <int F>
 __device__ __forceinline__ void unpack16(const uint4 &w, uint32_t *r, const Splice &k) {
@@ -89,13 +98,7 @@ __device__ __forceinline__ void unpack16(const uint4 &w, uint32_t *r, const Spli
     }
   } else {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const uint32_t x = u[i], y = u[i] >> 8;
-      r[4 * i + 0] = (x & k.m0) | k.c0;   // (1024 + n0, 1024 + n4)
-      r[4 * i + 1] = (x & k.m1) | k.c1;   // (  64 + n1,   64 + n5)
-      r[4 * i + 2] = (y & k.m0) | k.c0;   // (1024 + n2, 1024 + n6)
-      r[4 * i + 3] = (y & k.m1) | k.c1;   // (  64 + n3,   64 + n7)
-    }
+    for (int i = 0; i < 4; ++i) splice4(u[i], r + 4 * i, k);
   }
 }
 

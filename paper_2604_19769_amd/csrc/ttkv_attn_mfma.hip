@@ -6,49 +6,40 @@
 // kernel; only the lane mapping differs.
 //
 // One 16-token tile, lane = (c = lane % 16, kg = lane / 16):
-//   K rows are loaded in the MFMA A layout: lane (c, kg) holds 32 channels of token c, the 16-byte
-//   pieces kg, kg + 4, ... of the row (one piece for int4, two for int8, four for fp16 / bf16), spliced
-//   into packed 16-bit pairs as in the vector kernel.  Four 32-deep steps give
-//       S[token][column] = sum_d K[token][d] * Q[d][column]
-//   where a column is (quantization group, query head): the q operand is zero outside the
-//   column's group, so every column is a per-group dot product.  The splice offsets leave
-//   through the initial accumulator value.  In the MFMA result layout lane (c, kg) holds
-//   column c of tokens 4 kg .. 4 kg + 3.  The token's four fp16 meta values (scale / zero per
-//   group) reach that layout by one more product: meta words as A operand against a 0/1
-//   selector of the column's group, which is exact.  The groups of one head are then summed
-//   by DPP row rotations, which also leaves every column with its head's score.
-//   The softmax is per column (lane-local over 4 tokens, two lane exchanges over kg); its scale
-//   is applied inside the exponent.
-//   V rows are loaded like K rows and dequantized in packed fp16 while the lane still owns
-//   one token and one group: the centred code (int8: signed code, int4: code - 8) is taken out of the
-//   splice exactly and multiplied by the scale, one rounding to nearest even.  A product with the identity matrix brings
-//   the tile from [token][channel] to [channel][token]: the fp32 result (exact) has lane (c, kg)
-//   holding channel-row c for tokens 4 kg .. 4 kg + 3, exactly the A layout of
-//       O[channel][column] += sum_token V^T[channel][token] * P[token][column].
-//   Two 16-token tiles feed one 32-deep product.  The int4 zero points and scales ride along as a
-//   4-channel V (the meta words transposed the same way), giving sum_t p_t z_t and sum_t p_t s_t per group in fp32
-//   (zero point + 8 x scale is what the centred codes leave out).  P is rounded to
-//   fp16 once and that rounded value is used for the row sum as well, so the normalisation is consistent.
-//   Values stored channel-major per 32 tokens (TTKV_I4_ASYM_G64_T32) need neither the dequantization nor the
-//   transposition: a lane's 32-bit word IS eight tokens of one channel, i.e. after the splice the A operand of a
-//   32-deep product, and the token's scale goes into the other operand instead: B_g = fp16(p_t * s_{t,g}), one per
-//   channel group g (the four meta values of a token reach the score layout through the selector product that the
-//   key meta uses).  The splice offsets (1024 / 64 per nibble position) and the centre 8 are removed by one more
-//   product of B_g with a constant operand of "code 8" words; the zero points and the centre come back as
-//   sum_t p_t (z_{t,g} + 8 s_{t,g}) in fp32 on the vector units.
-//   Keys grouped over 128 tokens per channel have no channel groups (one column per head); the token
-//   group's scales fold into the q operand, carried as fp16 rounded product + exact remainder
-//   (two products per step), rebuilt for every 64 tokens in flight.
+//   K rows reach the MFMA A layout as 32 channels of token c per lane, spliced into packed 16-bit pairs as in the vector
+//   kernel.  Four 32-deep steps give
+//       S[token][head] = sum_d K[token][d] * Q[d][head]
+//   Quantized keys: the lane's channels are 8 bytes of each 32-byte stretch of the row, so a step (or two, int4) stays
+//   inside one channel group and every group has a product chain of its own; up to 16 heads are the columns, whatever
+//   the format, and no product is spent on zeros.  The splice offsets leave through the initial accumulator value.  In
+//   the MFMA result layout lane (c, kg) holds head c of tokens 4 kg .. 4 kg + 3; those tokens' meta words (scale, zero
+//   point per group) are read from LDS in that layout (the lanes of one kg read the same 16 bytes) and enter as fp16
+//   operands of fused multiply-adds.
+//   The softmax is per column (lane-local over 4 tokens, two lane exchanges over kg); its scale is applied inside the
+//   exponent.
+//   Quantized V: gfx950's transposing LDS reads (ds_read_b64_tr_b4 / _b8) hand lane (c, kg) the codes of ONE channel of
+//   eight tokens of a 32-token pair of tiles -- after the splice, whose offset (and the centre 8 of int4 codes) leaves
+//   exactly, the A operand of
+//       O[channel][head] += sum_token V^T[channel][token] * P_g[token][head],
+//   and the token's scale rides on the other operand: P_g = fp16(p_t * s_{t,g}), one per channel group g, the one
+//   rounding of the product.  The int4 zero points and the centre come back as sum_t p_t (z_{t,g} + 8 s_{t,g}) in fp32 on
+//   the vector units.  Values stored channel-major per 32 tokens (TTKV_I4_ASYM_G64_T32) are those operand words as they
+//   lie.
+//   fp16 / bf16 V, and int4 V beside keys grouped over tokens: rows like K's (the latter dequantized in packed fp16);
+//   a product with the identity matrix brings the tile from [token][channel] to [channel][token]: the fp32 result
+//   (exact) has lane (c, kg) holding channel-row c for tokens 4 kg .. 4 kg + 3, the A layout.  Two 16-token tiles feed
+//   one 32-deep product.  The zero points and scales ride along as a 4-channel V.  P is rounded to fp16 once and that
+//   rounded value is used for the row sum as well.
+//   Keys grouped over 128 tokens per channel have no channel groups; the token group's scales fold into the q operand,
+//   carried as fp16 rounded product + exact remainder (two products per step), rebuilt for every 64 tokens in flight.
 //
-// Column budget: (group, head) columns come 16 to a pass of the score product, heads padded to 4, 8 or 16 where
-// the keys have channel groups (idle columns cost nothing).  One pass serves int4 keys (2 groups) with up to 8
-// heads per KV head and int8 keys (4 groups) with up to 4; two passes (a second q operand and selector, summed
-// before the softmax) int8 keys with up to 8 heads and int4 keys with up to 16; four passes (one per group, the
-// instantiation for 16 heads runs two waves per SIMD and has the registers for four q operands) int8 keys with up
-// to 16.  fp16 / bf16 and keys grouped over tokens take any count up to 16.  More heads per KV head are cut into
-// blocks of 16, one workgroup and one pass over the bytes per block (measured, 64 q / 4 kv heads, int8 keys: one
-// block of 16 heads 5.8 TB/s of stored bytes against 4.0 as two blocks of 8).  Launches where the vector kernel is
-// as fast or faster (two heads per KV head of one format) stay on the vector kernel.
+// Bound: the memory system.  With every product taken out (same copies, same LDS reads) 8 x 64K tokens of K int8 / V int4
+// take the same 81 us for 64 / 4 heads, 16 ragged sequences of K int4 / V4c 182 us (187 with them).  What matters is
+// what keeps the copies fed and how the work is cut: 64 q / 4 kv heads, K int8 / V int4 110.3 -> 83.7 us per step
+// (before: four score passes against zero-padded operands, one per group, 228 registers), 32 / 8 at 128K tokens
+// 48.3 -> 44.6, block-sparse recall 129.5 -> 123.2; the error against 64 bits is a half of what rounding dequantized
+// values gave.  More heads per KV head than 16 are cut into blocks of 16, one workgroup and one pass over the bytes per
+// block.
 #include "ttkv_attn_dev.h"
 
 #include <algorithm>
@@ -105,7 +96,7 @@ constexpr int chan(int s, int i) {
     return 8 * (s / 2) + ((s % 2) ? (i < 2 ? 2 + 4 * i : 3 + 4 * (i - 2)) : (i < 2 ? 4 * i : 1 + 4 * (i - 2)));
   return 4 * s + i;
 }
-// A lane's 32 channels of a row are the 16-byte pieces kg, kg + 4, ... of it (piece x of the lane = bytes
+// A lane's 32 channels of a value row are the 16-byte pieces kg, kg + 4, ... of it (piece x of the lane = bytes
 // [64 x + 16 kg, + 16) of the row), so that every load instruction of a tile reads 64 contiguous bytes per row
 // (measured on a load-only kernel: 6.3 TB/s, against 5.3 TB/s when a lane's pieces are adjacent).  Element j
 // of the lane's slice (j = 4 s + i in unpack order for fp16 / bf16 / int8) is therefore row channel:
@@ -114,6 +105,15 @@ __device__ __forceinline__ constexpr int slice_channel(int kg, int j) {
   if (is_i4<F>()) return 32 * kg + j;                                     // one piece of 32 channels
   if (F == TTKV_I8_SYM_G32) return 64 * (j / 16) + 16 * kg + j % 16;      // two pieces of 16
   return 32 * (j / 8) + 8 * kg + j % 8;                                   // four pieces of 8
+}
+// Key rows with channel groups are sliced so that a 32-deep step stays inside one group: the lane takes 8 bytes of
+// each 32-byte stretch, bytes [32 x + 8 kg, + 8): int8 channels 32 x + 8 kg .. (group x, step x), int4 channels
+// 64 x + 16 kg .. (group x, steps 2 x and 2 x + 1).
+template <int F>
+__device__ __forceinline__ constexpr int key_channel(int kg, int j) {
+  if (F == TTKV_I4_ASYM_G64) return 64 * (j / 16) + 16 * kg + j % 16;
+  if (F == TTKV_I8_SYM_G32) return 32 * (j / 8) + 8 * kg + j % 8;
+  return slice_channel<F>(kg, j);
 }
 // Splice offset carried by k-value i of a step.
 template <int F>
@@ -128,7 +128,9 @@ constexpr float k_offset(int i) {
 // operand layout.  Inside LDS row r keeps its pieces in the order p ^ swz(r), which makes the 16 rows that the
 // lanes of one piece read at a time fall into 16 different bank groups; the copy realises the order by choosing
 // which piece each lane fetches.
-constexpr int kTileRowsLds = 8 * 1024, kTileLds = kTileRowsLds + 4 * 256;   // per wave: K rows, V rows, 4 planes of meta words
+// Per wave: K rows, V rows, and two buffers of four planes of meta words (K words 0 and 1 of the batch's tokens, V words
+// 0 and 1), used in turn: a batch's meta words stay readable while the next batch arrives.
+constexpr int kMetaLds = 4 * 256, kTileRowsLds = 8 * 1024, kTileLds = kTileRowsLds + 2 * kMetaLds;
 typedef const __attribute__((address_space(1))) void *gas_ptr;
 typedef __attribute__((address_space(3))) void *las_ptr;
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
@@ -147,28 +149,6 @@ __device__ __forceinline__ void wait_vmcnt() {
 }
 // LDS reads of a landed half and the wait for them as one block (no use of a result can be scheduled in between;
 // the reads are opaque to the compiler, which would otherwise wait for every copy in flight before an LDS read).
-// A batch is 32 tokens = two tiles.  Rows: int8 w[0..3] = tile 0 piece x = 0, 1 (a0, a1), tile 1 likewise, 2 KiB
-// further; int4 w[0..1] = the lane's one piece of tile 0, 1 (a0, 1 KiB further).  Meta: tile tt's two words from
-// m0 + 64 tt and m0 + 256 + 64 tt.
-__device__ __forceinline__ void lds_half_i4x2(uint32_t a0, uint32_t m0, u32x4 *w, uint32_t *m) {
-  asm volatile("ds_read_b128 %0, %6\n\tds_read_b128 %1, %6 offset:1024\n\t"
-               "ds_read_b32 %2, %7\n\tds_read_b32 %3, %7 offset:256\n\tds_read_b32 %4, %7 offset:64\n\t"
-               "ds_read_b32 %5, %7 offset:320\n\ts_waitcnt lgkmcnt(0)"
-               : "=&v"(w[0]), "=&v"(w[1]), "=&v"(m[0]), "=&v"(m[1]), "=&v"(m[2]), "=&v"(m[3])
-               : "v"(a0), "v"(m0) : "memory");
-}
-// a batch of 64 tokens = four tiles: w[tt] = the lane's one piece of tile tt (a0, 1 KiB apart); meta: tile tt's two
-// words from m0 + 64 tt and m0 + 256 + 64 tt
-__device__ __forceinline__ void lds_half_i4x4(uint32_t a0, uint32_t m0, u32x4 *w, uint32_t *m) {
-  asm volatile("ds_read_b128 %0, %12\n\tds_read_b128 %1, %12 offset:1024\n\tds_read_b128 %2, %12 offset:2048\n\t"
-               "ds_read_b128 %3, %12 offset:3072\n\t"
-               "ds_read_b32 %4, %13\n\tds_read_b32 %5, %13 offset:256\n\tds_read_b32 %6, %13 offset:64\n\t"
-               "ds_read_b32 %7, %13 offset:320\n\tds_read_b32 %8, %13 offset:128\n\tds_read_b32 %9, %13 offset:384\n\t"
-               "ds_read_b32 %10, %13 offset:192\n\tds_read_b32 %11, %13 offset:448\n\ts_waitcnt lgkmcnt(0)"
-               : "=&v"(w[0]), "=&v"(w[1]), "=&v"(w[2]), "=&v"(w[3]), "=&v"(m[0]), "=&v"(m[1]), "=&v"(m[2]), "=&v"(m[3]),
-                 "=&v"(m[4]), "=&v"(m[5]), "=&v"(m[6]), "=&v"(m[7])
-               : "v"(a0), "v"(m0) : "memory");
-}
 // fp16 / bf16: w[4 tt + x] = piece x of the lane of tile tt, from ax (tile 1: 4 KiB further); no meta words.
 __device__ __forceinline__ void lds_half_fp(uint32_t a0, uint32_t a1, uint32_t a2, uint32_t a3, u32x4 *w) {
   asm volatile("ds_read_b128 %0, %8\n\tds_read_b128 %1, %9\n\tds_read_b128 %2, %10\n\tds_read_b128 %3, %11\n\t"
@@ -177,26 +157,76 @@ __device__ __forceinline__ void lds_half_fp(uint32_t a0, uint32_t a1, uint32_t a
                : "=&v"(w[0]), "=&v"(w[1]), "=&v"(w[2]), "=&v"(w[3]), "=&v"(w[4]), "=&v"(w[5]), "=&v"(w[6]), "=&v"(w[7])
                : "v"(a0), "v"(a1), "v"(a2), "v"(a3) : "memory");
 }
-__device__ __forceinline__ void lds_half_i8(uint32_t a0, uint32_t a1, uint32_t m0, u32x4 *w, uint32_t *m) {
-  asm volatile("ds_read_b128 %0, %8\n\tds_read_b128 %1, %9\n\tds_read_b128 %2, %8 offset:2048\n\t"
-               "ds_read_b128 %3, %9 offset:2048\n\t"
-               "ds_read_b32 %4, %10\n\tds_read_b32 %5, %10 offset:256\n\tds_read_b32 %6, %10 offset:64\n\t"
-               "ds_read_b32 %7, %10 offset:320\n\ts_waitcnt lgkmcnt(0)"
-               : "=&v"(w[0]), "=&v"(w[1]), "=&v"(w[2]), "=&v"(w[3]), "=&v"(m[0]), "=&v"(m[1]), "=&v"(m[2]), "=&v"(m[3])
-               : "v"(a0), "v"(a1), "v"(m0) : "memory");
+// int8 key rows: w[4 tt + x] = the lane's 8 bytes of group x of tile tt, from ax (tile 1: 2 KiB further).
+__device__ __forceinline__ void lds_keys_i8(uint32_t a0, uint32_t a1, uint32_t a2, uint32_t a3, u32x2 *w) {
+  asm volatile("ds_read_b64 %0, %8\n\tds_read_b64 %1, %9\n\tds_read_b64 %2, %10\n\tds_read_b64 %3, %11\n\t"
+               "ds_read_b64 %4, %8 offset:2048\n\tds_read_b64 %5, %9 offset:2048\n\t"
+               "ds_read_b64 %6, %10 offset:2048\n\tds_read_b64 %7, %11 offset:2048\n\ts_waitcnt lgkmcnt(0)"
+               : "=&v"(w[0]), "=&v"(w[1]), "=&v"(w[2]), "=&v"(w[3]), "=&v"(w[4]), "=&v"(w[5]), "=&v"(w[6]), "=&v"(w[7])
+               : "v"(a0), "v"(a1), "v"(a2), "v"(a3) : "memory");
 }
+// int4 key rows: w[2 tt + x] = the lane's 8 bytes of group x of tile tt, from ax (tiles 1 KiB apart).
+__device__ __forceinline__ void lds_keys_i4(uint32_t a0, uint32_t a1, u32x2 *w) {
+  asm volatile("ds_read_b64 %0, %8\n\tds_read_b64 %1, %9\n\tds_read_b64 %2, %8 offset:1024\n\tds_read_b64 %3, %9 offset:1024\n\t"
+               "ds_read_b64 %4, %8 offset:2048\n\tds_read_b64 %5, %9 offset:2048\n\t"
+               "ds_read_b64 %6, %8 offset:3072\n\tds_read_b64 %7, %9 offset:3072\n\ts_waitcnt lgkmcnt(0)"
+               : "=&v"(w[0]), "=&v"(w[1]), "=&v"(w[2]), "=&v"(w[3]), "=&v"(w[4]), "=&v"(w[5]), "=&v"(w[6]), "=&v"(w[7])
+               : "v"(a0), "v"(a1) : "memory");
+}
+// Value rows, transposed on the way out of LDS (ds_read_b64_tr_*: the 16 lanes of one kg give the addresses of 16
+// stretches of 8 bytes, i.e. of 16 rows x 16 nibbles or 8 rows x 16 bytes, and lane c receives column c of that block).
+// int4, 64 tokens: lane L of the 16 names token 32 (L / 8) + kTok[L % 8] + 4 kg; block s of 16 channels is 8 bytes of
+// the row; w[s] = the lane's channel, x: tokens of tiles 0 and 1, y: of tiles 2 and 3.
+__device__ __forceinline__ void lds_values_i4x4(uint32_t a0, uint32_t a1, uint32_t a2, uint32_t a3, u32x2 *w) {
+  asm volatile("ds_read_b64_tr_b4 %0, %8\n\tds_read_b64_tr_b4 %1, %8 offset:8\n\tds_read_b64_tr_b4 %2, %9\n\t"
+               "ds_read_b64_tr_b4 %3, %9 offset:8\n\tds_read_b64_tr_b4 %4, %10\n\tds_read_b64_tr_b4 %5, %10 offset:8\n\t"
+               "ds_read_b64_tr_b4 %6, %11\n\tds_read_b64_tr_b4 %7, %11 offset:8\n\ts_waitcnt lgkmcnt(0)"
+               : "=&v"(w[0]), "=&v"(w[1]), "=&v"(w[2]), "=&v"(w[3]), "=&v"(w[4]), "=&v"(w[5]), "=&v"(w[6]), "=&v"(w[7])
+               : "v"(a0), "v"(a1), "v"(a2), "v"(a3) : "memory");
+}
+// int4, 32 tokens: lane L names token kTok[L % 8] + 4 kg and block 2 q + L / 8; w[q] = blocks 2 q (x) and 2 q + 1 (y).
+__device__ __forceinline__ void lds_values_i4x2(uint32_t a0, uint32_t a1, uint32_t a2, uint32_t a3, u32x2 *w) {
+  asm volatile("ds_read_b64_tr_b4 %0, %4\n\tds_read_b64_tr_b4 %1, %5\n\tds_read_b64_tr_b4 %2, %6\n\t"
+               "ds_read_b64_tr_b4 %3, %7\n\ts_waitcnt lgkmcnt(0)"
+               : "=&v"(w[0]), "=&v"(w[1]), "=&v"(w[2]), "=&v"(w[3]) : "v"(a0), "v"(a1), "v"(a2), "v"(a3) : "memory");
+}
+// int8, 32 tokens: lane L names token (L / 2) % 4 + 16 (L / 8) + 4 kg, bytes 8 (L % 2) of block s; w[s] = the lane's
+// channel of block s, tokens 4 kg .. of tile 0 (x) and of tile 1 (y).  Four blocks.
+__device__ __forceinline__ void lds_values_i8(uint32_t a0, uint32_t a1, uint32_t a2, uint32_t a3, u32x2 *w) {
+  asm volatile("ds_read_b64_tr_b8 %0, %4\n\tds_read_b64_tr_b8 %1, %5\n\tds_read_b64_tr_b8 %2, %6\n\t"
+               "ds_read_b64_tr_b8 %3, %7\n\ts_waitcnt lgkmcnt(0)"
+               : "=&v"(w[0]), "=&v"(w[1]), "=&v"(w[2]), "=&v"(w[3]) : "v"(a0), "v"(a1), "v"(a2), "v"(a3) : "memory");
+}
+// channel-major values: the lane's pieces, 1 KiB apart
+template <int NT>
+__device__ __forceinline__ void lds_pieces(uint32_t a0, u32x4 *w) {
+  if constexpr (NT == 4)
+    asm volatile("ds_read_b128 %0, %4\n\tds_read_b128 %1, %4 offset:1024\n\tds_read_b128 %2, %4 offset:2048\n\t"
+                 "ds_read_b128 %3, %4 offset:3072\n\ts_waitcnt lgkmcnt(0)"
+                 : "=&v"(w[0]), "=&v"(w[1]), "=&v"(w[2]), "=&v"(w[3]) : "v"(a0) : "memory");
+  else
+    asm volatile("ds_read_b128 %0, %2\n\tds_read_b128 %1, %2 offset:1024\n\ts_waitcnt lgkmcnt(0)"
+                 : "=&v"(w[0]), "=&v"(w[1]) : "v"(a0) : "memory");
+}
+// The two meta words of four consecutive tokens of two tiles: m[2 u + w] = words w of tile u, from a0 (tile 1: 64
+// bytes further, words 1 one plane further); lanes of one kg read the same addresses.
+__device__ __forceinline__ void lds_meta(uint32_t a0, u32x4 *m) {
+  asm volatile("ds_read_b128 %0, %4\n\tds_read_b128 %1, %4 offset:256\n\tds_read_b128 %2, %4 offset:64\n\t"
+               "ds_read_b128 %3, %4 offset:320\n\ts_waitcnt lgkmcnt(0)"
+               : "=&v"(m[0]), "=&v"(m[1]), "=&v"(m[2]), "=&v"(m[3]) : "v"(a0) : "memory");
+}
+// fp16 halves of a meta word
+__device__ __forceinline__ float half0(uint32_t w) { return (float)as_h2(w).x; }
+__device__ __forceinline__ float half1(uint32_t w) { return (float)as_h2(w).y; }
 
-// GT: query heads per KV head, padded to 4, 8 or 16, as a compile-time constant (quantized K: the column layout
-// and the group sum below depend on it; columns of heads beyond the real count stay zero), or 0 to take the real
-// count from the arguments (fp16 / bf16 / keys grouped over tokens: any count up to 16).
-template <int KF, int VF, int GT>
+// Any number of query heads up to 16 (the columns of both products).
+template <int KF, int VF>
 __device__ __forceinline__ void process_mfma(const FusedArgs &a, const TierView &tv, const Entry &en, const int32_t *sel,
                                              int chunk_tokens, int chunk, int seq, int hq0, int Gr, int hkv, char *s_buf,
                                              float (*s_m)[16], float (*s_l)[16]) {
   // sel: null, or the block ids behind a run made of selected blocks (ring block of token i: sel[i / bt])
   // hq0, Gr: first query head and number of heads of this workgroup's block of heads (all heads of the KV head,
-  // or a block of up to 8 / 16 of them)
-  const int G = GT ? GT : Gr;              // heads per group block of columns
+  // or a block of up to 16 of them)
   using FK = Fmt<KF>;
   using FV = Fmt<VF>;
   constexpr int NLK = FK::ROWB / 64, NLV = FV::ROWB / 64;   // 16-byte loads per lane per 16-token tile
@@ -216,7 +246,8 @@ __device__ __forceinline__ void process_mfma(const FusedArgs &a, const TierView 
   constexpr bool KQ = NGK > 1, VQ = NGV > 1;
   constexpr bool KT = KF == TTKV_I4_ASYM_T128;   // keys grouped over 128 tokens per channel: the scales fold into q
   constexpr bool KBF = KF == TTKV_BF16, VBF = VF == TTKV_BF16;
-  constexpr bool VT = VF == TTKV_I4_ASYM_G64_T32;   // values channel-major per 32 tokens: no dequantization, no transposition
+  constexpr bool VT = VF == TTKV_I4_ASYM_G64_T32;   // values stored channel-major per 32 tokens
+  constexpr bool V4 = PF && VF != TTKV_I8_SYM_G32;  // 4-bit codes as operand words (VT: as they lie; else transposed out of LDS)
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n = lane & 15, kg = lane >> 4;
@@ -226,28 +257,18 @@ __device__ __forceinline__ void process_mfma(const FusedArgs &a, const TierView 
   const int ring_tokens = tv.ring_blocks * tv.bt;
   const float cs = a.scale * kLog2e;       // scores are kept in the log2 domain
 
-  // (group, head) columns: groups x heads of them, 16 per pass of the score product (NP = 2 when they exceed
-  // one tile: int8 keys with 8 heads, int4 keys with 16; NP = 4: int8 keys with 16 heads).  Column n of pass pp is group (16 pp + n) / G of head n % G.
-  constexpr int NP = KQ ? (NGK * GT + 15) / 16 : 1;
-  const int g = n % G;                                   // head of this column
-  int gam[NP];                                           // K group of this column, per pass
-  bool col_on[NP];
-#pragma unroll
-  for (int pp = 0; pp < NP; ++pp) {
-    gam[pp] = KQ ? min((16 * pp + n) / G, NGK - 1) : 0;
-    col_on[pp] = 16 * pp + n < NGK * G && g < Gr;
-  }
+  const bool col_on = n < Gr;   // column = query head
 
-  // ---- q operand: 16 packed registers (step s: 2s, 2s+1), offset sum and plain sum of the column.  Element j
-  // of the lane's slice enters only if its channel lies in the column's group.
-  uint32_t qB[NP][16];
-  float off[NP], qs[NP];
+  // ---- q operand: 16 packed registers (step s: 4 s .. 4 s + 3); per channel group of the keys the sum that the
+  // splice offsets add to the products (it leaves with their initial value) and the plain sum (for the zero points).
+  uint32_t qB[16];
+  float off[NGK], qs[NGK];
   {
-    const uint4 *qrow = (const uint4 *)((const uint16_t *)a.q + ((int64_t)seq * a.Hq + hq0 + min(g, Gr - 1)) * 128);
+    const uint4 *qrow = (const uint4 *)((const uint16_t *)a.q + ((int64_t)seq * a.Hq + hq0 + min(n, Gr - 1)) * 128);
     uint32_t qw[16];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {     // 8 channels per 16-byte load
-      const uint4 w = qrow[slice_channel<KF>(kg, 8 * i) / 8];
+      const uint4 w = qrow[key_channel<KF>(kg, 8 * i) / 8];
       qw[4 * i] = w.x; qw[4 * i + 1] = w.y; qw[4 * i + 2] = w.z; qw[4 * i + 3] = w.w;
     }
     if constexpr (!KBF) {
@@ -261,35 +282,31 @@ __device__ __forceinline__ void process_mfma(const FusedArgs &a, const TierView 
       }
     }
     // Register r of the operand pairs with register r of unpack16: elements (2r, 2r+1) of the slice, or for int4
-    // (r = 4d + e) elements (8d + e, 8d + e + 4).  Both elements of a register lie in the same group.
+    // (r = 4d + e) elements (8d + e, 8d + e + 4).
     const h2 ones = {(_Float16)1.0f, (_Float16)1.0f};
+    float se[NGK], so[NGK];   // sums over the registers that carry splice offset 1024 / 64 (int4: even / odd)
 #pragma unroll
-    for (int pp = 0; pp < NP; ++pp) {
-      float se = 0.0f, so = 0.0f;   // sums over the registers that carry splice offset 1024 / 64 (int4: even / odd)
+    for (int gr = 0; gr < NGK; ++gr) se[gr] = so[gr] = 0.0f;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        uint32_t w;
-        int j0;   // first element of the register
-        if constexpr (is_i4<KF>()) {
-          const int dd = r / 4, e = r % 4;
-          j0 = 8 * dd + e;
-          w = __builtin_amdgcn_perm(qw[4 * dd + 2 + e / 2], qw[4 * dd + e / 2], (e & 1) ? 0x07060302u : 0x05040100u);
-        } else {
-          j0 = 2 * r;
-          w = qw[r];
-        }
-        const bool on = col_on[pp] && slice_channel<KF>(kg, j0) / (128 / NGK) == gam[pp];
-        qB[pp][r] = on ? w : 0u;
-        if constexpr (KQ) {   // quantized keys are dotted with fp16 queries
-          if ((r & 1) && KF == TTKV_I4_ASYM_G64) so = __builtin_amdgcn_fdot2(as_h2(qB[pp][r]), ones, so, false);
-          else se = __builtin_amdgcn_fdot2(as_h2(qB[pp][r]), ones, se, false);
-        }
+    for (int r = 0; r < 16; ++r) {
+      uint32_t w = qw[r];
+      if constexpr (is_i4<KF>()) {
+        const int dd = r / 4, e = r % 4;
+        w = __builtin_amdgcn_perm(qw[4 * dd + 2 + e / 2], qw[4 * dd + e / 2], (e & 1) ? 0x07060302u : 0x05040100u);
       }
-      qs[pp] = se + so;
-      off[pp] = KF == TTKV_I4_ASYM_G64 ? fmaf(1024.0f, se, 64.0f * so) : k_offset<KF>(0) * se;
-      // the column's group is spread over the channel slices of several lanes; the others contributed zero
-      off[pp] += __shfl_xor(off[pp], 16); off[pp] += __shfl_xor(off[pp], 32);
-      qs[pp] += __shfl_xor(qs[pp], 16);   qs[pp] += __shfl_xor(qs[pp], 32);
+      qB[r] = col_on ? w : 0u;
+      if constexpr (KQ) {   // quantized keys are dotted with fp16 queries
+        const int gr = r / (16 / NGK);
+        if ((r & 1) && KF == TTKV_I4_ASYM_G64) so[gr] = __builtin_amdgcn_fdot2(as_h2(qB[r]), ones, so[gr], false);
+        else se[gr] = __builtin_amdgcn_fdot2(as_h2(qB[r]), ones, se[gr], false);
+      }
+    }
+#pragma unroll
+    for (int gr = 0; gr < NGK; ++gr) {   // over the four channel slices
+      qs[gr] = se[gr] + so[gr];
+      off[gr] = KF == TTKV_I4_ASYM_G64 ? fmaf(1024.0f, se[gr], 64.0f * so[gr]) : k_offset<KF>(0) * se[gr];
+      off[gr] += __shfl_xor(off[gr], 16); off[gr] += __shfl_xor(off[gr], 32);
+      qs[gr] += __shfl_xor(qs[gr], 16);   qs[gr] += __shfl_xor(qs[gr], 32);
     }
   }
 
@@ -297,50 +314,19 @@ __device__ __forceinline__ void process_mfma(const FusedArgs &a, const TierView 
   const uint32_t one = VBF ? 0x3F80u : 0x3C00u;
   const uint32_t id0 = (n == 4 * kg ? one : 0u) | (n == 4 * kg + 1 ? one << 16 : 0u);
   const uint32_t id1 = (n == 4 * kg + 2 ? one : 0u) | (n == 4 * kg + 3 ? one << 16 : 0u);
-  // Selection operands that bring a token's four fp16 meta values (scale, zero per group) into the
-  // score layout: with the meta words as A operand, k-values 0..3 of the kg = 0 lanes, the product
-  // with a 0/1 column selector is exactly the scale (or zero) of the column's group, per token.
-  uint32_t bs0[NP], bs1[NP], bz0[NP], bz1[NP];
-#pragma unroll
-  for (int pp = 0; pp < NP; ++pp) {
-    bs0[pp] = bs1[pp] = bz0[pp] = bz1[pp] = 0;
-    if (KQ && kg == 0) {
-      const int ss = KF == TTKV_I4_ASYM_G64 ? 2 * gam[pp] : gam[pp];
-      bs0[pp] = ss == 0 ? 0x3C00u : (ss == 1 ? 0x3C000000u : 0u);
-      bs1[pp] = ss == 2 ? 0x3C00u : (ss == 3 ? 0x3C000000u : 0u);
-      if (KF == TTKV_I4_ASYM_G64) {
-        bz0[pp] = gam[pp] == 0 ? 0x3C000000u : 0u;
-        bz1[pp] = gam[pp] == 1 ? 0x3C000000u : 0u;
-      }
-    }
-  }
-  // VT: 0/1 selectors of the token's V meta value number v = 0..3 (s0, z0, s1, z1) for every column at once
-  uint32_t vm_sel[4][2];
-#pragma unroll
-  for (int v = 0; v < 4; ++v) {
-    vm_sel[v][0] = (VT && kg == 0 && v < 2) ? (v == 0 ? 0x3C00u : 0x3C000000u) : 0u;
-    vm_sel[v][1] = (VT && kg == 0 && v >= 2) ? (v == 2 ? 0x3C00u : 0x3C000000u) : 0u;
-  }
-  // byte selectors that duplicate the fp16 scale of the group of this lane's piece x out of the V meta words:
-  // int4 (s0, z0, s1, z1): one piece, group kg / 2; int8 (s0, s1, s2, s3): piece x lies in group 2 x + kg / 2
-  uint32_t vsel[2];
-#pragma unroll
-  for (int x = 0; x < 2; ++x) {
-    const uint32_t vh = VF == TTKV_I4_ASYM_G64 ? (kg >> 1) * 2 : 2 * x + (kg >> 1);
-    vsel[x] = (2 * vh) | ((2 * vh + 1) << 8) | ((2 * vh) << 16) | ((2 * vh + 1) << 24);
-  }
+  // byte selector that duplicates the fp16 scale of group kg / 2 of this lane's piece out of the V meta words
+  // (s0, z0, s1, z1): the values beside keys grouped over tokens are dequantized row by row
+  const uint32_t vh = (kg >> 1) * 2;
+  const uint32_t vsel = (2 * vh) | ((2 * vh + 1) << 8) | ((2 * vh) << 16) | ((2 * vh + 1) << 24);
   // minus (splice offset + centre) as packed fp16 pairs: int4 -(1024 + 8), -(64 + 8); int8 -(1024 + 128)
   uint32_t no_a = 0xE408E408u, no_b = 0xD480D480u, no_c = 0xE480E480u;
   asm volatile("" : "+s"(no_a), "+s"(no_b), "+s"(no_c));
 
   const f4 zero4 = f4{0.0f, 0.0f, 0.0f, 0.0f};
   f4 acc[8], accz = zero4;
-  f4 accoff[VT ? 2 : 1];          // VT: sum_t B_g[t] * (splice offset of t's nibble position + 8), per channel group
-  float zs[2] = {0.0f, 0.0f};     // VT: sum_t p_t (z_{t,g} + 8 s_{t,g})
+  float zs[2] = {0.0f, 0.0f};     // V4: sum_t p_t (z_{t,g} + 8 s_{t,g})
 #pragma unroll
   for (int s = 0; s < 8; ++s) acc[s] = zero4;
-#pragma unroll
-  for (int g2 = 0; g2 < (VT ? 2 : 1); ++g2) accoff[g2] = zero4;
   float m = -INFINITY, l = 0.0f;
 
   Splice sp;
@@ -348,7 +334,8 @@ __device__ __forceinline__ void process_mfma(const FusedArgs &a, const TierView 
 
   struct TileRegs {
     uint4 kw[NT][NLK], vw[NT][NLV];
-    uint2 kmeta[NT], vmeta[NT];
+    uint32_t vop[NT / 2][8][VF == TTKV_I8_SYM_G32 ? 2 : 1];   // PF: codes of channel 16 s + n, the pair's 8 tokens of this kg
+    uint2 vmeta[NT];
     uint4 gm[KT ? 8 : 1];   // KT: {scale, zero} of the lane's 32 channels for the token group of these tiles
   };
   const uint32_t kdoff = n * FK::ROWB + kg * 16, vdoff = n * FV::ROWB + kg * 16;
@@ -373,7 +360,7 @@ __device__ __forceinline__ void process_mfma(const FusedArgs &a, const TierView 
     constexpr bool FULL = decltype(full_tag)::value;
     int row0;
     const uint8_t *head = locate(i0, row0);
-    const uint8_t *kb = head + row0 * FK::ROWB, *kmb = head + tv.k_meta_off + row0 * 8;
+    const uint8_t *kb = head + row0 * FK::ROWB;
     const uint8_t *vb = head + tv.v_off + row0 * FV::ROWB, *vmb = head + tv.v_meta_off + row0 * 8;
     if constexpr (KT) {   // the 64 tokens in flight lie inside one aligned group of 128: its 128 meta rows x 4 B
       const uint4 *gp = (const uint4 *)(head + tv.k_meta_off + (row0 & ~127) * 4 + kg * 128);
@@ -387,46 +374,50 @@ __device__ __forceinline__ void process_mfma(const FusedArgs &a, const TierView 
       const uint32_t vo = FULL ? vdoff + tt * 16 * FV::ROWB : row * FV::ROWB + kg * 16;
 #pragma unroll
       for (int x = 0; x < NLK; ++x) t.kw[tt][x] = *(const uint4 *)(kb + ko + 64 * x);
-      if constexpr (VT) {
-        // piece hh = tt % 2 of the 32-token group tt / 2 (a group past the end re-reads the last live one):
-        // lane L's piece is number 64 hh + L of the group's 2 KiB
-        const uint32_t grp = FULL ? tt / 2 : min(tt / 2, (nv - 1) / 32);
-        t.vw[tt][0] = *(const uint4 *)(vb + grp * 2048 + (tt & 1) * 1024 + lane * 16);
-      } else {
 #pragma unroll
-        for (int x = 0; x < NLV; ++x) t.vw[tt][x] = *(const uint4 *)(vb + vo + 64 * x);
-      }
-      if constexpr (KQ) t.kmeta[tt] = *(const uint2 *)(kmb + row * 8);
+      for (int x = 0; x < NLV; ++x) t.vw[tt][x] = *(const uint4 *)(vb + vo + 64 * x);
       if constexpr (VQ) t.vmeta[tt] = *(const uint2 *)(vmb + row * 8);
     }
   };
 
   // ---- PF: the same rows as asynchronous copies into the wave's LDS and reads from there.
-  // LDS of the wave: K rows at 0, V rows at 4 KiB (row r at r ROWB, its piece p at 16 (p ^ swz(r))), then four
-  // planes of 64 meta words: K words 0 and 1 of the batch's tokens, V words 0 and 1.
+  // LDS of the wave: K rows at 0, V rows at 4 KiB (row r at r ROWB, its piece p at 16 (p ^ swz(r))), then the two
+  // buffers of meta planes.
   constexpr int PK = FK::ROWB / 16, PV = FV::ROWB / 16;              // pieces per row
   constexpr int NDK = TT * FK::ROWB / 1024, NDV = TT * FV::ROWB / 1024;   // copy instructions of 1 KiB per half
   constexpr int N_K = NDK + 2, N_V = NDV + 2;                          // with the two meta planes
   static_assert(!PF || PF64 || (NT == 2 && ((PK == 8 && NDK == 4) || (PK == 4 && NDK == 2)) && (NDV == 4 || NDV == 2)),
                 "the batch the LDS readers cover");
   auto swz = [](int pieces, int r) { return pieces == 4 ? (r >> 2) & 3 : (r >> 1) & 7; };
-  // per-lane byte offset of copy instruction j inside a full batch, minus j KiB (even and odd j differ for 8 pieces)
-  uint32_t dko[2], dvo[2];
+  // value rows: also different for the rows that the lanes of a transposing read name in different tiles
+  auto swzv = [](int pieces, int r) { return pieces == 4 ? ((r >> 2) ^ (r >> 4)) & 3 : ((r >> 1) & 7) ^ ((r >> 3) & 2); };
+  // per-lane byte offset of copy instruction j inside a full batch, minus j KiB: keys even and odd j differ for 8
+  // pieces, values by an exchange of pieces (their rows' order is that of j = 0 with vx(j) added by exclusive or)
+  uint32_t dko[2];
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
-    const int rk = j * (64 / PK) + lane / PK, rv = j * (64 / PV) + lane / PV;
+    const int rk = j * (64 / PK) + lane / PK;
     dko[j] = rk * FK::ROWB + ((lane % PK) ^ swz(PK, rk)) * 16 - j * 1024;
-    dvo[j] = rv * FV::ROWB + ((lane % PV) ^ swz(PV, rv)) * 16 - j * 1024;
   }
+  const uint32_t dvo = lane / PV * FV::ROWB + ((lane % PV) ^ swzv(PV, lane / PV)) * 16;
+  constexpr auto vx = [](int j) { return PV == 4 ? j * 16 : (j & 1) * 64 + (j >> 1) * 32; };
   const uint32_t lds0 = (uint32_t)(uintptr_t)(las_ptr)wbuf;
-  // where lane (n, kg) finds its piece kg (and kg + 4) of row n of tile 0
-  auto piece_addr = [&](int pieces, int rowb, int x) -> uint32_t {
-    return n * rowb + (((kg + 4 * x) ^ swz(pieces, n)) * 16);
-  };
-  const uint32_t lka0 = lds0 + piece_addr(PK, FK::ROWB, 0), lka1 = lds0 + piece_addr(PK, FK::ROWB, PK == 8 ? 1 : 0);
-  const uint32_t lva0 = VT ? lds0 + 4096 + lane * 16 : lds0 + 4096 + piece_addr(PV, FV::ROWB, 0);
-  const uint32_t lva1 = lds0 + 4096 + piece_addr(PV, FV::ROWB, PV == 8 ? 1 : 0);
-  const uint32_t lkm = lds0 + kTileRowsLds + n * 4, lvm = lkm + 512;
+  // the lane's 8 bytes of the 32-byte stretch x of row n: half kg % 2 of piece 2 x + kg / 2
+  uint32_t lka[4];
+#pragma unroll
+  for (int x = 0; x < 4; ++x) {
+    const int p = (2 * x) % PK + (kg >> 1);
+    lka[x] = lds0 + n * FK::ROWB + ((p ^ swz(PK, n)) * 16) + 8 * (kg & 1);
+  }
+  // what the lane names to the transposing value reads: its row's first piece (the others by exclusive or with 16 x piece)
+  uint32_t lva = lds0 + 4096 + lane * 16;
+  if constexpr (PF && !VT) {
+    const int r4 = 2 * (n & 1) + 16 * ((n >> 1) & 1) + ((n >> 2) & 1) + 4 * kg;   // kTok[n % 8] + 4 kg
+    const int row = PV == 8 ? ((n >> 1) & 3) + 16 * (n >> 3) + 4 * kg : PF64 ? r4 + 32 * (n >> 3) : r4;
+    const int half = PV == 8 ? n & 1 : PF64 ? 0 : n >> 3;
+    lva = lds0 + 4096 + row * FV::ROWB + swzv(PV, row) * 16 + 8 * half;
+  }
+  uint32_t meta_in = 0, meta_cur = 0;   // meta buffer (byte offset) of the batch being issued / computed
   const uint8_t *nx_head = nullptr;   // batch whose K half was issued last
   int nx_row0 = 0, nx_nv = 0;
   auto issue_k = [&](int i0) {
@@ -446,8 +437,8 @@ __device__ __forceinline__ void process_mfma(const FusedArgs &a, const TierView 
       }
     }
     const uint32_t mo = min(lane, nx_nv - 1) * 8;   // one lane per token (TT = 32: the upper lanes repeat the last row)
-    dma4(kmb + mo, wbuf + kTileRowsLds);
-    dma4(kmb + mo + 4, wbuf + kTileRowsLds + 256);
+    dma4(kmb + mo, wbuf + kTileRowsLds + meta_in);
+    dma4(kmb + mo + 4, wbuf + kTileRowsLds + meta_in + 256);
   };
   auto issue_v = [&]() {
     const uint8_t *vb = nx_head + tv.v_off + nx_row0 * FV::ROWB, *vmb = nx_head + tv.v_meta_off + nx_row0 * 8;
@@ -457,51 +448,107 @@ __device__ __forceinline__ void process_mfma(const FusedArgs &a, const TierView 
         dma16<2048>(vb + lane * 16, wbuf + 4096); dma16<3072>(vb + lane * 16, wbuf + 4096);
       }
     } else if (nx_nv == TT) {
-      dma16<0>(vb + dvo[0], wbuf + 4096); dma16<1024>(vb + dvo[1], wbuf + 4096);
+      dma16<0>(vb + dvo, wbuf + 4096); dma16<1024>(vb + (dvo ^ vx(1)), wbuf + 4096);
       if constexpr (NDV == 4) {
-        dma16<2048>(vb + dvo[0], wbuf + 4096); dma16<3072>(vb + dvo[1], wbuf + 4096);
+        dma16<2048>(vb + (dvo ^ vx(2)), wbuf + 4096); dma16<3072>(vb + (dvo ^ vx(3)), wbuf + 4096);
       }
     } else {
 #pragma unroll
       for (int j = 0; j < NDV; ++j) {
         const int r = j * (64 / PV) + lane / PV;
-        dma16(vb + min(r, nx_nv - 1) * FV::ROWB + ((lane % PV) ^ swz(PV, r)) * 16, wbuf + 4096 + j * 1024);
+        dma16(vb + min(r, nx_nv - 1) * FV::ROWB + ((lane % PV) ^ swzv(PV, r)) * 16, wbuf + 4096 + j * 1024);
       }
     }
     const uint32_t mo = min(lane, nx_nv - 1) * 8;
-    dma4(vmb + mo, wbuf + kTileRowsLds + 512);
-    dma4(vmb + mo + 4, wbuf + kTileRowsLds + 768);
+    dma4(vmb + mo, wbuf + kTileRowsLds + meta_in + 512);
+    dma4(vmb + mo + 4, wbuf + kTileRowsLds + meta_in + 768);
+    meta_in ^= kMetaLds;
+  };
+  // Rows in pinned host memory: the whole batch through registers into the same places (over PCIe the asynchronous
+  // copies were 3-4 % slower, and the streaming hint has nothing to gain there).  Lane (n, kg) moves piece kg (+ 4) of
+  // row n of every tile, one lane per token its meta words.
+  auto bring_host = [&](int i0) {
+    int row0;
+    const uint8_t *head = locate(i0, row0);
+    const int nv = min(TT, c1 - i0);
+    const uint8_t *kb = head + row0 * FK::ROWB, *vb = head + tv.v_off + row0 * FV::ROWB;
+    uint4 kw[NT][NLK], vw[NT][NLV];
+#pragma unroll
+    for (int tt = 0; tt < NT; ++tt) {
+      const uint32_t row = min(tt * 16 + n, nv - 1);   // rows past the end repeat the last live row
+#pragma unroll
+      for (int x = 0; x < NLK; ++x) kw[tt][x] = *(const uint4 *)(kb + row * FK::ROWB + kg * 16 + 64 * x);
+      if constexpr (VT) {
+        // piece hh = tt % 2 of the 32-token group tt / 2 (a group past the end repeats the last live one)
+        vw[tt][0] = *(const uint4 *)(vb + min(tt / 2, (nv - 1) / 32) * 2048 + (tt & 1) * 1024 + lane * 16);
+      } else {
+#pragma unroll
+        for (int x = 0; x < NLV; ++x) vw[tt][x] = *(const uint4 *)(vb + row * FV::ROWB + kg * 16 + 64 * x);
+      }
+    }
+    const uint32_t mo = (row0 + min(lane, nv - 1)) * 8;
+    const uint2 km = *(const uint2 *)(head + tv.k_meta_off + mo), vm = *(const uint2 *)(head + tv.v_meta_off + mo);
+#pragma unroll
+    for (int tt = 0; tt < NT; ++tt) {
+#pragma unroll
+      for (int x = 0; x < NLK; ++x)
+        *(uint4 *)(wbuf + (tt * 16 + n) * FK::ROWB + (((kg + 4 * x) ^ swz(PK, n)) * 16)) = kw[tt][x];
+      if constexpr (VT) {
+        *(uint4 *)(wbuf + 4096 + tt * 1024 + lane * 16) = vw[tt][0];
+      } else {
+#pragma unroll
+        for (int x = 0; x < NLV; ++x)
+          *(uint4 *)(wbuf + 4096 + (tt * 16 + n) * FV::ROWB + (((kg + 4 * x) ^ swzv(PV, tt * 16 + n)) * 16)) = vw[tt][x];
+      }
+    }
+    uint32_t *m = (uint32_t *)(wbuf + kTileRowsLds) + lane;   // buffer 0
+    m[0] = km.x;
+    m[64] = km.y;
+    m[128] = vm.x;
+    m[192] = vm.y;
   };
   auto fetch_k = [&](auto &t) {   // generic: compiled only where it is called, i.e. for the formats of PF
-    u32x4 w[4];
-    uint32_t mw[8];
-    if constexpr (PK == 8) lds_half_i8(lka0, lka1, lkm, w, mw);
-    else if constexpr (PF64) lds_half_i4x4(lka0, lkm, w, mw);
-    else lds_half_i4x2(lka0, lkm, w, mw);
+    u32x2 w[8];
+    if constexpr (PK == 8) lds_keys_i8(lka[0], lka[1], lka[2], lka[3], w);
+    else lds_keys_i4(lka[0], lka[1], w);
 #pragma unroll
-    for (int tt = 0; tt < NT; ++tt) {
+    for (int tt = 0; tt < NT; ++tt)
 #pragma unroll
       for (int x = 0; x < NLK; ++x) {
-        const u32x4 v = w[tt * NLK + x];
-        t.kw[tt][x] = uint4{v.x, v.y, v.z, v.w};
+        const u32x2 v0 = w[2 * (tt * NLK + x)], v1 = w[2 * (tt * NLK + x) + 1];
+        t.kw[tt][x] = uint4{v0.x, v0.y, v1.x, v1.y};
       }
-      t.kmeta[tt] = uint2{mw[2 * tt], mw[2 * tt + 1]};
-    }
   };
   auto fetch_v = [&](auto &t) {
-    u32x4 w[4];
-    uint32_t mw[8];
-    if constexpr (PV == 8) lds_half_i8(lva0, lva1, lvm, w, mw);
-    else if constexpr (PF64) lds_half_i4x4(lva0, lvm, w, mw);
-    else lds_half_i4x2(lva0, lvm, w, mw);
+    if constexpr (VT) {   // word w of piece hh: block 4 hh + w
+      u32x4 w[4];
+      lds_pieces<NT>(lva, w);
 #pragma unroll
-    for (int tt = 0; tt < NT; ++tt) {
+      for (int s = 0; s < 8; ++s)
 #pragma unroll
-      for (int x = 0; x < NLV; ++x) {
-        const u32x4 v = w[tt * NLV + x];
-        t.vw[tt][x] = uint4{v.x, v.y, v.z, v.w};
+        for (int pr = 0; pr < NT / 2; ++pr) t.vop[pr][s][0] = w[2 * pr + s / 4][s % 4];
+    } else {
+      u32x2 w[8];
+      if constexpr (PV == 8) {
+        lds_values_i8(lva, lva ^ 16, lva ^ 32, lva ^ 48, w);
+        lds_values_i8(lva ^ 64, lva ^ 80, lva ^ 96, lva ^ 112, w + 4);
+      } else if constexpr (PF64) {
+        lds_values_i4x4(lva, lva ^ 16, lva ^ 32, lva ^ 48, w);
+      } else {
+        lds_values_i4x2(lva, lva ^ 16, lva ^ 32, lva ^ 48, w);
       }
-      t.vmeta[tt] = uint2{mw[2 * tt], mw[2 * tt + 1]};
+#pragma unroll
+      for (int s = 0; s < 8; ++s) {
+        if constexpr (PV == 8) {
+          t.vop[0][s][0] = w[s].x;
+          t.vop[0][s][1] = w[s].y;
+        } else if constexpr (PF64) {
+          t.vop[0][s][0] = w[s].x;
+          t.vop[1][s][0] = w[s].y;
+        } else {
+          t.vop[0][s][0] = s % 2 ? w[s / 2].y : w[s / 2].x;
+        }
+      }
     }
   };
 
@@ -524,7 +571,7 @@ __device__ __forceinline__ void process_mfma(const FusedArgs &a, const TierView 
           const int r = 4 * dd + j;
           const h2 s2 = as_h2(__builtin_amdgcn_perm(m8[j + 4], m8[j], 0x05040100u));
           const h2 z2 = as_h2(__builtin_amdgcn_perm(m8[j + 4], m8[j], 0x07060302u));
-          const h2 q2 = as_h2(qB[0][r]);
+          const h2 q2 = as_h2(qB[r]);
           const h2 hi = q2 * s2;
           qh[r] = __builtin_bit_cast(uint32_t, hi);
           ql[r] = __builtin_bit_cast(uint32_t, __builtin_elementwise_fma(q2, s2, -hi));
@@ -542,44 +589,43 @@ __device__ __forceinline__ void process_mfma(const FusedArgs &a, const TierView 
     // ---- scores (log2 domain), column n of tokens 4 kg + i
     f4 S[NT];
     float mt = -INFINITY;
+    u32x4 km[4];   // the meta words of the lane's tokens 4 kg + i of two tiles, straight in the score layout
 #pragma unroll
     for (int tt = 0; tt < NT; ++tt) {
+      if constexpr (KQ)
+        if (tt % 2 == 0) lds_meta(lds0 + kTileRowsLds + meta_cur + 64 * tt + 16 * kg, km);
       uint32_t kr[16];
 #pragma unroll
       for (int x = 0; x < NLK; ++x) unpack16<KF>(t.kw[tt][x], kr + x * (16 / NLK), sp);
-      f4 sv[NP], ksv[NP], kzv[NP];
+      // one product chain per channel group
+      f4 sv[NGK];
 #pragma unroll
-      for (int pp = 0; pp < NP; ++pp) {
+      for (int gr = 0; gr < NGK; ++gr) {
         if constexpr (KT) {
-          sv[pp] = f4{-off_t, -off_t, -off_t, -off_t};
+          sv[gr] = f4{-off_t, -off_t, -off_t, -off_t};
 #pragma unroll
           for (int s = 0; s < 4; ++s) {
-            sv[pp] = mma32<false>(kr + 4 * s, qh + 4 * s, sv[pp]);
-            sv[pp] = mma32<false>(kr + 4 * s, ql + 4 * s, sv[pp]);
+            sv[gr] = mma32<false>(kr + 4 * s, qh + 4 * s, sv[gr]);
+            sv[gr] = mma32<false>(kr + 4 * s, ql + 4 * s, sv[gr]);
           }
         } else {
-          sv[pp] = f4{-off[pp], -off[pp], -off[pp], -off[pp]};
+          sv[gr] = f4{-off[gr], -off[gr], -off[gr], -off[gr]};
 #pragma unroll
-          for (int s = 0; s < 4; ++s) sv[pp] = mma32<KBF>(kr + 4 * s, qB[pp] + 4 * s, sv[pp]);
+          for (int s = gr * (4 / NGK); s < (gr + 1) * (4 / NGK); ++s) sv[gr] = mma32<KBF>(kr + 4 * s, qB + 4 * s, sv[gr]);
         }
-        ksv[pp] = kzv[pp] = zero4;
-        if constexpr (KQ) ksv[pp] = mma<false>(t.kmeta[tt].x, t.kmeta[tt].y, bs0[pp], bs1[pp], zero4);
-        if constexpr (KF == TTKV_I4_ASYM_G64) kzv[pp] = mma<false>(t.kmeta[tt].x, t.kmeta[tt].y, bz0[pp], bz1[pp], zero4);
       }
+      const u32x4 m0 = km[2 * (tt & 1)], m1 = km[2 * (tt & 1) + 1];
       f4 sc;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        float x = 0.0f;
-#pragma unroll
-        for (int pp = 0; pp < NP; ++pp) {
-          if constexpr (KF == TTKV_I8_SYM_G32) x = fmaf(sv[pp][i], ksv[pp][i], x);
-          else if constexpr (KF == TTKV_I4_ASYM_G64) x += fmaf(kzv[pp][i], qs[pp], sv[pp][i] * ksv[pp][i]);
-          else x = sv[pp][i];
-        }
-        if constexpr (KQ) {   // sum the groups of a head: cyclic over the columns with the same n % G
-          if constexpr (GT <= 8) x += dpp<0x128>(x);
-          if constexpr (GT <= 4) x += dpp<0x124>(x);
-          if constexpr (GT <= 2) x += dpp<0x122>(x);
+        float x = sv[0][i];
+        if constexpr (KF == TTKV_I8_SYM_G32) {        // scales of groups 0 .. 3
+          x *= half0(m0[i]);
+          x = fmaf(sv[1][i], half1(m0[i]), x);
+          x = fmaf(sv[2][i], half0(m1[i]), x);
+          x = fmaf(sv[3][i], half1(m1[i]), x);
+        } else if constexpr (KF == TTKV_I4_ASYM_G64) {   // scale, zero point of group 0; of group 1
+          x = fmaf(half1(m0[i]), qs[0], half1(m1[i]) * qs[1]) + fmaf(sv[0][i], half0(m0[i]), sv[1][i] * half0(m1[i]));
         }
         if (!FULL && tt * 16 + 4 * kg + i >= nv) x = -INFINITY;
         sc[i] = x;
@@ -596,8 +642,7 @@ __device__ __forceinline__ void process_mfma(const FusedArgs &a, const TierView 
       const float alpha = __builtin_amdgcn_exp2f((m - mn) * cs);
       l *= alpha;
       accz *= alpha;
-      if constexpr (VT) {
-        accoff[0] *= alpha; accoff[1] *= alpha;
+      if constexpr (V4) {
         zs[0] *= alpha; zs[1] *= alpha;
       }
 #pragma unroll
@@ -609,41 +654,60 @@ __device__ __forceinline__ void process_mfma(const FusedArgs &a, const TierView 
 
     // ---- weighted V, two 16-token tiles per 32-deep product
     before_v();
-    if constexpr (VT) {
-      // Values channel-major per 32 tokens: tiles tp, tp + 1 are one group; its two pieces are the A operands of the
-      // eight channel blocks as they lie (after the splice), the scales ride on the weights.  What is removed with
-      // the offsets is the spliced word of eight codes 8, so that a weight's rounding error multiplies code - 8.
-      const uint32_t code8[4] = {sp.c0 | 0x00080008u, sp.c1 | 0x00800080u, sp.c0 | 0x00080008u, sp.c1 | 0x00800080u};
+    if constexpr (PF) {
+      // The codes' words are the A operands of the eight channel blocks after the splice, whose offset leaves exactly
+      // (with the centre 8 of 4-bit codes); the scales ride on the weights.  One rounding per product: fp16(p s).
 #pragma unroll
       for (int tp = 0; tp < NT; tp += 2) {
-        uint32_t Bg[2][4];       // fp16(p_t * s_{t,g}) of the pair's 8 tokens per lane, per channel group g
+        u32x4 vm[4];             // meta words of the lane's tokens 4 kg + i: 4-bit (scale, zero point) of groups 0 and 1, 8-bit scales
+        lds_meta(lds0 + kTileRowsLds + meta_cur + 512 + 64 * tp + 16 * kg, vm);
+        uint32_t Bg[NGV][4];     // fp16(p_t * s_{t,g}) of the pair's 8 tokens per lane, per channel group g
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
           const int tt = tp + u;
-          // the token's meta values (s0, z0, s1, z1) in the score layout: tokens 4 kg + i of the tile, any column
-          f4 mv[4];
-#pragma unroll
-          for (int v = 0; v < 4; ++v) mv[v] = mma<false>(t.vmeta[tt].x, t.vmeta[tt].y, vm_sel[v][0], vm_sel[v][1], zero4);
-          float p[4];
+          const u32x4 m0 = vm[2 * u], m1 = vm[2 * u + 1];
+          float p[4], b[NGV][4];
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
             p[i] = __builtin_amdgcn_exp2f(fmaf(S[tt][i], cs, mcs));
             l += p[i];
-            zs[0] = fmaf(p[i], fmaf(8.0f, mv[0][i], mv[1][i]), zs[0]);   // zero point + the centre 8 * scale
-            zs[1] = fmaf(p[i], fmaf(8.0f, mv[2][i], mv[3][i]), zs[1]);
+            if constexpr (V4) {
+              zs[0] = fmaf(p[i], fmaf(8.0f, half0(m0[i]), half1(m0[i])), zs[0]);   // zero point + the centre 8 * scale
+              zs[1] = fmaf(p[i], fmaf(8.0f, half0(m1[i]), half1(m1[i])), zs[1]);
+              b[0][i] = p[i] * half0(m0[i]);
+              b[1][i] = p[i] * half0(m1[i]);
+            } else {
+              b[0][i] = p[i] * half0(m0[i]);
+              b[1][i] = p[i] * half1(m0[i]);
+              b[2][i] = p[i] * half0(m1[i]);
+              b[3][i] = p[i] * half1(m1[i]);
+            }
           }
-          Bg[0][2 * u] = pk(p[0] * mv[0][0], p[1] * mv[0][1]);
-          Bg[0][2 * u + 1] = pk(p[2] * mv[0][2], p[3] * mv[0][3]);
-          Bg[1][2 * u] = pk(p[0] * mv[2][0], p[1] * mv[2][1]);
-          Bg[1][2 * u + 1] = pk(p[2] * mv[2][2], p[3] * mv[2][3]);
+#pragma unroll
+          for (int gr = 0; gr < NGV; ++gr) {
+            Bg[gr][2 * u] = pk(b[gr][0], b[gr][1]);
+            Bg[gr][2 * u + 1] = pk(b[gr][2], b[gr][3]);
+          }
         }
 #pragma unroll
-        for (int hh = 0; hh < 2; ++hh) {
-          uint32_t vr[16];       // word w of piece hh -> registers 4 w .. 4 w + 3: channel 16 (4 hh + w) + (lane % 16)
-          unpack16<TTKV_I4_ASYM_G64>(t.vw[tp + hh][0], vr, sp);
+        for (int s = 0; s < 8; ++s) {
+          uint32_t vr[4];
+          const int gr = s / (8 / NGV);
+          if constexpr (V4) {
+            splice4(t.vop[tp / 2][s][0], vr, sp);
 #pragma unroll
-          for (int w = 0; w < 4; ++w) acc[4 * hh + w] = mma32<false>(vr + 4 * w, Bg[hh], acc[4 * hh + w]);
-          accoff[hh] = mma32<false>(code8, Bg[hh], accoff[hh]);
+            for (int r = 0; r < 4; ++r) vr[r] = __builtin_bit_cast(uint32_t, as_h2(vr[r]) + as_h2((r & 1) ? no_b : no_a));
+          } else {
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+              const uint32_t x = t.vop[tp / 2][s][h] ^ 0x80808080u;               // byte -> code + 128
+              vr[2 * h] = __builtin_amdgcn_perm(0x64646464u, x, 0x04010400u);      // (1024 + b0, 1024 + b1)
+              vr[2 * h + 1] = __builtin_amdgcn_perm(0x64646464u, x, 0x04030402u);
+            }
+#pragma unroll
+            for (int r = 0; r < 4; ++r) vr[r] = __builtin_bit_cast(uint32_t, as_h2(vr[r]) + as_h2(no_c));
+          }
+          acc[s] = mma32<false>(vr, Bg[gr], acc[s]);
         }
       }
     } else {
@@ -666,19 +730,13 @@ __device__ __forceinline__ void process_mfma(const FusedArgs &a, const TierView 
         for (int x = 0; x < NLV; ++x) unpack16<VF>(t.vw[tt][x], vr[u] + x * (16 / NLV), sp);
         if constexpr (VQ) {
           // codes -> code * scale in fp16 with one rounding (to nearest even), while the lane still owns one token
-          // and one group.  The splice holds offset + code; the centred code (int8: the signed code, int4: code - 8)
-          // is taken out first, which is exact, and then scaled, so that the one rounding is relative to a value of
+          // and one group.  The splice holds offset + code; the centred code (code - 8) is taken out first, which is exact, and then scaled, so that the one rounding is relative to a value of
           // the size of the element itself (scaling offset + code in one fused step and removing offset * scale
           // afterwards would round a value up to the row's whole range: an error of range x 2^-11 on its smallest
           // elements).  The int4 centre 8 * scale rejoins with the zero points at the end.
-          const uint32_t vsb0 = __builtin_amdgcn_perm(t.vmeta[tt].y, t.vmeta[tt].x, vsel[0]);
-          const uint32_t vsb1 = VF == TTKV_I8_SYM_G32 ? __builtin_amdgcn_perm(t.vmeta[tt].y, t.vmeta[tt].x, vsel[1]) : vsb0;
-          const h2 vs2[2] = {as_h2(vsb0), as_h2(vsb1)};
+          const h2 vs2 = as_h2(__builtin_amdgcn_perm(t.vmeta[tt].y, t.vmeta[tt].x, vsel));
 #pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const uint32_t no = VF == TTKV_I8_SYM_G32 ? no_c : ((r & 1) ? no_b : no_a);
-            vr[u][r] = __builtin_bit_cast(uint32_t, (as_h2(vr[u][r]) + as_h2(no)) * vs2[r / 8]);
-          }
+          for (int r = 0; r < 16; ++r) vr[u][r] = __builtin_bit_cast(uint32_t, (as_h2(vr[u][r]) + as_h2((r & 1) ? no_b : no_a)) * vs2);
         }
       }
 #pragma unroll
@@ -773,15 +831,13 @@ __device__ __forceinline__ void process_mfma(const FusedArgs &a, const TierView 
       compute_tiles(ra, c1 - i0, std::false_type{}, []() {});
     }
   };
-  // int8-key records in pinned host memory keep the register loads: over PCIe the copies through LDS are 3-4 %
-  // slower for them (measured), and the streaming hint has nothing to gain there.
   if constexpr (PF) {
+    TileRegs ra;
+    int i0 = c0 + wave * TT;
     if (!tv.in_host) {
       // While batch i is computed the copies of batch i + 1 are in flight: its K half is issued once batch i's K
       // rows are in registers, its V half once batch i's V rows are.  Loads complete in order, so "at most as
       // many outstanding as were issued after it" means a half has landed.
-      TileRegs ra;
-      int i0 = c0 + wave * TT;
       if (i0 < c1) {
         issue_k(i0);
         issue_v();
@@ -797,11 +853,16 @@ __device__ __forceinline__ void process_mfma(const FusedArgs &a, const TierView 
           fetch_v(ra);
           if (more) issue_v();
         });
+        meta_cur ^= kMetaLds;
       };
       for (; i0 + TT <= c1; i0 += 4 * TT) step(TT, std::true_type{});
       if (i0 < c1) step(c1 - i0, std::false_type{});
     } else {
-      register_loop();
+      for (; i0 < c1; i0 += 4 * TT) {
+        bring_host(i0);
+        fetch_k(ra);
+        compute_tiles(ra, min(TT, c1 - i0), std::false_type{}, [&]() { fetch_v(ra); });
+      }
     }
   } else if constexpr (PF2) {
     static_assert(!PF2 || (TT == 32 && NT == 2 && NLK == 4 && NLV == 4), "the batch the LDS readers cover");
@@ -818,14 +879,14 @@ __device__ __forceinline__ void process_mfma(const FusedArgs &a, const TierView 
   l += __shfl_xor(l, 16);
   l += __shfl_xor(l, 32);
   float z[2] = {0.0f, 0.0f};   // zero-point sum of the channels' group
-  if constexpr (VF == TTKV_I4_ASYM_G64)   // sum_t p_t * (zero + 8 * scale)
+  if constexpr (KT)   // sum_t p_t * (zero + 8 * scale)
     z[0] = z[1] = (kg >> 1) ? fmaf(8.0f, accz[2], accz[3]) : fmaf(8.0f, accz[0], accz[1]);
-  if constexpr (VT) {   // per channel group: the lanes' zero-point sums over their tokens, minus the splice offsets
+  if constexpr (V4) {   // per channel group: the lanes' zero-point sums over their tokens
 #pragma unroll
     for (int g2 = 0; g2 < 2; ++g2) {
       zs[g2] += __shfl_xor(zs[g2], 16);
       zs[g2] += __shfl_xor(zs[g2], 32);
-      z[g2] = zs[g2] - accoff[g2][0];   // every row of accoff holds the column's sum
+      z[g2] = zs[g2];
     }
   }
   float (*w_acc)[128] = (float (*)[128])wbuf;   // [head][channel]; the wave's last batch has been consumed
@@ -834,7 +895,7 @@ __device__ __forceinline__ void process_mfma(const FusedArgs &a, const TierView 
     for (int s = 0; s < 8; ++s)
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        if constexpr (VT) w_acc[n][16 * s + 4 * kg + i] = acc[s][i] + z[s / 4];   // block s row 4 kg + i, as the product leaves it
+        if constexpr (PF) w_acc[n][16 * s + 4 * kg + i] = acc[s][i] + z[s / 4];   // block s row 4 kg + i, as the product leaves it
         else w_acc[n][slice_channel<VF>(kg, chan<VF>(s, i))] = acc[s][i] + z[s / 4];
       }
     if (kg == 0) {
@@ -844,13 +905,10 @@ __device__ __forceinline__ void process_mfma(const FusedArgs &a, const TierView 
   }
 }
 
-// GQ: query heads per KV head the quantized-key cases are compiled for (4, 8 or 16; fp16 / bf16 tiers take any
-// count).  WIDE: the launch has a tier whose (group, head) columns need more than one pass of the score product
-// (int8 keys with 8 or 16 heads, int4 keys with 16); those cases hold further q operands, so they get
-// instantiations of their own and the one-pass cases keep their registers.
-// T128: the launch has a tier whose keys are grouped over 128 tokens per channel (its own instantiations as well).
-template <int GQ, bool WIDE, bool T128>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(GQ == 16 ? 2 : 3, GQ == 16 ? 2 : 3))) void attn_mfma_kernel(const FusedArgs a) {
+// FOUR_BIT: the launch has a tier with 4-bit keys or values.  Those cases take 180 registers, two workgroups per CU; the
+// others run three.  T128: also one whose keys are grouped over 128 tokens per channel.
+template <bool FOUR_BIT, bool T128>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FOUR_BIT ? 2 : 3, FOUR_BIT ? 2 : 3))) void attn_mfma_kernel(const FusedArgs a) {
   static_assert(kTileLds >= 16 * 128 * 4, "the wave's result fits its tile buffer");
   __shared__ __attribute__((aligned(256))) char s_buf[4 * kTileLds];   // per wave: batch in flight, then [head][channel] floats
   __shared__ float s_m[4][16], s_l[4][16];
@@ -886,27 +944,25 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(GQ == 16 ? 
   const int32_t *sel = resolve_selected(a, tv, en, seq, equal_items, chunk_tokens, chunk);
 
   const int combo = tv.k_fmt * 8 + tv.v_fmt;
-#define TTKV_MFMA_CASE(KF, VF, GT) process_mfma<KF, VF, GT>(a, tv, en, sel, chunk_tokens, chunk, seq, hq0, G, hkv, s_buf, s_m, s_l)
+#define TTKV_MFMA_CASE(KF, VF) process_mfma<KF, VF>(a, tv, en, sel, chunk_tokens, chunk, seq, hq0, G, hkv, s_buf, s_m, s_l)
   switch (combo) {
-    case TTKV_F16 * 8 + TTKV_F16: TTKV_MFMA_CASE(TTKV_F16, TTKV_F16, 0); break;
-    case TTKV_BF16 * 8 + TTKV_BF16: TTKV_MFMA_CASE(TTKV_BF16, TTKV_BF16, 0); break;
-    case TTKV_I8_SYM_G32 * 8 + TTKV_I8_SYM_G32:
-      if constexpr (GQ == 4 || ((GQ == 8 || GQ == 16) && WIDE)) TTKV_MFMA_CASE(TTKV_I8_SYM_G32, TTKV_I8_SYM_G32, GQ);
+    case TTKV_F16 * 8 + TTKV_F16: TTKV_MFMA_CASE(TTKV_F16, TTKV_F16); break;
+    case TTKV_BF16 * 8 + TTKV_BF16: TTKV_MFMA_CASE(TTKV_BF16, TTKV_BF16); break;
+    case TTKV_I8_SYM_G32 * 8 + TTKV_I8_SYM_G32: TTKV_MFMA_CASE(TTKV_I8_SYM_G32, TTKV_I8_SYM_G32); break;
+    case TTKV_I4_ASYM_T128 * 8 + TTKV_I4_ASYM_G64:
+      if constexpr (T128) TTKV_MFMA_CASE(TTKV_I4_ASYM_T128, TTKV_I4_ASYM_G64);
       break;
     case TTKV_I8_SYM_G32 * 8 + TTKV_I4_ASYM_G64:
-      if constexpr (GQ == 4 || ((GQ == 8 || GQ == 16) && WIDE)) TTKV_MFMA_CASE(TTKV_I8_SYM_G32, TTKV_I4_ASYM_G64, GQ);
-      break;
-    case TTKV_I4_ASYM_T128 * 8 + TTKV_I4_ASYM_G64:
-      if constexpr (T128) TTKV_MFMA_CASE(TTKV_I4_ASYM_T128, TTKV_I4_ASYM_G64, 0);
+      if constexpr (FOUR_BIT) TTKV_MFMA_CASE(TTKV_I8_SYM_G32, TTKV_I4_ASYM_G64);
       break;
     case TTKV_I8_SYM_G32 * 8 + TTKV_I4_ASYM_G64_T32:
-      if constexpr (GQ == 4 || ((GQ == 8 || GQ == 16) && WIDE)) TTKV_MFMA_CASE(TTKV_I8_SYM_G32, TTKV_I4_ASYM_G64_T32, GQ);
+      if constexpr (FOUR_BIT) TTKV_MFMA_CASE(TTKV_I8_SYM_G32, TTKV_I4_ASYM_G64_T32);
       break;
     case TTKV_I4_ASYM_G64 * 8 + TTKV_I4_ASYM_G64_T32:
-      if constexpr (GQ <= 8 || WIDE) TTKV_MFMA_CASE(TTKV_I4_ASYM_G64, TTKV_I4_ASYM_G64_T32, GQ);
+      if constexpr (FOUR_BIT) TTKV_MFMA_CASE(TTKV_I4_ASYM_G64, TTKV_I4_ASYM_G64_T32);
       break;
     default:
-      if constexpr (GQ <= 8 || WIDE) TTKV_MFMA_CASE(TTKV_I4_ASYM_G64, TTKV_I4_ASYM_G64, GQ);
+      if constexpr (FOUR_BIT) TTKV_MFMA_CASE(TTKV_I4_ASYM_G64, TTKV_I4_ASYM_G64);
       break;
   }
 #undef TTKV_MFMA_CASE
@@ -934,12 +990,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(GQ == 16 ? 
 
 }  // namespace
 
-// Can one 16-column tile hold every (group, head) column of these formats, and does the
-// single pass pay off (from four query heads per KV head on, measured)?
-// Heads one workgroup serves in a single pass over the bytes: the 16 columns of the second product, whatever the
-// stored format.  More heads per KV head are cut into blocks of this many.
-int mfma_block_heads(int k_fmt) { (void)k_fmt; return 16; }
-
 // Do the kernel's cases take these formats?
 bool attn_mfma_fits(int k_fmt, int v_fmt, int G) {
   if (G < 2) return false;
@@ -951,47 +1001,36 @@ bool attn_mfma_fits(int k_fmt, int v_fmt, int G) {
 // Does the single pass over the bytes pay off?  From two query heads per KV head on (measured against the vector
 // kernel's head pair at two heads: fp16 6.4 against 6.2 TB/s, int8 6.2 against 5.3, int4 5.2 against 4.5, K 8-bit /
 // V 4-bit 6.0 against 4.3, keys grouped over tokens 4.4 against 3.5).
-bool attn_mfma_pays(int G, bool has_mixed_or_t128) {
-  (void)has_mixed_or_t128;
-  return G >= 2;
-}
+bool attn_mfma_pays(int G) { return G >= 2; }
+
+bool attn_mfma_four_bit(int k_fmt, int v_fmt) { return !is_fp(k_fmt) && !(k_fmt == TTKV_I8_SYM_G32 && v_fmt == k_fmt); }
 
 namespace {
-int padded_heads(int G) { return G <= 4 ? 4 : (G <= 8 ? 8 : 16); }
-bool quantized_per_token(int k_fmt) { return k_fmt == TTKV_I8_SYM_G32 || k_fmt == TTKV_I4_ASYM_G64; }
-
-// What one launch needs: heads per block (the smallest any of its tiers takes), the padded count the
-// quantized-key cases are compiled for, two-pass cases, keys grouped over tokens.
+// What one launch needs: heads per block, 4-bit tiers, keys grouped over tokens, and whether the vector kernel's head pairs take it
+// (keys grouped over tokens beside int8 keys with more than 4 or int4 keys with more than 8 heads per KV head).
 struct MfmaShape {
-  int heads, padded;
-  bool wide, t128, mixed, ok;
+  int heads;
+  bool four_bit, t128, pairs, ok;
 };
 MfmaShape mfma_shape(const FusedArgs &a) {
   const int G = a.Hq / a.Hkv;
-  MfmaShape m{16, 4, false, false, false, true};
-  bool quant = false;
+  MfmaShape m{std::min(16, G), false, false, false, true};
+  bool many = false;
   for (int j = 0; j < a.n_entries; ++j) {
     const TierView &tv = a.tv[(a.e[j].tier_seq >> 16) & 0xff];
     m.ok &= attn_mfma_fits(tv.k_fmt, tv.v_fmt, G);
-    m.heads = std::min(m.heads, mfma_block_heads(tv.k_fmt));
+    m.four_bit |= attn_mfma_four_bit(tv.k_fmt, tv.v_fmt);
     m.t128 |= tv.k_fmt == TTKV_I4_ASYM_T128;
-    m.mixed |= tv.k_fmt == TTKV_I8_SYM_G32 && tv.v_fmt != tv.k_fmt;
-    quant |= quantized_per_token(tv.k_fmt);
+    many |= (tv.k_fmt == TTKV_I8_SYM_G32 && G > 4) || (tv.k_fmt == TTKV_I4_ASYM_G64 && G > 8);
   }
-  m.heads = std::min(m.heads, G);
-  if (quant) m.padded = padded_heads(m.heads);
-  for (int j = 0; j < a.n_entries; ++j) {
-    const int kf = a.tv[(a.e[j].tier_seq >> 16) & 0xff].k_fmt;
-    m.wide |= (kf == TTKV_I8_SYM_G32 && m.padded >= 8) || (kf == TTKV_I4_ASYM_G64 && m.padded == 16);
-  }
+  m.pairs = m.t128 && many;
   return m;
 }
 }  // namespace
 
 bool attn_mfma_eligible(const FusedArgs &a) {
   const MfmaShape m = mfma_shape(a);
-  // two-pass cases together with keys grouped over tokens have no instantiation: vector kernel
-  return m.ok && attn_mfma_pays(a.Hq / a.Hkv, m.t128 || m.mixed) && !(m.wide && m.t128);
+  return m.ok && attn_mfma_pays(a.Hq / a.Hkv) && !m.pairs;
 }
 
 hipError_t launch_attn_mfma(const FusedArgs &a0, hipStream_t s) {
@@ -1001,12 +1040,9 @@ hipError_t launch_attn_mfma(const FusedArgs &a0, hipStream_t s) {
   const int G = a.Hq / a.Hkv;
   const uint32_t n_hb = (G + m.heads - 1) / m.heads;
   const dim3 grid(((uint32_t)a.n_items * a.Hkv + 7) / 8 * 8 * n_hb);
-  if (m.t128 && m.padded == 8) hipLaunchKernelGGL((attn_mfma_kernel<8, false, true>), grid, dim3(256), 0, s, a);
-  else if (m.t128) hipLaunchKernelGGL((attn_mfma_kernel<4, false, true>), grid, dim3(256), 0, s, a);
-  else if (m.padded == 16) hipLaunchKernelGGL((attn_mfma_kernel<16, true, false>), grid, dim3(256), 0, s, a);
-  else if (m.padded == 8 && m.wide) hipLaunchKernelGGL((attn_mfma_kernel<8, true, false>), grid, dim3(256), 0, s, a);
-  else if (m.padded == 8) hipLaunchKernelGGL((attn_mfma_kernel<8, false, false>), grid, dim3(256), 0, s, a);
-  else hipLaunchKernelGGL((attn_mfma_kernel<4, false, false>), grid, dim3(256), 0, s, a);
+  if (m.t128) hipLaunchKernelGGL((attn_mfma_kernel<true, true>), grid, dim3(256), 0, s, a);
+  else if (m.four_bit) hipLaunchKernelGGL((attn_mfma_kernel<true, false>), grid, dim3(256), 0, s, a);
+  else hipLaunchKernelGGL((attn_mfma_kernel<false, false>), grid, dim3(256), 0, s, a);
   return hipGetLastError();
 }
 
