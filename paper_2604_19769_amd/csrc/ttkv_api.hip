@@ -329,7 +329,6 @@ void build_plan(const ttkv_cache *c, const int32_t *sel_blocks, const int32_t *s
         if (T.len[b] == 0 || count <= 0) continue;
         Run r{};
         r.tier = t; r.b = b;
-        r.rec_base = (int32_t)((int64_t)b * ds->stride);
         r.first_tok = (int32_t)(end_id - 1);
         r.len = host ? count : count * L.bt;     // blocks in fixed items, or their tokens as one run in equal items
         r.selected = true;
@@ -345,7 +344,6 @@ void build_plan(const ttkv_cache *c, const int32_t *sel_blocks, const int32_t *s
         if (T.len[b] == 0) continue;
         Run r{};
         r.tier = t; r.b = b;
-        r.rec_base = (int32_t)((int64_t)b * T.ring_blocks);
         r.first_tok = (int32_t)(T.start[b] % ring_tokens(T));
         r.len = (int32_t)T.len[b];
         r.no_table = false;
@@ -908,8 +906,8 @@ static ttkv_status decode_impl(Handle *h, const ttkv_cache *c, const void *q, in
   const size_t mis = (256 - ((uintptr_t)workspace & 255)) & 255;
   if (ws_bytes < mis + slots_bytes) return TTKV_ERR_WORKSPACE;
   const int64_t stride = (int64_t)((ws_bytes - mis - slots_bytes) / (rows * 130 * sizeof(float)));
-  if (stride < std::max(1, P.max_parts)) return TTKV_ERR_WORKSPACE;
-  const int32_t part_stride = (int32_t)std::min<int64_t>(stride, 1 << 20);
+  if (stride < std::max(1, P.max_parts) || P.max_parts > TTKV_MAX_PARTS) return TTKV_ERR_WORKSPACE;
+  const int32_t part_stride = (int32_t)std::min<int64_t>(stride, TTKV_MAX_PARTS);
   if (check_only) return TTKV_OK;   // nothing enqueued so far
   if (!trace && !P.fetch.empty() && copy != compute && (st = ensure_events(h)) != TTKV_OK) return st;
   HipChain hip_chain(h, compute, copy);
@@ -943,6 +941,7 @@ static ttkv_status decode_impl(Handle *h, const ttkv_cache *c, const void *q, in
   if (ds) {
     const ttkv_tier &T = c->tier[c->n_tiers - 1];
     a.sel_ids = ds->ids;
+    a.sel_stride = ds->stride;
     for (int b = 0; b < c->batch; ++b) {
       const int64_t live_end = T.start[b] + T.len[b];
       a.sel_last_ntok[b] = T.len[b] ? (int32_t)(live_end - (live_end - 1) / T.block_tokens * T.block_tokens) : 0;
@@ -973,13 +972,8 @@ static ttkv_status decode_impl(Handle *h, const ttkv_cache *c, const void *q, in
     int items = 0;
     for (size_t i = r0; i < r1; ++i) {
       const Run &r = *order[i];
-      Entry &e = a.e[i - r0];
-      e.tier_seq = (r.no_table ? (1 << 24) : 0) | (r.selected ? (1 << 25) : 0) | (r.tier << 16) | r.b;
-      e.rec_base = r.rec_base;
-      e.first_tok = r.first_tok;
-      e.len = r.len;
-      e.item_start = items;
-      e.part_base = r.part_base;
+      a.e[i - r0] = make_entry(r.tier, r.b, r.part_base, (r.no_table ? kEntryNoTable : 0) | (r.selected ? kEntrySelected : 0),
+                               r.no_table ? r.rec_base : r.first_tok, r.len, items);
       items += r.n_chunks;
     }
     a.n_items = items;
@@ -1007,12 +1001,7 @@ static ttkv_status decode_impl(Handle *h, const ttkv_cache *c, const void *q, in
     a.tv[0] = make_slot_view(T, L, dst, f.nrec);
     a.chunk[0] = f.chunk;
     a.n_entries = 1;
-    a.e[0].tier_seq = (1 << 24) | f.b;
-    a.e[0].rec_base = 0;
-    a.e[0].first_tok = 0;
-    a.e[0].len = f.ntok;
-    a.e[0].item_start = 0;
-    a.e[0].part_base = f.part_base;
+    a.e[0] = make_entry(0, f.b, f.part_base, kEntryNoTable, 0, f.ntok, 0);
     a.n_items = (f.ntok + f.chunk - 1) / f.chunk;
     TTKV_HIP(h, ch.attend(issued, slot, a, &nk, &nm));
     if (copy != compute) TTKV_HIP(h, ch.record(EV_FREED + slot, 0));

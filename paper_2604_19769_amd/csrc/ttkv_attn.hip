@@ -41,7 +41,7 @@ using namespace dev;
 
 // Everything one wave accumulates for one item.
 template <int KF, int VF, int G>
-__device__ __forceinline__ void process(const FusedArgs &a, const TierView &tv, const Entry &en, const int32_t *sel,
+__device__ __forceinline__ void process(const FusedArgs &a, const TierView &tv, const RunView &en, const int32_t *sel,
                                         int chunk_tokens, int chunk, int seq, int hkv, int hq0, float (*s_acc)[4][G][128],
                                         float (*s_m)[G], float (*s_l)[G]) {
   // sel: null, or the block ids behind a run made of selected blocks (ring block of token i: sel[i / bt])
@@ -386,15 +386,15 @@ __global__ __launch_bounds__(256) void attn_fused_kernel(const FusedArgs a) {
     const int mid = (lo + hi + 1) >> 1;
     if (a.e[mid].item_start <= item) lo = mid; else hi = mid - 1;
   }
-  Entry en = a.e[lo];
-  const int tier = (en.tier_seq >> 16) & 0xff, seq = en.tier_seq & 0xffff;
+  RunView en = run_view(a, lo);
+  const int tier = en.tier, seq = en.seq, item_start = a.e[lo].item_start;
   TierView tv = a.tv[tier];
-  if (en.tier_seq & (1 << 24)) tv.table = nullptr;   // the run names pool records directly
+  if (en.flags & kEntryNoTable) tv.table = nullptr;   // the run names pool records directly
   int chunk_tokens = a.chunk[tier];
   const bool equal_items = chunk_tokens == 0;
-  if (equal_items) chunk_tokens = even_chunk(en.len, (lo + 1 < a.n_entries ? a.e[lo + 1].item_start : a.n_items) - en.item_start);
-  const int part = en.part_base + item - en.item_start;   // this item's partial
-  int chunk = item - en.item_start;
+  if (equal_items) chunk_tokens = even_chunk(en.len, (lo + 1 < a.n_entries ? a.e[lo + 1].item_start : a.n_items) - item_start);
+  const int part = en.part_base + item - item_start;   // this item's partial
+  int chunk = item - item_start;
   const int32_t *sel = resolve_selected(a, tv, en, seq, equal_items, chunk_tokens, chunk);
 
   const int combo = tv.k_fmt * 8 + tv.v_fmt;
@@ -568,7 +568,7 @@ hipError_t launch_attn(const FusedArgs &a, hipStream_t s, int *n_kernels, int *n
   const uint32_t bases = ((uint32_t)a.n_items * a.Hkv + 7) / 8 * 8;
   dim3 grid(bases * (Gtot / G));
   bool t128 = false;
-  for (int j = 0; j < a.n_entries; ++j) t128 |= a.tv[(a.e[j].tier_seq >> 16) & 0xff].k_fmt == TTKV_I4_ASYM_T128;
+  for (int j = 0; j < a.n_entries; ++j) t128 |= a.tv[entry_tier(a.e[j])].k_fmt == TTKV_I4_ASYM_T128;
   if (G == 1) {
     if (t128) hipLaunchKernelGGL((attn_fused_kernel<1, true>), grid, dim3(256), 0, s, a);
     else hipLaunchKernelGGL((attn_fused_kernel<1, false>), grid, dim3(256), 0, s, a);

@@ -115,6 +115,27 @@ __device__ __forceinline__ float group_sum(float v) {
   if constexpr (LPT >= 16) v += dpp<0x140>(v);  // row_mirror: lane i <- lane 15-i = the other half's sum
   return v;
 }
+// One run of the launch, unpacked.
+struct RunView {
+  int tier, seq, part_base;
+  uint32_t flags;
+  int rec_base;    // record of ring block 0 (no block table) or the run's first pool record
+  int first_tok;   // ring token index of the run's first token, 0 for runs that name records; selected: newest block id
+  int len;
+};
+__device__ __forceinline__ RunView run_view(const FusedArgs &a, int i) {
+  const Entry e = a.e[i];
+  RunView r;
+  r.tier = entry_tier(e);
+  r.seq = (e.head >> 20) & 63;
+  r.part_base = e.head & (TTKV_MAX_PARTS - 1);
+  r.flags = e.head & (kEntryNoTable | kEntrySelected);
+  const bool direct = r.flags & kEntryNoTable;
+  r.rec_base = direct ? e.at : r.seq * a.tv[r.tier].ring_blocks;
+  r.first_tok = direct ? 0 : e.at;
+  r.len = e.len;
+  return r;
+}
 // A run whose blocks are named by the device-side selection (ids ascending, so only the last can be the tier's
 // partly filled newest block).  Two forms, told apart by the tier's item size in the launch arguments:
 //   fixed items (host tiers): item `chunk` of the run is sub-chunk chunk % ipb of the run's (chunk / ipb)-th
@@ -123,23 +144,21 @@ __device__ __forceinline__ float group_sum(float v) {
 //     run; token i of it lies in block ids[i / bt], which the tile address look-up follows (`sel`), so an item may
 //     span several blocks and small blocks cost no more than large ones.
 // Either way everything after this sees an ordinary run.  Returns the run's id list for the second form.
-__device__ __forceinline__ const int32_t *resolve_selected(const FusedArgs &a, const TierView &tv, Entry &en, int seq,
+__device__ __forceinline__ const int32_t *resolve_selected(const FusedArgs &a, const TierView &tv, RunView &en, int seq,
                                                            bool equal_items, int chunk_tokens, int &chunk) {
-  if (!(en.tier_seq & (1 << 25))) return nullptr;
+  if (!(en.flags & kEntrySelected)) return nullptr;
+  const int32_t *ids = a.sel_ids + seq * a.sel_stride;
   if (equal_items) {
-    const int32_t *ids = a.sel_ids + en.rec_base;
     if (ids[en.len / tv.bt - 1] == en.first_tok) en.len -= tv.bt - a.sel_last_ntok[seq];
     en.first_tok = 0;
-    en.rec_base = seq * tv.ring_blocks;
     return ids;
   }
   const int ipb = (tv.bt + chunk_tokens - 1) / chunk_tokens;
   const int blk = chunk / ipb;
   chunk -= blk * ipb;
-  const int32_t id = a.sel_ids[en.rec_base + blk];
+  const int32_t id = ids[blk];
   en.len = id == en.first_tok ? a.sel_last_ntok[seq] : tv.bt;
   en.first_tok = (id % tv.ring_blocks) * tv.bt;
-  en.rec_base = seq * tv.ring_blocks;
   return nullptr;
 }
 

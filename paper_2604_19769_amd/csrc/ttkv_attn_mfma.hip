@@ -221,7 +221,7 @@ __device__ __forceinline__ float half1(uint32_t w) { return (float)as_h2(w).y; }
 
 // Any number of query heads up to 16 (the columns of both products).
 template <int KF, int VF>
-__device__ __forceinline__ void process_mfma(const FusedArgs &a, const TierView &tv, const Entry &en, const int32_t *sel,
+__device__ __forceinline__ void process_mfma(const FusedArgs &a, const TierView &tv, const RunView &en, const int32_t *sel,
                                              int chunk_tokens, int chunk, int seq, int hq0, int Gr, int hkv, char *s_buf,
                                              float (*s_m)[16], float (*s_l)[16]) {
   // sel: null, or the block ids behind a run made of selected blocks (ring block of token i: sel[i / bt])
@@ -932,15 +932,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FOUR_BIT ? 
     const int mid = (lo + hi + 1) >> 1;
     if (a.e[mid].item_start <= item) lo = mid; else hi = mid - 1;
   }
-  Entry en = a.e[lo];
-  const int tier = (en.tier_seq >> 16) & 0xff, seq = en.tier_seq & 0xffff;
+  RunView en = run_view(a, lo);
+  const int tier = en.tier, seq = en.seq, item_start = a.e[lo].item_start;
   TierView tv = a.tv[tier];
-  if (en.tier_seq & (1 << 24)) tv.table = nullptr;   // the run names pool records directly
+  if (en.flags & kEntryNoTable) tv.table = nullptr;   // the run names pool records directly
   int chunk_tokens = a.chunk[tier];
   const bool equal_items = chunk_tokens == 0;
-  if (equal_items) chunk_tokens = even_chunk(en.len, (lo + 1 < a.n_entries ? a.e[lo + 1].item_start : a.n_items) - en.item_start);
-  const int part = en.part_base + item - en.item_start;   // this item's partial
-  int chunk = item - en.item_start;
+  if (equal_items) chunk_tokens = even_chunk(en.len, (lo + 1 < a.n_entries ? a.e[lo + 1].item_start : a.n_items) - item_start);
+  const int part = en.part_base + item - item_start;   // this item's partial
+  int chunk = item - item_start;
   const int32_t *sel = resolve_selected(a, tv, en, seq, equal_items, chunk_tokens, chunk);
 
   const int combo = tv.k_fmt * 8 + tv.v_fmt;
@@ -1017,7 +1017,7 @@ MfmaShape mfma_shape(const FusedArgs &a) {
   MfmaShape m{std::min(16, G), false, false, false, true};
   bool many = false;
   for (int j = 0; j < a.n_entries; ++j) {
-    const TierView &tv = a.tv[(a.e[j].tier_seq >> 16) & 0xff];
+    const TierView &tv = a.tv[entry_tier(a.e[j])];
     m.ok &= attn_mfma_fits(tv.k_fmt, tv.v_fmt, G);
     m.four_bit |= attn_mfma_four_bit(tv.k_fmt, tv.v_fmt);
     m.t128 |= tv.k_fmt == TTKV_I4_ASYM_T128;

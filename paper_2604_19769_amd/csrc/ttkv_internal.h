@@ -62,28 +62,17 @@ struct TierView {
   int32_t in_host;        // the records are pinned host memory, read over PCIe
 };
 
-// Per-launch sequence table, passed by value in the kernel arguments so that no
-// host->device copy is needed per step.
-struct SeqTable {
-  int32_t n_seq;
-  int32_t seq_id[TTKV_MAX_BATCH];       // sequence (batch index) of entry j
-  int32_t rec_base[TTKV_MAX_BATCH];     // record index of ring block 0 when there is no block table
-  int32_t first_tok[TTKV_MAX_BATCH];    // ring token index of the entry's first token (multiple of 64)
-  int32_t len[TTKV_MAX_BATCH];          // tokens
-  int32_t item_start[TTKV_MAX_BATCH + 1];  // prefix sum of work items (chunks) per entry
-  int32_t part_base[TTKV_MAX_BATCH];    // first partial index this launch writes for the entry
-};
-
 // ---------------------------------------------------------------- the split-K plan of one attention call
 // One run of consecutive tokens of one (tier, sequence) attended by the fused
 // kernel in place: a device tier, a host tier read over PCIe by the kernel itself,
 // or a run of selected blocks.
 struct Run {
   int tier, b;
-  int32_t rec_base, first_tok, len;
+  int32_t rec_base;   // no_table: first pool record
+  int32_t first_tok, len;
   bool no_table;
-  bool selected;   // blocks named by the device-side selection (rec_base: index of the first id, first_tok: newest block
-                   // id; len: their number for a host tier, their tokens for a tier in HBM)
+  bool selected;   // blocks named by the device-side selection (first_tok: newest block id; len: their number for a host
+                   // tier, their tokens for a tier in HBM)
   int part_base, n_chunks;
 };
 // Selection left on the device by the top-k kernel: ids [batch][stride], min(k, live blocks) of them per sequence.
@@ -192,19 +181,26 @@ struct ConvArgs {
 hipError_t launch_convert(const ConvArgs &a, hipStream_t s, int *n_kernels);
 
 // One launch of the fused attention kernel: up to TTKV_MAX_ENTRIES runs of tokens,
-// each belonging to one (tier, sequence), all passed by value (no per-step upload).
-#define TTKV_MAX_ENTRIES 120
+// each belonging to one (tier, sequence), all passed by value (no per-step upload).  16 bytes per run, so that one
+// launch takes three tiers of 64 sequences: with 24 (120 runs) the 128 runs of 64 sequences in two tiers made two
+// launches, the second one nearly empty (64 x 4K tokens: 118.3 us per step, 110.3 in one launch).
+#define TTKV_MAX_ENTRIES 208
 struct Entry {
-  int32_t tier_seq;     // bit 24: ignore the block table (rec_base is a pool record); bits 16-23 tier; low 16 sequence
-                        // bit 25: the run is made of blocks named by the device-side selection: rec_base = index of
-                        // its first id in FusedArgs::sel_ids, first_tok = id of the tier's newest live block, len =
-                        // the number of blocks (tier cut into fixed items) or their tokens (equal items)
-  int32_t rec_base;     // record of ring block 0 (no table) or of the run's first block
-  int32_t first_tok;    // ring token index of the run's first token (multiple of 64)
-  int32_t len;          // tokens
+  // bits 0-19 first partial index of the run, 20-25 sequence, 26-27 tier, 28: the run names pool records directly
+  // (no block table), 29: it is made of blocks named by the device-side selection
+  uint32_t head;
+  int32_t at;           // ring token index of the run's first token (multiple of 64); bit 28: its first pool record;
+                        // bit 29: id of the tier's newest live block
+  int32_t len;          // tokens; bit 29: the number of blocks (tier cut into fixed items) or their tokens (equal items)
   int32_t item_start;   // first work item (chunk) of the run in this launch
-  int32_t part_base;    // first partial index of the run
 };
+constexpr uint32_t kEntryNoTable = 1u << 28, kEntrySelected = 1u << 29;
+inline Entry make_entry(int tier, int seq, int part_base, uint32_t flags, int32_t at, int32_t len, int32_t item_start) {
+  return Entry{(uint32_t)part_base | (uint32_t)seq << 20 | (uint32_t)tier << 26 | flags, at, len, item_start};
+}
+__host__ __device__ inline int entry_tier(const Entry &e) { return (e.head >> 26) & 3; }
+static_assert(TTKV_MAX_BATCH <= 64 && TTKV_MAX_TIERS <= 4, "an entry's sequence and tier fields");
+#define TTKV_MAX_PARTS (1 << 20)
 // A run of `len` tokens cut into n items of equal size, a multiple of 64 tokens (the last item may be shorter).
 // The host plans with it and the kernels derive an item's size from the run's length and item count with it.
 __host__ __device__ inline int even_chunk(int len, int n) { return ((len + n - 1) / n + 63) / 64 * 64; }
@@ -220,7 +216,8 @@ struct FusedArgs {
   int32_t Hq, Hkv;
   float scale;
   int32_t mfma_heads;   // set by the matrix-core launcher: query heads one workgroup serves
-  const int32_t *sel_ids;                    // device: block ids (Eq. 1) chosen by the top-k kernel, for runs with bit 25
+  const int32_t *sel_ids;                    // device: block ids (Eq. 1) chosen by the top-k kernel [batch][sel_stride], for selected runs
+  int32_t sel_stride;
   int32_t sel_last_ntok[TTKV_MAX_BATCH];     // live tokens in the newest block of the selected tier, per sequence
 };
 static_assert(sizeof(FusedArgs) <= 4096, "kernel arguments are passed by value");
