@@ -905,7 +905,7 @@ __device__ __forceinline__ void process_mfma(const FusedArgs &a, const TierView 
   }
 }
 
-// FOUR_BIT: the launch has a tier with 4-bit keys or values.  Those cases take 180 registers, two workgroups per CU; the
+// FOUR_BIT: the launch has a tier with 4-bit keys or values.  Those cases are held to two workgroups per CU (the plan counts on it); the
 // others run three.  T128: also one whose keys are grouped over 128 tokens per channel.
 template <bool FOUR_BIT, bool T128>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FOUR_BIT ? 2 : 3, FOUR_BIT ? 2 : 3))) void attn_mfma_kernel(const FusedArgs a) {
