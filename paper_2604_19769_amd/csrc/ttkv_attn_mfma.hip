@@ -22,7 +22,8 @@
 //   exactly, the A operand of
 //       O[channel][head] += sum_token V^T[channel][token] * P_g[token][head],
 //   and the token's scale rides on the other operand: P_g = fp16(p_t * s_{t,g}), one per channel group g, the one
-//   rounding of the product.  The int4 zero points and the centre come back as sum_t p_t (z_{t,g} + 8 s_{t,g}) in fp32 on
+//   rounding of the product; the weights p carry a power of two that keeps it in fp16's normal range whatever the size
+//   of the values (wexp below).  The int4 zero points and the centre come back as sum_t p_t (z_{t,g} + 8 s_{t,g}) in fp32 on
 //   the vector units.  Values stored channel-major per 32 tokens (TTKV_I4_ASYM_G64_T32) are those operand words as they
 //   lie.
 //   fp16 / bf16 V, and int4 V beside keys grouped over tokens: rows like K's (the latter dequantized in packed fp16);
@@ -37,8 +38,9 @@
 // take the same 81 us for 64 / 4 heads, 16 ragged sequences of K int4 / V4c 182 us (187 with them).  What matters is
 // what keeps the copies fed and how the work is cut: 64 q / 4 kv heads, K int8 / V int4 110.3 -> 83.7 us per step
 // (before: four score passes against zero-padded operands, one per group, 228 registers), 32 / 8 at 128K tokens
-// 48.3 -> 44.6, block-sparse recall 129.5 -> 123.2; the error against 64 bits is a half of what rounding dequantized
-// values gave.  More heads per KV head than 16 are cut into blocks of 16, one workgroup and one pass over the bytes per
+// 48.3 -> 44.6, block-sparse recall 129.5 -> 123.2.  Error against 64 bits, 4096 tokens, 2-norm: int8 values of standard
+// deviation 1 to 0.005 1.8e-4 (rounding dequantized values: 2.8e-4), beside a token 7 above the rest 1e-6 (1.8e-4); int4
+// 2.0e-4 (2.7e-4) and 1e-6 (1.4e-4).  More heads per KV head than 16 are cut into blocks of 16, one workgroup and one pass over the bytes per
 // block.
 #include "ttkv_attn_dev.h"
 
@@ -215,6 +217,28 @@ __device__ __forceinline__ void lds_meta(uint32_t a0, u32x4 *m) {
                "ds_read_b128 %3, %4 offset:320\n\ts_waitcnt lgkmcnt(0)"
                : "=&v"(m[0]), "=&v"(m[1]), "=&v"(m[2]), "=&v"(m[3]) : "v"(a0) : "memory");
 }
+// The same with the two words of the lane's own token (one lane per token, from t0), for what is decided per batch.
+__device__ __forceinline__ void lds_meta_own(uint32_t a0, uint32_t t0, u32x4 *m, uint32_t *t) {
+  asm volatile("ds_read_b32 %4, %7\n\tds_read_b32 %5, %7 offset:256\n\t"
+               "ds_read_b128 %0, %6\n\tds_read_b128 %1, %6 offset:256\n\tds_read_b128 %2, %6 offset:64\n\t"
+               "ds_read_b128 %3, %6 offset:320\n\ts_waitcnt lgkmcnt(0)"
+               : "=&v"(m[0]), "=&v"(m[1]), "=&v"(m[2]), "=&v"(m[3]), "=&v"(t[0]), "=&v"(t[1]) : "v"(a0), "v"(t0) : "memory");
+}
+typedef unsigned short us2 __attribute__((ext_vector_type(2)));
+// the larger halves of two words, as unsigned numbers
+__device__ __forceinline__ uint32_t halves_max(uint32_t a, uint32_t b) {
+  return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(us2, a), __builtin_bit_cast(us2, b)));
+}
+// the largest value of the wave's lanes (16-bit numbers)
+__device__ __forceinline__ uint32_t wave_max16(uint32_t v) {
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xf, 0xf, true));    // quad_perm [1,0,3,2]
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xf, 0xf, true));    // quad_perm [2,3,0,1]
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xf, 0xf, true));   // row_half_mirror
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x140, 0xf, 0xf, true));   // row_mirror
+  return max(max((uint32_t)__builtin_amdgcn_readlane((int)v, 0), (uint32_t)__builtin_amdgcn_readlane((int)v, 16)),
+             max((uint32_t)__builtin_amdgcn_readlane((int)v, 32), (uint32_t)__builtin_amdgcn_readlane((int)v, 48)));
+}
+__device__ __forceinline__ float pow2(int e) { return __uint_as_float((uint32_t)(127 + e) << 23); }   // |e| < 127
 // fp16 halves of a meta word
 __device__ __forceinline__ float half0(uint32_t w) { return (float)as_h2(w).x; }
 __device__ __forceinline__ float half1(uint32_t w) { return (float)as_h2(w).y; }
@@ -327,7 +351,16 @@ __device__ __forceinline__ void process_mfma(const FusedArgs &a, const TierView 
   float zs[2] = {0.0f, 0.0f};     // V4: sum_t p_t (z_{t,g} + 8 s_{t,g})
 #pragma unroll
   for (int s = 0; s < 8; ++s) acc[s] = zero4;
-  float m = -INFINITY, l = 0.0f;
+  float m = -INFINITY, l = 0.0f, mcs = INFINITY;   // a token's weight: exp2(score cs + mcs)
+  // PF: the value operand is fp16(p s), and with p <= 1 that falls into fp16's subnormals or to zero for value scales
+  // well below 1 (std 0.02 beside a token 7 above the rest: an error of 1.7e-2 of the output).  So the weights carry a
+  // power of two that brings the largest value scale the wave has met to [2^14, 2^15): mcs = wexp - m cs, in l,
+  // zs and acc alike; it leaves them at the end.  s_top: the largest fp16 number (as bits, ordered
+  // like the numbers) of that scale's binade, so that only a scale of another binade takes the branch below.
+  uint32_t s_top = 0;
+  int wexp = 0;
+  // (a maximum beyond 4 million has no bits left for it: such a column keeps weights up to 1)
+  auto shift_of = [&](float mx) { return PF ? fmaf(-mx, cs, fabsf(mx * cs) < 4194304.0f ? (float)wexp : 0.0f) : -mx * cs; };
 
   Splice sp;
   sp.init();
@@ -385,7 +418,7 @@ __device__ __forceinline__ void process_mfma(const FusedArgs &a, const TierView 
   // buffers of meta planes.
   constexpr int PK = FK::ROWB / 16, PV = FV::ROWB / 16;              // pieces per row
   constexpr int NDK = TT * FK::ROWB / 1024, NDV = TT * FV::ROWB / 1024;   // copy instructions of 1 KiB per half
-  constexpr int N_K = NDK + 2, N_V = NDV + 2;                          // with the two meta planes
+  constexpr int N_K = NDK + 4, N_V = NDV;                              // with the four meta planes
   static_assert(!PF || PF64 || (NT == 2 && ((PK == 8 && NDK == 4) || (PK == 4 && NDK == 2)) && (NDV == 4 || NDV == 2)),
                 "the batch the LDS readers cover");
   auto swz = [](int pieces, int r) { return pieces == 4 ? (r >> 2) & 3 : (r >> 1) & 7; };
@@ -439,9 +472,13 @@ __device__ __forceinline__ void process_mfma(const FusedArgs &a, const TierView 
     const uint32_t mo = min(lane, nx_nv - 1) * 8;   // one lane per token (TT = 32: the upper lanes repeat the last row)
     dma4(kmb + mo, wbuf + kTileRowsLds + meta_in);
     dma4(kmb + mo + 4, wbuf + kTileRowsLds + meta_in + 256);
+    const uint8_t *vmb = nx_head + tv.v_meta_off + nx_row0 * 8;   // the values' too: their scales are looked at with the scores
+    dma4(vmb + mo, wbuf + kTileRowsLds + meta_in + 512);
+    dma4(vmb + mo + 4, wbuf + kTileRowsLds + meta_in + 768);
+    meta_in ^= kMetaLds;
   };
   auto issue_v = [&]() {
-    const uint8_t *vb = nx_head + tv.v_off + nx_row0 * FV::ROWB, *vmb = nx_head + tv.v_meta_off + nx_row0 * 8;
+    const uint8_t *vb = nx_head + tv.v_off + nx_row0 * FV::ROWB;
     if constexpr (VT) {   // whole 2 KiB groups (lengths are multiples of 32), copied as they lie
       dma16<0>(vb + lane * 16, wbuf + 4096); dma16<1024>(vb + lane * 16, wbuf + 4096);
       if constexpr (PF64) {   // the second group: inside the record even when the run ends before it (its weights are 0)
@@ -459,10 +496,6 @@ __device__ __forceinline__ void process_mfma(const FusedArgs &a, const TierView 
         dma16(vb + min(r, nx_nv - 1) * FV::ROWB + ((lane % PV) ^ swzv(PV, r)) * 16, wbuf + 4096 + j * 1024);
       }
     }
-    const uint32_t mo = min(lane, nx_nv - 1) * 8;
-    dma4(vmb + mo, wbuf + kTileRowsLds + meta_in + 512);
-    dma4(vmb + mo + 4, wbuf + kTileRowsLds + meta_in + 768);
-    meta_in ^= kMetaLds;
   };
   // Rows in pinned host memory: the whole batch through registers into the same places (over PCIe the asynchronous
   // copies were 3-4 % slower, and the streaming hint has nothing to gain there).  Lane (n, kg) moves piece kg (+ 4) of
@@ -530,8 +563,10 @@ __device__ __forceinline__ void process_mfma(const FusedArgs &a, const TierView 
     } else {
       u32x2 w[8];
       if constexpr (PV == 8) {
-        lds_values_i8(lva, lva ^ 16, lva ^ 32, lva ^ 48, w);
-        lds_values_i8(lva ^ 64, lva ^ 80, lva ^ 96, lva ^ 112, w + 4);
+        uint32_t va = lva;
+        asm volatile("" : "+v"(va));   // formed again in every batch: kept, the eight addresses made the loop spill
+        lds_values_i8(va, va ^ 16, va ^ 32, va ^ 48, w);
+        lds_values_i8(va ^ 64, va ^ 80, va ^ 96, va ^ 112, w + 4);
       } else if constexpr (PF64) {
         lds_values_i4x4(lva, lva ^ 16, lva ^ 32, lva ^ 48, w);
       } else {
@@ -589,11 +624,22 @@ __device__ __forceinline__ void process_mfma(const FusedArgs &a, const TierView 
     // ---- scores (log2 domain), column n of tokens 4 kg + i
     f4 S[NT];
     float mt = -INFINITY;
+    uint32_t top = 0;   // PF: the largest value scale of the lane's own token (one lane per token)
     u32x4 km[4];   // the meta words of the lane's tokens 4 kg + i of two tiles, straight in the score layout
 #pragma unroll
     for (int tt = 0; tt < NT; ++tt) {
       if constexpr (KQ)
-        if (tt % 2 == 0) lds_meta(lds0 + kTileRowsLds + meta_cur + 64 * tt + 16 * kg, km);
+        if (tt % 2 == 0) {
+          const uint32_t plane = lds0 + kTileRowsLds + meta_cur;
+          if (tt == 0) {
+            uint32_t own[2];
+            lds_meta_own(plane + 16 * kg, plane + 512 + 4 * lane, km, own);
+            top = halves_max(own[0], own[1]);                       // scales are not negative
+            top = V4 ? top & 0xffffu : max(top & 0xffffu, top >> 16);
+          } else {
+            lds_meta(plane + 64 * tt + 16 * kg, km);
+          }
+        }
       uint32_t kr[16];
 #pragma unroll
       for (int x = 0; x < NLK; ++x) unpack16<KF>(t.kw[tt][x], kr + x * (16 / NLK), sp);
@@ -637,9 +683,16 @@ __device__ __forceinline__ void process_mfma(const FusedArgs &a, const TierView 
     // ---- online softmax (base 2) per column; m is kept in raw score units, the scale enters the exponent
     mt = fmaxf(mt, __shfl_xor(mt, 16));
     mt = fmaxf(mt, __shfl_xor(mt, 32));
-    if (__any(mt > m)) {
-      const float mn = fmaxf(m, mt);
-      const float alpha = __builtin_amdgcn_exp2f((m - mn) * cs);
+    if (__any(mt > m || top > s_top)) {
+      const float mn = fmaxf(m, mt), old = mcs;
+      if constexpr (PF) {
+        if (__any(top > s_top)) {
+          s_top = wave_max16(top) | 0x3ffu;
+          wexp = 29 - max((int)(s_top >> 10), 1);
+        }
+      }
+      mcs = shift_of(mn);
+      const float alpha = PF ? __builtin_amdgcn_exp2f(mcs - old) : __builtin_amdgcn_exp2f((m - mn) * cs);
       l *= alpha;
       accz *= alpha;
       if constexpr (V4) {
@@ -649,7 +702,6 @@ __device__ __forceinline__ void process_mfma(const FusedArgs &a, const TierView 
       for (int s = 0; s < 8; ++s) acc[s] *= alpha;
       m = mn;
     }
-    const float mcs = -m * cs;
     const h2 ones = {(_Float16)1.0f, (_Float16)1.0f};
 
     // ---- weighted V, two 16-token tiles per 32-deep product
@@ -889,18 +941,21 @@ __device__ __forceinline__ void process_mfma(const FusedArgs &a, const TierView 
       z[g2] = zs[g2];
     }
   }
+  // what the weights are relative to (log2 domain), and the power of two they carry
+  const float wcol = PF && fabsf(m * cs) < 4194304.0f ? (float)wexp : 0.0f, unscale = pow2(-(int)wcol);
+  const float m2 = PF ? wcol - mcs : m * cs;
   float (*w_acc)[128] = (float (*)[128])wbuf;   // [head][channel]; the wave's last batch has been consumed
   if (n < Gr) {
 #pragma unroll
     for (int s = 0; s < 8; ++s)
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        if constexpr (PF) w_acc[n][16 * s + 4 * kg + i] = acc[s][i] + z[s / 4];   // block s row 4 kg + i, as the product leaves it
+        if constexpr (PF) w_acc[n][16 * s + 4 * kg + i] = (acc[s][i] + z[s / 4]) * unscale;   // block s row 4 kg + i, as the product leaves it
         else w_acc[n][slice_channel<VF>(kg, chan<VF>(s, i))] = acc[s][i] + z[s / 4];
       }
     if (kg == 0) {
-      s_m[wave][n] = m * cs;   // log2 domain
-      s_l[wave][n] = l;
+      s_m[wave][n] = m2;
+      s_l[wave][n] = l * unscale;
     }
   }
 }
