@@ -73,6 +73,11 @@ struct Divisor {
   }
 };
 
+// The zero point to subtract.  One of minus infinity (a minimum below fp16's range) would make every quotient infinite,
+// which the correction step turns into NaN; the codes are then the top one, and any finite number far below the values
+// gives them: with a finite scale above 0 the group spans less than 2^20, so its values lie above -2^44.
+__device__ __forceinline__ float zero_of(float z) { return fmaxf(z, -1152921504606846976.0f); }
+
 template <int CTRL>
 __device__ __forceinline__ uint32_t lanes_max(uint32_t v) {
   return max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xf, 0xf, true));
@@ -130,7 +135,7 @@ __device__ __forceinline__ Q2Scale q2_codes(const float (&x)[8], float (&n)[8]) 
   const float s = h2f(sh), z = h2f(zh);
   const Divisor d(s);
 #pragma unroll
-  for (int i = 0; i < 8; ++i) n[i] = d.code(x[i] - z, 0.0f, 15.0f);
+  for (int i = 0; i < 8; ++i) n[i] = d.code(x[i] - zero_of(z), 0.0f, 15.0f);
   return Q2Scale{(uint32_t)sh | ((uint32_t)zh << 16), s, z};
 }
 
@@ -657,7 +662,7 @@ __device__ __forceinline__ void keys_t128(const Source &src, int g, uint8_t *hea
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
     const Divisor d(s_q[0][l16 * 8 + i]);
-    const float z = s_q[1][l16 * 8 + i];
+    const float z = zero_of(s_q[1][l16 * 8 + i]);
 #pragma unroll
     for (int p = 0; p < 8; ++p) x[p][i] = d.code(x[p][i] - z, 0.0f, 15.0f);
   }

@@ -84,3 +84,32 @@ def test_fp32_source(n):
         check(p)
     finally:
         p.close()
+
+
+@pytest.mark.parametrize("name", ["rows", "channel_major", "over_tokens", "summary"])
+def test_zero_points_beyond_half_precision(name):
+    """Minima outside fp16's range (bf16 values may lie there): a zero point of minus infinity puts every element of the
+    group at the top code, one of plus infinity at code 0, whatever the scale; ordinary rows beside them."""
+    g = synth.rng(31)
+    k, v = synth.kv(78, 2, 256, "bf16")
+    ramp = g.random((2, 256, 128)).astype(np.float32)
+    for x in (k, v):
+        x[:, 1::5] = -1e5 + 4e4 * ramp[:, 1::5]          # finite scale, zero point -inf
+        x[:, 2::7] = 1e5 + 4e4 * ramp[:, 2::7]           # zero point +inf
+        x[:, 3::11] = -1e5                               # and a scale of zero
+        x[:, 4::13] = 3e6 * (ramp[:, 4::13] - 0.5)       # scale infinite as well
+    if name == "over_tokens":
+        k[:, :128] = -1e5 + 4e4 * ramp[:, :128]
+        k[:, 128:, ::2] = 1e5
+    spec = {"rows": ("i4", "i4"), "channel_major": ("i8", "i4c"), "over_tokens": ("i4t", "i4"), "summary": ("i4", "i4")}[name]
+    tiers = [dict(k_fmt="bf16", v_fmt="bf16", capacity=128, block_tokens=128, ring_blocks=3),
+             dict(k_fmt=spec[0], v_fmt=spec[1], capacity=10**9, block_tokens=128, ring_blocks=4, summary=name == "summary")]
+    p = Pair(1, 4, 2, tiers, "bf16")
+    try:
+        for x in (k, v):
+            x[...] = synth.round_to(x, "bf16")
+        p.ora.append(1, 0, k, v, 0)
+        p.gpu.append(1, dev(k, "bf16"), dev(v, "bf16"), seq=0)
+        p.assert_state_equal()
+    finally:
+        p.close()
