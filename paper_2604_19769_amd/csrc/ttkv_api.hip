@@ -504,6 +504,7 @@ ttkv_status append_impl(Handle *h, ttkv_cache *c, int32_t tier, int32_t seq, con
   a.n_seq = b1 - b0;
   a.Hkv = c->n_kv_heads;
   a.n_tokens = (int32_t)n_tokens;
+  a.to_host = host_variant;
   fill_via(a, c, tier, through != 0);
 
   // host tier without a workspace: the kernels store into the pinned records themselves (PCIe writes)

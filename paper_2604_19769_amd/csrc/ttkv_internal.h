@@ -167,6 +167,7 @@ struct ConvArgs {
   int32_t seq_id[TTKV_MAX_BATCH];
   int32_t dst_first_tok[TTKV_MAX_BATCH];   // ring token index where the first row lands
   int32_t dst_rec_base[TTKV_MAX_BATCH];
+  int32_t to_host;                         // the rows belong to a pinned tier: stored there directly, or copied from staging records
   int32_t n_via;                           // intermediate formats a value passes through first
   uint32_t via_k, via_v;                   // 8 bits each, the first in the low ones
   // summaries of the destination tier (nullable)

@@ -177,18 +177,25 @@ struct Raw {
   uint4 a, b;
 };
 // Rows are read once and written once: both with the streaming hint.  Tiering 2 x 32 heads x 8192 tokens into fp16 +
-// int4, the stores' part of it: 83.5 -> 77.2 us; scales and zeros, a few bytes per row, go through the caches.
+// int4, the stores' part of it: 83.5 -> 77.2 us; scales and zeros, a few bytes per row, go through the caches.  Not so
+// for a tier in pinned memory, whose writes over PCIe the caches gather: 8 heads x 16384 tokens stored there directly,
+// int4 365 us with the hint, 351 without; int8 682 and 644; K int8 / V int4 channel-major 524 and 500.
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ uint4 ld16(const uint8_t *p) {
   const u32x4 v = __builtin_nontemporal_load((const u32x4 *)p);
   return uint4{v.x, v.y, v.z, v.w};
 }
-__device__ __forceinline__ void st_stream(uint8_t *p, const uint4 &v) {
-  __builtin_nontemporal_store(u32x4{v.x, v.y, v.z, v.w}, (u32x4 *)p);
+__device__ __forceinline__ u32x4 as_vec(const uint4 &v) { return u32x4{v.x, v.y, v.z, v.w}; }
+__device__ __forceinline__ u32x2 as_vec(const uint2 &v) { return u32x2{v.x, v.y}; }
+__device__ __forceinline__ uint32_t as_vec(uint32_t v) { return v; }
+template <bool STREAM, typename T>
+__device__ __forceinline__ void st_row(uint8_t *p, const T &v) {
+  const auto x = as_vec(v);
+  typedef decltype(as_vec(v)) V;
+  if constexpr (STREAM) __builtin_nontemporal_store(x, (V *)p);
+  else *(V *)p = x;
 }
-__device__ __forceinline__ void st_stream(uint8_t *p, const uint2 &v) { __builtin_nontemporal_store(u32x2{v.x, v.y}, (u32x2 *)p); }
-__device__ __forceinline__ void st_stream(uint8_t *p, uint32_t v) { __builtin_nontemporal_store(v, (uint32_t *)p); }
 template <int F>
 __device__ __forceinline__ void load_row(Raw &w, const uint8_t *code, const uint8_t *meta, int l16) {
   if constexpr (F == TTKV_F32) {
@@ -333,14 +340,17 @@ __device__ __forceinline__ void pass_through(const Source &c, float (&x)[8]) {
 // ---------------------------------------------------------------- one unit
 // Where a unit's rows land: `head` is the KV head's part of the destination block, `row0` the block row of the
 // unit's row 0; rows [lo, hi) of the unit are live and row lo is token t_lo of the call.
+// S: rows stored with the streaming hint.
+template <bool S>
 struct Unit {
+  static constexpr bool STREAM = S;
   uint8_t *head;
   int code_off, meta_off, row0;
   int lo, hi, t_lo;
 };
 
-template <int SRC, int THREADS, int ROWS>
-__device__ __forceinline__ void load_unit(const Source &c, const Unit &u, Raw (&raw)[ROWS * 16 / THREADS]) {
+template <int SRC, int THREADS, int ROWS, typename U>
+__device__ __forceinline__ void load_unit(const Source &c, const U &u, Raw (&raw)[ROWS * 16 / THREADS]) {
   const RowSource s = row_source<SRC>(c, u.t_lo);
   const int l16 = threadIdx.x & 15, r = threadIdx.x >> 4;
   if (u.lo == 0 && u.hi == ROWS && s.split >= ROWS) {   // every row live and in one block: one base, constant offsets
@@ -360,8 +370,8 @@ __device__ __forceinline__ void load_unit(const Source &c, const Unit &u, Raw (&
 // s_t32 instead.
 constexpr int kT32Stride = 20;   // words per row of codes: rows 4 apart fall 16 banks apart
 constexpr int kT32Bytes = CHUNK * kT32Stride * 4 + 2 * 2048;
-template <int DST>
-__device__ __forceinline__ void put_row(const Unit &u, int i, int l16, const float (&x)[8], uint32_t *s_t32) {
+template <int DST, typename U>
+__device__ __forceinline__ void put_row(const U &u, int i, int l16, const float (&x)[8], uint32_t *s_t32) {
   uint8_t *const code = u.head + u.code_off, *const meta = u.head + u.meta_off;
   const bool live = i >= u.lo && i < u.hi;
   const uint32_t row = u.row0 + i;
@@ -380,21 +390,21 @@ __device__ __forceinline__ void put_row(const Unit &u, int i, int l16, const flo
       }
       w[k] = lo16 | (hi16 << 16);
     }
-    if (live) st_stream(code + row * 256 + l16 * 16, uint4{w[0], w[1], w[2], w[3]});
+    if (live) st_row<U::STREAM>(code + row * 256 + l16 * 16, uint4{w[0], w[1], w[2], w[3]});
   } else if constexpr (DST == TTKV_I8_SYM_G32) {
     float s;
     const uint16_t sh = q1_codes(x, n, &s);
     const bool zero = s == 0.0f;
     const uint2 w = {zero ? 0u : pack_bytes(n), zero ? 0u : pack_bytes(n + 4)};
     if (live) {
-      st_stream(code + row * 128 + l16 * 8, w);
+      st_row<U::STREAM>(code + row * 128 + l16 * 8, w);
       if ((l16 & 3) == 0) *(uint16_t *)(meta + row * 8 + (l16 >> 2) * 2) = sh;
     }
   } else if constexpr (DST == TTKV_I4_ASYM_G64 || DST == TTKV_I4_ASYM_G64_T32) {
     const Q2Scale q = q2_codes(x, n);
     const uint32_t w = pack_nibbles(n);
     if constexpr (DST == TTKV_I4_ASYM_G64) {
-      if (live) st_stream(code + row * 64 + l16 * 4, w);
+      if (live) st_row<U::STREAM>(code + row * 64 + l16 * 4, w);
     } else {
       s_t32[i * kT32Stride + l16] = w;
     }
@@ -408,8 +418,8 @@ __device__ __forceinline__ void keep_values(float (*s_x)[128], int i, int l16, c
 }
 
 // The unit's loaded rows.  SUM: the arriving values also go to s_x.
-template <int SRC, int DST, int THREADS, int ROWS, bool SUM>
-__device__ __forceinline__ void convert_unit(const Source &c, const Unit &u, const Raw (&raw)[ROWS * 16 / THREADS],
+template <int SRC, int DST, int THREADS, int ROWS, bool SUM, typename U>
+__device__ __forceinline__ void convert_unit(const Source &c, const U &u, const Raw (&raw)[ROWS * 16 / THREADS],
                                              float (*s_x)[128], uint32_t *s_t32) {
   const int l16 = threadIdx.x & 15;
 #pragma unroll
@@ -417,7 +427,7 @@ __device__ __forceinline__ void convert_unit(const Source &c, const Unit &u, con
     const int i = p * (THREADS / 16) + (threadIdx.x >> 4);
     constexpr bool COPY = SRC == DST && (DST == TTKV_F16 || DST == TTKV_BF16);
     if (COPY && !SUM && c.n_via == 0) {   // bytes as they are
-      if (i >= u.lo && i < u.hi) st_stream(u.head + u.code_off + (u.row0 + i) * 256 + l16 * 16, raw[p].a);
+      if (i >= u.lo && i < u.hi) st_row<U::STREAM>(u.head + u.code_off + (u.row0 + i) * 256 + l16 * 16, raw[p].a);
       continue;
     }
     float x[8];
@@ -442,8 +452,8 @@ __device__ __forceinline__ void convert_unit(const Source &c, const Unit &u, con
 // A thread takes the words of eight such tokens (eight channels each) and turns them by 8 x 8 nibbles in registers --
 // nibbles by masks, then bytes by v_perm, 32 operations for 8 words instead of 24 per word gathered one by one -- and
 // the words meet in LDS in the group's order, pieces permuted inside eights to spread them over the banks.
-template <int THREADS>
-__device__ __forceinline__ void store_t32(const Unit &u, uint32_t *s_t32) {
+template <int THREADS, typename U>
+__device__ __forceinline__ void store_t32(const U &u, uint32_t *s_t32) {
   uint4 *const s_out = (uint4 *)(s_t32 + CHUNK * kT32Stride);
   __syncthreads();
   if (threadIdx.x < 128) {
@@ -473,7 +483,7 @@ __device__ __forceinline__ void store_t32(const Unit &u, uint32_t *s_t32) {
   __syncthreads();
   for (int idx = threadIdx.x; idx < 256; idx += THREADS) {
     const int g = idx >> 7, p = idx & 127, turn = 2 * ((p >> 4) & 3) + (p >> 6);
-    if (g * 32 >= u.lo && g * 32 < u.hi) st_stream(u.head + u.code_off + (u.row0 + g * 32) * 64 + p * 16, s_out[g * 128 + (p ^ turn)]);
+    if (g * 32 >= u.lo && g * 32 < u.hi) st_row<U::STREAM>(u.head + u.code_off + (u.row0 + g * 32) * 64 + p * 16, s_out[g * 128 + (p ^ turn)]);
   }
 }
 
@@ -484,8 +494,8 @@ __device__ __forceinline__ void store_t32(const Unit &u, uint32_t *s_t32) {
 // token order, so the sums are reproducible bit for bit; what made the former kernel (one thread per channel,
 // reading and re-quantizing one row after the other from memory) 331 us of the 572 us tiering of 4 x 32768 tokens
 // was the chain of loads, not the additions.
-template <int THREADS>
-__device__ __forceinline__ void sum_unit(const Source &src, Unit u, int src_fmt, int dst_fmt, int rows_lo, int rows_hi, float *k_sum,
+template <int THREADS, typename U>
+__device__ __forceinline__ void sum_unit(const Source &src, U u, int src_fmt, int dst_fmt, int rows_lo, int rows_hi, float *k_sum,
                                          uint16_t *k_summary, float inv_bt, char *s_buf) {
   // k_sum, k_summary: the block's; rows [rows_lo, rows_hi) of the block arrive, row rows_lo is token u.t_lo
   float (*s_x)[SUM_ROWS][128] = (float (*)[SUM_ROWS][128])s_buf;            // two buffers
@@ -544,7 +554,7 @@ __device__ __forceinline__ void sum_unit(const Source &src, Unit u, int src_fmt,
 
 // Grid: x = K units then V units of one (entry, KV head), y = entry x KV head.  SUM: K units are whole destination
 // blocks and keep the key sums (dst_fmt of K may be NO_STORE: sums only); otherwise every unit is 64 rows.
-template <bool SUM>
+template <bool SUM, bool STREAM>
 __global__ __launch_bounds__(SUM ? SUM_THREADS : 256, SUM ? 6 : 8) void convert_rows_kernel(const ConvArgs a, int k_units, int k_dst_fmt) {
   constexpr int THREADS = SUM ? SUM_THREADS : 256;
   constexpr int SUM_BYTES = 2 * SUM_ROWS * 128 * 4 + 512;
@@ -557,7 +567,7 @@ __global__ __launch_bounds__(SUM ? SUM_THREADS : 256, SUM ? 6 : 8) void convert_
   const TierView dst = a.dst;
   const Source src = make_source(a, which, j, h, seq);
   const int src_fmt = src.flat ? a.s.flat_fmt : which ? src.tier.v_fmt : src.tier.k_fmt;
-  Unit u;
+  Unit<STREAM> u;
   u.code_off = which ? dst.v_off : 0;
   u.meta_off = which ? dst.v_meta_off : dst.k_meta_off;
 
@@ -610,7 +620,7 @@ __global__ __launch_bounds__(SUM ? SUM_THREADS : 256, SUM ? 6 : 8) void convert_
 // group turned by 90 degrees): one workgroup per (token group, KV head, entry).  The group's 128 arriving rows are
 // read once and stay in registers (a 16-lane group holds rows r, r + 16, ..; 8 channels per lane); the ranges meet
 // over the lanes and waves, one thread per channel forms the scale, and the rows are coded from the registers.
-template <int SRC>
+template <int SRC, bool STREAM>
 __device__ __forceinline__ void keys_t128(const Source &src, int g, uint8_t *head, int k_meta_off, int row0, float (*s_lo)[128],
                                           float (*s_hi)[128], float (*s_q)[128]) {
   const int l16 = threadIdx.x & 15, wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -668,8 +678,9 @@ __device__ __forceinline__ void keys_t128(const Source &src, int g, uint8_t *hea
   }
 #pragma unroll
   for (int p = 0; p < 8; ++p)
-    st_stream(head + (row0 + p * 16 + (threadIdx.x >> 4)) * 64 + l16 * 4, pack_nibbles(x[p]));
+    st_row<STREAM>(head + (row0 + p * 16 + (threadIdx.x >> 4)) * 64 + l16 * 4, pack_nibbles(x[p]));
 }
+template <bool STREAM>
 __global__ __launch_bounds__(256) void convert_keys_t128_kernel(const ConvArgs a) {
   __shared__ float s_lo[4][128], s_hi[4][128], s_q[2][128];
   const int g = blockIdx.x, j = blockIdx.y / a.Hkv, h = blockIdx.y - j * a.Hkv;
@@ -680,15 +691,16 @@ __global__ __launch_bounds__(256) void convert_keys_t128_kernel(const ConvArgs a
   const int tok = wrap(a.dst_first_tok[j] + g * 128, dst);
   const int r = tok / dst.bt, row0 = tok - r * dst.bt;
   uint8_t *const head = block_head(dst, seq, dst_rec_base, r, h);
-#define TTKV_T128(S, D) keys_t128<S>(src, g, head, dst.k_meta_off, row0, s_lo, s_hi, s_q)
+#define TTKV_T128(S, D) keys_t128<S, STREAM>(src, g, head, dst.k_meta_off, row0, s_lo, s_hi, s_q)
   TTKV_FOR_SOURCES(0, TTKV_T128)
 #undef TTKV_T128
 }
 
 }  // namespace
 
-// Converts the rows and, where the destination keeps block summaries (a.k_sum), their key sums.
-hipError_t launch_convert(const ConvArgs &a, hipStream_t s, int *n_kernels) {
+namespace {
+template <bool STREAM>
+hipError_t launch(const ConvArgs &a, hipStream_t s, int *n_kernels) {
   if ((int64_t)a.n_seq * a.Hkv * a.n_tokens <= 0) return hipSuccess;
   const unsigned y = (unsigned)(a.n_seq * a.Hkv);
   int chunks = 0, blocks = 0;      // units of the entry that needs most
@@ -698,18 +710,24 @@ hipError_t launch_convert(const ConvArgs &a, hipStream_t s, int *n_kernels) {
   }
   const bool t128 = a.dst.k_fmt == TTKV_I4_ASYM_T128;   // whole aligned groups (the caller has checked)
   if (t128) {
-    hipLaunchKernelGGL(convert_keys_t128_kernel, dim3(a.n_tokens / 128, y), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(convert_keys_t128_kernel<STREAM>, dim3(a.n_tokens / 128, y), dim3(256), 0, s, a);
     ++*n_kernels;
   }
   if (a.k_sum) {
-    hipLaunchKernelGGL(convert_rows_kernel<true>, dim3(blocks + chunks, y), dim3(SUM_THREADS), 0, s, a, blocks,
+    hipLaunchKernelGGL((convert_rows_kernel<true, STREAM>), dim3(blocks + chunks, y), dim3(SUM_THREADS), 0, s, a, blocks,
                        t128 ? NO_STORE : a.dst.k_fmt);
   } else {
     const int k_units = t128 ? 0 : chunks;
-    hipLaunchKernelGGL(convert_rows_kernel<false>, dim3(k_units + chunks, y), dim3(256), 0, s, a, k_units, a.dst.k_fmt);
+    hipLaunchKernelGGL((convert_rows_kernel<false, STREAM>), dim3(k_units + chunks, y), dim3(256), 0, s, a, k_units, a.dst.k_fmt);
   }
   ++*n_kernels;
   return hipGetLastError();
+}
+}  // namespace
+
+// Converts the rows and, where the destination keeps block summaries (a.k_sum), their key sums.
+hipError_t launch_convert(const ConvArgs &a, hipStream_t s, int *n_kernels) {
+  return a.to_host ? launch<false>(a, s, n_kernels) : launch<true>(a, s, n_kernels);
 }
 
 }  // namespace ttkv
