@@ -97,12 +97,11 @@ struct SplitMemo {
   bool valid;
   uint32_t sig;      // tiers, formats, head counts, batch
   int n_runs;
-  bool sel;          // the last tier was a device-side selection
   int step;          // index into the table of rounds
   int64_t bytes;     // bytes of one pass over one KV head when it was chosen
 };
 struct Plan {
-  SplitMemo memo;
+  SplitMemo memo[2];   // of the plans over everything, and of those with a device-side selection
   std::vector<Run> runs;
   std::vector<Fetch> fetch;
   std::vector<const Run *> order;   // launch order of `runs`
