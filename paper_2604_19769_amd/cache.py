@@ -216,18 +216,25 @@ class TieredCache:
         assert q.is_contiguous() and k_new.is_contiguous() and v_new.is_contiguous()
         assert tuple(k_new.shape) == tuple(v_new.shape) == (self.B, self.Hkv, 1, 128)
         stride = self._select_buffers(k)
-        # parts: every other tier as usual; the last one min(k, live blocks) blocks of fixed items -- an upper bound
-        # is what a dense pass over everything would use, at the lengths the attention will see
-        self.len[0] += 1
-        parts = B.ttkv_count_parts(self.h, self.c, None, None, 0, 0)
-        self.len[0] -= 1
-        last = self.cfg[-1]
-        per_block = max(1, last.block_tokens // (2048 if last.mem == "host" else 256))
-        parts += per_block * min(k, int(max((l + last.block_tokens - 1) // last.block_tokens for l in self.len[-1]))) + 1
-        ws = self._workspace(max(parts, 1))
-        B.ttkv_decode_step_topk(self.h, self.c, q, q_fmt, k_new, v_new, fmt, self.out, self.lse, k, self.sel_blocks,
-                                self.sel_count, stride, self.sel_scratch, self.sel_scratch.numel(), ws, ws.numel(),
-                                self._compute())
+        # The split of a selection is planned inside the call, which refuses a workspace that is too small for it before
+        # anything is enqueued: the workspace is sized once from a dense plan's parts and grows when it is refused (no
+        # run is cut finer than into items of 256 tokens, which bounds it).
+        self._parts_age = None
+        if self.ws is None or self.ws_slots != self.n_slots:
+            self.len[0] += 1
+            parts = B.ttkv_count_parts(self.h, self.c, None, None, 0, 0)
+            self.len[0] -= 1
+            self._workspace(max(parts, 1))
+        while True:
+            try:
+                B.ttkv_decode_step_topk(self.h, self.c, q, q_fmt, k_new, v_new, fmt, self.out, self.lse, k, self.sel_blocks,
+                                        self.sel_count, stride, self.sel_scratch, self.sel_scratch.numel(), self.ws,
+                                        self.ws.numel(), self._compute())
+                break
+            except B.TTKVError as e:
+                if e.status != B.ERR_WORKSPACE or self.ws_parts > sum(int(n.max()) // 64 + 2 for n in self.len):
+                    raise
+                self._workspace(2 * self.ws_parts)
         return self.out, self.lse
 
     def _evict_if_due(self, overlap):
