@@ -258,7 +258,8 @@ double played_loss(const ItemGroup *g, int n, int slots, double ideal) {
   return place_in_units(g, n, slots, kItemCost, span) / span;
 }
 
-double choose_item_bytes(const ttkv_cache *c, const bool *dense, int target_items, const int64_t *last_tokens, SplitMemo *memo) {
+double choose_item_bytes(const ttkv_cache *c, const bool *dense, int target_items, const int64_t *last_tokens, int default_target, SplitMemo *memo) {
+  // default_target: default_items
   // last_tokens: null, or the tokens of the last tier that are attended, per sequence (its selected blocks)
   // The runs, gathered once: length and bytes per token (at most batch x tiers of them).
   struct RunShape { int32_t len, per_token, finest; };
@@ -280,9 +281,8 @@ double choose_item_bytes(const ttkv_cache *c, const bool *dense, int target_item
   if (S == 0) return 1.0;
   const int Hkv = c->n_kv_heads, G = c->n_q_heads / Hkv;
   if (target_items) return std::max(1.0, (double)S * Hkv / target_items);
-  const int legacy = default_items(c);
-  const bool vector_kernel = legacy == 2560;
-  const int resident = vector_kernel ? 1024 : legacy;                             // workgroups on the chip at once
+  const bool vector_kernel = default_target == 2560;
+  const int resident = vector_kernel ? 1024 : default_target;                             // workgroups on the chip at once
   const int per_item = Hkv * (vector_kernel ? G / attn_group_width(G) : (G + 15) / 16);   // workgroups per item
   // the vector kernel's default of 2.5 rounds is as fast as one round when the items are equal (measured)
   static const float steps_v[] = {2.5f, 1.0f, 1.5f, 2.0f, 3.0f, 4.0f, 5.0f, 6.0f};
@@ -375,7 +375,8 @@ void build_plan(const ttkv_cache *c, const int32_t *sel_blocks, const int32_t *s
       const int64_t live = T.len[b] ? (T.start[b] + T.len[b] + T.block_tokens - 1) / T.block_tokens - T.start[b] / T.block_tokens : 0;
       sel_tokens[b] = std::max<int64_t>(0, std::min<int64_t>(std::min(ds->k, ds->stride), live)) * T.block_tokens;
     }
-  const double item_bytes = choose_item_bytes(c, P->even, target_items, ds ? sel_tokens : nullptr, &P->memo[ds != nullptr]);
+  P->resident_items = default_items(c);
+  const double item_bytes = choose_item_bytes(c, P->even, target_items, ds ? sel_tokens : nullptr, P->resident_items, &P->memo[ds != nullptr]);
   for (int t = 0; t < c->n_tiers; ++t) {
     const ttkv_tier &T = c->tier[t];
     const Layout L = make_layout(T, c->n_kv_heads);
@@ -390,7 +391,7 @@ void build_plan(const ttkv_cache *c, const int32_t *sel_blocks, const int32_t *s
       // alone fills the chip, finer items, down to 256 tokens, when few blocks are selected.
       int64_t n_sel = 0;
       for (int b = 0; b < c->batch; ++b) n_sel += sel_count[b];
-      const int legacy = default_items(c), resident = legacy == 2560 ? 1024 : legacy;
+      const int resident = P->resident_items == 2560 ? 1024 : P->resident_items;
       const int64_t wgs = std::max<int64_t>(1, n_sel * c->n_kv_heads);
       const int ipb = (int)std::min<int64_t>(L.bt / 256, std::max<int64_t>(1, (resident + wgs - 1) / wgs));
       P->chunk[t] = ((L.bt + ipb - 1) / ipb + 63) / 64 * 64;
@@ -492,6 +493,7 @@ void build_plan(const ttkv_cache *c, const int32_t *sel_blocks, const int32_t *s
       }
     }
   }
+  for (Run &r : P->runs) r.item_bytes = (int64_t)(r.len / r.n_chunks) * per_token_bytes(c->tier[r.tier]);
   P->max_parts = 0;
   for (int b = 0; b < c->batch; ++b) P->max_parts = std::max(P->max_parts, P->parts[b]);
 }
@@ -1037,15 +1039,16 @@ static ttkv_status decode_impl(Handle *h, const ttkv_cache *c, const void *q, in
   // among the tiers in HBM the runs with the largest items first (as played_loss plays them through): what is left for the
   // last round is then small.  Multi-head 32K: 115.4 -> 110.7 us.  The vector kernel keeps a ragged batch in the order of
   // its sequences, whose neighbours read adjacent chunks (3 sequences of up to 26K tokens, 32 heads: 60.9 us, sorted 63.5).
-  bool sorted = default_items(c) != 2560;
+  bool sorted = P.resident_items != 2560;
   if (!sorted) {
     sorted = true;
     for (int t = 0; t < c->n_tiers; ++t)
       for (int b = 1; b < c->batch; ++b) sorted &= c->tier[t].len[b] == c->tier[t].len[0];
   }
-  const auto first_hbm = std::find_if(order.begin(), order.end(), [&](const Run *r) { return c->tier[r->tier].mem != TTKV_MEM_HOST_PINNED; });
-  auto item_bytes = [&](const Run *r) { return (int64_t)(r->len / r->n_chunks) * per_token_bytes(c->tier[r->tier]); };
-  if (sorted) std::stable_sort(first_hbm, order.end(), [&](const Run *x, const Run *y) { return item_bytes(x) > item_bytes(y); });
+  if (sorted) {   // in place (a stable sort takes a buffer from the heap in every call): equal items stay in plan order
+    const auto first_hbm = std::find_if(order.begin(), order.end(), [&](const Run *r) { return c->tier[r->tier].mem != TTKV_MEM_HOST_PINNED; });
+    std::sort(first_hbm, order.end(), [](const Run *x, const Run *y) { return x->item_bytes != y->item_bytes ? x->item_bytes > y->item_bytes : x < y; });
+  }
   // a timed call may issue its launch(es) several times back to back (same arguments, same partials): the event
   // pair's own cost is then spread over them
   const int reps = timed ? std::max(1, h->time_repeat) : 1;

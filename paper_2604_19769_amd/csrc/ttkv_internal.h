@@ -74,6 +74,7 @@ struct Run {
   bool selected;   // blocks named by the device-side selection (first_tok: newest block id; len: their number for a host
                    // tier, their tokens for a tier in HBM)
   int part_base, n_chunks;
+  int64_t item_bytes;   // of one of its items (one KV head)
 };
 // Selection left on the device by the top-k kernel: ids [batch][stride], min(k, live blocks) of them per sequence.
 struct DevSel {
@@ -109,6 +110,7 @@ struct Plan {
   bool even[TTKV_MAX_TIERS];   // the tier's runs are cut into items of equal size each (chunk[] is then the size aimed at)
   int parts[TTKV_MAX_BATCH];
   int max_parts;
+  int resident_items;   // the kernel's default split (default_items)
   size_t slot_bytes;
   ttkv_status status;
 };
