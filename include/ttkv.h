@@ -245,9 +245,10 @@ ttkv_status ttkv_decode_attn(ttkv_handle h, const ttkv_cache *c, const void *q, 
  * results as ttkv_decode_attn with n_slots = 0 (host tiers read in place) and both streams = `stream`, but the
  * split partials live in an array of TTKV_NOALLOC_SCRATCH_BYTES (16 MiB) that is part of the library's device
  * code: each GPU the library runs on holds its own copy from the first call on it until the process ends.  The
- * call allocates nothing on the device and calls no allocating routine.  WORKSPACE if the partials this cache
- * needs right now, batch x n_q_heads x ttkv_count_parts(.., n_slots 0) x 520 bytes, exceed the array; nothing
- * is enqueued then.  All calls on one GPU share that GPU's array: two calls whose kernels may overlap on one
+ * call allocates nothing on the device and calls no allocating routine.  Where the partials of the default split,
+ * batch x n_q_heads x ttkv_count_parts(.., n_slots 0) x 520 bytes, exceed the array, a coarser split is taken (the
+ * result is the same up to fp32 rounding); WORKSPACE if none fits, or if a split set by ttkv_set_split does not;
+ * nothing is enqueued then.  All calls on one GPU share that GPU's array: two calls whose kernels may overlap on one
  * GPU (different streams, different threads) race; calls on one stream are ordered and safe.  Nothing in the
  * array needs clearing between calls (every part the merge reads is written by the same call first). */
 ttkv_status ttkv_decode_attn_noalloc(ttkv_handle h, const ttkv_cache *c, const void *q, int32_t q_fmt, float *out,

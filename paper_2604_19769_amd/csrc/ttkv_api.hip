@@ -961,7 +961,8 @@ static ttkv_status decode_impl(Handle *h, const ttkv_cache *c, const void *q, in
                                const int32_t *sel_blocks, const int32_t *sel_count, int32_t sel_stride, void *workspace,
                                size_t ws_bytes, int32_t n_slots, void *compute_, void *copy_, const void *k_new,
                                const void *v_new, int32_t new_fmt, bool check_only = false, const DevSel *ds = nullptr,
-                               Chain *trace = nullptr) {
+                               Chain *trace = nullptr, bool fixed_ws = false) {
+  // fixed_ws: the caller cannot bring a larger workspace; a coarser split than the default one is taken where that fits
   ttkv_status st = validate_cache(c, h ? h->check_tables : true);
   if (st != TTKV_OK) return st;
   if (!q || !out || (q_fmt != TTKV_F16 && q_fmt != TTKV_BF16)) return TTKV_ERR_INVALID_ARG;
@@ -986,6 +987,9 @@ static ttkv_status decode_impl(Handle *h, const ttkv_cache *c, const void *q, in
   const size_t mis = (256 - ((uintptr_t)workspace & 255)) & 255;
   if (ws_bytes < mis + slots_bytes) return TTKV_ERR_WORKSPACE;
   const int64_t stride = (int64_t)((ws_bytes - mis - slots_bytes) / (rows * 130 * sizeof(float)));
+  if (fixed_ws && h->target_items == 0)
+    for (int target = P.resident_items; P.max_parts > stride && target > 0; target /= 2)
+      build_plan(c, sel_blocks, sel_count, sel_stride, staged, target, &P, ds);
   if (stride < std::max(1, P.max_parts) || P.max_parts > TTKV_MAX_PARTS) return TTKV_ERR_WORKSPACE;
   const int32_t part_stride = (int32_t)std::min<int64_t>(stride, TTKV_MAX_PARTS);
   if (check_only) return TTKV_OK;   // nothing enqueued so far
@@ -1198,7 +1202,7 @@ ttkv_status ttkv_decode_attn_noalloc(ttkv_handle hh, const ttkv_cache *c, const 
   if (st != TTKV_OK) return st;
   // the partials need no clearing: every part the merge reads is written by this call's attention launch first
   return decode_impl(h, c, q, q_fmt, out, lse, sel_blocks, sel_count, sel_stride, ws, TTKV_NOALLOC_SCRATCH_BYTES, 0, stream,
-                     stream, nullptr, nullptr, 0);
+                     stream, nullptr, nullptr, 0, false, nullptr, nullptr, true);
 }
 
 ttkv_status ttkv_decode_step(ttkv_handle hh, ttkv_cache *c, const void *q, int32_t q_fmt, const void *k_new,

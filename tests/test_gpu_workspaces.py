@@ -4,6 +4,7 @@ import numpy as np
 import pytest
 import torch
 
+from paper_2604_19769_amd import binding as B
 from paper_2604_19769_amd.cache import TierConfig, TieredCache
 
 pytestmark = pytest.mark.gpu
@@ -38,5 +39,34 @@ def test_a_selection_that_cuts_the_other_tiers_finer(batch, Hq, Hkv, k, tiers):
             assert torch.allclose(lse, torch.full_like(lse, float(np.log(attended))), atol=1e-4)
         c.step(q, z, z)        # and a dense step with the same workspace
         torch.cuda.synchronize()
+    finally:
+        c.close()
+
+
+@pytest.mark.parametrize("batch,Hq,Hkv,tiers", [
+    (53, 64, 2, [("f16", "f16", 128, 1), ("i8", "i8", 128, 6879)]),
+    (26, 64, 2, [("f16", "f16", 128, 1593), ("i4", "i4", 128, 24623)]),
+])
+def test_noalloc_takes_a_coarser_split_where_the_default_one_does_not_fit(batch, Hq, Hkv, tiers):
+    """The default split's partials exceed the library's array (16 MiB); the same result as with a workspace, up to the
+    rounding of another split: fp16 weights, 2^-11 of the values."""
+    c = zeros_cache(batch, Hq, Hkv, tiers, False)
+    try:
+        g = torch.Generator(device="cuda:0")
+        g.manual_seed(5)
+        for t, (_, _, bt, n) in enumerate(tiers):
+            c.len[t][:] = 0
+            k, v = (torch.randn(batch, Hkv, n, 128, generator=g, device="cuda:0").half() for _ in range(2))
+            c.append(t, k, v)
+        parts = B.ttkv_count_parts(c.h, c.c)
+        assert batch * Hq * parts * 520 > B.TTKV_NOALLOC_SCRATCH_BYTES
+        q = torch.randn(batch, Hq, 128, generator=g, device="cuda:0").half()
+        ref, ref_lse = (x.clone() for x in c.decode(q))
+        out, lse = torch.full_like(ref, 7.0), torch.full_like(ref_lse, 7.0)
+        B.ttkv_decode_attn_noalloc(c.h, c.c, q, B.F16, out, lse, None, None, 0, torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        assert float((out - ref).abs().max()) <= 2e-3 * float(ref.abs().max())
+        assert torch.allclose(lse, ref_lse, atol=1e-4)
+        assert B.ttkv_count_parts(c.h, c.c) == parts       # the default stays the default
     finally:
         c.close()
