@@ -108,7 +108,9 @@ int copy_granule(int64_t rec_bytes) {
 // Default split-K granularity, in workgroups resident at once on 256 CUs: 2.5 rounds of 4 per CU for the vector
 // kernel (flat between 1 and 3 rounds, measured), exactly one round of the grouped-query matrix-core kernel: 2 per CU
 // with 4-bit tiers, 3 without.  (Two are also the better choice for int8 tiers with many heads: 64 q / 4 kv heads,
-// 4 x 100K tokens, 81.9 us with 512 items, 89.4 with 768.)
+// 4 x 100K tokens, 81.9 us with 512 items, 89.4 with 768.)  Launches with keys grouped over tokens that go to the vector
+// kernel's head pairs all the same keep the matrix-core counts: 2 x 51K tokens 129 us with 8 heads per KV head and
+// 129-134 with 16, against 148 and 183-185 with the vector kernel's 2560.
 int default_items(const ttkv_cache *c) {
   const int G = c->n_q_heads / c->n_kv_heads;
   bool two_per_cu = false;
@@ -116,7 +118,7 @@ int default_items(const ttkv_cache *c) {
     if (!attn_mfma_fits(c->tier[t].k_fmt, c->tier[t].v_fmt, G)) return 2560;
     two_per_cu |= attn_mfma_four_bit(c->tier[t].k_fmt, c->tier[t].v_fmt) || (G > 8 && !is_fp(c->tier[t].k_fmt));
   }
-  return !attn_mfma_pays(G) ? 2560 : two_per_cu ? 512 : 768;
+  return two_per_cu ? 512 : 768;
 }
 
 inline int per_token_bytes(const ttkv_tier &U) {

@@ -1045,7 +1045,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FOUR_BIT ? 
 
 }  // namespace
 
-// Do the kernel's cases take these formats?
+// Do the kernel's cases take these formats?  From two query heads per KV head on (measured against the vector kernel's
+// head pair at two heads: fp16 6.4 against 6.2 TB/s, int8 6.2 against 5.3, int4 5.2 against 4.5, K 8-bit / V 4-bit 6.0
+// against 4.3, keys grouped over tokens 4.4 against 3.5).
 bool attn_mfma_fits(int k_fmt, int v_fmt, int G) {
   if (G < 2) return false;
   if (v_fmt == TTKV_I4_ASYM_G64_T32) return k_fmt == TTKV_I8_SYM_G32 || k_fmt == TTKV_I4_ASYM_G64;
@@ -1053,40 +1055,36 @@ bool attn_mfma_fits(int k_fmt, int v_fmt, int G) {
   return true;
 }
 
-// Does the single pass over the bytes pay off?  From two query heads per KV head on (measured against the vector
-// kernel's head pair at two heads: fp16 6.4 against 6.2 TB/s, int8 6.2 against 5.3, int4 5.2 against 4.5, K 8-bit /
-// V 4-bit 6.0 against 4.3, keys grouped over tokens 4.4 against 3.5).
-bool attn_mfma_pays(int G) { return G >= 2; }
-
 bool attn_mfma_four_bit(int k_fmt, int v_fmt) { return !is_fp(k_fmt) && !(k_fmt == TTKV_I8_SYM_G32 && v_fmt == k_fmt); }
 
 namespace {
-// What one launch needs: heads per block, 4-bit tiers, keys grouped over tokens, and whether the vector kernel's head pairs take it
-// (keys grouped over tokens beside int8 keys with more than 4 or int4 keys with more than 8 heads per KV head).
+// Key formats that stay with the vector kernel's head pairs when keys grouped over tokens are in the same launch: the
+// former score product had no case for them.  This one has, and the pairs are not the faster route any more (2 x 51K
+// tokens, 8 heads per KV head 129 us against 41, 16 heads 134 against 29).
+bool pairs_beside_t128(int k_fmt, int G) { return (k_fmt == TTKV_I8_SYM_G32 && G > 4) || (k_fmt == TTKV_I4_ASYM_G64 && G > 8); }
+
+// What one launch needs: heads per block, 4-bit tiers, keys grouped over tokens.  ok: the kernel takes it.
 struct MfmaShape {
   int heads;
-  bool four_bit, t128, pairs, ok;
+  bool four_bit, t128, ok;
 };
 MfmaShape mfma_shape(const FusedArgs &a) {
   const int G = a.Hq / a.Hkv;
-  MfmaShape m{std::min(16, G), false, false, false, true};
-  bool many = false;
+  MfmaShape m{std::min(16, G), false, false, true};
+  bool pairs = false;
   for (int j = 0; j < a.n_entries; ++j) {
     const TierView &tv = a.tv[entry_tier(a.e[j])];
     m.ok &= attn_mfma_fits(tv.k_fmt, tv.v_fmt, G);
     m.four_bit |= attn_mfma_four_bit(tv.k_fmt, tv.v_fmt);
     m.t128 |= tv.k_fmt == TTKV_I4_ASYM_T128;
-    many |= (tv.k_fmt == TTKV_I8_SYM_G32 && G > 4) || (tv.k_fmt == TTKV_I4_ASYM_G64 && G > 8);
+    pairs |= pairs_beside_t128(tv.k_fmt, G);
   }
-  m.pairs = m.t128 && many;
+  m.ok &= !(m.t128 && pairs);
   return m;
 }
 }  // namespace
 
-bool attn_mfma_eligible(const FusedArgs &a) {
-  const MfmaShape m = mfma_shape(a);
-  return m.ok && attn_mfma_pays(a.Hq / a.Hkv) && !m.pairs;
-}
+bool attn_mfma_eligible(const FusedArgs &a) { return mfma_shape(a).ok; }
 
 hipError_t launch_attn_mfma(const FusedArgs &a0, hipStream_t s) {
   const MfmaShape m = mfma_shape(a0);
