@@ -69,7 +69,7 @@ typedef enum {
   TTKV_ERR_INVALID_ARG = 1, /* NULL / out-of-range / inconsistent argument */
   TTKV_ERR_CAPACITY = 2,    /* a tier ring would overflow, or too few tokens to evict */
   TTKV_ERR_UNSUPPORTED = 3, /* head_dim != 128, format combination without a kernel */
-  TTKV_ERR_WORKSPACE = 4,   /* workspace smaller than ttkv_workspace_bytes() */
+  TTKV_ERR_WORKSPACE = 4,   /* workspace smaller than ttkv_workspace_bytes(), or more than 2^20 parts per row */
   TTKV_ERR_HIP = 5          /* a HIP launch / copy / event call failed; code in ttkv_stats */
 } ttkv_status;
 
@@ -167,7 +167,9 @@ int32_t ttkv_count_parts(ttkv_handle h, const ttkv_cache *c, const int32_t *sel_
  * (tier, sequence) run is cut into items of equal size (multiples of 64 tokens, 256 to 8192).
  * 0 restores the default: chosen per call from the lengths -- the number of rounds of resident
  * workgroups that suits the kernel the cache's formats and head counts select, raised in steps
- * until the items of all runs are within 10 % of each other and the last round is filled.
+ * until the items of all runs are within 10 % of each other and the last round is filled; where two
+ * workgroups per CU run (2 or more heads per KV head and 4-bit tiers, or more than 8 and int8), until the
+ * items placed one after the other, largest first, end within 3 % of an even split.
  * More items: better balance over 256 CUs, more partials. */
 ttkv_status ttkv_set_split(ttkv_handle h, int32_t target_items);
 /* Paged tiers (Eq. (1): the index maps a block to where it is stored): by default every call that takes the handle

@@ -33,12 +33,12 @@ __device__ __forceinline__ uint16_t f2h(float f) { return __half_as_ushort(__flo
 
 // ---------------------------------------------------------------- the recipes, eight channels per lane
 // The codes of Sec. 4.2 are rint(RN(y / s)), one IEEE division per element.  The divisor is an fp16 number common to
-// the group, so its correctly rounded reciprocal r is formed once, and q = y r, q + (y - q s) r (two fused steps) IS
-// the correctly rounded quotient: checked against the division for every fp16 mantissa of s and every fp32 mantissa
-// of y.  Three operations per element where a division takes ten; a rounded product with an exact fallback near
-// half-integers, used here before, cost as much and sent a tenth of the rows through the divisions (keys and scales
-// are both fp16, so exact ties are common).  Adding 1.5 x 2^23 rounds to nearest even and leaves the integer in the
-// low mantissa bits, from where the codes are packed without conversions.
+// the group, so its correctly rounded reciprocal r is formed once, and q = y r, q + (y - q s) r (two fused steps,
+// Markstein's correction) IS the correctly rounded quotient: equal to the division for every fp16 mantissa of s with
+// every fp32 mantissa of y (a test takes all 2^33 pairs).  Three operations per element where a division takes ten; a
+// rounded product with an exact fallback near half-integers, used here before, cost as much and sent a tenth of the rows
+// through the divisions (keys and scales are both fp16, so exact ties are common).  Adding 1.5 x 2^23 rounds to nearest
+// even and leaves the integer in the low mantissa bits, from where the codes are packed without conversions.
 constexpr float kMagic = 12582912.0f;
 __device__ __forceinline__ float clamped(float t, float lo, float hi) {
   return __builtin_amdgcn_fmed3f(t, lo, hi);   // NaN: the lower bound, as fmin(fmax(NaN, lo), hi)

@@ -1,6 +1,10 @@
 """The conversion kernels' shortcuts against the recipes they stand for (Sec. 4.2: one IEEE operation per step), emulated
 in fp32 with numpy: the division by the constants 15 and 127, and by a group's fp16 scale, in three operations each.  (The GPU tests compare the kernels' codes and
 key sums with the oracle's.)"""
+import ctypes as C
+import os
+import subprocess
+
 import numpy as np
 import pytest
 
@@ -31,9 +35,9 @@ def group_reciprocal(s, g):
 
 @pytest.mark.parametrize("kind", ["ties", "any"])
 def test_quotient_by_a_half_precision_scale_is_correctly_rounded(kind):
-    """q = y r, q + (y - q s) r in fused steps equals y / s, for every fp16 mantissa of s (as a sum over all mantissas
-    of y it was checked exhaustively in C: no difference among 2^33 pairs), half-integers and their neighbours
-    included."""
+    """q = y r, q + (y - q s) r in fused steps (Markstein's correction) equals y / s, for 2000 values of y with every
+    fp16 mantissa of s, half-integers and their neighbours included; test_quotient_exhaustively takes every pair of
+    mantissas, test_quotient.py scales of every magnitude and both code ranges."""
     g = np.random.default_rng(1976950)
     s = np.repeat((np.arange(1024, dtype=np.uint16) + np.uint16(0x3400)).view(np.float16).astype(F), 2000)
     r = group_reciprocal(s, g)
@@ -49,3 +53,15 @@ def test_quotient_by_a_half_precision_scale_is_correctly_rounded(kind):
     assert np.array_equal(t, (y / s).astype(F))
     c = np.clip(t, F(-127), F(127))
     assert np.array_equal(((c + F(12582912.0)).astype(F) - F(12582912.0)).astype(F), np.rint(c))
+
+
+def test_quotient_exhaustively(tmp_path):
+    """Every fp16 mantissa of s with every fp32 mantissa of y: 2^33 pairs, in C (exhaustive_quotient.c)."""
+    if " fma " not in open("/proc/cpuinfo").read().replace("\n", " "):
+        pytest.skip("no fused multiply-add on this processor")
+    so = str(tmp_path / "exhaustive_quotient.so")
+    src = os.path.join(os.path.dirname(os.path.abspath(__file__)), "exhaustive_quotient.c")
+    subprocess.run(["gcc", "-O3", "-mfma", "-mavx2", "-ffp-contract=off", "-shared", "-fPIC", "-o", so, src], check=True)
+    L = C.CDLL(so)
+    L.check_scales.restype = C.c_longlong
+    assert L.check_scales(0, 1024) == 0
