@@ -360,7 +360,12 @@ __device__ __forceinline__ void process_mfma(const FusedArgs &a, const TierView 
   uint32_t s_top = 0;
   int wexp = 0;
   // (a maximum beyond 4 million has no bits left for it: such a column keeps weights up to 1)
-  auto shift_of = [&](float mx) { return PF ? fmaf(-mx, cs, fabsf(mx * cs) < 4194304.0f ? (float)wexp : 0.0f) : -mx * cs; };
+  // Product and difference rounded one after the other: wexp - mcs, the reference of the item's result, is then exact.
+  auto shift_of = [&](float mx) {
+#pragma clang fp contract(off)
+    const float r = mx * cs;
+    return PF ? (fabsf(r) < 4194304.0f ? (float)wexp : 0.0f) - r : -r;
+  };
 
   Splice sp;
   sp.init();
