@@ -218,11 +218,11 @@ __device__ __forceinline__ void lds_meta(uint32_t a0, u32x4 *m) {
                : "=&v"(m[0]), "=&v"(m[1]), "=&v"(m[2]), "=&v"(m[3]) : "v"(a0) : "memory");
 }
 // The same with the two words of the lane's own token (one lane per token, from t0), for what is decided per batch.
-__device__ __forceinline__ void lds_meta_own(uint32_t a0, uint32_t t0, u32x4 *m, uint32_t *t) {
-  asm volatile("ds_read_b32 %4, %7\n\tds_read_b32 %5, %7 offset:256\n\t"
-               "ds_read_b128 %0, %6\n\tds_read_b128 %1, %6 offset:256\n\tds_read_b128 %2, %6 offset:64\n\t"
-               "ds_read_b128 %3, %6 offset:320\n\ts_waitcnt lgkmcnt(0)"
-               : "=&v"(m[0]), "=&v"(m[1]), "=&v"(m[2]), "=&v"(m[3]), "=&v"(t[0]), "=&v"(t[1]) : "v"(a0), "v"(t0) : "memory");
+__device__ __forceinline__ void lds_meta_own(uint32_t a0, uint32_t t0, u32x4 *m, u32x2 *t) {
+  asm volatile("ds_read2_b32 %4, %6 offset1:64\n\t"
+               "ds_read_b128 %0, %5\n\tds_read_b128 %1, %5 offset:256\n\tds_read_b128 %2, %5 offset:64\n\t"
+               "ds_read_b128 %3, %5 offset:320\n\ts_waitcnt lgkmcnt(0)"
+               : "=&v"(m[0]), "=&v"(m[1]), "=&v"(m[2]), "=&v"(m[3]), "=&v"(*t) : "v"(a0), "v"(t0) : "memory");
 }
 typedef unsigned short us2 __attribute__((ext_vector_type(2)));
 // the larger halves of two words, as unsigned numbers
@@ -637,9 +637,9 @@ __device__ __forceinline__ void process_mfma(const FusedArgs &a, const TierView 
         if (tt % 2 == 0) {
           const uint32_t plane = lds0 + kTileRowsLds + meta_cur;
           if (tt == 0) {
-            uint32_t own[2];
-            lds_meta_own(plane + 16 * kg, plane + 512 + 4 * lane, km, own);
-            top = halves_max(own[0], own[1]);                       // scales are not negative
+            u32x2 own;
+            lds_meta_own(plane + 16 * kg, plane + 512 + 4 * lane, km, &own);
+            top = halves_max(own.x, own.y);                       // scales are not negative
             top = V4 ? top & 0xffffu : max(top & 0xffffu, top >> 16);
           } else {
             lds_meta(plane + 64 * tt + 16 * kg, km);
