@@ -5,43 +5,41 @@
 // the layout changes).  Same work items, same partials and same record layout as the vector
 // kernel; only the lane mapping differs.
 //
-// One 16-token tile, lane = (c = lane % 16, kg = lane / 16):
-//   K rows reach the MFMA A layout as 32 channels of token c per lane, spliced into packed 16-bit pairs as in the vector
-//   kernel.  Four 32-deep steps give
-//       S[token][head] = sum_d K[token][d] * Q[d][head]
-//   Quantized keys: the lane's channels are 8 bytes of each 32-byte stretch of the row, so a step (or two, int4) stays
-//   inside one channel group and every group has a product chain of its own; up to 16 heads are the columns, whatever
-//   the format, and no product is spent on zeros.  The splice offsets leave through the initial accumulator value.  In
-//   the MFMA result layout lane (c, kg) holds head c of tokens 4 kg .. 4 kg + 3; those tokens' meta words (scale, zero
-//   point per group) are read from LDS in that layout (the lanes of one kg read the same 16 bytes) and enter as fp16
-//   operands of fused multiply-adds.
-//   The softmax is per column (lane-local over 4 tokens, two lane exchanges over kg); its scale is applied inside the
-//   exponent.
-//   Quantized V: gfx950's transposing LDS reads (ds_read_b64_tr_b4 / _b8) hand lane (c, kg) the codes of ONE channel of
-//   eight tokens of a 32-token pair of tiles -- after the splice, whose offset (and the centre 8 of int4 codes) leaves
-//   exactly, the A operand of
-//       O[channel][head] += sum_token V^T[channel][token] * P_g[token][head],
-//   and the token's scale rides on the other operand: P_g = fp16(p_t * s_{t,g}), one per channel group g, the one
-//   rounding of the product; the weights p carry a power of two that keeps it in fp16's normal range whatever the size
-//   of the values (wexp below).  The int4 zero points and the centre come back as sum_t p_t (z_{t,g} + 8 s_{t,g}) in fp32 on
-//   the vector units.  Values stored channel-major per 32 tokens (TTKV_I4_ASYM_G64_T32) are those operand words as they
-//   lie.
-//   fp16 / bf16 V, and int4 V beside keys grouped over tokens: rows like K's (the latter dequantized in packed fp16);
-//   a product with the identity matrix brings the tile from [token][channel] to [channel][token]: the fp32 result
+// One 16-token tile, lane = (c = lane % 16, kg = lane / 16); a K row reaches the product as 32 channels of token c per lane
+// in four 32-deep steps.
+//
+// Quantized tiers (process_quant): heads are the rows and tokens the columns of the score product,
+//       S[head][token] = sum_d Q[head][d] K[token][d],
+//   with the heads of up to four tiles in the 16 rows (QuantShape), so that the softmax has 4 scores per lane and chain at any
+//   number of heads, all of one token, whose scales and zero points are the lane's own.  The lane's channels are 8 bytes of
+//   each 32-byte stretch of the row, so a step (or two, int4) stays inside one channel group and every group has a product
+//   chain of its own.  Codes enter as fp16 subnormals: no splice constant, no offset (int8: 128).
+//   Values: gfx950's transposing LDS reads (ds_read_b64_tr_b4 / _b8) hand lane (c, kg) the codes of ONE channel of eight
+//   tokens of a 32-token pair of tiles -- with the masks applied the A operand of
+//       O[channel][group, head] += sum_token V^T[channel][token] * P[token][group, head],
+//   and the token's scale rides on the other operand, P = p_t s_{t,g}, whose (channel group, head) pairs fill the product's
+//   16 columns; it goes through LDS (stored per token, read transposed per head: ds_read_b64_tr_b16) as an fp16 number and
+//   its remainder, 22 bits.  The weights p carry a power of two that keeps both in fp16's range whatever the size of the
+//   values (wexp below).  The codes' centre (128; 8) leaves with a product of the same weights with a constant, the int4
+//   zero points and the centre come back as sum_t p_t (z_{t,g} + 8 s_{t,g}) in fp32.  Values stored channel-major per 32
+//   tokens (TTKV_I4_ASYM_G64_T32) are those operand words as they lie.
+//
+// fp16 / bf16 tiers and keys grouped over tokens (process_rows): tokens are the rows, heads the columns of S; lane (c, kg)
+//   holds head c of tokens 4 kg .. 4 kg + 3 and the softmax is per column.  V rows like K's (int4 ones dequantized in packed
+//   fp16); a product with the identity matrix brings the tile from [token][channel] to [channel][token]: the fp32 result
 //   (exact) has lane (c, kg) holding channel-row c for tokens 4 kg .. 4 kg + 3, the A layout.  Two 16-token tiles feed
 //   one 32-deep product.  The zero points and scales ride along as a 4-channel V.  P is rounded to fp16 once and that
 //   rounded value is used for the row sum as well.
 //   Keys grouped over 128 tokens per channel have no channel groups; the token group's scales fold into the q operand,
 //   carried as fp16 rounded product + exact remainder (two products per step), rebuilt for every 64 tokens in flight.
 //
-// Bound: the memory system.  With every product taken out (same copies, same LDS reads) 8 x 64K tokens of K int8 / V int4
-// take the same 81 us for 64 / 4 heads, 16 ragged sequences of K int4 / V4c 182 us (187 with them).  What matters is
-// what keeps the copies fed and how the work is cut: 64 q / 4 kv heads, K int8 / V int4 110.3 -> 83.7 us per step
-// (before: four score passes against zero-padded operands, one per group, 228 registers), 32 / 8 at 128K tokens
-// 48.3 -> 44.6, block-sparse recall 129.5 -> 123.2.  Error against 64 bits, 4096 tokens, 2-norm: int8 values of standard
-// deviation 1 to 0.005 1.8e-4 (rounding dequantized values: 2.8e-4), beside a token 7 above the rest 1e-6 (1.8e-4); int4
-// 2.0e-4 (2.7e-4) and 1e-6 (1.4e-4).  More heads per KV head than 16 are cut into blocks of 16, one workgroup and one pass over the bytes per
-// block.
+// Bound: the memory system; vector instructions where they are too many.  Quantized loop, 32 / 8 heads, vector
+// instructions per 64 tokens of int4 (32 of int8): 624 -> 280 (337 -> 160) against the form with heads as columns of both
+// products, one rounding of p s and splice constants; one step, us, before -> now: 128K tokens of three formats 42.9 -> 39,
+// 16 ragged sequences of K int4 / V4c 187 -> 178, block-sparse recall 122 -> 118; 64 / 4 heads, K int8 / V int4, 83.7 -> 84
+// (77 with everything but copies and LDS reads taken out).  Error against 64 bits (2-norm, keys with outlier channels,
+// 4K to 64K tokens): int8 0.9e-4 -> 1.4e-5 to 4e-5, int4 0.95e-4 -> 1e-5.  More heads per KV head than 16 are cut into
+// blocks of 16, one workgroup and one pass over the bytes per block.
 #include "ttkv_attn_dev.h"
 
 #include <algorithm>
@@ -117,22 +115,19 @@ __device__ __forceinline__ constexpr int key_channel(int kg, int j) {
   if (F == TTKV_I8_SYM_G32) return 32 * (j / 8) + 8 * kg + j % 8;
   return slice_channel<F>(kg, j);
 }
-// Splice offset carried by k-value i of a step.
-template <int F>
-constexpr float k_offset(int i) {
-  return is_i4<F>() ? (i < 2 ? 1024.0f : 64.0f) : (F == TTKV_I8_SYM_G32 ? 1152.0f : 0.0f);
-}
 
 // ---- tiles of quantized rows prefetched through LDS
 // The rows of a batch of tiles are copied global -> LDS asynchronously (no registers in between), the K half and
 // the V half separately, while the batch before is being computed; the copy instructions read whole rows (whole
-// 128-byte lines, so they carry the streaming hint), and the lanes then read their 16-byte pieces from LDS in the
-// operand layout.  Inside LDS row r keeps its pieces in the order p ^ swz(r), which makes the 16 rows that the
-// lanes of one piece read at a time fall into 16 different bank groups; the copy realises the order by choosing
-// which piece each lane fetches.
-// Per wave: K rows, V rows, and two buffers of four planes of meta words (K words 0 and 1 of the batch's tokens, V words
-// 0 and 1), used in turn: a batch's meta words stay readable while the next batch arrives.
-constexpr int kMetaLds = 4 * 256, kTileRowsLds = 8 * 1024, kTileLds = kTileRowsLds + 2 * kMetaLds;
+// 128-byte lines, so they carry the streaming hint), and the lanes then read their pieces from LDS in the operand
+// layout.  Inside LDS row r keeps its pieces in the order p ^ swz(r), which spreads the 16 rows that the
+// lanes of one piece read at a time over the banks; the copy realises the order by choosing which piece each lane fetches.
+// Per wave: a batch's K rows, V rows and four planes of meta words (K words 0 and 1 of the batch's tokens, V words 0 and
+// 1), then the weights.  At the end the wave's result takes the first 8 KiB, its sums the meta planes behind them.  (Two
+// batches in flight gained nothing: 86 against 87 us for 8 x 64K tokens of K int8 / V int4.)
+constexpr int kTileRowsLds = 8 * 1024, kMetaLds = 4 * 256, kBatchLds = kTileRowsLds + kMetaLds, kWeightsLds = 2 * 2048;
+constexpr int kTileLds = kBatchLds + kWeightsLds;
+constexpr int kSumsLds = kTileRowsLds + 512;   // 16 references, 16 sums of weights
 typedef const __attribute__((address_space(1))) void *gas_ptr;
 typedef __attribute__((address_space(3))) void *las_ptr;
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
@@ -210,20 +205,6 @@ __device__ __forceinline__ void lds_pieces(uint32_t a0, u32x4 *w) {
     asm volatile("ds_read_b128 %0, %2\n\tds_read_b128 %1, %2 offset:1024\n\ts_waitcnt lgkmcnt(0)"
                  : "=&v"(w[0]), "=&v"(w[1]) : "v"(a0) : "memory");
 }
-// The two meta words of four consecutive tokens of two tiles: m[2 u + w] = words w of tile u, from a0 (tile 1: 64
-// bytes further, words 1 one plane further); lanes of one kg read the same addresses.
-__device__ __forceinline__ void lds_meta(uint32_t a0, u32x4 *m) {
-  asm volatile("ds_read_b128 %0, %4\n\tds_read_b128 %1, %4 offset:256\n\tds_read_b128 %2, %4 offset:64\n\t"
-               "ds_read_b128 %3, %4 offset:320\n\ts_waitcnt lgkmcnt(0)"
-               : "=&v"(m[0]), "=&v"(m[1]), "=&v"(m[2]), "=&v"(m[3]) : "v"(a0) : "memory");
-}
-// The same with the two words of the lane's own token (one lane per token, from t0), for what is decided per batch.
-__device__ __forceinline__ void lds_meta_own(uint32_t a0, uint32_t t0, u32x4 *m, u32x2 *t) {
-  asm volatile("ds_read2_b32 %4, %6 offset1:64\n\t"
-               "ds_read_b128 %0, %5\n\tds_read_b128 %1, %5 offset:256\n\tds_read_b128 %2, %5 offset:64\n\t"
-               "ds_read_b128 %3, %5 offset:320\n\ts_waitcnt lgkmcnt(0)"
-               : "=&v"(m[0]), "=&v"(m[1]), "=&v"(m[2]), "=&v"(m[3]), "=&v"(*t) : "v"(a0), "v"(t0) : "memory");
-}
 typedef unsigned short us2 __attribute__((ext_vector_type(2)));
 // the larger halves of two words, as unsigned numbers
 __device__ __forceinline__ uint32_t halves_max(uint32_t a, uint32_t b) {
@@ -238,55 +219,76 @@ __device__ __forceinline__ uint32_t wave_max16(uint32_t v) {
   return max(max((uint32_t)__builtin_amdgcn_readlane((int)v, 0), (uint32_t)__builtin_amdgcn_readlane((int)v, 16)),
              max((uint32_t)__builtin_amdgcn_readlane((int)v, 32), (uint32_t)__builtin_amdgcn_readlane((int)v, 48)));
 }
+// the two values of the lanes 16 (32) apart by exclusive or, in the same order in both
+__device__ __forceinline__ f2 both16(float v) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return f2{__uint_as_float(r[0]), __uint_as_float(r[1])};
+}
+__device__ __forceinline__ f2 both32(float v) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return f2{__uint_as_float(r[0]), __uint_as_float(r[1])};
+}
+// the largest value of the lane's row of 16
+__device__ __forceinline__ float row_max(float v) {
+  v = fmaxf(v, dpp<0xB1>(v));
+  v = fmaxf(v, dpp<0x4E>(v));
+  v = fmaxf(v, dpp<0x141>(v));
+  return fmaxf(v, dpp<0x140>(v));
+}
 __device__ __forceinline__ float pow2(int e) { return __uint_as_float((uint32_t)(127 + e) << 23); }   // |e| < 127
 // fp16 halves of a meta word
 __device__ __forceinline__ float half0(uint32_t w) { return (float)as_h2(w).x; }
 __device__ __forceinline__ float half1(uint32_t w) { return (float)as_h2(w).y; }
 
-// Any number of query heads up to 16 (the columns of both products).
+// Head section and row inside it of the item's token i, of a run or of the blocks that `sel` names.  The block table
+// does not change during the launch and the index is wave-uniform: it is read through the constant address space (a
+// scalar load); so are the selected ids, written by the launch before this one.
+struct Place {
+  int block, row;   // ring block (selected: index into the ids), row inside it
+};
+typedef const __attribute__((address_space(4))) int32_t *const_i32;
+__device__ __forceinline__ Place place_of(const TierView &tv, const RunView &en, int i) {
+  int tok = en.first_tok + i;
+  const int ring_tokens = tv.ring_blocks * tv.bt;
+  if (tok >= ring_tokens) tok -= ring_tokens;
+  const int rb = tok / tv.bt;
+  return Place{rb, tok - rb * tv.bt};
+}
+__device__ __forceinline__ const uint8_t *head_at(const TierView &tv, const RunView &en, const int32_t *sel, int seq, int hkv, int block) {
+  int rb = block;
+  if (sel) rb = ((const_i32)(uintptr_t)sel)[rb] % tv.ring_blocks;
+  const int64_t rec = tv.table ? (int64_t)((const_i32)(uintptr_t)tv.table)[(int64_t)seq * tv.ring_blocks + rb]
+                               : (int64_t)en.rec_base + rb;
+  return tv.base + rec * tv.rec_bytes + (int64_t)hkv * tv.head_bytes;
+}
+
+// fp16 / bf16 tiers, and keys grouped over tokens: any number of query heads up to 16 (the columns of both products).
 template <int KF, int VF>
-__device__ __forceinline__ void process_mfma(const FusedArgs &a, const TierView &tv, const RunView &en, const int32_t *sel,
-                                             int chunk_tokens, int chunk, int seq, int hq0, int Gr, int hkv, char *s_buf,
-                                             float (*s_m)[16], float (*s_l)[16]) {
+__device__ __forceinline__ void process_rows(const FusedArgs &a, const TierView &tv, const RunView &en, const int32_t *sel,
+                                             int chunk_tokens, int chunk, int seq, int hq0, int Gr, int hkv, char *wbuf) {
+  // wbuf: the wave's LDS, a batch of tiles in flight, at the end its result
   // sel: null, or the block ids behind a run made of selected blocks (ring block of token i: sel[i / bt])
   // hq0, Gr: first query head and number of heads of this workgroup's block of heads (all heads of the KV head,
   // or a block of up to 16 of them)
   using FK = Fmt<KF>;
   using FV = Fmt<VF>;
   constexpr int NLK = FK::ROWB / 64, NLV = FV::ROWB / 64;   // 16-byte loads per lane per 16-token tile
-  // Quantized keys: rows prefetched through LDS (asynchronous global -> LDS copies with the streaming hint, the batch
-  // after next in flight while one is computed).  Measured per format against register loads: K8/V8 5.2 -> 6.0-6.2
-  // TB/s, K8/V4 4.9-5.1 -> 5.7-5.8 (batches of 32 tokens); int4 keys in batches of 64 tokens: with channel-major
-  // values 5.2 -> 5.97 (of which 32 -> 64 tokens per batch 5.85 -> 5.97), with token-major values 5.09 -> 5.27 (in
-  // batches of 32 they gained nothing: their unpack / dequantize / transpose arithmetic fills the issue slots).
-  // fp16 / bf16 rows take the one-region variant further down.
-  constexpr bool PF = (KF == TTKV_I8_SYM_G32 && (VF == TTKV_I8_SYM_G32 || VF == TTKV_I4_ASYM_G64 || VF == TTKV_I4_ASYM_G64_T32)) ||
-                      (KF == TTKV_I4_ASYM_G64 && (VF == TTKV_I4_ASYM_G64_T32 || VF == TTKV_I4_ASYM_G64));
-  // tiles in flight per wave (int4 on register loads: 4; with 2 that kernel is 10 % slower)
-  constexpr bool PF64 = KF == TTKV_I4_ASYM_G64 && (VF == TTKV_I4_ASYM_G64_T32 || VF == TTKV_I4_ASYM_G64);   // prefetched in batches of 64 tokens
-  constexpr int NT = PF64 ? 4 : (NLK == 4 || PF) ? 2 : 4 / NLK;
+  constexpr int NT = NLK == 4 ? 2 : 4 / NLK;   // tiles in flight per wave (int4 on register loads: 4; with 2 that kernel is 10 % slower)
   constexpr int TT = 16 * NT;
-  constexpr int NGK = n_groups<KF>(), NGV = n_groups<VF>();
-  constexpr bool KQ = NGK > 1, VQ = NGV > 1;
+  constexpr bool VQ = n_groups<VF>() > 1;
   constexpr bool KT = KF == TTKV_I4_ASYM_T128;   // keys grouped over 128 tokens per channel: the scales fold into q
   constexpr bool KBF = KF == TTKV_BF16, VBF = VF == TTKV_BF16;
-  constexpr bool VT = VF == TTKV_I4_ASYM_G64_T32;   // values stored channel-major per 32 tokens
-  constexpr bool V4 = PF && VF != TTKV_I8_SYM_G32;  // 4-bit codes as operand words (VT: as they lie; else transposed out of LDS)
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n = lane & 15, kg = lane >> 4;
-  char *const wbuf = s_buf + wave * kTileLds;   // the wave's LDS: a batch of tiles in flight, at the end its result
   const int c0 = chunk * chunk_tokens;
   const int c1 = min(en.len, c0 + chunk_tokens);
-  const int ring_tokens = tv.ring_blocks * tv.bt;
   const float cs = a.scale * kLog2e;       // scores are kept in the log2 domain
 
   const bool col_on = n < Gr;   // column = query head
 
-  // ---- q operand: 16 packed registers (step s: 4 s .. 4 s + 3); per channel group of the keys the sum that the
-  // splice offsets add to the products (it leaves with their initial value) and the plain sum (for the zero points).
+  // ---- q operand: 16 packed registers (step s: 4 s .. 4 s + 3)
   uint32_t qB[16];
-  float off[NGK], qs[NGK];
   {
     const uint4 *qrow = (const uint4 *)((const uint16_t *)a.q + ((int64_t)seq * a.Hq + hq0 + min(n, Gr - 1)) * 128);
     uint32_t qw[16];
@@ -307,10 +309,6 @@ __device__ __forceinline__ void process_mfma(const FusedArgs &a, const TierView 
     }
     // Register r of the operand pairs with register r of unpack16: elements (2r, 2r+1) of the slice, or for int4
     // (r = 4d + e) elements (8d + e, 8d + e + 4).
-    const h2 ones = {(_Float16)1.0f, (_Float16)1.0f};
-    float se[NGK], so[NGK];   // sums over the registers that carry splice offset 1024 / 64 (int4: even / odd)
-#pragma unroll
-    for (int gr = 0; gr < NGK; ++gr) se[gr] = so[gr] = 0.0f;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       uint32_t w = qw[r];
@@ -319,18 +317,6 @@ __device__ __forceinline__ void process_mfma(const FusedArgs &a, const TierView 
         w = __builtin_amdgcn_perm(qw[4 * dd + 2 + e / 2], qw[4 * dd + e / 2], (e & 1) ? 0x07060302u : 0x05040100u);
       }
       qB[r] = col_on ? w : 0u;
-      if constexpr (KQ) {   // quantized keys are dotted with fp16 queries
-        const int gr = r / (16 / NGK);
-        if ((r & 1) && KF == TTKV_I4_ASYM_G64) so[gr] = __builtin_amdgcn_fdot2(as_h2(qB[r]), ones, so[gr], false);
-        else se[gr] = __builtin_amdgcn_fdot2(as_h2(qB[r]), ones, se[gr], false);
-      }
-    }
-#pragma unroll
-    for (int gr = 0; gr < NGK; ++gr) {   // over the four channel slices
-      qs[gr] = se[gr] + so[gr];
-      off[gr] = KF == TTKV_I4_ASYM_G64 ? fmaf(1024.0f, se[gr], 64.0f * so[gr]) : k_offset<KF>(0) * se[gr];
-      off[gr] += __shfl_xor(off[gr], 16); off[gr] += __shfl_xor(off[gr], 32);
-      qs[gr] += __shfl_xor(qs[gr], 16);   qs[gr] += __shfl_xor(qs[gr], 32);
     }
   }
 
@@ -342,37 +328,20 @@ __device__ __forceinline__ void process_mfma(const FusedArgs &a, const TierView 
   // (s0, z0, s1, z1): the values beside keys grouped over tokens are dequantized row by row
   const uint32_t vh = (kg >> 1) * 2;
   const uint32_t vsel = (2 * vh) | ((2 * vh + 1) << 8) | ((2 * vh) << 16) | ((2 * vh + 1) << 24);
-  // minus (splice offset + centre) as packed fp16 pairs: int4 -(1024 + 8), -(64 + 8); int8 -(1024 + 128)
-  uint32_t no_a = 0xE408E408u, no_b = 0xD480D480u, no_c = 0xE480E480u;
-  asm volatile("" : "+s"(no_a), "+s"(no_b), "+s"(no_c));
+  // minus (splice offset + centre) as packed fp16 pairs: -(1024 + 8), -(64 + 8)
+  uint32_t no_a = 0xE408E408u, no_b = 0xD480D480u;
+  asm volatile("" : "+s"(no_a), "+s"(no_b));
 
   const f4 zero4 = f4{0.0f, 0.0f, 0.0f, 0.0f};
   f4 acc[8], accz = zero4;
-  float zs[2] = {0.0f, 0.0f};     // V4: sum_t p_t (z_{t,g} + 8 s_{t,g})
 #pragma unroll
   for (int s = 0; s < 8; ++s) acc[s] = zero4;
   float m = -INFINITY, l = 0.0f, mcs = INFINITY;   // a token's weight: exp2(score cs + mcs)
-  // PF: the value operand is fp16(p s), and with p <= 1 that falls into fp16's subnormals or to zero for value scales
-  // well below 1 (std 0.02 beside a token 7 above the rest: an error of 1.7e-2 of the output).  So the weights carry a
-  // power of two that brings the largest value scale the wave has met to [2^14, 2^15): mcs = wexp - m cs, in l,
-  // zs and acc alike; it leaves them at the end.  s_top: the largest fp16 number (as bits, ordered
-  // like the numbers) of that scale's binade, so that only a scale of another binade takes the branch below.
-  uint32_t s_top = 0;
-  int wexp = 0;
-  // (a maximum beyond 4 million has no bits left for it: such a column keeps weights up to 1)
-  // Product and difference rounded one after the other: wexp - mcs, the reference of the item's result, is then exact.
-  auto shift_of = [&](float mx) {
-#pragma clang fp contract(off)
-    const float r = mx * cs;
-    return PF ? (fabsf(r) < 4194304.0f ? (float)wexp : 0.0f) - r : -r;
-  };
-
   Splice sp;
   sp.init();
 
   struct TileRegs {
     uint4 kw[NT][NLK], vw[NT][NLV];
-    uint32_t vop[NT / 2][8][VF == TTKV_I8_SYM_G32 ? 2 : 1];   // PF: codes of channel 16 s + n, the pair's 8 tokens of this kg
     uint2 vmeta[NT];
     uint4 gm[KT ? 8 : 1];   // KT: {scale, zero} of the lane's 32 channels for the token group of these tiles
   };
@@ -381,18 +350,10 @@ __device__ __forceinline__ void process_mfma(const FusedArgs &a, const TierView 
   // Plain loads here, not the non-temporal ones of the vector kernel: the load instructions of a tile share
   // cache lines (each reads 64 of a line's 128 bytes), and lines fetched with the streaming hint do not
   // survive until the next instruction.
-  // Head section and row inside it of the chunk's token i.  The block table does not change during the launch and
-  // the index is wave-uniform: it is read through the constant address space (a scalar load).
   auto locate = [&](int i, int &row0) -> const uint8_t * {
-    int tok0 = en.first_tok + i;
-    if (tok0 >= ring_tokens) tok0 -= ring_tokens;
-    int rb = tok0 / tv.bt;
-    row0 = tok0 - rb * tv.bt;
-    typedef const __attribute__((address_space(4))) int32_t *const_i32;
-    if (sel) rb = ((const_i32)(uintptr_t)sel)[rb] % tv.ring_blocks;   // written by the launch before this one: a scalar load
-    const int64_t rec = tv.table ? (int64_t)((const_i32)(uintptr_t)tv.table)[(int64_t)seq * tv.ring_blocks + rb]
-                                 : (int64_t)en.rec_base + rb;
-    return tv.base + rec * tv.rec_bytes + (int64_t)hkv * tv.head_bytes;
+    const Place p = place_of(tv, en, i);
+    row0 = p.row;
+    return head_at(tv, en, sel, seq, hkv, p.block);
   };
   auto load_tiles = [&](TileRegs &t, int i0, int nv, auto full_tag) {
     constexpr bool FULL = decltype(full_tag)::value;
@@ -415,180 +376,6 @@ __device__ __forceinline__ void process_mfma(const FusedArgs &a, const TierView 
 #pragma unroll
       for (int x = 0; x < NLV; ++x) t.vw[tt][x] = *(const uint4 *)(vb + vo + 64 * x);
       if constexpr (VQ) t.vmeta[tt] = *(const uint2 *)(vmb + row * 8);
-    }
-  };
-
-  // ---- PF: the same rows as asynchronous copies into the wave's LDS and reads from there.
-  // LDS of the wave: K rows at 0, V rows at 4 KiB (row r at r ROWB, its piece p at 16 (p ^ swz(r))), then the two
-  // buffers of meta planes.
-  constexpr int PK = FK::ROWB / 16, PV = FV::ROWB / 16;              // pieces per row
-  constexpr int NDK = TT * FK::ROWB / 1024, NDV = TT * FV::ROWB / 1024;   // copy instructions of 1 KiB per half
-  constexpr int N_K = NDK + 4, N_V = NDV;                              // with the four meta planes
-  static_assert(!PF || PF64 || (NT == 2 && ((PK == 8 && NDK == 4) || (PK == 4 && NDK == 2)) && (NDV == 4 || NDV == 2)),
-                "the batch the LDS readers cover");
-  auto swz = [](int pieces, int r) { return pieces == 4 ? (r >> 2) & 3 : (r >> 1) & 7; };
-  // value rows: also different for the rows that the lanes of a transposing read name in different tiles
-  auto swzv = [](int pieces, int r) { return pieces == 4 ? ((r >> 2) ^ (r >> 4)) & 3 : ((r >> 1) & 7) ^ ((r >> 3) & 2); };
-  // per-lane byte offset of copy instruction j inside a full batch, minus j KiB: keys even and odd j differ for 8
-  // pieces, values by an exchange of pieces (their rows' order is that of j = 0 with vx(j) added by exclusive or)
-  uint32_t dko[2];
-#pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    const int rk = j * (64 / PK) + lane / PK;
-    dko[j] = rk * FK::ROWB + ((lane % PK) ^ swz(PK, rk)) * 16 - j * 1024;
-  }
-  const uint32_t dvo = lane / PV * FV::ROWB + ((lane % PV) ^ swzv(PV, lane / PV)) * 16;
-  constexpr auto vx = [](int j) { return PV == 4 ? j * 16 : (j & 1) * 64 + (j >> 1) * 32; };
-  const uint32_t lds0 = (uint32_t)(uintptr_t)(las_ptr)wbuf;
-  // the lane's 8 bytes of the 32-byte stretch x of row n: half kg % 2 of piece 2 x + kg / 2
-  uint32_t lka[4];
-#pragma unroll
-  for (int x = 0; x < 4; ++x) {
-    const int p = (2 * x) % PK + (kg >> 1);
-    lka[x] = lds0 + n * FK::ROWB + ((p ^ swz(PK, n)) * 16) + 8 * (kg & 1);
-  }
-  // what the lane names to the transposing value reads: its row's first piece (the others by exclusive or with 16 x piece)
-  uint32_t lva = lds0 + 4096 + lane * 16;
-  if constexpr (PF && !VT) {
-    const int r4 = 2 * (n & 1) + 16 * ((n >> 1) & 1) + ((n >> 2) & 1) + 4 * kg;   // kTok[n % 8] + 4 kg
-    const int row = PV == 8 ? ((n >> 1) & 3) + 16 * (n >> 3) + 4 * kg : PF64 ? r4 + 32 * (n >> 3) : r4;
-    const int half = PV == 8 ? n & 1 : PF64 ? 0 : n >> 3;
-    lva = lds0 + 4096 + row * FV::ROWB + swzv(PV, row) * 16 + 8 * half;
-  }
-  uint32_t meta_in = 0, meta_cur = 0;   // meta buffer (byte offset) of the batch being issued / computed
-  const uint8_t *nx_head = nullptr;   // batch whose K half was issued last
-  int nx_row0 = 0, nx_nv = 0;
-  auto issue_k = [&](int i0) {
-    nx_head = locate(i0, nx_row0);
-    nx_nv = min(TT, c1 - i0);
-    const uint8_t *kb = nx_head + nx_row0 * FK::ROWB, *kmb = nx_head + tv.k_meta_off + nx_row0 * 8;
-    if (nx_nv == TT) {
-      dma16<0>(kb + dko[0], wbuf); dma16<1024>(kb + dko[1], wbuf);
-      if constexpr (NDK == 4) {
-        dma16<2048>(kb + dko[0], wbuf); dma16<3072>(kb + dko[1], wbuf);
-      }
-    } else {
-#pragma unroll
-      for (int j = 0; j < NDK; ++j) {
-        const int r = j * (64 / PK) + lane / PK;   // LDS row; rows past the end repeat the last live row
-        dma16(kb + min(r, nx_nv - 1) * FK::ROWB + ((lane % PK) ^ swz(PK, r)) * 16, wbuf + j * 1024);
-      }
-    }
-    const uint32_t mo = min(lane, nx_nv - 1) * 8;   // one lane per token (TT = 32: the upper lanes repeat the last row)
-    dma4(kmb + mo, wbuf + kTileRowsLds + meta_in);
-    dma4(kmb + mo + 4, wbuf + kTileRowsLds + meta_in + 256);
-    const uint8_t *vmb = nx_head + tv.v_meta_off + nx_row0 * 8;   // the values' too: their scales are looked at with the scores
-    dma4(vmb + mo, wbuf + kTileRowsLds + meta_in + 512);
-    dma4(vmb + mo + 4, wbuf + kTileRowsLds + meta_in + 768);
-    meta_in ^= kMetaLds;
-  };
-  auto issue_v = [&]() {
-    const uint8_t *vb = nx_head + tv.v_off + nx_row0 * FV::ROWB;
-    if constexpr (VT) {   // whole 2 KiB groups (lengths are multiples of 32), copied as they lie
-      dma16<0>(vb + lane * 16, wbuf + 4096); dma16<1024>(vb + lane * 16, wbuf + 4096);
-      if constexpr (PF64) {   // the second group: inside the record even when the run ends before it (its weights are 0)
-        dma16<2048>(vb + lane * 16, wbuf + 4096); dma16<3072>(vb + lane * 16, wbuf + 4096);
-      }
-    } else if (nx_nv == TT) {
-      dma16<0>(vb + dvo, wbuf + 4096); dma16<1024>(vb + (dvo ^ vx(1)), wbuf + 4096);
-      if constexpr (NDV == 4) {
-        dma16<2048>(vb + (dvo ^ vx(2)), wbuf + 4096); dma16<3072>(vb + (dvo ^ vx(3)), wbuf + 4096);
-      }
-    } else {
-#pragma unroll
-      for (int j = 0; j < NDV; ++j) {
-        const int r = j * (64 / PV) + lane / PV;
-        dma16(vb + min(r, nx_nv - 1) * FV::ROWB + ((lane % PV) ^ swzv(PV, r)) * 16, wbuf + 4096 + j * 1024);
-      }
-    }
-  };
-  // Rows in pinned host memory: the whole batch through registers into the same places (over PCIe the asynchronous
-  // copies were 3-4 % slower, and the streaming hint has nothing to gain there).  Lane (n, kg) moves piece kg (+ 4) of
-  // row n of every tile, one lane per token its meta words.
-  auto bring_host = [&](int i0) {
-    int row0;
-    const uint8_t *head = locate(i0, row0);
-    const int nv = min(TT, c1 - i0);
-    const uint8_t *kb = head + row0 * FK::ROWB, *vb = head + tv.v_off + row0 * FV::ROWB;
-    uint4 kw[NT][NLK], vw[NT][NLV];
-#pragma unroll
-    for (int tt = 0; tt < NT; ++tt) {
-      const uint32_t row = min(tt * 16 + n, nv - 1);   // rows past the end repeat the last live row
-#pragma unroll
-      for (int x = 0; x < NLK; ++x) kw[tt][x] = *(const uint4 *)(kb + row * FK::ROWB + kg * 16 + 64 * x);
-      if constexpr (VT) {
-        // piece hh = tt % 2 of the 32-token group tt / 2 (a group past the end repeats the last live one)
-        vw[tt][0] = *(const uint4 *)(vb + min(tt / 2, (nv - 1) / 32) * 2048 + (tt & 1) * 1024 + lane * 16);
-      } else {
-#pragma unroll
-        for (int x = 0; x < NLV; ++x) vw[tt][x] = *(const uint4 *)(vb + row * FV::ROWB + kg * 16 + 64 * x);
-      }
-    }
-    const uint32_t mo = (row0 + min(lane, nv - 1)) * 8;
-    const uint2 km = *(const uint2 *)(head + tv.k_meta_off + mo), vm = *(const uint2 *)(head + tv.v_meta_off + mo);
-#pragma unroll
-    for (int tt = 0; tt < NT; ++tt) {
-#pragma unroll
-      for (int x = 0; x < NLK; ++x)
-        *(uint4 *)(wbuf + (tt * 16 + n) * FK::ROWB + (((kg + 4 * x) ^ swz(PK, n)) * 16)) = kw[tt][x];
-      if constexpr (VT) {
-        *(uint4 *)(wbuf + 4096 + tt * 1024 + lane * 16) = vw[tt][0];
-      } else {
-#pragma unroll
-        for (int x = 0; x < NLV; ++x)
-          *(uint4 *)(wbuf + 4096 + (tt * 16 + n) * FV::ROWB + (((kg + 4 * x) ^ swzv(PV, tt * 16 + n)) * 16)) = vw[tt][x];
-      }
-    }
-    uint32_t *m = (uint32_t *)(wbuf + kTileRowsLds) + lane;   // buffer 0
-    m[0] = km.x;
-    m[64] = km.y;
-    m[128] = vm.x;
-    m[192] = vm.y;
-  };
-  auto fetch_k = [&](auto &t) {   // generic: compiled only where it is called, i.e. for the formats of PF
-    u32x2 w[8];
-    if constexpr (PK == 8) lds_keys_i8(lka[0], lka[1], lka[2], lka[3], w);
-    else lds_keys_i4(lka[0], lka[1], w);
-#pragma unroll
-    for (int tt = 0; tt < NT; ++tt)
-#pragma unroll
-      for (int x = 0; x < NLK; ++x) {
-        const u32x2 v0 = w[2 * (tt * NLK + x)], v1 = w[2 * (tt * NLK + x) + 1];
-        t.kw[tt][x] = uint4{v0.x, v0.y, v1.x, v1.y};
-      }
-  };
-  auto fetch_v = [&](auto &t) {
-    if constexpr (VT) {   // word w of piece hh: block 4 hh + w
-      u32x4 w[4];
-      lds_pieces<NT>(lva, w);
-#pragma unroll
-      for (int s = 0; s < 8; ++s)
-#pragma unroll
-        for (int pr = 0; pr < NT / 2; ++pr) t.vop[pr][s][0] = w[2 * pr + s / 4][s % 4];
-    } else {
-      u32x2 w[8];
-      if constexpr (PV == 8) {
-        uint32_t va = lva;
-        asm volatile("" : "+v"(va));   // formed again in every batch: kept, the eight addresses made the loop spill
-        lds_values_i8(va, va ^ 16, va ^ 32, va ^ 48, w);
-        lds_values_i8(va ^ 64, va ^ 80, va ^ 96, va ^ 112, w + 4);
-      } else if constexpr (PF64) {
-        lds_values_i4x4(lva, lva ^ 16, lva ^ 32, lva ^ 48, w);
-      } else {
-        lds_values_i4x2(lva, lva ^ 16, lva ^ 32, lva ^ 48, w);
-      }
-#pragma unroll
-      for (int s = 0; s < 8; ++s) {
-        if constexpr (PV == 8) {
-          t.vop[0][s][0] = w[s].x;
-          t.vop[0][s][1] = w[s].y;
-        } else if constexpr (PF64) {
-          t.vop[0][s][0] = w[s].x;
-          t.vop[1][s][0] = w[s].y;
-        } else {
-          t.vop[0][s][0] = s % 2 ? w[s / 2].y : w[s / 2].x;
-        }
-      }
     }
   };
 
@@ -629,55 +416,25 @@ __device__ __forceinline__ void process_mfma(const FusedArgs &a, const TierView 
     // ---- scores (log2 domain), column n of tokens 4 kg + i
     f4 S[NT];
     float mt = -INFINITY;
-    uint32_t top = 0;   // PF: the largest value scale of the lane's own token (one lane per token)
-    u32x4 km[4];   // the meta words of the lane's tokens 4 kg + i of two tiles, straight in the score layout
 #pragma unroll
     for (int tt = 0; tt < NT; ++tt) {
-      if constexpr (KQ)
-        if (tt % 2 == 0) {
-          const uint32_t plane = lds0 + kTileRowsLds + meta_cur;
-          if (tt == 0) {
-            u32x2 own;
-            lds_meta_own(plane + 16 * kg, plane + 512 + 4 * lane, km, &own);
-            top = halves_max(own.x, own.y);                       // scales are not negative
-            top = V4 ? top & 0xffffu : max(top & 0xffffu, top >> 16);
-          } else {
-            lds_meta(plane + 64 * tt + 16 * kg, km);
-          }
-        }
       uint32_t kr[16];
 #pragma unroll
       for (int x = 0; x < NLK; ++x) unpack16<KF>(t.kw[tt][x], kr + x * (16 / NLK), sp);
-      // one product chain per channel group
-      f4 sv[NGK];
+      f4 sv = KT ? f4{-off_t, -off_t, -off_t, -off_t} : zero4;
 #pragma unroll
-      for (int gr = 0; gr < NGK; ++gr) {
+      for (int s = 0; s < 4; ++s) {
         if constexpr (KT) {
-          sv[gr] = f4{-off_t, -off_t, -off_t, -off_t};
-#pragma unroll
-          for (int s = 0; s < 4; ++s) {
-            sv[gr] = mma32<false>(kr + 4 * s, qh + 4 * s, sv[gr]);
-            sv[gr] = mma32<false>(kr + 4 * s, ql + 4 * s, sv[gr]);
-          }
+          sv = mma32<false>(kr + 4 * s, qh + 4 * s, sv);
+          sv = mma32<false>(kr + 4 * s, ql + 4 * s, sv);
         } else {
-          sv[gr] = f4{-off[gr], -off[gr], -off[gr], -off[gr]};
-#pragma unroll
-          for (int s = gr * (4 / NGK); s < (gr + 1) * (4 / NGK); ++s) sv[gr] = mma32<KBF>(kr + 4 * s, qB + 4 * s, sv[gr]);
+          sv = mma32<KBF>(kr + 4 * s, qB + 4 * s, sv);
         }
       }
-      const u32x4 m0 = km[2 * (tt & 1)], m1 = km[2 * (tt & 1) + 1];
       f4 sc;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        float x = sv[0][i];
-        if constexpr (KF == TTKV_I8_SYM_G32) {        // scales of groups 0 .. 3
-          x *= half0(m0[i]);
-          x = fmaf(sv[1][i], half1(m0[i]), x);
-          x = fmaf(sv[2][i], half0(m1[i]), x);
-          x = fmaf(sv[3][i], half1(m1[i]), x);
-        } else if constexpr (KF == TTKV_I4_ASYM_G64) {   // scale, zero point of group 0; of group 1
-          x = fmaf(half1(m0[i]), qs[0], half1(m1[i]) * qs[1]) + fmaf(sv[0][i], half0(m0[i]), sv[1][i] * half0(m1[i]));
-        }
+        float x = sv[i];
         if (!FULL && tt * 16 + 4 * kg + i >= nv) x = -INFINITY;
         sc[i] = x;
         mt = fmaxf(mt, x);
@@ -688,21 +445,11 @@ __device__ __forceinline__ void process_mfma(const FusedArgs &a, const TierView 
     // ---- online softmax (base 2) per column; m is kept in raw score units, the scale enters the exponent
     mt = fmaxf(mt, __shfl_xor(mt, 16));
     mt = fmaxf(mt, __shfl_xor(mt, 32));
-    if (__any(mt > m || top > s_top)) {
-      const float mn = fmaxf(m, mt), old = mcs;
-      if constexpr (PF) {
-        if (__any(top > s_top)) {
-          s_top = wave_max16(top) | 0x3ffu;
-          wexp = 29 - max((int)(s_top >> 10), 1);
-        }
-      }
-      mcs = shift_of(mn);
-      const float alpha = PF ? __builtin_amdgcn_exp2f(mcs - old) : __builtin_amdgcn_exp2f((m - mn) * cs);
+    if (__any(mt > m)) {
+      const float mn = fmaxf(m, mt), alpha = __builtin_amdgcn_exp2f((m - mn) * cs);
+      mcs = -(mn * cs);
       l *= alpha;
       accz *= alpha;
-      if constexpr (V4) {
-        zs[0] *= alpha; zs[1] *= alpha;
-      }
 #pragma unroll
       for (int s = 0; s < 8; ++s) acc[s] *= alpha;
       m = mn;
@@ -711,63 +458,6 @@ __device__ __forceinline__ void process_mfma(const FusedArgs &a, const TierView 
 
     // ---- weighted V, two 16-token tiles per 32-deep product
     before_v();
-    if constexpr (PF) {
-      // The codes' words are the A operands of the eight channel blocks after the splice, whose offset leaves exactly
-      // (with the centre 8 of 4-bit codes); the scales ride on the weights.  One rounding per product: fp16(p s).
-#pragma unroll
-      for (int tp = 0; tp < NT; tp += 2) {
-        u32x4 vm[4];             // meta words of the lane's tokens 4 kg + i: 4-bit (scale, zero point) of groups 0 and 1, 8-bit scales
-        lds_meta(lds0 + kTileRowsLds + meta_cur + 512 + 64 * tp + 16 * kg, vm);
-        uint32_t Bg[NGV][4];     // fp16(p_t * s_{t,g}) of the pair's 8 tokens per lane, per channel group g
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-          const int tt = tp + u;
-          const u32x4 m0 = vm[2 * u], m1 = vm[2 * u + 1];
-          float p[4], b[NGV][4];
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            p[i] = __builtin_amdgcn_exp2f(fmaf(S[tt][i], cs, mcs));
-            l += p[i];
-            if constexpr (V4) {
-              zs[0] = fmaf(p[i], fmaf(8.0f, half0(m0[i]), half1(m0[i])), zs[0]);   // zero point + the centre 8 * scale
-              zs[1] = fmaf(p[i], fmaf(8.0f, half0(m1[i]), half1(m1[i])), zs[1]);
-              b[0][i] = p[i] * half0(m0[i]);
-              b[1][i] = p[i] * half0(m1[i]);
-            } else {
-              b[0][i] = p[i] * half0(m0[i]);
-              b[1][i] = p[i] * half1(m0[i]);
-              b[2][i] = p[i] * half0(m1[i]);
-              b[3][i] = p[i] * half1(m1[i]);
-            }
-          }
-#pragma unroll
-          for (int gr = 0; gr < NGV; ++gr) {
-            Bg[gr][2 * u] = pk(b[gr][0], b[gr][1]);
-            Bg[gr][2 * u + 1] = pk(b[gr][2], b[gr][3]);
-          }
-        }
-#pragma unroll
-        for (int s = 0; s < 8; ++s) {
-          uint32_t vr[4];
-          const int gr = s / (8 / NGV);
-          if constexpr (V4) {
-            splice4(t.vop[tp / 2][s][0], vr, sp);
-#pragma unroll
-            for (int r = 0; r < 4; ++r) vr[r] = __builtin_bit_cast(uint32_t, as_h2(vr[r]) + as_h2((r & 1) ? no_b : no_a));
-          } else {
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-              const uint32_t x = t.vop[tp / 2][s][h] ^ 0x80808080u;               // byte -> code + 128
-              vr[2 * h] = __builtin_amdgcn_perm(0x64646464u, x, 0x04010400u);      // (1024 + b0, 1024 + b1)
-              vr[2 * h + 1] = __builtin_amdgcn_perm(0x64646464u, x, 0x04030402u);
-            }
-#pragma unroll
-            for (int r = 0; r < 4; ++r) vr[r] = __builtin_bit_cast(uint32_t, as_h2(vr[r]) + as_h2(no_c));
-          }
-          acc[s] = mma32<false>(vr, Bg[gr], acc[s]);
-        }
-      }
-    } else {
 #pragma unroll
     for (int tp = 0; tp < NT; tp += 2) {
       uint32_t pB[4];          // softmax weights of the pair, rounded to fp16: the B operand
@@ -811,7 +501,6 @@ __device__ __forceinline__ void process_mfma(const FusedArgs &a, const TierView 
         const uint32_t A[4] = {pk(d0[0], d0[1]), pk(d0[2], d0[3]), pk(d1[0], d1[1]), pk(d1[2], d1[3])};
         accz = mma32<false>(A, pB, accz);
       }
-    }
     }
   };
 
@@ -888,40 +577,7 @@ __device__ __forceinline__ void process_mfma(const FusedArgs &a, const TierView 
       compute_tiles(ra, c1 - i0, std::false_type{}, []() {});
     }
   };
-  if constexpr (PF) {
-    TileRegs ra;
-    int i0 = c0 + wave * TT;
-    if (!tv.in_host) {
-      // While batch i is computed the copies of batch i + 1 are in flight: its K half is issued once batch i's K
-      // rows are in registers, its V half once batch i's V rows are.  Loads complete in order, so "at most as
-      // many outstanding as were issued after it" means a half has landed.
-      if (i0 < c1) {
-        issue_k(i0);
-        issue_v();
-      }
-      auto step = [&](int nv, auto full_tag) {
-        const bool more = i0 + 4 * TT < c1;   // wave-uniform
-        wait_vmcnt<N_V>();
-        fetch_k(ra);
-        if (more) issue_k(i0 + 4 * TT);
-        compute_tiles(ra, nv, full_tag, [&]() {
-          if (more) wait_vmcnt<N_K>();
-          else wait_vmcnt<0>();
-          fetch_v(ra);
-          if (more) issue_v();
-        });
-        meta_cur ^= kMetaLds;
-      };
-      for (; i0 + TT <= c1; i0 += 4 * TT) step(TT, std::true_type{});
-      if (i0 < c1) step(c1 - i0, std::false_type{});
-    } else {
-      for (; i0 < c1; i0 += 4 * TT) {
-        bring_host(i0);
-        fetch_k(ra);
-        compute_tiles(ra, min(TT, c1 - i0), std::false_type{}, [&]() { fetch_v(ra); });
-      }
-    }
-  } else if constexpr (PF2) {
+  if constexpr (PF2) {
     static_assert(!PF2 || (TT == 32 && NT == 2 && NLK == 4 && NLV == 4), "the batch the LDS readers cover");
     // also for a tier in pinned host memory: the copies read whole 256-byte rows, where the register loads ask
     // for 64 bytes of a row per instruction -- over PCIe 55.7 against 42.8 GB/s (measured)
@@ -935,43 +591,791 @@ __device__ __forceinline__ void process_mfma(const FusedArgs &a, const TierView 
   // chan(s, i); the zero-point sums of that channel's group are added here
   l += __shfl_xor(l, 16);
   l += __shfl_xor(l, 32);
-  float z[2] = {0.0f, 0.0f};   // zero-point sum of the channels' group
+  float z = 0.0f;   // zero-point sum of the channels' group
   if constexpr (KT)   // sum_t p_t * (zero + 8 * scale)
-    z[0] = z[1] = (kg >> 1) ? fmaf(8.0f, accz[2], accz[3]) : fmaf(8.0f, accz[0], accz[1]);
-  if constexpr (V4) {   // per channel group: the lanes' zero-point sums over their tokens
-#pragma unroll
-    for (int g2 = 0; g2 < 2; ++g2) {
-      zs[g2] += __shfl_xor(zs[g2], 16);
-      zs[g2] += __shfl_xor(zs[g2], 32);
-      z[g2] = zs[g2];
-    }
-  }
-  // what the weights are relative to (log2 domain), and the power of two they carry
-  const float wcol = PF && fabsf(m * cs) < 4194304.0f ? (float)wexp : 0.0f, unscale = pow2(-(int)wcol);
-  const float m2 = PF ? wcol - mcs : m * cs;
+    z = (kg >> 1) ? fmaf(8.0f, accz[2], accz[3]) : fmaf(8.0f, accz[0], accz[1]);
   float (*w_acc)[128] = (float (*)[128])wbuf;   // [head][channel]; the wave's last batch has been consumed
   if (n < Gr) {
 #pragma unroll
     for (int s = 0; s < 8; ++s)
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        if constexpr (PF) w_acc[n][16 * s + 4 * kg + i] = (acc[s][i] + z[s / 4]) * unscale;   // block s row 4 kg + i, as the product leaves it
-        else w_acc[n][slice_channel<VF>(kg, chan<VF>(s, i))] = acc[s][i] + z[s / 4];
+        w_acc[n][slice_channel<VF>(kg, chan<VF>(s, i))] = acc[s][i] + z;
       }
     if (kg == 0) {
-      s_m[wave][n] = m2;
-      s_l[wave][n] = l * unscale;
+      ((float *)(wbuf + kSumsLds))[n] = m * cs;
+      ((float *)(wbuf + kSumsLds))[16 + n] = l;
     }
   }
 }
 
-// FOUR_BIT: the launch has a tier with 4-bit keys or values.  Those cases are held to two workgroups per CU (the plan counts on it); the
-// others run three.  T128: also one whose keys are grouped over 128 tokens per channel.
-template <bool FOUR_BIT, bool T128>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FOUR_BIT ? 2 : 3, FOUR_BIT ? 2 : 3))) void attn_mfma_kernel(const FusedArgs a) {
-  static_assert(kTileLds >= 16 * 128 * 4, "the wave's result fits its tile buffer");
-  __shared__ __attribute__((aligned(256))) char s_buf[4 * kTileLds];   // per wave: batch in flight, then [head][channel] floats
-  __shared__ float s_m[4][16], s_l[4][16];
+// ---------------------------------------------------------------- quantized tiers
+// How the heads of a workgroup and the tiles of a batch share the rows of a score product (heads are its rows, tokens
+// its columns).  HS: 4, 8 or 16 places for heads (the smallest that holds the block's heads); the 16 rows then take the
+// heads of 16 / HS tiles at once, each tile's product with the queries in its own rows and zeros in the others.  So the
+// softmax works on 4 tokens x heads per lane whatever HS is (with the heads as columns, 12 of 16 lanes had nothing to
+// do at four heads per KV head), every lane has one token of a chain, and that token's scales are the lane's own.
+template <int KF, int VF, int HS>
+struct QuantShape {
+  static constexpr int NT = KF == TTKV_I8_SYM_G32 ? 2 : 4, TT = 16 * NT;   // tiles, tokens of a batch
+  static constexpr int TPC = NT < 16 / HS ? NT : 16 / HS, NC = NT / TPC;   // tiles per score chain, chains
+  static constexpr int KPT = 4 / TPC, NE = HS / KPT;   // lanes' kg per tile; rows used of a lane's four
+  // row 4 kg + i, i < NE: tile kg / KPT of the chain, head (kg % KPT) NE + i
+  static constexpr int NGK = n_groups<KF>(), NGV = n_groups<VF>();
+  static constexpr bool K4 = KF == TTKV_I4_ASYM_G64, V4 = VF != TTKV_I8_SYM_G32, VT = VF == TTKV_I4_ASYM_G64_T32;
+  // The weights' way to the value product, whose columns are (channel group, head) pairs, 16 per operand set:
+  static constexpr int GR = HS * NGV > 32 ? 2 : NGV, NR = NGV / GR;   // channel groups that pass LDS at a time
+  static constexpr int RB = GR * HS * 2;                             // bytes per token there
+  static constexpr bool BY_PAIR = TT * RB > 2048;                    // only a pair of tiles at a time
+  static constexpr int NB = GR * HS > 16 ? GR * HS / 16 : 1, GPS = GR / NB, SETS = NB * NR;   // operand sets; groups in each
+  // A tile's weights in LDS: slots of 16 tokens x U bytes, one per kg of the tile (and half of the groups, where a lane has
+  // 32 bytes of a token); the tokens of slot q lie at (token U) ^ 64 q, so that the four slots a transposing read touches
+  // at a time, and the 16 tokens a store does, fall into different banks (rows of a token's 64 bytes before: four-way
+  // conflicts, 128 cycles per batch of 32 tokens and 16 heads).
+  static constexpr int U = GR * NE * 2 >= 16 ? 16 : 8;
+  static constexpr bool HALVES = GR * NE * 2 == 32;
+  static __device__ __forceinline__ uint32_t place(int slot, int token) { return slot * 16 * U + ((token * U) ^ (U == 16 ? slot * 64 : 0)); }
+  static_assert(NE == 4 || (NE == 2 && HS == 4), "rows per lane");
+  static_assert((BY_PAIR ? 32 : TT) * RB <= 2048, "the weights' place in LDS");
+  // column n of operand set b
+  static __device__ __forceinline__ int head_of(int n) {
+    return NE == 4 ? 4 * ((n >> 2) % KPT) + (n & 3) : 2 * ((n >> 2) & 1) + (n & 1);
+  }
+  static __device__ __forceinline__ int group_of(int n) {   // within the set
+    return NE == 4 ? ((n >> 2) / KPT) % GPS : (2 * (n >> 3) + ((n >> 1) & 1)) % GPS;
+  }
+  static __device__ __forceinline__ bool spare(int n) { return n >= GPS * HS; }   // a column that repeats another one
+};
+
+// The weights of four rows of 16 halves for lane c = one of 16: column c of them (transposing reads); from a0, their
+// remainders 2 KiB further: w[2 i] and w[2 i + 1] for O_i.
+template <int O0, int O1>
+__device__ __forceinline__ void lds_weights(uint32_t a0, u32x2 *w) {
+  asm volatile("ds_read_b64_tr_b16 %0, %4 offset:%5\n\tds_read_b64_tr_b16 %1, %4 offset:%7\n\t"
+               "ds_read_b64_tr_b16 %2, %4 offset:%6\n\tds_read_b64_tr_b16 %3, %4 offset:%8\n\ts_waitcnt lgkmcnt(0)"
+               : "=&v"(w[0]), "=&v"(w[1]), "=&v"(w[2]), "=&v"(w[3])
+               : "v"(a0), "n"(O0), "n"(O1), "n"(O0 + 2048), "n"(O1 + 2048) : "memory");
+}
+template <int O0, int O1, int O2, int O3>   // the last two from a1
+__device__ __forceinline__ void lds_weights(uint32_t a0, uint32_t a1, u32x2 *w) {
+  asm volatile("ds_read_b64_tr_b16 %0, %8 offset:%10\n\tds_read_b64_tr_b16 %1, %8 offset:%14\n\t"
+               "ds_read_b64_tr_b16 %2, %8 offset:%11\n\tds_read_b64_tr_b16 %3, %8 offset:%15\n\t"
+               "ds_read_b64_tr_b16 %4, %9 offset:%12\n\tds_read_b64_tr_b16 %5, %9 offset:%16\n\t"
+               "ds_read_b64_tr_b16 %6, %9 offset:%13\n\tds_read_b64_tr_b16 %7, %9 offset:%17\n\ts_waitcnt lgkmcnt(0)"
+               : "=&v"(w[0]), "=&v"(w[1]), "=&v"(w[2]), "=&v"(w[3]), "=&v"(w[4]), "=&v"(w[5]), "=&v"(w[6]), "=&v"(w[7])
+               : "v"(a0), "v"(a1), "n"(O0), "n"(O1), "n"(O2), "n"(O3), "n"(O0 + 2048), "n"(O1 + 2048), "n"(O2 + 2048),
+                 "n"(O3 + 2048) : "memory");
+}
+// 32 channels of a query, 8 from each address
+__device__ __forceinline__ void lds_query(uint32_t a0, uint32_t a1, uint32_t a2, uint32_t a3, u32x4 *w) {
+  asm volatile("ds_read_b128 %0, %4\n\tds_read_b128 %1, %5\n\tds_read_b128 %2, %6\n\tds_read_b128 %3, %7\n\t"
+               "s_waitcnt lgkmcnt(0)"
+               : "=&v"(w[0]), "=&v"(w[1]), "=&v"(w[2]), "=&v"(w[3]) : "v"(a0), "v"(a1), "v"(a2), "v"(a3) : "memory");
+}
+template <int OFF>
+__device__ __forceinline__ void lds_put(uint32_t a0, u32x4 w) {
+  asm volatile("ds_write_b128 %0, %1 offset:%2" ::"v"(a0), "v"(w), "n"(OFF) : "memory");
+}
+template <int OFF>
+__device__ __forceinline__ void lds_put(uint32_t a0, u32x2 w) {
+  asm volatile("ds_write_b64 %0, %1 offset:%2" ::"v"(a0), "v"(w), "n"(OFF) : "memory");
+}
+// The four meta words of the lane's token of NC chains: w[2 j] = the keys', w[2 j + 1] = the values'; chains STEP bytes
+// apart, the second word of a pair one plane (256 bytes) further, the values' two planes.
+template <int NC, int STEP>
+__device__ __forceinline__ void lds_meta(uint32_t a0, u32x2 *w) {
+  if constexpr (NC == 1) {
+    asm volatile("ds_read2_b32 %0, %2 offset1:64\n\tds_read2_b32 %1, %2 offset0:128 offset1:192\n\ts_waitcnt lgkmcnt(0)"
+                 : "=&v"(w[0]), "=&v"(w[1]) : "v"(a0) : "memory");
+  } else if constexpr (NC == 2) {
+    asm volatile("ds_read2_b32 %0, %4 offset1:64\n\tds_read2_b32 %1, %4 offset0:128 offset1:192\n\t"
+                 "ds_read2_b32 %2, %4 offset0:%5 offset1:%6\n\tds_read2_b32 %3, %4 offset0:%7 offset1:%8\n\ts_waitcnt lgkmcnt(0)"
+                 : "=&v"(w[0]), "=&v"(w[1]), "=&v"(w[2]), "=&v"(w[3])
+                 : "v"(a0), "n"(STEP / 4), "n"(STEP / 4 + 64), "n"(STEP / 4 + 128), "n"(STEP / 4 + 192) : "memory");
+  } else {
+    static_assert(STEP == 64, "the offsets below");
+    asm volatile("ds_read2_b32 %0, %8 offset1:64\n\tds_read2_b32 %1, %8 offset0:128 offset1:192\n\t"
+                 "ds_read2_b32 %2, %8 offset0:16 offset1:80\n\tds_read2_b32 %3, %8 offset0:144 offset1:208\n\t"
+                 "ds_read2_b32 %4, %8 offset0:32 offset1:96\n\tds_read2_b32 %5, %8 offset0:160 offset1:224\n\t"
+                 "ds_read2_b32 %6, %8 offset0:48 offset1:112\n\tds_read2_b32 %7, %8 offset0:176 offset1:240\n\t"
+                 "s_waitcnt lgkmcnt(0)"
+                 : "=&v"(w[0]), "=&v"(w[1]), "=&v"(w[2]), "=&v"(w[3]), "=&v"(w[4]), "=&v"(w[5]), "=&v"(w[6]), "=&v"(w[7])
+                 : "v"(a0) : "memory");
+  }
+}
+// Codes as fp16 bit patterns, i.e. as subnormal numbers: the matrix cores take them as they are, there is no offset to
+// remove and no rounding.  The products are aligned by the operands' exponents before they are added, so a code in the
+// lowest bits loses what its leading zeros take: in the sums over thousands of values that showed (2e-4 of the result at
+// 64K tokens, biased), so int4 values sit four bits up: (n0, n4) (n1, n5) (n2, n6) (n3, n7) as 16 code x 2^-24.  Keys,
+// summed over 64 channels, save two operations: registers 0 and 2 hold code x 2^-24, and the factor 16 sits on the queries
+// (a score's error stays below 2e-6 of its terms).  Four int8 codes: (code + 128) x 2^-24.
+constexpr uint32_t kCodeMask = 0x000F000Fu, kCodeFlip = 0x80808080u;
+struct CodeMasks {
+  uint32_t lo, hi, flip;   // in registers: a literal would be fetched with every instruction
+  __device__ __forceinline__ CodeMasks() : lo(kCodeMask), hi(kCodeMask << 4), flip(kCodeFlip) { asm volatile("" : "+s"(lo), "+s"(hi), "+s"(flip)); }
+};
+__device__ __forceinline__ void key_codes4(uint32_t x, uint32_t *r, const CodeMasks &k) {
+  const uint32_t y = x >> 8;
+  r[0] = x & k.lo;
+  r[1] = x & k.hi;
+  r[2] = y & k.lo;
+  r[3] = y & k.hi;
+}
+__device__ __forceinline__ void value_codes4(uint32_t x, uint32_t *r, const CodeMasks &k) {
+  r[0] = (x << 4) & k.hi;
+  r[1] = x & k.hi;
+  r[2] = (x >> 4) & k.hi;
+  r[3] = (x >> 8) & k.hi;
+}
+// both halves of a register times f
+__device__ __forceinline__ uint32_t pk_scale(uint32_t w, _Float16 f) { return __builtin_bit_cast(uint32_t, as_h2(w) * h2{f, f}); }
+__device__ __forceinline__ void codes8(uint32_t w, uint32_t *r, const CodeMasks &k) {
+  const uint32_t x = w ^ k.flip;
+  r[0] = __builtin_amdgcn_perm(0u, x, 0x0c010c00u);
+  r[1] = __builtin_amdgcn_perm(0u, x, 0x0c030c02u);
+}
+// The same value, as if formed here: what is derived from it is not kept in registers through the loop.
+__device__ __forceinline__ uint32_t fresh(uint32_t v) {
+  asm volatile("" : "+v"(v));
+  return v;
+}
+
+template <int KF, int VF, int HS>__device__ __forceinline__ void process_quant(const FusedArgs &a, const TierView &tv, const RunView &en, const int32_t *sel,
+                                              int chunk_tokens, int chunk, int n_items, int seq, int hq0, int Gr, int hkv, char *wbuf) {
+  // sel, hq0, Gr, wbuf: as process_rows.  n_items: 0, the item is chunk_tokens tokens in a row; else the run's items take
+  // turns at its batches, so that at any time they read one stretch of memory (32 / 8 heads, 128K tokens 40.2 -> 39.3 us,
+  // 64 x 4K tokens 120 -> 118 us).
+  using FK = Fmt<KF>;
+  using FV = Fmt<VF>;
+  using Q = QuantShape<KF, VF, HS>;
+  constexpr int NT = Q::NT, TT = Q::TT, TPC = Q::TPC, NC = Q::NC, KPT = Q::KPT, NE = Q::NE, NGK = Q::NGK, NGV = Q::NGV;
+  constexpr bool K4 = Q::K4, V4 = Q::V4, VT = Q::VT;
+  constexpr int PK = FK::ROWB / 16, PV = FV::ROWB / 16;                   // 16-byte pieces per row
+  constexpr int NDK = TT * FK::ROWB / 1024, NDV = TT * FV::ROWB / 1024;   // copy instructions of 1 KiB per half
+  constexpr int N_K = NDK + 4, N_V = NDV;                                 // with the four meta planes
+  static_assert(NDK == 4 && (NDV == 4 || NDV == 2), "the batch the LDS readers cover");
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int n = lane & 15, kg = lane >> 4;
+  const int step_tokens = 4 * TT * max(n_items, 1);
+  const int c0 = n_items ? chunk * 4 * TT : chunk * chunk_tokens;
+  const int c1 = n_items ? en.len : min(en.len, c0 + chunk_tokens);
+
+  // ---- where a batch lies, and its copies into the wave's LDS: K rows at 0, V rows at 4 KiB (row r at r ROWB, its
+  // piece p at 16 (p ^ swz(r))), then the two buffers of meta planes, then the weights.
+  auto swz = [](int pieces, int r) { return pieces == 4 ? (r >> 2) & 3 : (r >> 1) & 7; };
+  // value rows: also different for the rows that the lanes of a transposing read name in different tiles
+  auto swzv = [](int pieces, int r) { return pieces == 4 ? ((r >> 2) ^ (r >> 4)) & 3 : ((r >> 1) & 7) ^ ((r >> 3) & 2); };
+  // per-lane byte offset of copy instruction j inside a full batch, minus j KiB: keys even and odd j differ for 8
+  // pieces, values by an exchange of pieces (their rows' order is that of j = 0 with vx(j) added by exclusive or)
+  uint32_t dko[2];
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const int rk = j * (64 / PK) + lane / PK;
+    dko[j] = rk * FK::ROWB + ((lane % PK) ^ swz(PK, rk)) * 16 - j * 1024;
+  }
+  const uint32_t dvo = lane / PV * FV::ROWB + ((lane % PV) ^ swzv(PV, lane / PV)) * 16;
+  constexpr auto vx = [](int j) { return PV == 4 ? j * 16 : (j & 1) * 64 + (j >> 1) * 32; };
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(las_ptr)wbuf;
+  const uint8_t *nx_head = nullptr;     // batch whose K half was issued last
+  int nx_row0 = 0, nx_nv = 0;
+  // The wave's batches lie step_tokens apart: block and row move on by additions, and the next batch's record is looked up
+  // before it is asked for.
+  const int first = c0 + wave * TT;
+  const int step_blocks = step_tokens / tv.bt, step_rows = step_tokens - step_blocks * tv.bt;
+  Place at = place_of(tv, en, min(first, en.len - 1));
+  const uint8_t *at_head = head_at(tv, en, sel, seq, hkv, at.block);
+  auto advance = [&](int i0) {   // to the batch after i0, if there is one
+    if (i0 + step_tokens >= c1) return;
+    at.row += step_rows;
+    at.block += step_blocks;
+    if (at.row >= tv.bt) {
+      at.row -= tv.bt;
+      ++at.block;
+    }
+    if (!sel && at.block >= tv.ring_blocks) at.block -= tv.ring_blocks;
+    at_head = head_at(tv, en, sel, seq, hkv, at.block);
+  };
+  auto issue_k = [&](int i0) {
+    nx_head = at_head;
+    nx_row0 = at.row;
+    nx_nv = min(TT, c1 - i0);
+    const uint8_t *kb = nx_head + nx_row0 * FK::ROWB, *kmb = nx_head + tv.k_meta_off + nx_row0 * 8;
+    if (nx_nv == TT) {
+      dma16<0>(kb + dko[0], wbuf); dma16<1024>(kb + dko[1], wbuf);
+      dma16<2048>(kb + dko[0], wbuf); dma16<3072>(kb + dko[1], wbuf);
+    } else {
+      const int ln = (int)fresh(lane);
+#pragma unroll
+      for (int j = 0; j < NDK; ++j) {
+        const int r = j * (64 / PK) + ln / PK;   // LDS row; rows past the end repeat the last live row
+        dma16(kb + min(r, nx_nv - 1) * FK::ROWB + ((ln % PK) ^ swz(PK, r)) * 16, wbuf + j * 1024);
+      }
+    }
+    const uint32_t mo = min(lane, nx_nv - 1) * 8;   // one lane per token (TT = 32: the upper lanes repeat the last row)
+    dma4(kmb + mo, wbuf + kTileRowsLds);
+    dma4(kmb + mo + 4, wbuf + kTileRowsLds + 256);
+    const uint8_t *vmb = nx_head + tv.v_meta_off + nx_row0 * 8;   // the values' too: their scales are looked at with the scores
+    dma4(vmb + mo, wbuf + kTileRowsLds + 512);
+    dma4(vmb + mo + 4, wbuf + kTileRowsLds + 768);
+  };
+  auto issue_v = [&](int i0) {   // of the batch at i0, whose K half was issued last
+    const uint8_t *vb = nx_head + tv.v_off + nx_row0 * FV::ROWB;
+    if constexpr (VT) {   // whole 2 KiB groups (lengths are multiples of 32), copied as they lie
+      dma16<0>(vb + lane * 16, wbuf + 4096); dma16<1024>(vb + lane * 16, wbuf + 4096);
+      if constexpr (NT == 4) {   // the second group: inside the record even when the run ends before it (its weights are 0)
+        dma16<2048>(vb + lane * 16, wbuf + 4096); dma16<3072>(vb + lane * 16, wbuf + 4096);
+      }
+    } else if (nx_nv == TT) {
+      dma16<0>(vb + dvo, wbuf + 4096); dma16<1024>(vb + (dvo ^ vx(1)), wbuf + 4096);
+      if constexpr (NDV == 4) {
+        dma16<2048>(vb + (dvo ^ vx(2)), wbuf + 4096); dma16<3072>(vb + (dvo ^ vx(3)), wbuf + 4096);
+      }
+    } else {
+      const int ln = (int)fresh(lane);
+#pragma unroll
+      for (int j = 0; j < NDV; ++j) {
+        const int r = j * (64 / PV) + ln / PV;
+        dma16(vb + min(r, nx_nv - 1) * FV::ROWB + ((ln % PV) ^ swzv(PV, r)) * 16, wbuf + 4096 + j * 1024);
+      }
+    }
+    advance(i0);
+  };
+  // Rows in pinned host memory: the whole batch through registers into the same places (over PCIe the asynchronous
+  // copies were 3-4 % slower, and the streaming hint has nothing to gain there).  Lane (n, kg) moves piece kg (+ 4) of
+  // row n of every tile, one lane per token its meta words.
+  constexpr int NLK = FK::ROWB / 64, NLV = FV::ROWB / 64;   // 16-byte loads per lane per 16-token tile
+  auto bring_host = [&](int i0) {
+    const int lane = (int)fresh(threadIdx.x & 63), n = lane & 15, kg = lane >> 4;
+    const uint8_t *const head = at_head;
+    const int nv = min(TT, c1 - i0), row0 = at.row;
+    advance(i0);
+    const uint8_t *kb = head + row0 * FK::ROWB, *vb = head + tv.v_off + row0 * FV::ROWB;
+    u32x4 kw[NT][NLK], vw[NT][NLV];
+#pragma unroll
+    for (int tt = 0; tt < NT; ++tt) {
+      const uint32_t row = min(tt * 16 + n, nv - 1);   // rows past the end repeat the last live row
+#pragma unroll
+      for (int x = 0; x < NLK; ++x) kw[tt][x] = *(const u32x4 *)(kb + row * FK::ROWB + kg * 16 + 64 * x);
+      if constexpr (VT) {
+        // piece hh = tt % 2 of the 32-token group tt / 2 (a group past the end repeats the last live one)
+        vw[tt][0] = *(const u32x4 *)(vb + min(tt / 2, (nv - 1) / 32) * 2048 + (tt & 1) * 1024 + lane * 16);
+      } else {
+#pragma unroll
+        for (int x = 0; x < NLV; ++x) vw[tt][x] = *(const u32x4 *)(vb + row * FV::ROWB + kg * 16 + 64 * x);
+      }
+    }
+    const uint32_t mo = (row0 + min(lane, nv - 1)) * 8;
+    const uint2 km = *(const uint2 *)(head + tv.k_meta_off + mo), vm = *(const uint2 *)(head + tv.v_meta_off + mo);
+#pragma unroll
+    for (int tt = 0; tt < NT; ++tt) {
+#pragma unroll
+      for (int x = 0; x < NLK; ++x)
+        *(u32x4 *)(wbuf + (tt * 16 + n) * FK::ROWB + (((kg + 4 * x) ^ swz(PK, n)) * 16)) = kw[tt][x];
+      if constexpr (VT) {
+        *(u32x4 *)(wbuf + 4096 + tt * 1024 + lane * 16) = vw[tt][0];
+      } else {
+#pragma unroll
+        for (int x = 0; x < NLV; ++x)
+          *(u32x4 *)(wbuf + 4096 + (tt * 16 + n) * FV::ROWB + (((kg + 4 * x) ^ swzv(PV, tt * 16 + n)) * 16)) = vw[tt][x];
+      }
+    }
+    uint32_t *m = (uint32_t *)(wbuf + kTileRowsLds) + lane;
+    m[0] = km.x;
+    m[64] = km.y;
+    m[128] = vm.x;
+    m[192] = vm.y;
+  };
+
+  if (first >= c1) {   // no batch for this wave (wave-uniform): an empty part
+    if (lane < 16) {
+      ((float *)(wbuf + kSumsLds))[lane] = -INFINITY;
+      ((float *)(wbuf + kSumsLds))[16 + lane] = 0.0f;
+    }
+    for (int idx = lane; idx < Gr * 32; idx += 64) ((float4 *)wbuf)[idx] = float4{0.0f, 0.0f, 0.0f, 0.0f};
+    return;
+  }
+
+  // ---- the queries.  Their rows come through LDS like everything else, in front of the first batch, so that a count of
+  // the copies behind them says when they have landed: they are prepared while the batch is on its way (loads into
+  // registers are waited for with everything in flight wherever paths with other counts meet; so 3.1 us passed from the
+  // look-up of the item to its first keys).  Up to 8 heads wait in the weights' place, 16 in that of the values, which are
+  // then copied after them.
+  constexpr bool Q_IN_V = HS == 16;
+  char *const q_lds = wbuf + (Q_IN_V ? 4096 : kBatchLds);
+#pragma unroll
+  for (int i = 0; i < HS / 4; ++i) {
+    const int h = min(4 * i + (lane >> 4), Gr - 1);
+    dma16((const uint8_t *)a.q + ((int64_t)seq * a.Hq + hq0 + h) * 256 + n * 16, q_lds + 1024 * i);
+  }
+  if (tv.in_host) {
+    wait_vmcnt<0>();
+  } else {
+    issue_k(first);
+    if constexpr (!Q_IN_V) issue_v(first);
+    wait_vmcnt<N_K + (Q_IN_V ? 0 : N_V)>();
+  }
+  const int my_row = n & 3, row_kg = n >> 2;                       // row n = 4 row_kg + my_row
+  const int row_head = (row_kg % KPT) * NE + my_row;
+  uint32_t qw[16];            // lane (c = n, kg): 32 channels of the head of row c
+  {
+    u32x4 w[4];
+    const uint32_t q0 = (uint32_t)(uintptr_t)(las_ptr)q_lds + min(row_head, HS - 1) * 256;
+    lds_query(q0 + key_channel<KF>(kg, 0) * 2, q0 + key_channel<KF>(kg, 8) * 2, q0 + key_channel<KF>(kg, 16) * 2,
+              q0 + key_channel<KF>(kg, 24) * 2, w);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) qw[i] = w[i / 4][i % 4];
+  }
+  if constexpr (Q_IN_V)
+    if (!tv.in_host) issue_v(first);
+  float unit = a.scale * kLog2e * (K4 ? 0x1p20f : 0x1p24f);   // a score is its product times this, in the log2 domain
+  uint32_t qA[TPC][16];      // row operand of the chain's tiles
+  f4 off[NGK];               // int8: minus what the code offset 128 adds to a row's product, per channel group
+  float qs[K4 ? 2 : 1][NE];  // int4: a row's sum per channel group (for the zero points), in the product's units
+  {
+    if (a.q_fmt == TTKV_BF16) {   // bf16 -> fp16 (exact inside the fp16 normal range, clamped outside)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const float lo = fminf(fmaxf(__uint_as_float(qw[i] << 16), -65504.0f), 65504.0f);
+        const float hi = fminf(fmaxf(__uint_as_float(qw[i] & 0xffff0000u), -65504.0f), 65504.0f);
+        qw[i] = (uint32_t)__half_as_ushort(__float2half_rn(lo)) | ((uint32_t)__half_as_ushort(__float2half_rn(hi)) << 16);
+      }
+    }
+    const bool row_on = my_row < NE && row_head < Gr;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) qw[i] = row_on ? qw[i] : 0u;
+    if constexpr (K4) {
+      // 16 q on the even registers; where that would leave fp16's range (|q| >= 4095 somewhere) all a sixteenth of it
+      uint32_t top = 0;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) top = halves_max(top, qw[i] & 0x7fff7fffu);
+      const bool big = __any((top & 0xffffu) > 0x6bffu || (top >> 16) > 0x6bffu);
+      const _Float16 fe = big ? (_Float16)1.0f : (_Float16)16.0f, fo = big ? (_Float16)0.0625f : (_Float16)1.0f;
+      if (big) unit *= 16.0f;
+      uint32_t t[16];
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {   // register r = 4 d + e: elements (8 d + e, 8 d + e + 4) of the slice
+        const int dd = r / 4, e = r % 4;
+        t[r] = pk_scale(__builtin_amdgcn_perm(qw[4 * dd + 2 + e / 2], qw[4 * dd + e / 2], (e & 1) ? 0x07060302u : 0x05040100u),
+                        (r & 1) ? fo : fe);
+      }
+#pragma unroll
+      for (int r = 0; r < 16; ++r) qw[r] = t[r];
+    }
+    // the rows' sums per channel group, by a product with ones: in every lane those of its own rows
+#pragma unroll
+    for (int gr = 0; gr < NGK; ++gr) {
+      const uint32_t ev = K4 ? 0x2C002C00u : 0x3C003C00u, one4[4] = {ev, 0x3C003C00u, ev, 0x3C003C00u};   // int4: 1/16 for 16 q
+      f4 sum = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+      for (int s = gr * (4 / NGK); s < (gr + 1) * (4 / NGK); ++s) sum = mma32<false>(qw + 4 * s, one4, sum);
+      if constexpr (K4) {
+#pragma unroll
+        for (int e = 0; e < NE; ++e) qs[gr][e] = sum[e] * 0x1p-20f;
+      } else {
+        off[gr] = sum * (-128.0f * 0x1p-24f);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < TPC; ++u)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) qA[u][r] = TPC == 1 || row_kg / KPT == u ? qw[r] : 0u;
+  }
+
+  // ---- addresses of the LDS reads
+  // the lane's 8 bytes of the first 32-byte stretch of row n: half kg % 2 of piece kg / 2 (stretch x: by exclusive or with 32 x)
+  const uint32_t lka = lds0 + n * FK::ROWB + (((kg >> 1) ^ swz(PK, n)) * 16) + 8 * (kg & 1);
+  // what the lane names to the transposing value reads: its row's first piece (the others by exclusive or with 16 x piece)
+  uint32_t lva = lds0 + 4096 + lane * 16;
+  if constexpr (!VT) {
+    const int r4 = 2 * (n & 1) + 16 * ((n >> 1) & 1) + ((n >> 2) & 1) + 4 * kg;   // kTok[n % 8] + 4 kg
+    const int row = PV == 8 ? ((n >> 1) & 3) + 16 * (n >> 3) + 4 * kg : NT == 4 ? r4 + 32 * (n >> 3) : r4;
+    const int half = PV == 8 ? n & 1 : NT == 4 ? 0 : n >> 3;
+    lva = lds0 + 4096 + row * FV::ROWB + swzv(PV, row) * 16 + 8 * half;
+  }
+  const int my_tok = 16 * (kg / KPT) + n;                             // the lane's token of chain 0
+  const uint32_t lma = lds0 + kTileRowsLds + 4 * my_tok;
+  // weights: where the lane's go (the second half of its groups a slot distance further), and what it names to a transposing
+  // read: quad n % 4 of token 4 kg + n / 4
+  const uint32_t lp0 = lds0 + kBatchLds;
+  const uint32_t lpw = lp0 + (my_tok & ~15) * Q::RB + Q::place(kg % KPT, n);
+  const int quad = n & 3;
+  const uint32_t lpr = lp0 + (NE == 4 ? Q::place(quad % KPT, 4 * kg + (n >> 2)) + ((quad / KPT) % Q::GPS) * 8
+                                      : Q::place(quad & 1, 4 * kg + (n >> 2)) + ((quad >> 1) % (Q::GR / 2)) * 8);
+  // KPT slots further: 16 U KPT bytes, and the tokens' turn by exclusive or
+  auto second_half = [&](uint32_t at) -> uint32_t { return Q::HALVES ? (fresh(at) ^ (64 * KPT)) + 16 * Q::U * KPT : at; };
+
+  const f4 zero4 = f4{0.0f, 0.0f, 0.0f, 0.0f};
+  f4 acc[8], accc[Q::SETS];       // accc: the centre's share of every channel's sum (the same in all four rows)
+  float zs[V4 ? 2 : 1][NE];       // sum_t p_t (z_{t,g} + 8 s_{t,g}) over the lane's tokens
+  float l[NE], mcs[NE];           // a token's weight: exp2(score unit + mcs)
+#pragma unroll
+  for (int s = 0; s < 8; ++s) acc[s] = zero4;
+#pragma unroll
+  for (int b = 0; b < Q::SETS; ++b) accc[b] = zero4;
+#pragma unroll
+  for (int e = 0; e < NE; ++e) {
+    l[e] = 0.0f;
+    mcs[e] = INFINITY;
+#pragma unroll
+    for (int g = 0; g < (V4 ? 2 : 1); ++g) zs[g][e] = 0.0f;
+  }
+  // The value operand is fp16(p s), and with p <= 1 that falls into fp16's subnormals or to zero for value scales well
+  // below 1 (std 0.02 beside a token 7 above the rest: an error of 1.7e-2 of the output).  So the weights carry a power
+  // of two, 2^wexp, that brings the largest value scale the wave has met, with room for twice as large ones, to [2^8, 2^9); it is in l, zs and acc alike and
+  // leaves them at the end.  s_top: the largest fp16 number (as bits, ordered like the numbers) of that scale's binade,
+  // so that only a scale beyond that room takes the branch below.
+  // The weights' reference is a score that no other one exceeds by more than a factor 2^kHeadroom in weight: it moves
+  // once or twice per item, where the running maximum of 16 heads moves in most batches.
+  constexpr int kHeadroom = 5;
+  uint32_t s_top = 0;
+  int wexp = 0;
+  float limit = -INFINITY;         // of the exponents; the first batch always exceeds it
+  // A reference beyond 4 million has no bits left for the power of two: weights of such a head carry none.  Product and
+  // difference are rounded one after the other: factor - mcs, the reference of the item's result, is then exact.
+  uint32_t plain = 0;              // bit e: the weights of element e's head carry no power of two
+
+  const CodeMasks codes;
+
+  u32x2 kw[8], meta[2 * NC];
+  uint32_t vop[NT / 2][8][VF == TTKV_I8_SYM_G32 ? 2 : 1];   // codes of channel 16 s + n, the pair's 8 tokens of this kg
+  auto fetch_k = [&]() {
+    const uint32_t ka = fresh(lka);
+    if constexpr (PK == 8) lds_keys_i8(ka, ka ^ 32, ka ^ 64, ka ^ 96, kw);
+    else lds_keys_i4(ka, ka ^ 32, kw);
+    lds_meta<NC, 64 * TPC>(lma, meta);
+  };
+  auto fetch_v = [&]() {
+    const uint32_t va = fresh(lva);
+    if constexpr (VT) {   // word w of piece hh: block 4 hh + w
+      u32x4 w[4];
+      lds_pieces<NT>(va, w);
+#pragma unroll
+      for (int s = 0; s < 8; ++s)
+#pragma unroll
+        for (int pr = 0; pr < NT / 2; ++pr) vop[pr][s][0] = w[2 * pr + s / 4][s % 4];
+    } else {
+      u32x2 w[8];
+      if constexpr (PV == 8) {
+        lds_values_i8(va, va ^ 16, va ^ 32, va ^ 48, w);
+        lds_values_i8(va ^ 64, va ^ 80, va ^ 96, va ^ 112, w + 4);
+      } else if constexpr (NT == 4) {
+        lds_values_i4x4(va, va ^ 16, va ^ 32, va ^ 48, w);
+      } else {
+        lds_values_i4x2(va, va ^ 16, va ^ 32, va ^ 48, w);
+      }
+#pragma unroll
+      for (int s = 0; s < 8; ++s) {
+        if constexpr (PV == 8) {
+          vop[0][s][0] = w[s].x;
+          vop[0][s][1] = w[s].y;
+        } else if constexpr (NT == 4) {
+          vop[0][s][0] = w[s].x;
+          vop[1][s][0] = w[s].y;
+        } else {
+          vop[0][s][0] = s % 2 ? w[s / 2].y : w[s / 2].x;
+        }
+      }
+    }
+  };
+
+  // before_v runs between the softmax and the first use of the batch's V half.
+  auto compute = [&](int nv, auto before_v) __attribute__((always_inline)) {
+    // ---- scores: element e of chain j is head (kg % KPT) NE + e of token 16 TPC j + my_tok
+    float x[NC][NE];
+    uint32_t top = 0;   // the largest value scale of the lane's tokens
+#pragma unroll
+    for (int j = 0; j < NC; ++j) {
+      const uint32_t m0 = meta[2 * j].x, m1 = meta[2 * j].y;
+      float v[NE];
+#pragma unroll
+      for (int gr = 0; gr < NGK; ++gr) {   // one product chain per channel group
+        f4 sv = K4 ? zero4 : off[gr];
+#pragma unroll
+        for (int u = 0; u < TPC; ++u) {
+          const u32x2 w = kw[(j * TPC + u) * NGK + gr];   // the lane's 8 bytes of the group
+          if constexpr (K4) {
+            uint32_t kr[8];
+            key_codes4(w.x, kr, codes);
+            key_codes4(w.y, kr + 4, codes);
+            sv = mma32<false>(qA[u] + 8 * gr, kr, sv);
+            sv = mma32<false>(qA[u] + 8 * gr + 4, kr + 4, sv);
+          } else {
+            uint32_t kr[4];
+            codes8(w.x, kr, codes);
+            codes8(w.y, kr + 2, codes);
+            sv = mma32<false>(qA[u] + 4 * gr, kr, sv);
+          }
+        }
+#pragma unroll
+        for (int e = 0; e < NE; ++e) {
+          if constexpr (K4) {   // the group's zero point and scale
+            const uint32_t m = gr ? m1 : m0;
+            v[e] = gr ? fmaf(half1(m), qs[gr][e], v[e]) : half1(m) * qs[gr][e];
+            v[e] = fmaf(sv[e], half0(m), v[e]);
+          } else {              // the group's scale
+            const uint32_t m = gr / 2 ? m1 : m0;
+            v[e] = gr ? fmaf(sv[e], gr % 2 ? half1(m) : half0(m), v[e]) : sv[e] * half0(m);
+          }
+        }
+      }
+#pragma unroll
+      for (int e = 0; e < NE; ++e) {
+        x[j][e] = v[e];
+      }
+      const uint32_t t = halves_max(meta[2 * j + 1].x, meta[2 * j + 1].y);   // scales are not negative
+      top = max(top, V4 ? t & 0xffffu : max(t & 0xffffu, t >> 16));
+    }
+
+    if (nv < TT)   // wave-uniform
+#pragma unroll
+      for (int j = 0; j < NC; ++j)
+#pragma unroll
+        for (int e = 0; e < NE; ++e) x[j][e] = 16 * TPC * j + my_tok < nv ? x[j][e] : -INFINITY;
+
+    // ---- online softmax (base 2)
+    float p[NC][NE];   // exponents, then weights
+    float most = -INFINITY;
+#pragma unroll
+    for (int j = 0; j < NC; ++j)
+#pragma unroll
+      for (int e = 0; e < NE; ++e) {
+        p[j][e] = fmaf(x[j][e], unit, mcs[e]);
+        most = fmaxf(most, p[j][e]);
+      }
+    if (__any(most > limit || top > s_top)) {
+      const int before = wexp;
+      if (__any(top > s_top)) {
+        s_top = (wave_max16(top) | 0x3ffu) + 0x400u;   // a binade of room
+        wexp = 29 - kHeadroom - max((int)(s_top >> 10), 1);
+      }
+      float alpha[NE];
+      limit = INFINITY;
+      const uint32_t was_plain = plain;
+      plain = 0;
+#pragma unroll
+      for (int e = 0; e < NE; ++e) {
+#pragma clang fp contract(off)
+        float mx = x[0][e];
+#pragma unroll
+        for (int j = 1; j < NC; ++j) mx = fmaxf(mx, x[j][e]);
+        mx = row_max(mx);   // over the 16 tokens, then the chain's tiles
+        if constexpr (TPC == 4) mx = fmaxf(both16(mx).x, both16(mx).y);
+        if constexpr (TPC >= 2) mx = fmaxf(both32(mx).x, both32(mx).y);
+        // the reference so far: factor - mcs, minus infinity before the first batch
+        const float old = mcs[e];
+        const float r_old = ((was_plain >> e) & 1 ? 0.0f : (float)before) - old;
+        const float r = fmaxf(r_old, mx * unit);
+        const bool none = !(fabsf(r) < 4194304.0f);
+        const float f = none ? 0.0f : (float)wexp;
+        plain |= none ? 1u << e : 0u;
+        mcs[e] = f - r;
+        limit = fminf(limit, f + (float)kHeadroom);
+        alpha[e] = __builtin_amdgcn_exp2f(mcs[e] - old);
+        l[e] *= alpha[e];
+        if constexpr (V4) {
+          zs[0][e] *= alpha[e];
+          zs[1][e] *= alpha[e];
+        }
+      }
+      // a column's factor: that of its head
+      float ac = 0.0f;
+      const int h = Q::head_of((int)fresh(n));
+#pragma unroll
+      for (int e = 0; e < NE; ++e) {
+        const float v = KPT == 1 ? alpha[e] : __shfl(alpha[e], 16 * (h / NE));   // one kg per tile: every lane has all heads
+        if (h % NE == e) ac = v;
+      }
+#pragma unroll
+      for (int s = 0; s < 8; ++s) acc[s] *= ac;
+#pragma unroll
+      for (int b = 0; b < Q::SETS; ++b) accc[b] *= ac;
+#pragma unroll
+      for (int j = 0; j < NC; ++j)
+#pragma unroll
+        for (int e = 0; e < NE; ++e) p[j][e] = fmaf(x[j][e], unit, mcs[e]);
+    }
+    float vs[NC][NGV];   // the values' scales as they meet the weights
+#pragma unroll
+    for (int j = 0; j < NC; ++j) {
+      const uint32_t m0 = meta[2 * j + 1].x, m1 = meta[2 * j + 1].y;
+      float z[2] = {0.0f, 0.0f};
+      if constexpr (V4) {   // zero point + the centre 8 x scale
+        z[0] = fmaf(8.0f, half0(m0), half1(m0));
+        z[1] = fmaf(8.0f, half0(m1), half1(m1));
+        vs[j][0] = half0(m0);
+        vs[j][1] = half0(m1);
+      } else {
+        vs[j][0] = half0(m0); vs[j][1] = half1(m0);
+        vs[j][2] = half0(m1); vs[j][3] = half1(m1);
+      }
+#pragma unroll
+      for (int e = 0; e < NE; ++e) {
+        p[j][e] = __builtin_amdgcn_exp2f(p[j][e]);
+        l[e] += p[j][e];
+        if constexpr (V4) {
+          zs[0][e] = fmaf(p[j][e], z[0], zs[0][e]);
+          zs[1][e] = fmaf(p[j][e], z[1], zs[1][e]);
+        }
+      }
+    }
+
+    // ---- weighted V, two 16-token tiles per 32-deep product.  The codes' words are the A operands of the eight channel
+    // blocks; the weights, times the scales of a channel group, go through LDS into the B operand's layout (rows of a
+    // token in, columns of a (group, head) out).  They meet the values with 22 bits, as fp16(p s) and its remainder: two
+    // products, which are not what bounds the loop.  (With fp16(p s) alone the error is 1e-4, and keeping it there takes
+    // the running maximum as reference, so that the largest weight is a power of two.)
+    auto put_weights = [&](int j, int round, auto at_tag) __attribute__((always_inline)) {   // chain j, channel groups GR round ..
+      constexpr int AT = decltype(at_tag)::value;
+      uint32_t w[Q::GR * NE / 2], r[Q::GR * NE / 2];
+#pragma unroll
+      for (int g = 0; g < Q::GR; ++g)
+#pragma unroll
+        for (int e = 0; e < NE; e += 2) {
+          const float s = vs[j][Q::GR * round + g];
+          const uint32_t x = pk(p[j][e] * s, p[j][e + 1] * s);
+          w[(g * NE + e) / 2] = x;
+          r[(g * NE + e) / 2] = pk(fmaf(p[j][e], s, -half0(x)), fmaf(p[j][e + 1], s, -half1(x)));
+        }
+      if constexpr (Q::GR * NE == 4) {
+        lds_put<AT>(lpw, u32x2{w[0], w[1]});
+        lds_put<AT + 2048>(lpw, u32x2{r[0], r[1]});
+      } else {
+        lds_put<AT>(lpw, u32x4{w[0], w[1], w[2], w[3]});
+        lds_put<AT + 2048>(lpw, u32x4{r[0], r[1], r[2], r[3]});
+        if constexpr (Q::HALVES) {
+          lds_put<AT>(second_half(lpw), u32x4{w[4], w[5], w[6], w[7]});
+          lds_put<AT + 2048>(second_half(lpw), u32x4{r[4], r[5], r[6], r[7]});
+        }
+      }
+    };
+    auto product = [&](int pr, int b, const u32x2 *w) __attribute__((always_inline)) {   // pair pr, operand set b
+      const uint32_t B[4] = {w[0].x, w[0].y, w[2].x, w[2].y}, R[4] = {w[1].x, w[1].y, w[3].x, w[3].y};
+      constexpr int BPG = 8 / NGV;   // channel blocks per group
+#pragma unroll
+      for (int s = b * Q::GPS * BPG; s < (b + 1) * Q::GPS * BPG; ++s) {
+        uint32_t vr[4];
+        if constexpr (V4) {
+          value_codes4(vop[pr][s][0], vr, codes);
+        } else {
+          codes8(vop[pr][s][0], vr, codes);
+          codes8(vop[pr][s][VF == TTKV_I8_SYM_G32 ? 1 : 0], vr + 2, codes);
+        }
+        acc[s] = mma32<false>(vr, R, acc[s]);
+        acc[s] = mma32<false>(vr, B, acc[s]);
+      }
+      const uint32_t cc[4] = {0x00800080u, 0x00800080u, 0x00800080u, 0x00800080u};   // the centre as a code: int4 16 x 8, int8 128
+      accc[b] = mma32<false>(cc, R, accc[b]);
+      accc[b] = mma32<false>(cc, B, accc[b]);
+    };
+    constexpr int T16 = 16 * Q::RB, SET = Q::HALVES ? 0 : Q::GPS * 8;   // bytes of a tile's weights; to the second operand set
+    if constexpr (Q::BY_PAIR) {
+      static_assert(!Q::BY_PAIR || (NC == 4 && Q::NR == 1 && Q::NB == 2), "one tile per chain, two sets");
+      u32x2 w[16];
+      put_weights(0, 0, std::integral_constant<int, 0>{});
+      put_weights(1, 0, std::integral_constant<int, T16>{});
+      lds_weights<0, T16, Q::GPS * 8, T16 + Q::GPS * 8>(lpr, lpr, w);
+      put_weights(NC - 2, 0, std::integral_constant<int, 0>{});
+      put_weights(NC - 1, 0, std::integral_constant<int, T16>{});
+      lds_weights<0, T16, Q::GPS * 8, T16 + Q::GPS * 8>(lpr, lpr, w + 8);
+      before_v();
+#pragma unroll
+      for (int pr = 0; pr < NT / 2; ++pr)
+#pragma unroll
+        for (int b = 0; b < Q::NB; ++b) product(pr, b, w + 8 * pr + 4 * b);
+    } else if constexpr (NT == 4) {   // one operand set, both pairs
+      static_assert(NT != 4 || Q::BY_PAIR || (Q::SETS == 1 && Q::NR == 1), "one set");
+      put_weights(0, 0, std::integral_constant<int, 0>{});
+      if constexpr (NC == 2) put_weights(NC - 1, 0, std::integral_constant<int, 2 * T16>{});
+      u32x2 w[8];
+      lds_weights<0, T16, 2 * T16, 3 * T16>(lpr, lpr, w);
+      before_v();
+      product(0, 0, w);
+      product(NT / 2 - 1, 0, w + 4);
+    } else {
+      u32x2 w[4 * Q::SETS];
+#pragma unroll
+      for (int round = 0; round < Q::NR; ++round) {
+        put_weights(0, round, std::integral_constant<int, 0>{});
+        if constexpr (NC == 2) put_weights(NC - 1, round, std::integral_constant<int, T16>{});
+        if constexpr (Q::NB == 2) lds_weights<0, T16, SET, T16 + SET>(lpr, second_half(lpr), w + 8 * round);
+        else lds_weights<0, T16>(lpr, w + 4 * round);
+      }
+      before_v();
+#pragma unroll
+      for (int b = 0; b < Q::SETS; ++b) product(0, b, w + 4 * b);
+    }
+  };
+
+  // While batch i is computed the copies of batch i + 1 are in flight: its K half is issued once batch i's K rows and meta
+  // words are in registers, its V half once batch i's V rows are.  Loads complete in order, so "at most as many
+  // outstanding as were issued after it" means a half has landed.
+  for (int i0 = first; i0 < c1; i0 += step_tokens) {
+    const bool more = !tv.in_host && i0 + step_tokens < c1;   // wave-uniform
+    if (tv.in_host) bring_host(i0);
+    else wait_vmcnt<N_V>();
+    fetch_k();
+    if (more) issue_k(i0 + step_tokens);
+    compute(min(TT, c1 - i0), [&]() {
+      if (more) wait_vmcnt<N_K>();
+      else wait_vmcnt<0>();
+      fetch_v();
+      if (more) issue_v(i0 + step_tokens);
+    });
+  }
+
+  // ---- the wave's result.  Sums over the lane's tokens come together; a head's zero-point sums, and what its weights
+  // carry, reach the columns through LDS.
+  float *const s_head = (float *)(wbuf + kTileRowsLds);   // [head][4], where the meta words were
+#pragma unroll
+  for (int e = 0; e < NE; ++e) {
+    auto over_tokens = [&](float v) {
+      v = group_sum<16>(v);
+      if constexpr (TPC == 4) v = both16(v).x + both16(v).y;
+      if constexpr (TPC >= 2) v = both32(v).x + both32(v).y;
+      return v;
+    };
+    l[e] = over_tokens(l[e]);
+    float z[2] = {0.0f, 0.0f};
+    if constexpr (V4) {
+      z[0] = over_tokens(zs[0][e]);
+      z[1] = over_tokens(zs[1][e]);
+    }
+    const float w = (plain >> e) & 1 ? 0.0f : (float)wexp, unscale = pow2(-(int)w);
+    const int h = (kg % KPT) * NE + e;
+    if (n == 0 && kg < KPT) {
+      s_head[4 * h] = z[0] * unscale;
+      s_head[4 * h + 1] = z[1] * unscale;
+      s_head[4 * h + 2] = unscale * (V4 ? 0x1p20f : 0x1p24f);
+      ((float *)(wbuf + kSumsLds))[h] = w - mcs[e];   // log2 domain
+      ((float *)(wbuf + kSumsLds))[16 + h] = l[e] * unscale;
+    }
+  }
+  const int h = Q::head_of(n);
+  if (h < Gr && !Q::spare(n)) {
+    float (*w_acc)[128] = (float (*)[128])wbuf;   // [head][channel]; the wave's last batch has been consumed
+    const float back = s_head[4 * h + 2];
+#pragma unroll
+    for (int s = 0; s < 8; ++s) {
+      const int g = s / (8 / NGV), b = g / Q::GPS;
+      if (g % Q::GPS != Q::group_of(n)) continue;
+      const float z = V4 ? s_head[4 * h + g] : 0.0f;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) w_acc[h][16 * s + 4 * kg + i] = fmaf(acc[s][i] - accc[b][i], back, z);
+    }
+  }
+}
+
+// What the tiers of a launch hold: each kind is compiled without the cases it does not meet, so that their registers do
+// not count.  With 4-bit keys or values, and for int8 with more than 8 heads, two workgroups per CU (the plan counts on
+// it), otherwise three.  HS: places for heads (QuantShape).
+enum LaunchKind { FP_ONLY, WITH_INT8, WITH_4BIT, WITH_T128 };
+constexpr int waves_per_simd(int kind, int hs) { return kind == FP_ONLY || (kind == WITH_INT8 && hs <= 8) ? 3 : 2; }
+template <int KIND, int HS>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(waves_per_simd(KIND, HS), waves_per_simd(KIND, HS)))) void attn_mfma_kernel(const FusedArgs a) {
+  static_assert(kTileRowsLds >= 16 * 128 * 4 && 3 * 4 * kTileLds <= 160 * 1024, "the wave's result; three workgroups per CU");
+  __shared__ __attribute__((aligned(256))) char s_buf[4 * kTileLds];   // per wave: batches in flight, then [head][channel] floats
+  char *const wbuf = s_buf + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * kTileLds;
 
   // Linear workgroup id -> (item, KV head, block of heads).  More heads per KV head than one tile takes are cut
   // into blocks of mfma_heads; the blocks of one (item, KV head) read the same bytes and get ids 8 apart, so that
@@ -998,46 +1402,52 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FOUR_BIT ? 
   if (en.flags & kEntryNoTable) tv.table = nullptr;   // the run names pool records directly
   int chunk_tokens = a.chunk[tier];
   const bool equal_items = chunk_tokens == 0;
-  if (equal_items) chunk_tokens = even_chunk(en.len, (lo + 1 < a.n_entries ? a.e[lo + 1].item_start : a.n_items) - item_start);
+  const int n_even = equal_items ? (lo + 1 < a.n_entries ? a.e[lo + 1].item_start : a.n_items) - item_start : 0;
+  if (equal_items) chunk_tokens = even_chunk(en.len, n_even);
   const int part = en.part_base + item - item_start;   // this item's partial
   int chunk = item - item_start;
   const int32_t *sel = resolve_selected(a, tv, en, seq, equal_items, chunk_tokens, chunk);
 
   const int combo = tv.k_fmt * 8 + tv.v_fmt;
-#define TTKV_MFMA_CASE(KF, VF) process_mfma<KF, VF>(a, tv, en, sel, chunk_tokens, chunk, seq, hq0, G, hkv, s_buf, s_m, s_l)
+#define TTKV_ROWS(KF, VF) process_rows<KF, VF>(a, tv, en, sel, chunk_tokens, chunk, seq, hq0, G, hkv, wbuf)
+#define TTKV_QUANT(KF, VF) process_quant<KF, VF, HS>(a, tv, en, sel, chunk_tokens, chunk, n_even, seq, hq0, G, hkv, wbuf)
   switch (combo) {
-    case TTKV_F16 * 8 + TTKV_F16: TTKV_MFMA_CASE(TTKV_F16, TTKV_F16); break;
-    case TTKV_BF16 * 8 + TTKV_BF16: TTKV_MFMA_CASE(TTKV_BF16, TTKV_BF16); break;
-    case TTKV_I8_SYM_G32 * 8 + TTKV_I8_SYM_G32: TTKV_MFMA_CASE(TTKV_I8_SYM_G32, TTKV_I8_SYM_G32); break;
+    case TTKV_F16 * 8 + TTKV_F16: TTKV_ROWS(TTKV_F16, TTKV_F16); break;
+    case TTKV_BF16 * 8 + TTKV_BF16: TTKV_ROWS(TTKV_BF16, TTKV_BF16); break;
+    case TTKV_I8_SYM_G32 * 8 + TTKV_I8_SYM_G32:
+      if constexpr (KIND >= WITH_INT8) TTKV_QUANT(TTKV_I8_SYM_G32, TTKV_I8_SYM_G32);
+      break;
     case TTKV_I4_ASYM_T128 * 8 + TTKV_I4_ASYM_G64:
-      if constexpr (T128) TTKV_MFMA_CASE(TTKV_I4_ASYM_T128, TTKV_I4_ASYM_G64);
+      if constexpr (KIND == WITH_T128) TTKV_ROWS(TTKV_I4_ASYM_T128, TTKV_I4_ASYM_G64);
       break;
     case TTKV_I8_SYM_G32 * 8 + TTKV_I4_ASYM_G64:
-      if constexpr (FOUR_BIT) TTKV_MFMA_CASE(TTKV_I8_SYM_G32, TTKV_I4_ASYM_G64);
+      if constexpr (KIND >= WITH_4BIT) TTKV_QUANT(TTKV_I8_SYM_G32, TTKV_I4_ASYM_G64);
       break;
     case TTKV_I8_SYM_G32 * 8 + TTKV_I4_ASYM_G64_T32:
-      if constexpr (FOUR_BIT) TTKV_MFMA_CASE(TTKV_I8_SYM_G32, TTKV_I4_ASYM_G64_T32);
+      if constexpr (KIND >= WITH_4BIT) TTKV_QUANT(TTKV_I8_SYM_G32, TTKV_I4_ASYM_G64_T32);
       break;
     case TTKV_I4_ASYM_G64 * 8 + TTKV_I4_ASYM_G64_T32:
-      if constexpr (FOUR_BIT) TTKV_MFMA_CASE(TTKV_I4_ASYM_G64, TTKV_I4_ASYM_G64_T32);
+      if constexpr (KIND >= WITH_4BIT) TTKV_QUANT(TTKV_I4_ASYM_G64, TTKV_I4_ASYM_G64_T32);
       break;
     default:
-      if constexpr (FOUR_BIT) TTKV_MFMA_CASE(TTKV_I4_ASYM_G64, TTKV_I4_ASYM_G64);
+      if constexpr (KIND >= WITH_4BIT) TTKV_QUANT(TTKV_I4_ASYM_G64, TTKV_I4_ASYM_G64);
       break;
   }
-#undef TTKV_MFMA_CASE
+#undef TTKV_ROWS
+#undef TTKV_QUANT
   __syncthreads();
 
   // ---- merge the four waves (each with its own running max) and write the item's partials
   for (int idx = threadIdx.x; idx < G * 128; idx += 256) {
     const int g = idx >> 7, dch = idx & 127;
-    const float M = fmaxf(fmaxf(s_m[0][g], s_m[1][g]), fmaxf(s_m[2][g], s_m[3][g]));
+    auto wave_sums = [&](int w) { return (const float *)(s_buf + w * kTileLds + kSumsLds); };
+    const float M = fmaxf(fmaxf(wave_sums(0)[g], wave_sums(1)[g]), fmaxf(wave_sums(2)[g], wave_sums(3)[g]));
     float o = 0.0f, ll = 0.0f;
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
-      const float wgt = s_m[w][g] == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(s_m[w][g] - M);
+      const float m = wave_sums(w)[g], wgt = m == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(m - M);
       o = fmaf(((const float *)(s_buf + w * kTileLds))[g * 128 + dch], wgt, o);
-      ll = fmaf(s_l[w][g], wgt, ll);
+      ll = fmaf(wave_sums(w)[16 + g], wgt, ll);
     }
     const int64_t prow = ((int64_t)seq * a.Hq + hq0 + g) * a.part_stride + part;
     a.pacc[prow * 128 + dch] = o;
@@ -1068,18 +1478,19 @@ namespace {
 // tokens, 8 heads per KV head 129 us against 41, 16 heads 134 against 29).
 bool pairs_beside_t128(int k_fmt, int G) { return (k_fmt == TTKV_I8_SYM_G32 && G > 4) || (k_fmt == TTKV_I4_ASYM_G64 && G > 8); }
 
-// What one launch needs: heads per block, 4-bit tiers, keys grouped over tokens.  ok: the kernel takes it.
+// What one launch needs: heads per block, quantized tiers, 4-bit ones, keys grouped over tokens.  ok: the kernel takes it.
 struct MfmaShape {
   int heads;
-  bool four_bit, t128, ok;
+  bool quantized, four_bit, t128, ok;
 };
 MfmaShape mfma_shape(const FusedArgs &a) {
   const int G = a.Hq / a.Hkv;
-  MfmaShape m{std::min(16, G), false, false, true};
+  MfmaShape m{std::min(16, G), false, false, false, true};
   bool pairs = false;
   for (int j = 0; j < a.n_entries; ++j) {
     const TierView &tv = a.tv[entry_tier(a.e[j])];
     m.ok &= attn_mfma_fits(tv.k_fmt, tv.v_fmt, G);
+    m.quantized |= !is_fp(tv.k_fmt);
     m.four_bit |= attn_mfma_four_bit(tv.k_fmt, tv.v_fmt);
     m.t128 |= tv.k_fmt == TTKV_I4_ASYM_T128;
     pairs |= pairs_beside_t128(tv.k_fmt, G);
@@ -1098,9 +1509,16 @@ hipError_t launch_attn_mfma(const FusedArgs &a0, hipStream_t s) {
   const int G = a.Hq / a.Hkv;
   const uint32_t n_hb = (G + m.heads - 1) / m.heads;
   const dim3 grid(((uint32_t)a.n_items * a.Hkv + 7) / 8 * 8 * n_hb);
-  if (m.t128) hipLaunchKernelGGL((attn_mfma_kernel<true, true>), grid, dim3(256), 0, s, a);
-  else if (m.four_bit) hipLaunchKernelGGL((attn_mfma_kernel<true, false>), grid, dim3(256), 0, s, a);
-  else hipLaunchKernelGGL((attn_mfma_kernel<false, false>), grid, dim3(256), 0, s, a);
+  auto go = [&](auto hs) {
+    constexpr int HS = decltype(hs)::value;
+    if (m.t128) hipLaunchKernelGGL((attn_mfma_kernel<WITH_T128, HS>), grid, dim3(256), 0, s, a);
+    else if (m.four_bit) hipLaunchKernelGGL((attn_mfma_kernel<WITH_4BIT, HS>), grid, dim3(256), 0, s, a);
+    else hipLaunchKernelGGL((attn_mfma_kernel<WITH_INT8, HS>), grid, dim3(256), 0, s, a);
+  };
+  if (!m.quantized) hipLaunchKernelGGL((attn_mfma_kernel<FP_ONLY, 4>), grid, dim3(256), 0, s, a);
+  else if (m.heads <= 4) go(std::integral_constant<int, 4>{});
+  else if (m.heads <= 8) go(std::integral_constant<int, 8>{});
+  else go(std::integral_constant<int, 16>{});
   return hipGetLastError();
 }
 
