@@ -74,8 +74,20 @@ TierView make_view(const ttkv_tier &T, const Layout &L) {
   v.k_fmt = T.k_fmt;
   v.v_fmt = T.v_fmt;
   v.in_host = T.mem == TTKV_MEM_HOST_PINNED;
+  v.bt_magic = magic_bt(T.ring_blocks * (int64_t)T.block_tokens, L.bt);
   return v;
 }
+
+}  // namespace
+void ttkv::set_items(FusedArgs &a, int n_entries, int n_items) {
+  a.n_entries = n_entries;
+  a.n_items = n_items;
+  for (int i = n_entries; i % 16; ++i) a.start[i] = INT32_MAX;
+  for (int k = 0; k < TTKV_MAX_ENTRIES / 16; ++k) a.coarse[k] = 16 * k < n_entries ? a.start[16 * k] : INT32_MAX;
+  a.G = a.Hq / a.Hkv;
+  a.hkv_magic = a.Hkv > 1 && (int64_t)n_items * a.Hkv * a.Hkv < (1ll << 31) ? (uint32_t)(((1ll << 32) + a.Hkv - 1) / a.Hkv) : 0;
+}
+namespace {
 
 // A staging area holding `nrec` consecutive records in the tier's layout.
 TierView make_slot_view(const ttkv_tier &T, const Layout &L, void *slot, int nrec) {
@@ -84,6 +96,7 @@ TierView make_slot_view(const ttkv_tier &T, const Layout &L, void *slot, int nre
   v.table = nullptr;
   v.ring_blocks = nrec;
   v.in_host = 0;
+  v.bt_magic = magic_bt((int64_t)nrec * L.bt, L.bt);
   return v;
 }
 
@@ -1062,15 +1075,15 @@ static ttkv_status decode_impl(Handle *h, const ttkv_cache *c, const void *q, in
   for (int rep = 0; rep < reps; ++rep)
   for (size_t r0 = 0; r0 < order.size(); r0 += TTKV_MAX_ENTRIES) {
     const size_t r1 = std::min(order.size(), r0 + TTKV_MAX_ENTRIES);
-    a.n_entries = (int32_t)(r1 - r0);
     int items = 0;
     for (size_t i = r0; i < r1; ++i) {
       const Run &r = *order[i];
       a.e[i - r0] = make_entry(r.tier, r.b, r.part_base, (r.no_table ? kEntryNoTable : 0) | (r.selected ? kEntrySelected : 0),
-                               r.no_table ? r.rec_base : r.first_tok, r.len, items);
+                               r.no_table ? r.rec_base : r.first_tok, r.len);
+      a.start[i - r0] = items;
       items += r.n_chunks;
     }
-    a.n_items = items;
+    set_items(a, (int)(r1 - r0), items);
     TTKV_HIP(h, ch.attend(-1, -1, a, &nk, &nm));
   }
   if (timed) {
@@ -1094,9 +1107,9 @@ static ttkv_status decode_impl(Handle *h, const ttkv_cache *c, const void *q, in
     }
     a.tv[0] = make_slot_view(T, L, dst, f.nrec);
     a.chunk[0] = f.chunk;
-    a.n_entries = 1;
-    a.e[0] = make_entry(0, f.b, f.part_base, kEntryNoTable, 0, f.ntok, 0);
-    a.n_items = (f.ntok + f.chunk - 1) / f.chunk;
+    a.e[0] = make_entry(0, f.b, f.part_base, kEntryNoTable, 0, f.ntok);
+    a.start[0] = 0;
+    set_items(a, 1, (f.ntok + f.chunk - 1) / f.chunk);
     TTKV_HIP(h, ch.attend(issued, slot, a, &nk, &nm));
     if (copy != compute) TTKV_HIP(h, ch.record(EV_FREED + slot, 0));
     ++issued;

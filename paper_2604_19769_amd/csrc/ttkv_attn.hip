@@ -135,7 +135,7 @@ __device__ __forceinline__ void process(const FusedArgs &a, const TierView &tv, 
     constexpr bool FULL = decltype(full_tag)::value;
     int tok0 = en.first_tok + i0;
     if (tok0 >= ring_tokens) tok0 -= ring_tokens;
-    int rb = tok0 / tv.bt;
+    int rb = div_bt(tok0, tv.bt, tv.bt_magic);
     const int row0 = tok0 - rb * tv.bt;
     if (sel) rb = sel[rb] % tv.ring_blocks;
     const int64_t rec = tv.table ? (int64_t)tv.table[(int64_t)seq * tv.ring_blocks + rb] : (int64_t)en.rec_base + rb;
@@ -372,27 +372,24 @@ __global__ __launch_bounds__(256) void attn_fused_kernel(const FusedArgs a) {
   // to the 8 XCDs (id % 8), each with its own L2: the groups of one (item, KV head), which read
   // the same K/V bytes, get ids 8 apart so that they land on the same XCD at the same time and
   // the second reader is served from that L2.
-  const int Gtot = a.Hq / a.Hkv;
-  const uint32_t n_hz = Gtot / G;
+  touch_arguments(a);
+  const int Gtot = a.G;
+  const uint32_t n_hz = Gtot == G ? 1 : Gtot / G;
   const uint32_t id = blockIdx.x;
-  const uint32_t base = ((id >> 3) / n_hz) * 8 + (id & 7);
+  const uint32_t base = n_hz == 1 ? id : ((id >> 3) / n_hz) * 8 + (id & 7);
   if (base >= (uint32_t)a.n_items * a.Hkv) return;
-  const int item = base / a.Hkv;
-  const int hkv = base % a.Hkv;
-  const int hq0 = hkv * Gtot + ((id >> 3) % n_hz) * G;
+  const int item = item_of(a, base);
+  const int hkv = base - item * a.Hkv;
+  const int hq0 = hkv * Gtot + (n_hz == 1 ? 0 : (int)((id >> 3) % n_hz) * G);
 
-  int lo = 0, hi = a.n_entries - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (a.e[mid].item_start <= item) lo = mid; else hi = mid - 1;
-  }
+  const int lo = find_run(a, item);
   RunView en = run_view(a, lo);
-  const int tier = en.tier, seq = en.seq, item_start = a.e[lo].item_start;
+  const int tier = en.tier, seq = en.seq, item_start = a.start[lo];
   TierView tv = a.tv[tier];
   if (en.flags & kEntryNoTable) tv.table = nullptr;   // the run names pool records directly
   int chunk_tokens = a.chunk[tier];
   const bool equal_items = chunk_tokens == 0;
-  if (equal_items) chunk_tokens = even_chunk(en.len, (lo + 1 < a.n_entries ? a.e[lo + 1].item_start : a.n_items) - item_start);
+  if (equal_items) chunk_tokens = even_chunk(en.len, (lo + 1 < a.n_entries ? a.start[lo + 1] : a.n_items) - item_start);
   const int part = en.part_base + item - item_start;   // this item's partial
   int chunk = item - item_start;
   const int32_t *sel = resolve_selected(a, tv, en, seq, equal_items, chunk_tokens, chunk);

@@ -126,7 +126,8 @@ __device__ __forceinline__ constexpr int key_channel(int kg, int j) {
 // 1), then the weights.  At the end the wave's result takes the first 8 KiB, its sums the meta planes behind them.  (Two
 // batches in flight gained nothing: 86 against 87 us for 8 x 64K tokens of K int8 / V int4.)
 constexpr int kTileRowsLds = 8 * 1024, kMetaLds = 4 * 256, kBatchLds = kTileRowsLds + kMetaLds, kWeightsLds = 2 * 2048;
-constexpr int kTileLds = kBatchLds + kWeightsLds;
+constexpr int kOffLds = 256;   // int8 keys: the rows' offsets per channel group, [group][kg]
+constexpr int kTileLds = kBatchLds + kWeightsLds + kOffLds;
 constexpr int kSumsLds = kTileRowsLds + 512;   // 16 references, 16 sums of weights
 typedef const __attribute__((address_space(1))) void *gas_ptr;
 typedef __attribute__((address_space(3))) void *las_ptr;
@@ -161,6 +162,17 @@ __device__ __forceinline__ void lds_keys_i8(uint32_t a0, uint32_t a1, uint32_t a
                "ds_read_b64 %6, %10 offset:2048\n\tds_read_b64 %7, %11 offset:2048\n\ts_waitcnt lgkmcnt(0)"
                : "=&v"(w[0]), "=&v"(w[1]), "=&v"(w[2]), "=&v"(w[3]), "=&v"(w[4]), "=&v"(w[5]), "=&v"(w[6]), "=&v"(w[7])
                : "v"(a0), "v"(a1), "v"(a2), "v"(a3) : "memory");
+}
+// The same with off[g], the four rows' offsets of group g, from o.
+__device__ __forceinline__ void lds_keys_i8(uint32_t a0, uint32_t a1, uint32_t a2, uint32_t a3, uint32_t o, u32x2 *w, f4 *off) {
+  asm volatile("ds_read_b64 %0, %12\n\tds_read_b64 %1, %13\n\tds_read_b64 %2, %14\n\tds_read_b64 %3, %15\n\t"
+               "ds_read_b64 %4, %12 offset:2048\n\tds_read_b64 %5, %13 offset:2048\n\t"
+               "ds_read_b64 %6, %14 offset:2048\n\tds_read_b64 %7, %15 offset:2048\n\t"
+               "ds_read_b128 %8, %16\n\tds_read_b128 %9, %16 offset:64\n\tds_read_b128 %10, %16 offset:128\n\t"
+               "ds_read_b128 %11, %16 offset:192\n\ts_waitcnt lgkmcnt(0)"
+               : "=&v"(w[0]), "=&v"(w[1]), "=&v"(w[2]), "=&v"(w[3]), "=&v"(w[4]), "=&v"(w[5]), "=&v"(w[6]), "=&v"(w[7]),
+                 "=&v"(off[0]), "=&v"(off[1]), "=&v"(off[2]), "=&v"(off[3])
+               : "v"(a0), "v"(a1), "v"(a2), "v"(a3), "v"(o) : "memory");
 }
 // int4 key rows: w[2 tt + x] = the lane's 8 bytes of group x of tile tt, from ax (tiles 1 KiB apart).
 __device__ __forceinline__ void lds_keys_i4(uint32_t a0, uint32_t a1, u32x2 *w) {
@@ -251,12 +263,13 @@ __device__ __forceinline__ Place place_of(const TierView &tv, const RunView &en,
   int tok = en.first_tok + i;
   const int ring_tokens = tv.ring_blocks * tv.bt;
   if (tok >= ring_tokens) tok -= ring_tokens;
-  const int rb = tok / tv.bt;
+  const int rb = div_bt(tok, tv.bt, tv.bt_magic);
   return Place{rb, tok - rb * tv.bt};
 }
 __device__ __forceinline__ const uint8_t *head_at(const TierView &tv, const RunView &en, const int32_t *sel, int seq, int hkv, int block) {
   int rb = block;
-  if (sel) rb = ((const_i32)(uintptr_t)sel)[rb] % tv.ring_blocks;
+  // (a remainder is worked out on the vector unit; without the read all addresses behind it stay there)
+  if (sel) rb = __builtin_amdgcn_readfirstlane(((const_i32)(uintptr_t)sel)[rb] % tv.ring_blocks);
   const int64_t rec = tv.table ? (int64_t)((const_i32)(uintptr_t)tv.table)[(int64_t)seq * tv.ring_blocks + rb]
                                : (int64_t)en.rec_base + rb;
   return tv.base + rec * tv.rec_bytes + (int64_t)hkv * tv.head_bytes;
@@ -782,7 +795,7 @@ template <int KF, int VF, int HS>__device__ __forceinline__ void process_quant(c
   // The wave's batches lie step_tokens apart: block and row move on by additions, and the next batch's record is looked up
   // before it is asked for.
   const int first = c0 + wave * TT;
-  const int step_blocks = step_tokens / tv.bt, step_rows = step_tokens - step_blocks * tv.bt;
+  const int step_blocks = div_bt(step_tokens, tv.bt, tv.bt_magic), step_rows = step_tokens - step_blocks * tv.bt;
   Place at = place_of(tv, en, min(first, en.len - 1));
   const uint8_t *at_head = head_at(tv, en, sel, seq, hkv, at.block);
   auto advance = [&](int i0) {   // to the batch after i0, if there is one
@@ -930,7 +943,11 @@ template <int KF, int VF, int HS>__device__ __forceinline__ void process_quant(c
     if (!tv.in_host) issue_v(first);
   float unit = a.scale * kLog2e * (K4 ? 0x1p20f : 0x1p24f);   // a score is its product times this, in the log2 domain
   uint32_t qA[TPC][16];      // row operand of the chain's tiles
-  f4 off[NGK];               // int8: minus what the code offset 128 adds to a row's product, per channel group
+  // Int8: minus what the code offset 128 adds to a row's product, per channel group.  With two tiles' rows of queries as well
+  // (8 places) these 16 registers make the loop spill, and a reload from scratch waits for every copy in flight (28 / 4
+  // heads, 2 x 23K tokens 22.0 -> 23.3 us): there they are read from LDS with the keys; elsewhere that costs 2 %.
+  constexpr bool OFF_LDS = !K4 && HS == 8;
+  f4 off[NGK];
   float qs[K4 ? 2 : 1][NE];  // int4: a row's sum per channel group (for the zero points), in the product's units
   {
     if (a.q_fmt == TTKV_BF16) {   // bf16 -> fp16 (exact inside the fp16 normal range, clamped outside)
@@ -974,6 +991,8 @@ template <int KF, int VF, int HS>__device__ __forceinline__ void process_quant(c
         for (int e = 0; e < NE; ++e) qs[gr][e] = sum[e] * 0x1p-20f;
       } else {
         off[gr] = sum * (-128.0f * 0x1p-24f);
+        if constexpr (OFF_LDS)   // the 16 lanes of a kg store the same; as an opaque store, which waits for no copy in flight
+          lds_put<0>(lds0 + kBatchLds + kWeightsLds + 64 * gr + 16 * kg, __builtin_bit_cast(u32x4, off[gr]));
       }
     }
 #pragma unroll
@@ -1041,7 +1060,8 @@ template <int KF, int VF, int HS>__device__ __forceinline__ void process_quant(c
   uint32_t vop[NT / 2][8][VF == TTKV_I8_SYM_G32 ? 2 : 1];   // codes of channel 16 s + n, the pair's 8 tokens of this kg
   auto fetch_k = [&]() {
     const uint32_t ka = fresh(lka);
-    if constexpr (PK == 8) lds_keys_i8(ka, ka ^ 32, ka ^ 64, ka ^ 96, kw);
+    if constexpr (PK == 8 && OFF_LDS) lds_keys_i8(ka, ka ^ 32, ka ^ 64, ka ^ 96, lds0 + kBatchLds + kWeightsLds + 16 * kg, kw, off);
+    else if constexpr (PK == 8) lds_keys_i8(ka, ka ^ 32, ka ^ 64, ka ^ 96, kw);
     else lds_keys_i4(ka, ka ^ 32, kw);
     lds_meta<NC, 64 * TPC>(lma, meta);
   };
@@ -1380,29 +1400,27 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(waves_per_s
   // Linear workgroup id -> (item, KV head, block of heads).  More heads per KV head than one tile takes are cut
   // into blocks of mfma_heads; the blocks of one (item, KV head) read the same bytes and get ids 8 apart, so that
   // they run on the same XCD at the same time and the later readers are served from its L2.
-  const int Gtot = a.Hq / a.Hkv;
-  const uint32_t n_hb = (Gtot + a.mfma_heads - 1) / a.mfma_heads;
+  touch_arguments(a);
+  const int Gtot = a.G;
   const uint32_t id = blockIdx.x;
-  const uint32_t base = ((id >> 3) / n_hb) * 8 + (id & 7);
+  const bool blocks = Gtot > a.mfma_heads;                    // more than one block of heads
+  const uint32_t n_hb = blocks ? (Gtot + a.mfma_heads - 1) / a.mfma_heads : 1;
+  const uint32_t base = blocks ? ((id >> 3) / n_hb) * 8 + (id & 7) : id;
   if (base >= (uint32_t)a.n_items * a.Hkv) return;
-  const int item = base / a.Hkv;
-  const int hkv = base % a.Hkv;
-  const int hb0 = ((id >> 3) % n_hb) * a.mfma_heads;          // first head of the block within the KV head's heads
+  const int item = item_of(a, base);
+  const int hkv = base - item * a.Hkv;
+  const int hb0 = blocks ? ((id >> 3) % n_hb) * a.mfma_heads : 0;          // first head of the block within the KV head's heads
   const int hq0 = hkv * Gtot + hb0;
   const int G = min(a.mfma_heads, Gtot - hb0);                // heads in this block
 
-  int lo = 0, hi = a.n_entries - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (a.e[mid].item_start <= item) lo = mid; else hi = mid - 1;
-  }
+  const int lo = find_run(a, item);
   RunView en = run_view(a, lo);
-  const int tier = en.tier, seq = en.seq, item_start = a.e[lo].item_start;
+  const int tier = en.tier, seq = en.seq, item_start = a.start[lo];
   TierView tv = a.tv[tier];
   if (en.flags & kEntryNoTable) tv.table = nullptr;   // the run names pool records directly
   int chunk_tokens = a.chunk[tier];
   const bool equal_items = chunk_tokens == 0;
-  const int n_even = equal_items ? (lo + 1 < a.n_entries ? a.e[lo + 1].item_start : a.n_items) - item_start : 0;
+  const int n_even = equal_items ? (lo + 1 < a.n_entries ? a.start[lo + 1] : a.n_items) - item_start : 0;
   if (equal_items) chunk_tokens = even_chunk(en.len, n_even);
   const int part = en.part_base + item - item_start;   // this item's partial
   int chunk = item - item_start;

@@ -60,7 +60,18 @@ struct TierView {
   int32_t bt, ring_blocks;
   int32_t k_fmt, v_fmt;
   int32_t in_host;        // the records are pinned host memory, read over PCIe
+  uint32_t bt_magic;      // ring tokens / bt by a multiplication (div_bt); 0: by a division
 };
+// A division by the block size (a multiple of 64) for every look-up of a token costs some 25 instructions and a chain of
+// latencies: x / d = (x ceil(2^31 / d)) >> 31 exactly as long as x d < 2^31, with x = token / 64 and d = bt / 64.
+inline uint32_t magic_bt(int64_t ring_tokens, int32_t bt) {
+  const int64_t d = bt / 64;
+  return bt % 64 == 0 && d > 0 && (ring_tokens / 64 + 1) * d < (1ll << 31) ? (uint32_t)(((1ll << 31) + d - 1) / d) : 0;
+}
+__host__ __device__ inline uint32_t mul_high(uint32_t x, uint32_t y) { return (uint32_t)(((uint64_t)x * y) >> 32); }
+__host__ __device__ inline int div_bt(int tok, int bt, uint32_t magic) {
+  return magic ? (int)mul_high((uint32_t)tok >> 6 << 1, magic) : tok / bt;
+}
 
 // ---------------------------------------------------------------- the split-K plan of one attention call
 // One run of consecutive tokens of one (tier, sequence) attended by the fused
@@ -194,11 +205,10 @@ struct Entry {
   int32_t at;           // ring token index of the run's first token (multiple of 64); bit 28: its first pool record;
                         // bit 29: id of the tier's newest live block
   int32_t len;          // tokens; bit 29: the number of blocks (tier cut into fixed items) or their tokens (equal items)
-  int32_t item_start;   // first work item (chunk) of the run in this launch
 };
 constexpr uint32_t kEntryNoTable = 1u << 28, kEntrySelected = 1u << 29;
-inline Entry make_entry(int tier, int seq, int part_base, uint32_t flags, int32_t at, int32_t len, int32_t item_start) {
-  return Entry{(uint32_t)part_base | (uint32_t)seq << 20 | (uint32_t)tier << 26 | flags, at, len, item_start};
+inline Entry make_entry(int tier, int seq, int part_base, uint32_t flags, int32_t at, int32_t len) {
+  return Entry{(uint32_t)part_base | (uint32_t)seq << 20 | (uint32_t)tier << 26 | flags, at, len};
 }
 __host__ __device__ inline int entry_tier(const Entry &e) { return (e.head >> 26) & 3; }
 static_assert(TTKV_MAX_BATCH <= 64 && TTKV_MAX_TIERS <= 4, "an entry's sequence and tier fields");
@@ -207,22 +217,30 @@ static_assert(TTKV_MAX_BATCH <= 64 && TTKV_MAX_TIERS <= 4, "an entry's sequence 
 // The host plans with it and the kernels derive an item's size from the run's length and item count with it.
 __host__ __device__ inline int even_chunk(int len, int n) { return ((len + n - 1) / n + 63) / 64 * 64; }
 struct FusedArgs {
+  // what every workgroup reads first, in one line
+  int32_t n_entries, n_items;
+  int32_t Hq, Hkv;
+  int32_t G;               // query heads per KV head
+  int32_t mfma_heads;      // set by the matrix-core launcher: query heads one workgroup serves
+  uint32_t hkv_magic;      // workgroup / Hkv by a multiplication; 0: by a division
+  int32_t part_stride;
+  const void *q;
+  float *pm, *pl, *pacc;
+  // First work item (chunk) of each run in this launch, INT32_MAX behind the last one, and of every sixteenth run: an item
+  // finds its run by one or two loads of 64 bytes whatever their number (a binary search is a chain of up to seven).
+  int32_t start[TTKV_MAX_ENTRIES], coarse[TTKV_MAX_ENTRIES / 16];
+  int32_t q_fmt;
+  float scale;
+  int32_t sel_stride;
   TierView tv[TTKV_MAX_TIERS];
   int32_t chunk[TTKV_MAX_TIERS];   // tokens per item of the tier's runs; 0: every run in items of equal size (even_chunk)
   Entry e[TTKV_MAX_ENTRIES];
-  int32_t n_entries, n_items;
-  const void *q;
-  int32_t q_fmt;
-  float *pm, *pl, *pacc;
-  int32_t part_stride;
-  int32_t Hq, Hkv;
-  float scale;
-  int32_t mfma_heads;   // set by the matrix-core launcher: query heads one workgroup serves
   const int32_t *sel_ids;                    // device: block ids (Eq. 1) chosen by the top-k kernel [batch][sel_stride], for selected runs
-  int32_t sel_stride;
   int32_t sel_last_ntok[TTKV_MAX_BATCH];     // live tokens in the newest block of the selected tier, per sequence
 };
 static_assert(sizeof(FusedArgs) <= 4096, "kernel arguments are passed by value");
+static_assert(TTKV_MAX_ENTRIES % 16 == 0, "coarse");
+void set_items(FusedArgs &a, int n_entries, int n_items);   // the look-up tables behind `start`
 hipError_t launch_attn(const FusedArgs &a, hipStream_t s, int *n_kernels, int *n_mfma);
 bool attn_supported(int k_fmt, int v_fmt, int G);
 int attn_group_width(int Gtot);
