@@ -7,9 +7,10 @@
 // group converts one row at a time (8 channels per lane).  Block and record look-ups, and the division by the block
 // size, happen once per unit on the scalar unit; source and destination formats are compile-time inside the unit;
 // all of a unit's loads are in flight before the first conversion.  Where keys also feed block summaries a unit is a
-// whole destination block (see sum_unit).  Bound: memory for the plain copies (5.3 TB/s of read + write), fp16 -> int8
-// (5.2) and fp16 -> int4 (4.8; a copy of 2 GiB reaches 4.9), vector instructions where a second recipe comes first
-// (int4 through int8 with key sums, 2.7).  The one generic body before -- a 64-bit address and a division by the block
+// whole destination block (see sum_rows).  Bound: memory for the plain copies (5.3 TB/s of read + write), fp16 -> int8
+// (5.2) and fp16 -> int4 (4.8; a copy of 2 GiB reaches 4.9); a second recipe in front (int4 through int8) issues 139
+// vector instructions per four rows, as long as their bytes take: 88 us for 430 MB (4.9 TB/s; 103 with 176 instructions),
+// with key sums about 100 (153).  The one generic body before -- a 64-bit address and a division by the block
 // size per row, a near-tie branch per element, exchanges through LDS -- reached 3.0 for int4: tiering 2 x 32 heads x
 // 8192 tokens into fp16 + int4 105.6 -> 77.4 us; 8 heads x 32768 tokens into fp16 + K int8 / V int4 channel-major, one
 // launch instead of two, 60 -> 43.5 us.
@@ -24,8 +25,8 @@ namespace ttkv {
 namespace {
 
 constexpr int CHUNK = 64;             // rows of a unit; block sizes are multiples of it
-constexpr int SUM_THREADS = 512;      // workgroup of the launches that also keep key sums,
-constexpr int SUM_ROWS = 32;          // and the rows it converts between two barriers
+constexpr int SUM_THREADS = 512;      // workgroup of small launches that also keep key sums (256 threads in large ones);
+                                      // between two barriers it converts a row per 16 threads
 constexpr int NO_STORE = -1;          // destination "format" of a unit that only feeds the key sums
 
 __device__ __forceinline__ float h2f(uint16_t h) { return __half2float(__ushort_as_half(h)); }
@@ -83,8 +84,36 @@ __device__ __forceinline__ uint32_t lanes_max(uint32_t v) {
   return max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xf, 0xf, true));
 }
 
+// Nearly every group is ordinary: no NaN, a scale that is a normal fp16 number, and (Q2) a zero point within 3/8 of a
+// scale of the minimum.  Its quotients then round to codes inside the range by themselves (d / s is at most
+// 127 (1 + 2^-10), 15 (1 + 2^-10) + 3/8), so clamps, fixups and the treatment of scales of zero drop out; a wave with any
+// other group takes the general recipe.  The quotient of an ordinary group costs two steps, q = y r + RN(y r'), where
+// r' = RN((1 - s r) r) is what r lacks: off by 2^-46 before its one rounding, and a 24-bit y over an 11-bit s lies at
+// least 2^-12 ulp from any midpoint, so this is the correctly rounded quotient as well.
+__device__ __forceinline__ bool normal_half(float s) { return s >= 6.103515625e-05f && s <= 65504.0f; }   // false for NaN
+__device__ __forceinline__ bool every_lane(bool ok) { return __builtin_amdgcn_ballot_w64(!ok) == 0; }
+__device__ __forceinline__ float reciprocal(float s) {   // RN(1 / s) of a normal fp16 number
+  const float r0 = __builtin_amdgcn_rcpf(s);
+  return __builtin_fmaf(__builtin_fmaf(-s, r0, 1.0f), r0, r0);
+}
+template <int D>
+__device__ __forceinline__ float div_const_finite(float d) {
+  constexpr float c = 1.0f / (float)D;
+  const float y = d * c;
+  float q = __builtin_fmaf(__builtin_fmaf(-(float)D, y, d), c, y);
+  asm("" : "+v"(q));   // rounded to fp32 before it is rounded to fp16, not in one mixed instruction
+  return q;
+}
+// Largest magnitude, smallest value: NaN if any of the eight is one.
+__device__ __forceinline__ float max_abs(const float (&x)[8]) {
+  float m = __builtin_elementwise_maximum(fabsf(x[0]), fabsf(x[1]));
+#pragma unroll
+  for (int i = 2; i < 8; ++i) m = __builtin_elementwise_maximum(m, fabsf(x[i]));
+  return m;
+}
+
 // Q1: n[i] = 1.5 x 2^23 + code as a float; the group is 4 lanes.  Returns the fp16 scale bits.
-__device__ __forceinline__ uint16_t q1_codes(const float (&x)[8], float (&n)[8], float *s_out) {
+__device__ __forceinline__ uint16_t q1_general(const float (&x)[8], float (&n)[8], float *s_out) {
   float amax = 0.0f;   // a group's NaNs do not count
 #pragma unroll
   for (int i = 0; i < 8; ++i) amax = fmaxf(amax, fabsf(x[i]));
@@ -99,14 +128,32 @@ __device__ __forceinline__ uint16_t q1_codes(const float (&x)[8], float (&n)[8],
   *s_out = s;
   return sh;
 }
-
-__device__ __forceinline__ void q2_range(const float (&x)[8], float *lo_out, float *hi_out) {
-  float lo = x[0], hi = x[0];
+// HALF: the values have at most 11 significant bits (fp16, bf16).  Quotients of two such numbers are half-integers or
+// at least 2^-12 away from one, so y r (off by 2^-17) rounded to multiples of 2^-13 by adding 1536 decides every code and
+// keeps every tie, and the second addition rounds to even: two steps per code.
+template <bool HALF>
+__device__ __forceinline__ uint16_t q1_codes(const float (&x)[8], float (&n)[8], float *s_out) {
+  uint32_t bits = __float_as_uint(max_abs(x));   // NaN lies above infinity and passes to the whole group
+  bits = lanes_max<0xB1>(bits);
+  bits = lanes_max<0x4E>(bits);
+  const uint16_t sh = f2h(div_const_finite<127>(__uint_as_float(bits)));
+  const float s = h2f(sh);
+  if (__builtin_expect(!every_lane(normal_half(s)), 0)) return q1_general(x, n, s_out);
+  const float r = reciprocal(s);
+  if constexpr (HALF) {
 #pragma unroll
-  for (int i = 1; i < 8; ++i) {
-    lo = fminf(lo, x[i]);
-    hi = fmaxf(hi, x[i]);
+    for (int i = 0; i < 8; ++i) n[i] = __builtin_fmaf(x[i], r, 1536.0f) + (kMagic - 1536.0f);
+  } else {
+    const float rest = __builtin_fmaf(-s, r, 1.0f) * r;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) n[i] = __builtin_fmaf(x[i], r, x[i] * rest) + kMagic;
   }
+  *s_out = s;
+  return sh;
+}
+
+__device__ __forceinline__ void q2_range(float *lo_out, float *hi_out) {
+  float lo = *lo_out, hi = *hi_out;
   // over the group's eight lanes; as one block because the compiler would quiet every exchanged value first (18
   // instructions instead of 6).  A lane exchange reads a register two issue slots after it is written at the earliest.
   asm("s_nop 1\n\t"
@@ -128,14 +175,39 @@ struct Q2Scale {
   uint32_t word;   // fp16 {scale, zero} as stored
   float s, z;
 };
-__device__ __forceinline__ Q2Scale q2_codes(const float (&x)[8], float (&n)[8]) {
-  float lo, hi;
-  q2_range(x, &lo, &hi);
+__device__ __forceinline__ Q2Scale q2_general(const float (&x)[8], float (&n)[8]) {
+  float lo = x[0], hi = x[0];
+#pragma unroll
+  for (int i = 1; i < 8; ++i) {
+    lo = fminf(lo, x[i]);
+    hi = fmaxf(hi, x[i]);
+  }
+  q2_range(&lo, &hi);
   const uint16_t sh = f2h(div_const<15>(hi - lo)), zh = f2h(lo);
   const float s = h2f(sh), z = h2f(zh);
   const Divisor d(s);
 #pragma unroll
   for (int i = 0; i < 8; ++i) n[i] = d.code(x[i] - zero_of(z), 0.0f, 15.0f);
+  return Q2Scale{(uint32_t)sh | ((uint32_t)zh << 16), s, z};
+}
+__device__ __forceinline__ Q2Scale q2_codes(const float (&x)[8], float (&n)[8]) {
+  float lo = x[0], hi = x[0];   // NaN if one of the eight is
+#pragma unroll
+  for (int i = 1; i < 8; ++i) {
+    lo = __builtin_elementwise_minimum(lo, x[i]);
+    hi = __builtin_elementwise_maximum(hi, x[i]);
+  }
+  const float own = lo;
+  q2_range(&lo, &hi);
+  const uint16_t sh = f2h(div_const_finite<15>(hi - lo)), zh = f2h(lo);
+  const float s = h2f(sh), z = h2f(zh);
+  if (__builtin_expect(!every_lane(normal_half(s) && fabsf(own - own) == 0.0f && fabsf(lo - z) <= 0.375f * s), 0)) return q2_general(x, n);
+  const float r = reciprocal(s), rest = __builtin_fmaf(-s, r, 1.0f) * r;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const float y = x[i] - z;
+    n[i] = __builtin_fmaf(y, r, y * rest) + kMagic;
+  }
   return Q2Scale{(uint32_t)sh | ((uint32_t)zh << 16), s, z};
 }
 
@@ -157,9 +229,10 @@ __device__ __forceinline__ uint32_t pack_nibbles(const float (&n)[8]) {
 
 // The values a format decompresses to (a token that passed through a tier).  code x scale is exact in fp32 (at most
 // 7 + 11 bits), so the offset of the codes leaves in the same fused step.
+template <bool HALF>
 __device__ __forceinline__ void roundtrip_q1(float (&x)[8]) {
   float n[8], s;
-  q1_codes(x, n, &s);
+  q1_codes<HALF>(x, n, &s);
   const float off = -kMagic * s;
 #pragma unroll
   for (int i = 0; i < 8; ++i) x[i] = __builtin_fmaf(n[i], s, off);
@@ -323,16 +396,17 @@ __device__ __forceinline__ void load_from(const RowSource &s, int i, int l16, Ra
 }
 // The formats a token has passed through before this one (Sec. 4.2's recipes, applied and taken back): at most two,
 // the fp formats change nothing.  Written out because a loop over them would copy the eight values in every turn.
+template <int SRC>
 __device__ __forceinline__ void pass_through(const Source &c, float (&x)[8]) {
   static_assert(TTKV_MAX_TIERS == 4, "tiers 1 and 2 lie above the last one");
   if (c.n_via > 0) {
     const uint32_t f = c.via & 0xff;
-    if (f == TTKV_I8_SYM_G32) roundtrip_q1(x);
+    if (f == TTKV_I8_SYM_G32) roundtrip_q1<SRC == TTKV_F16 || SRC == TTKV_BF16>(x);
     if (f == TTKV_I4_ASYM_G64) roundtrip_q2(x);
   }
   if (c.n_via > 1) {
     const uint32_t f = c.via >> 8;
-    if (f == TTKV_I8_SYM_G32) roundtrip_q1(x);
+    if (f == TTKV_I8_SYM_G32) roundtrip_q1<false>(x);
     if (f == TTKV_I4_ASYM_G64) roundtrip_q2(x);
   }
 }
@@ -393,7 +467,7 @@ __device__ __forceinline__ void put_row(const U &u, int i, int l16, const float 
     if (live) st_row<U::STREAM>(code + row * 256 + l16 * 16, uint4{w[0], w[1], w[2], w[3]});
   } else if constexpr (DST == TTKV_I8_SYM_G32) {
     float s;
-    const uint16_t sh = q1_codes(x, n, &s);
+    const uint16_t sh = q1_codes<false>(x, n, &s);
     const bool zero = s == 0.0f;
     const uint2 w = {zero ? 0u : pack_bytes(n), zero ? 0u : pack_bytes(n + 4)};
     if (live) {
@@ -432,7 +506,7 @@ __device__ __forceinline__ void convert_unit(const Source &c, const U &u, const 
     }
     float x[8];
     expand<SRC>(raw[p], x);
-    pass_through(c, x);
+    pass_through<SRC>(c, x);
     if constexpr (SUM) keep_values(s_x, i, l16, x);
     put_row<DST>(u, i, l16, x, s_t32);
   }
@@ -488,55 +562,50 @@ __device__ __forceinline__ void store_t32(const U &u, uint32_t *s_t32) {
 }
 
 // Keys of one destination block, converted like any other unit and summed per channel in token order (fp32) for the
-// block's mean key: a block that was partly filled before continues from its stored sum.  The arriving values of 32
-// rows go to LDS, where the two waves whose turn it is add them up (one channel per lane) while the other waves
-// convert the next 32 rows; the running sums pass from turn to turn through LDS.  The order of the additions is the
+// block's mean key: a block that was partly filled before continues from its stored sum.  The arriving values of 16 rows
+// (32 with 512 threads) go to LDS, where the two waves whose turn it is add them up (one channel per lane) while the other
+// waves convert the next rows; the running sums pass from turn to turn through LDS.  The order of the additions is the
 // token order, so the sums are reproducible bit for bit; what made the former kernel (one thread per channel,
 // reading and re-quantizing one row after the other from memory) 331 us of the 572 us tiering of 4 x 32768 tokens
 // was the chain of loads, not the additions.
-template <int THREADS, typename U>
-__device__ __forceinline__ void sum_unit(const Source &src, U u, int src_fmt, int dst_fmt, int rows_lo, int rows_hi, float *k_sum,
-                                         uint16_t *k_summary, float inv_bt, char *s_buf) {
-  // k_sum, k_summary: the block's; rows [rows_lo, rows_hi) of the block arrive, row rows_lo is token u.t_lo
-  float (*s_x)[SUM_ROWS][128] = (float (*)[SUM_ROWS][128])s_buf;            // two buffers
-  float *s_sum = (float *)(s_buf + 2 * SUM_ROWS * 128 * sizeof(float));
+// One loop per pair of formats: with the formats looked up in every turn, the waves whose turn it was waited for their next
+// rows before they began to add (tiering 4 x 32768 tokens three deep 180 us, now 162) and the kernel took 74 registers
+// instead of 56.
+template <int SRC, int DST, int THREADS, typename U>
+__device__ __forceinline__ void sum_rows(const Source &src, U u, int rows_lo, int rows_hi, float *k_sum, uint16_t *k_summary,
+                                         float inv_bt, char *s_buf) {
+  constexpr int ROWS = THREADS / 16;
+  float (*s_x)[ROWS][128] = (float (*)[ROWS][128])s_buf;            // two buffers
+  float *s_sum = (float *)(s_buf + 2 * ROWS * 128 * sizeof(float));
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int t0 = u.t_lo;
   auto place = [&](int row0) {
     u.row0 = row0;
     u.lo = max(rows_lo - row0, 0);
-    u.hi = min(rows_hi - row0, SUM_ROWS);
+    u.hi = min(rows_hi - row0, ROWS);
     u.t_lo = t0 + row0 + u.lo - rows_lo;
   };
-  Raw raw[SUM_ROWS * 16 / THREADS];
-#define TTKV_LOAD_UNIT(S, D) load_unit<S, THREADS, SUM_ROWS>(src, u, raw)
-  place(rows_lo / SUM_ROWS * SUM_ROWS);
-  TTKV_FOR_SOURCES(0, TTKV_LOAD_UNIT)
+  Raw raw[1];
+  place(rows_lo / ROWS * ROWS);
+  load_unit<SRC, THREADS, ROWS>(src, u, raw);
+  if (threadIdx.x < 128) s_sum[threadIdx.x] = rows_lo ? k_sum[threadIdx.x] : 0.0f;   // the threads that add first
   for (int c = 0;; ++c) {
-#define TTKV_SUM_UNIT(S, D) convert_unit<S, D, THREADS, SUM_ROWS, true>(src, u, raw, s_x[c & 1], nullptr)
-    switch (dst_fmt) {
-      case TTKV_F16: TTKV_SUM_UNIT(TTKV_F16, TTKV_F16); break;
-      case TTKV_BF16: TTKV_SUM_UNIT(TTKV_BF16, TTKV_BF16); break;
-      case TTKV_I8_SYM_G32: TTKV_FOR_SOURCES(TTKV_I8_SYM_G32, TTKV_SUM_UNIT) break;
-      case TTKV_I4_ASYM_G64: TTKV_FOR_SOURCES(TTKV_I4_ASYM_G64, TTKV_SUM_UNIT) break;
-      default: TTKV_FOR_SOURCES(NO_STORE, TTKV_SUM_UNIT) break;
-    }
-#undef TTKV_SUM_UNIT
-    const int lo = u.lo, hi = u.hi, next = u.row0 + SUM_ROWS;
+    convert_unit<SRC, DST, THREADS, ROWS, true>(src, u, raw, s_x[c & 1], nullptr);
+    const int lo = u.lo, hi = u.hi, next = u.row0 + ROWS;
     const bool more = next < rows_hi;
     if (more) {
       place(next);
-      TTKV_FOR_SOURCES(0, TTKV_LOAD_UNIT)
+      load_unit<SRC, THREADS, ROWS>(src, u, raw);
     }
     __syncthreads();
     const int turn = wave - 2 * (c % (THREADS / 128));
     if (turn == 0 || turn == 1) {
       const int ch = turn * 64 + lane;
-      float sum = c ? s_sum[ch] : rows_lo ? k_sum[ch] : 0.0f;
+      float sum = s_sum[ch];
       const float *x = &s_x[c & 1][0][ch];
-      if (lo == 0 && hi == SUM_ROWS) {
+      if (lo == 0 && hi == ROWS) {
 #pragma unroll 16
-        for (int r = 0; r < SUM_ROWS; ++r) sum = sum + x[r * 128];
+        for (int r = 0; r < ROWS; ++r) sum = sum + x[r * 128];
       } else {
         for (int r = lo; r < hi; ++r) sum = sum + x[r * 128];
       }
@@ -549,15 +618,27 @@ __device__ __forceinline__ void sum_unit(const Source &src, U u, int src_fmt, in
     }
     if (!more) break;
   }
-#undef TTKV_LOAD_UNIT
+}
+template <int THREADS, typename U>
+__device__ __forceinline__ void sum_unit(const Source &src, const U &u, int src_fmt, int dst_fmt, int rows_lo, int rows_hi, float *k_sum,
+                                         uint16_t *k_summary, float inv_bt, char *s_buf) {
+  // k_sum, k_summary: the block's; rows [rows_lo, rows_hi) of the block arrive, row rows_lo is token u.t_lo
+#define TTKV_SUM_ROWS(S, D) sum_rows<S, D, THREADS>(src, u, rows_lo, rows_hi, k_sum, k_summary, inv_bt, s_buf)
+  switch (dst_fmt) {
+    case TTKV_F16: TTKV_SUM_ROWS(TTKV_F16, TTKV_F16); break;
+    case TTKV_BF16: TTKV_SUM_ROWS(TTKV_BF16, TTKV_BF16); break;
+    case TTKV_I8_SYM_G32: TTKV_FOR_SOURCES(TTKV_I8_SYM_G32, TTKV_SUM_ROWS) break;
+    case TTKV_I4_ASYM_G64: TTKV_FOR_SOURCES(TTKV_I4_ASYM_G64, TTKV_SUM_ROWS) break;
+    default: TTKV_FOR_SOURCES(NO_STORE, TTKV_SUM_ROWS) break;
+  }
+#undef TTKV_SUM_ROWS
 }
 
 // Grid: x = K units then V units of one (entry, KV head), y = entry x KV head.  SUM: K units are whole destination
 // blocks and keep the key sums (dst_fmt of K may be NO_STORE: sums only); otherwise every unit is 64 rows.
-template <bool SUM, bool STREAM>
-__global__ __launch_bounds__(SUM ? SUM_THREADS : 256, SUM ? 6 : 8) void convert_rows_kernel(const ConvArgs a, int k_units, int k_dst_fmt) {
-  constexpr int THREADS = SUM ? SUM_THREADS : 256;
-  constexpr int SUM_BYTES = 2 * SUM_ROWS * 128 * 4 + 512;
+template <bool SUM, bool STREAM, int THREADS>
+__global__ __launch_bounds__(THREADS, THREADS == 256 ? 8 : 6) void convert_rows_kernel(const ConvArgs a, int k_units, int k_dst_fmt) {
+  constexpr int SUM_BYTES = 2 * (THREADS / 16) * 128 * 4 + 512;
   __shared__ __align__(16) char s_buf[SUM ? (SUM_BYTES > kT32Bytes ? SUM_BYTES : kT32Bytes) : kT32Bytes];
   const int j = blockIdx.y / a.Hkv, h = blockIdx.y - j * a.Hkv, seq = a.seq_id[j];
   const int which = (int)blockIdx.x >= k_units;
@@ -636,7 +717,7 @@ __device__ __forceinline__ void keys_t128(const Source &src, int g, uint8_t *hea
 #pragma unroll
     for (int p = 0; p < 8; ++p) {
       expand<SRC>(raw[p], x[p]);
-      pass_through(src, x[p]);
+      pass_through<SRC>(src, x[p]);
     }
   }
 #pragma unroll
@@ -714,11 +795,18 @@ hipError_t launch(const ConvArgs &a, hipStream_t s, int *n_kernels) {
     ++*n_kernels;
   }
   if (a.k_sum) {
-    hipLaunchKernelGGL((convert_rows_kernel<true, STREAM>), dim3(blocks + chunks, y), dim3(SUM_THREADS), 0, s, a, blocks,
-                       t128 ? NO_STORE : a.dst.k_fmt);
+    const int k_dst = t128 ? NO_STORE : a.dst.k_fmt;
+    // A block's keys are one workgroup's work from end to end.  With four blocks per CU and more, eight small workgroups
+    // per CU keep it busy across each other's barriers (2560 blocks of 256 tokens: step 166 us, 187 with 512 threads); with
+    // fewer the time is that of one block, which more threads shorten (640 blocks 59.5 and 56.8 us; evictions of 128 rows:
+    // 256 blocks 22.2 and 18.5, 384 27.0 and 25.3, 512 29.7 and 30.3).
+    if ((int64_t)blocks * y >= 1024)
+      hipLaunchKernelGGL((convert_rows_kernel<true, STREAM, 256>), dim3(blocks + chunks, y), dim3(256), 0, s, a, blocks, k_dst);
+    else
+      hipLaunchKernelGGL((convert_rows_kernel<true, STREAM, SUM_THREADS>), dim3(blocks + chunks, y), dim3(SUM_THREADS), 0, s, a, blocks, k_dst);
   } else {
     const int k_units = t128 ? 0 : chunks;
-    hipLaunchKernelGGL((convert_rows_kernel<false, STREAM>), dim3(k_units + chunks, y), dim3(256), 0, s, a, k_units, a.dst.k_fmt);
+    hipLaunchKernelGGL((convert_rows_kernel<false, STREAM, 256>), dim3(k_units + chunks, y), dim3(256), 0, s, a, k_units, a.dst.k_fmt);
   }
   ++*n_kernels;
   return hipGetLastError();
