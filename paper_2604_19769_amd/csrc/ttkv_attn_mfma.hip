@@ -126,8 +126,13 @@ __device__ __forceinline__ constexpr int key_channel(int kg, int j) {
 // 1), then the weights.  At the end the wave's result takes the first 8 KiB, its sums the meta planes behind them.  (Two
 // batches in flight gained nothing: 86 against 87 us for 8 x 64K tokens of K int8 / V int4.)
 constexpr int kTileRowsLds = 8 * 1024, kMetaLds = 4 * 256, kBatchLds = kTileRowsLds + kMetaLds, kWeightsLds = 2 * 2048;
-constexpr int kOffLds = 256;   // int8 keys: the rows' offsets per channel group, [group][kg]
-constexpr int kTileLds = kBatchLds + kWeightsLds + kOffLds;
+constexpr int kTileLds = kBatchLds + kWeightsLds;
+// Behind the four waves' places, int8 keys: the rows' offsets per channel group, [group][kg].  All waves of a workgroup have
+// the same queries and store the same numbers.  (A copy per wave would make three workgroups 40 bytes larger than a CU's
+// LDS: it is given out in units of 1280 bytes, and 54272 become 55040.  With two resident, 16 sequences of 2664 fp16 + 8704
+// int8 tokens, 32 / 8 heads, take 85.4 us instead of 79.)
+constexpr int kOffLds = 256;
+constexpr int lds_given(int bytes) { return (bytes + 1279) / 1280 * 1280; }
 constexpr int kSumsLds = kTileRowsLds + 512;   // 16 references, 16 sums of weights
 typedef const __attribute__((address_space(1))) void *gas_ptr;
 typedef __attribute__((address_space(3))) void *las_ptr;
@@ -947,6 +952,7 @@ template <int KF, int VF, int HS>__device__ __forceinline__ void process_quant(c
   // (8 places) these 16 registers make the loop spill, and a reload from scratch waits for every copy in flight (28 / 4
   // heads, 2 x 23K tokens 22.0 -> 23.3 us): there they are read from LDS with the keys; elsewhere that costs 2 %.
   constexpr bool OFF_LDS = !K4 && HS == 8;
+  const uint32_t lds_off = lds0 + (4 - wave) * kTileLds;
   f4 off[NGK];
   float qs[K4 ? 2 : 1][NE];  // int4: a row's sum per channel group (for the zero points), in the product's units
   {
@@ -992,7 +998,7 @@ template <int KF, int VF, int HS>__device__ __forceinline__ void process_quant(c
       } else {
         off[gr] = sum * (-128.0f * 0x1p-24f);
         if constexpr (OFF_LDS)   // the 16 lanes of a kg store the same; as an opaque store, which waits for no copy in flight
-          lds_put<0>(lds0 + kBatchLds + kWeightsLds + 64 * gr + 16 * kg, __builtin_bit_cast(u32x4, off[gr]));
+          lds_put<0>(lds_off + 64 * gr + 16 * kg, __builtin_bit_cast(u32x4, off[gr]));
       }
     }
 #pragma unroll
@@ -1060,7 +1066,7 @@ template <int KF, int VF, int HS>__device__ __forceinline__ void process_quant(c
   uint32_t vop[NT / 2][8][VF == TTKV_I8_SYM_G32 ? 2 : 1];   // codes of channel 16 s + n, the pair's 8 tokens of this kg
   auto fetch_k = [&]() {
     const uint32_t ka = fresh(lka);
-    if constexpr (PK == 8 && OFF_LDS) lds_keys_i8(ka, ka ^ 32, ka ^ 64, ka ^ 96, lds0 + kBatchLds + kWeightsLds + 16 * kg, kw, off);
+    if constexpr (PK == 8 && OFF_LDS) lds_keys_i8(ka, ka ^ 32, ka ^ 64, ka ^ 96, lds_off + 16 * kg, kw, off);
     else if constexpr (PK == 8) lds_keys_i8(ka, ka ^ 32, ka ^ 64, ka ^ 96, kw);
     else lds_keys_i4(ka, ka ^ 32, kw);
     lds_meta<NC, 64 * TPC>(lma, meta);
@@ -1393,8 +1399,8 @@ enum LaunchKind { FP_ONLY, WITH_INT8, WITH_4BIT, WITH_T128 };
 constexpr int waves_per_simd(int kind, int hs) { return kind == FP_ONLY || (kind == WITH_INT8 && hs <= 8) ? 3 : 2; }
 template <int KIND, int HS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(waves_per_simd(KIND, HS), waves_per_simd(KIND, HS)))) void attn_mfma_kernel(const FusedArgs a) {
-  static_assert(kTileRowsLds >= 16 * 128 * 4 && 3 * 4 * kTileLds <= 160 * 1024, "the wave's result; three workgroups per CU");
-  __shared__ __attribute__((aligned(256))) char s_buf[4 * kTileLds];   // per wave: batches in flight, then [head][channel] floats
+  static_assert(kTileRowsLds >= 16 * 128 * 4 && 3 * lds_given(4 * kTileLds + kOffLds) <= 160 * 1024, "the wave's result; three workgroups per CU");
+  __shared__ __attribute__((aligned(256))) char s_buf[4 * kTileLds + kOffLds];   // per wave: batches in flight, then [head][channel] floats
   char *const wbuf = s_buf + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * kTileLds;
 
   // Linear workgroup id -> (item, KV head, block of heads).  More heads per KV head than one tile takes are cut
