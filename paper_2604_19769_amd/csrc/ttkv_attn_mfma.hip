@@ -1056,7 +1056,8 @@ template <int KF, int VF, int HS>__device__ __forceinline__ void process_quant(c
   uint32_t s_top = 0;
   int wexp = 0;
   float limit = -INFINITY;         // of the exponents; the first batch always exceeds it
-  // A reference beyond 4 million has no bits left for the power of two: weights of such a head carry none.  Product and
+  // A reference beyond 4 million has no bits left for the power of two: weights of such a head carry none, and no headroom
+  // either (32 times a value scale of 8736, as int4 values that span fp16's range have, is beyond fp16).  Product and
   // difference are rounded one after the other: factor - mcs, the reference of the item's result, is then exact.
   uint32_t plain = 0;              // bit e: the weights of element e's head carry no power of two
 
@@ -1196,7 +1197,7 @@ template <int KF, int VF, int HS>__device__ __forceinline__ void process_quant(c
         const float f = none ? 0.0f : (float)wexp;
         plain |= none ? 1u << e : 0u;
         mcs[e] = f - r;
-        limit = fminf(limit, f + (float)kHeadroom);
+        limit = fminf(limit, none ? 0.0f : f + (float)kHeadroom);
         alpha[e] = __builtin_amdgcn_exp2f(mcs[e] - old);
         l[e] *= alpha[e];
         if constexpr (V4) {
