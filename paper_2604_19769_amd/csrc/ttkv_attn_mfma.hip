@@ -726,7 +726,9 @@ __device__ __forceinline__ void lds_meta(uint32_t a0, u32x2 *w) {
 // lowest bits loses what its leading zeros take: in the sums over thousands of values that showed (2e-4 of the result at
 // 64K tokens, biased), so int4 values sit four bits up: (n0, n4) (n1, n5) (n2, n6) (n3, n7) as 16 code x 2^-24.  Keys,
 // summed over 64 channels, save two operations: registers 0 and 2 hold code x 2^-24, and the factor 16 sits on the queries
-// (a score's error stays below 2e-6 of its terms).  Four int8 codes: (code + 128) x 2^-24.
+// (a score's error stays below 2e-6 of its terms).  Where 16 q would leave fp16's range they are taken like values, by a loop
+// of its own: no factor on the queries then, whose smaller heads would lose bits by one below 1.  Four int8 codes:
+// (code + 128) x 2^-24.
 constexpr uint32_t kCodeMask = 0x000F000Fu, kCodeFlip = 0x80808080u;
 struct CodeMasks {
   uint32_t lo, hi, flip;   // in registers: a literal would be fetched with every instruction
@@ -955,6 +957,7 @@ template <int KF, int VF, int HS>__device__ __forceinline__ void process_quant(c
   const uint32_t lds_off = lds0 + (4 - wave) * kTileLds;
   f4 off[NGK];
   float qs[K4 ? 2 : 1][NE];  // int4: a row's sum per channel group (for the zero points), in the product's units
+  bool big = false;          // int4: some |q| of the workgroup's heads is 4095 or more
   {
     if (a.q_fmt == TTKV_BF16) {   // bf16 -> fp16 (exact inside the fp16 normal range, clamped outside)
 #pragma unroll
@@ -968,19 +971,18 @@ template <int KF, int VF, int HS>__device__ __forceinline__ void process_quant(c
 #pragma unroll
     for (int i = 0; i < 16; ++i) qw[i] = row_on ? qw[i] : 0u;
     if constexpr (K4) {
-      // 16 q on the even registers; where that would leave fp16's range (|q| >= 4095 somewhere) all a sixteenth of it
+      // 16 q on the even registers, unless that leaves fp16's range
       uint32_t top = 0;
 #pragma unroll
       for (int i = 0; i < 16; ++i) top = halves_max(top, qw[i] & 0x7fff7fffu);
-      const bool big = __any((top & 0xffffu) > 0x6bffu || (top >> 16) > 0x6bffu);
-      const _Float16 fe = big ? (_Float16)1.0f : (_Float16)16.0f, fo = big ? (_Float16)0.0625f : (_Float16)1.0f;
-      if (big) unit *= 16.0f;
+      big = __any((top & 0xffffu) > 0x6bffu || (top >> 16) > 0x6bffu);
+      const _Float16 fe = big ? (_Float16)1.0f : (_Float16)16.0f;
       uint32_t t[16];
 #pragma unroll
       for (int r = 0; r < 16; ++r) {   // register r = 4 d + e: elements (8 d + e, 8 d + e + 4) of the slice
         const int dd = r / 4, e = r % 4;
-        t[r] = pk_scale(__builtin_amdgcn_perm(qw[4 * dd + 2 + e / 2], qw[4 * dd + e / 2], (e & 1) ? 0x07060302u : 0x05040100u),
-                        (r & 1) ? fo : fe);
+        t[r] = __builtin_amdgcn_perm(qw[4 * dd + 2 + e / 2], qw[4 * dd + e / 2], (e & 1) ? 0x07060302u : 0x05040100u);
+        if (r % 2 == 0) t[r] = pk_scale(t[r], fe);
       }
 #pragma unroll
       for (int r = 0; r < 16; ++r) qw[r] = t[r];
@@ -988,7 +990,7 @@ template <int KF, int VF, int HS>__device__ __forceinline__ void process_quant(c
     // the rows' sums per channel group, by a product with ones: in every lane those of its own rows
 #pragma unroll
     for (int gr = 0; gr < NGK; ++gr) {
-      const uint32_t ev = K4 ? 0x2C002C00u : 0x3C003C00u, one4[4] = {ev, 0x3C003C00u, ev, 0x3C003C00u};   // int4: 1/16 for 16 q
+      const uint32_t ev = K4 && !big ? 0x2C002C00u : 0x3C003C00u, one4[4] = {ev, 0x3C003C00u, ev, 0x3C003C00u};   // 1/16 for 16 q
       f4 sum = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
       for (int s = gr * (4 / NGK); s < (gr + 1) * (4 / NGK); ++s) sum = mma32<false>(qw + 4 * s, one4, sum);
@@ -1107,7 +1109,7 @@ template <int KF, int VF, int HS>__device__ __forceinline__ void process_quant(c
   };
 
   // before_v runs between the softmax and the first use of the batch's V half.
-  auto compute = [&](int nv, auto before_v) __attribute__((always_inline)) {
+  auto compute = [&](int nv, auto big_tag, auto before_v) __attribute__((always_inline)) {
     // ---- scores: element e of chain j is head (kg % KPT) NE + e of token 16 TPC j + my_tok
     float x[NC][NE];
     uint32_t top = 0;   // the largest value scale of the lane's tokens
@@ -1123,8 +1125,12 @@ template <int KF, int VF, int HS>__device__ __forceinline__ void process_quant(c
           const u32x2 w = kw[(j * TPC + u) * NGK + gr];   // the lane's 8 bytes of the group
           if constexpr (K4) {
             uint32_t kr[8];
-            key_codes4(w.x, kr, codes);
-            key_codes4(w.y, kr + 4, codes);
+            auto take = [&](uint32_t x, uint32_t *r) {
+              if constexpr (decltype(big_tag)::value) value_codes4(x, r, codes);
+              else key_codes4(x, r, codes);
+            };
+            take(w.x, kr);
+            take(w.y, kr + 4);
             sv = mma32<false>(qA[u] + 8 * gr, kr, sv);
             sv = mma32<false>(qA[u] + 8 * gr + 4, kr + 4, sv);
           } else {
@@ -1337,18 +1343,25 @@ template <int KF, int VF, int HS>__device__ __forceinline__ void process_quant(c
   // While batch i is computed the copies of batch i + 1 are in flight: its K half is issued once batch i's K rows and meta
   // words are in registers, its V half once batch i's V rows are.  Loads complete in order, so "at most as many
   // outstanding as were issued after it" means a half has landed.
-  for (int i0 = first; i0 < c1; i0 += step_tokens) {
-    const bool more = !tv.in_host && i0 + step_tokens < c1;   // wave-uniform
-    if (tv.in_host) bring_host(i0);
-    else wait_vmcnt<N_V>();
-    fetch_k();
-    if (more) issue_k(i0 + step_tokens);
-    compute(min(TT, c1 - i0), [&]() {
-      if (more) wait_vmcnt<N_K>();
-      else wait_vmcnt<0>();
-      fetch_v();
-      if (more) issue_v(i0 + step_tokens);
-    });
+  auto loop = [&](auto big_tag) __attribute__((always_inline)) {
+    for (int i0 = first; i0 < c1; i0 += step_tokens) {
+      const bool more = !tv.in_host && i0 + step_tokens < c1;   // wave-uniform
+      if (tv.in_host) bring_host(i0);
+      else wait_vmcnt<N_V>();
+      fetch_k();
+      if (more) issue_k(i0 + step_tokens);
+      compute(min(TT, c1 - i0), big_tag, [&]() {
+        if (more) wait_vmcnt<N_K>();
+        else wait_vmcnt<0>();
+        fetch_v();
+        if (more) issue_v(i0 + step_tokens);
+      });
+    }
+  };
+  if (!K4 || !big) {
+    loop(std::false_type{});
+  } else {
+    if constexpr (K4) loop(std::true_type{});
   }
 
   // ---- the wave's result.  Sums over the lane's tokens come together; a head's zero-point sums, and what its weights

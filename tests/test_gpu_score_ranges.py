@@ -1,5 +1,5 @@
 """Grouped-query attention over quantized tiers at the ends of the score range that the entry points accept: scores so large
-that the weights of their heads carry no power of two."""
+that the weights of their heads carry no power of two, and heads whose queries differ by a factor of millions."""
 import numpy as np
 import pytest
 import torch
@@ -59,3 +59,29 @@ def test_scores_of_millions_beside_the_largest_values(kfmt, vfmt, G, ordinary, m
     # exact codes, weights of 22 bits, sums of n terms in fp32: a few units of 2^-22; the window's value rows differ from the
     # dequantized ones only for the heads that see it
     assert np.linalg.norm(out - ro) <= 1e-5 * np.linalg.norm(ro)
+
+
+@pytest.mark.parametrize("mem", ["device", "host"])
+@pytest.mark.parametrize("G", [2, 4, 8, 16])
+@pytest.mark.parametrize("kfmt,vfmt", [f for f in FORMATS if f[0] == "i4"])
+def test_small_queries_beside_large_ones(kfmt, vfmt, G, mem):
+    """A head with queries of 5000 does not take bits from the heads beside it: theirs are some 2.5e-4 here (fp16's smallest
+    normal number is 6e-5) over keys up to 60000, scores around 10.  An error of up to 2^-21 in every second query element (what
+    is left of one as a sixteenth of it, an fp16 subnormal) moves these scores by 7e-3."""
+    n = 1088
+    g = synth.rng(synth.SEED_BASE + 950 + G)
+    k = synth.round_to(g.uniform(-60000.0, 60000.0, (1, n + 63, 128)).astype(np.float32), "f16")
+    v = synth.normal(g, (1, n + 63, 128), "f16")
+    q = synth.round_to(2.5e-4 * g.standard_normal((1, G, 128)).astype(np.float32), "f16")
+    q[:, :, 0] = synth.round_to(np.array([0.002], np.float32), "f16")[0]
+    k[:, n:] = 0.0
+    k[:, n:, 0] = -60000.0                     # the window, whose weights are rounded to 16 bits: e^-40 of the others
+    q[:, G // 2] = 0.0
+    q[:, G // 2, 7] = 5000.0
+    out, lse, ro, rl = run(kfmt, vfmt, q, k, v, mem)
+    small = np.arange(G) != G // 2
+    assert np.all(np.isfinite(out))
+    assert_close(out[small], ro[small], "out")
+    # codes are exact, products summed in fp32: 2^-21 of a score's terms (some 100 together) at the most, i.e. 5e-5 of a weight
+    assert np.linalg.norm(out[small] - ro[small]) <= 2e-4 * np.linalg.norm(ro[small])
+    assert np.abs(lse[small] - rl[small]).max() <= 2e-4
