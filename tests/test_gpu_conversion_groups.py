@@ -3,6 +3,7 @@ near the minimum) and of key sums in launches of many blocks: the two-step quoti
 fp32, and codes, scales, zeros and mean keys bit for bit against the oracle."""
 import numpy as np
 import pytest
+import torch
 
 from paper_2604_19769_amd import synth
 from ttkv_testlib import Pair
@@ -79,3 +80,45 @@ def test_groups_and_sums(name, blocks):
             assert np.array_equal(p.gpu.dump_summary(len(tiers) - 1, 0, blk), mu), blk
     finally:
         p.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("summary", [False, True])
+@pytest.mark.parametrize("bad", [np.nan, -np.nan, np.inf])
+def test_groups_with_nan_beside_others(bad, summary):
+    """A NaN does not count for its group's range, takes the lowest code and leaves every other byte alone, in waves with
+    zero, tiny and ordinary groups; an infinity makes the scale of its own group infinite and changes no other group."""
+    spec = [dict(k_fmt="i8", v_fmt="i4", capacity=10**9, block_tokens=64, ring_blocks=8, summary=summary)]
+    k, v = synth.kv(1976962, 2, 300, "f16")
+    k, v = groups(k, "f16"), groups(v, "f16")
+    at = np.zeros((300, 128), bool)
+    at[3::16, 7] = at[9::16, 70] = at[10::16, 100] = at[14::64, 33] = True
+    dump = []
+    for x in (0, bad):
+        p = Pair(1, 2, 2, spec, "f16")
+        try:
+            kv = []
+            for t in (k, v):
+                t = t.copy()
+                t[:, at] = x if x else np.roll(t, 1, axis=2)[:, at]    # a neighbour in the same group: the range as without it
+                kv.append(torch.from_numpy(t).cuda().half().contiguous())
+            p.gpu.append(0, *kv, seq=0)
+            dump.append(p.gpu.dump_tier(0, 0))
+        finally:
+            p.close()
+    without, got = dump
+    nib = lambda d: np.stack([d & 15, d >> 4], -1).reshape(2, 300, 128)
+    codes = [(without["k"], got["k"], 32, 0x81), (nib(without["v"]), nib(got["v"]), 64, 0)]
+    for (a, b, g, low), name in zip(codes, "kv"):
+        own = at.reshape(300, 128 // g, g)
+        other = ~(np.broadcast_to(own.any(-1, keepdims=True), own.shape).reshape(300, 128) if np.isinf(bad) else at)
+        assert np.array_equal(a[:, other], b[:, other]), name
+        ma, mb = (d[name + "_meta"].view(np.uint16).reshape(2, 300, 128 // g, -1) for d in (without, got))
+        if np.isinf(bad):
+            hit = own.any(-1)
+            assert np.array_equal(ma[:, ~hit], mb[:, ~hit]), name
+            assert np.all(mb[:, hit][..., 0] == 0x7c00), name
+        else:
+            zero = (ma[..., 0] == 0)[..., None].repeat(g, -1).reshape(2, 300, 128)[:, at]   # a scale of zero: code 0 whatever the value
+            assert np.array_equal(ma, mb), name
+            assert np.array_equal(b[:, at][~zero], np.full((~zero).sum(), low, b.dtype)), name
