@@ -1064,6 +1064,8 @@ template <int KF, int VF, int HS>__device__ __forceinline__ void process_quant(c
   uint32_t plain = 0;              // bit e: the weights of element e's head carry no power of two
 
   const CodeMasks codes;
+  u32x4 centre = {0x00800080u, 0x00800080u, 0x00800080u, 0x00800080u};   // the centre as a code: int4 16 x 8, int8 128
+  if constexpr (K4) asm volatile("" : "+v"(centre));   // with two loops below it would be formed in every batch
 
   u32x2 kw[8], meta[2 * NC];
   uint32_t vop[NT / 2][8][VF == TTKV_I8_SYM_G32 ? 2 : 1];   // codes of channel 16 s + n, the pair's 8 tokens of this kg
@@ -1117,9 +1119,12 @@ template <int KF, int VF, int HS>__device__ __forceinline__ void process_quant(c
     for (int j = 0; j < NC; ++j) {
       const uint32_t m0 = meta[2 * j].x, m1 = meta[2 * j].y;
       float v[NE];
+      // One product chain per channel group, all before the first result is used: one after the other each result was waited
+      // for (64 / 4 heads, 8 x 64K tokens of K int8 / V int4 81.0 -> 80.0 us; 64 / 2 heads, 24 x 21K tokens 86.4 -> 85.3).
+      f4 sv[NGK];
 #pragma unroll
-      for (int gr = 0; gr < NGK; ++gr) {   // one product chain per channel group
-        f4 sv = K4 ? zero4 : off[gr];
+      for (int gr = 0; gr < NGK; ++gr) {
+        sv[gr] = K4 ? zero4 : off[gr];
 #pragma unroll
         for (int u = 0; u < TPC; ++u) {
           const u32x2 w = kw[(j * TPC + u) * NGK + gr];   // the lane's 8 bytes of the group
@@ -1131,27 +1136,29 @@ template <int KF, int VF, int HS>__device__ __forceinline__ void process_quant(c
             };
             take(w.x, kr);
             take(w.y, kr + 4);
-            sv = mma32<false>(qA[u] + 8 * gr, kr, sv);
-            sv = mma32<false>(qA[u] + 8 * gr + 4, kr + 4, sv);
+            sv[gr] = mma32<false>(qA[u] + 8 * gr, kr, sv[gr]);
+            sv[gr] = mma32<false>(qA[u] + 8 * gr + 4, kr + 4, sv[gr]);
           } else {
             uint32_t kr[4];
             codes8(w.x, kr, codes);
             codes8(w.y, kr + 2, codes);
-            sv = mma32<false>(qA[u] + 4 * gr, kr, sv);
+            sv[gr] = mma32<false>(qA[u] + 4 * gr, kr, sv[gr]);
           }
         }
+      }
+#pragma unroll
+      for (int gr = 0; gr < NGK; ++gr)
 #pragma unroll
         for (int e = 0; e < NE; ++e) {
           if constexpr (K4) {   // the group's zero point and scale
             const uint32_t m = gr ? m1 : m0;
             v[e] = gr ? fmaf(half1(m), qs[gr][e], v[e]) : half1(m) * qs[gr][e];
-            v[e] = fmaf(sv[e], half0(m), v[e]);
+            v[e] = fmaf(sv[gr][e], half0(m), v[e]);
           } else {              // the group's scale
             const uint32_t m = gr / 2 ? m1 : m0;
-            v[e] = gr ? fmaf(sv[e], gr % 2 ? half1(m) : half0(m), v[e]) : sv[e] * half0(m);
+            v[e] = gr ? fmaf(sv[gr][e], gr % 2 ? half1(m) : half0(m), v[e]) : sv[gr][e] * half0(m);
           }
         }
-      }
 #pragma unroll
       for (int e = 0; e < NE; ++e) {
         x[j][e] = v[e];
@@ -1297,7 +1304,7 @@ template <int KF, int VF, int HS>__device__ __forceinline__ void process_quant(c
         acc[s] = mma32<false>(vr, R, acc[s]);
         acc[s] = mma32<false>(vr, B, acc[s]);
       }
-      const uint32_t cc[4] = {0x00800080u, 0x00800080u, 0x00800080u, 0x00800080u};   // the centre as a code: int4 16 x 8, int8 128
+      const uint32_t cc[4] = {centre.x, centre.y, centre.z, centre.w};
       accc[b] = mma32<false>(cc, R, accc[b]);
       accc[b] = mma32<false>(cc, B, accc[b]);
     };
