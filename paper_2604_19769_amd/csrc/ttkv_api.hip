@@ -120,8 +120,9 @@ int copy_granule(int64_t rec_bytes) {
 
 // Default split-K granularity, in workgroups resident at once on 256 CUs: 2.5 rounds of 4 per CU for the vector
 // kernel (flat between 1 and 3 rounds, measured), exactly one round of the grouped-query matrix-core kernel: 2 per CU
-// with 4-bit tiers, 3 without.  (Two are also the better choice for int8 tiers with many heads: 64 q / 4 kv heads,
-// 4 x 100K tokens, 81.9 us with 512 items, 89.4 with 768.)  Launches with keys grouped over tokens that go to the vector
+// with 4-bit tiers, 3 without.  (Two items per CU for int8 tiers with many heads as well, although three fit: 64 q / 4 kv
+// heads, 98K tokens 29.7 us with 512 items and 34.6 with 768; 64 / 2 heads, 24 x 21K tokens 94.2 and 97.3; the other way
+// round 16 x 16K tokens 61.5 and 59.7, 4 x 100K tokens 83.4 and 80.4.)  Launches with keys grouped over tokens that go to the vector
 // kernel's head pairs all the same keep the matrix-core counts: 2 x 51K tokens 129 us with 8 heads per KV head and
 // 129-134 with 16, against 148 and 183-185 with the vector kernel's 2560.
 int default_items(const ttkv_cache *c) {

@@ -760,7 +760,8 @@ __device__ __forceinline__ uint32_t fresh(uint32_t v) {
   return v;
 }
 
-template <int KF, int VF, int HS>__device__ __forceinline__ void process_quant(const FusedArgs &a, const TierView &tv, const RunView &en, const int32_t *sel,
+template <int KF, int VF, int HS, bool OFF_LDS>
+__device__ __forceinline__ void process_quant(const FusedArgs &a, const TierView &tv, const RunView &en, const int32_t *sel,
                                               int chunk_tokens, int chunk, int n_items, int seq, int hq0, int Gr, int hkv, char *wbuf) {
   // sel, hq0, Gr, wbuf: as process_rows.  n_items: 0, the item is chunk_tokens tokens in a row; else the run's items take
   // turns at its batches, so that at any time they read one stretch of memory (32 / 8 heads, 128K tokens 40.2 -> 39.3 us,
@@ -950,10 +951,9 @@ template <int KF, int VF, int HS>__device__ __forceinline__ void process_quant(c
     if (!tv.in_host) issue_v(first);
   float unit = a.scale * kLog2e * (K4 ? 0x1p20f : 0x1p24f);   // a score is its product times this, in the log2 domain
   uint32_t qA[TPC][16];      // row operand of the chain's tiles
-  // Int8: minus what the code offset 128 adds to a row's product, per channel group.  With two tiles' rows of queries as well
-  // (8 places) these 16 registers make the loop spill, and a reload from scratch waits for every copy in flight (28 / 4
-  // heads, 2 x 23K tokens 22.0 -> 23.3 us): there they are read from LDS with the keys; elsewhere that costs 2 %.
-  constexpr bool OFF_LDS = !K4 && HS == 8;
+  // Int8: minus what the code offset 128 adds to a row's product, per channel group.  OFF_LDS: where these 16 registers would
+  // make the loop spill, and a reload from scratch waits for every copy in flight (28 / 4 heads, 2 x 23K tokens 22.0 -> 23.3
+  // us), they are read from LDS with the keys; elsewhere that costs 1-2 %.
   const uint32_t lds_off = lds0 + (4 - wave) * kTileLds;
   f4 off[NGK];
   float qs[K4 ? 2 : 1][NE];  // int4: a row's sum per channel group (for the zero points), in the product's units
@@ -1333,17 +1333,17 @@ template <int KF, int VF, int HS>__device__ __forceinline__ void process_quant(c
       product(0, 0, w);
       product(NT / 2 - 1, 0, w + 4);
     } else {
-      u32x2 w[4 * Q::SETS];
 #pragma unroll
-      for (int round = 0; round < Q::NR; ++round) {
+      for (int round = 0; round < Q::NR; ++round) {   // a round's products before the next one's weights: half as many in registers
+        u32x2 w[4 * Q::NB];
         put_weights(0, round, std::integral_constant<int, 0>{});
         if constexpr (NC == 2) put_weights(NC - 1, round, std::integral_constant<int, T16>{});
-        if constexpr (Q::NB == 2) lds_weights<0, T16, SET, T16 + SET>(lpr, second_half(lpr), w + 8 * round);
-        else lds_weights<0, T16>(lpr, w + 4 * round);
-      }
-      before_v();
+        if constexpr (Q::NB == 2) lds_weights<0, T16, SET, T16 + SET>(lpr, second_half(lpr), w);
+        else lds_weights<0, T16>(lpr, w);
+        if (round == 0) before_v();
 #pragma unroll
-      for (int b = 0; b < Q::SETS; ++b) product(0, b, w + 4 * b);
+        for (int b = 0; b < Q::NB; ++b) product(0, Q::NB * round + b, w + 4 * b);
+      }
     }
   };
 
@@ -1414,12 +1414,15 @@ template <int KF, int VF, int HS>__device__ __forceinline__ void process_quant(c
 }
 
 // What the tiers of a launch hold: each kind is compiled without the cases it does not meet, so that their registers do
-// not count.  With 4-bit keys or values, and for int8 with more than 8 heads, two workgroups per CU (the plan counts on
-// it), otherwise three.  HS: places for heads (QuantShape).
+// not count.  With 4-bit keys or values two workgroups per CU, otherwise three (int8 and 16 heads with two: 64 / 2 heads, 98K
+// tokens 39.5 us against 37.1, 24 x 21K tokens 104.3 against 102.8; 64 / 4 heads, 16 x 16K tokens 61.0 against 59.5).
+// HS: places for heads (QuantShape).
 enum LaunchKind { FP_ONLY, WITH_INT8, WITH_4BIT, WITH_T128 };
-constexpr int waves_per_simd(int kind, int hs) { return kind == FP_ONLY || (kind == WITH_INT8 && hs <= 8) ? 3 : 2; }
+constexpr int waves_per_simd(int kind) { return kind == FP_ONLY || kind == WITH_INT8 ? 3 : 2; }
+// Two tiles' rows of queries (8 places), or three workgroups per CU with 16.
+constexpr bool offsets_in_lds(int kind, int hs) { return hs == 8 || (hs == 16 && kind == WITH_INT8); }
 template <int KIND, int HS>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(waves_per_simd(KIND, HS), waves_per_simd(KIND, HS)))) void attn_mfma_kernel(const FusedArgs a) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(waves_per_simd(KIND), waves_per_simd(KIND)))) void attn_mfma_kernel(const FusedArgs a) {
   static_assert(kTileRowsLds >= 16 * 128 * 4 && 3 * lds_given(4 * kTileLds + kOffLds) <= 160 * 1024, "the wave's result; three workgroups per CU");
   __shared__ __attribute__((aligned(256))) char s_buf[4 * kTileLds + kOffLds];   // per wave: batches in flight, then [head][channel] floats
   char *const wbuf = s_buf + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * kTileLds;
@@ -1455,7 +1458,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(waves_per_s
 
   const int combo = tv.k_fmt * 8 + tv.v_fmt;
 #define TTKV_ROWS(KF, VF) process_rows<KF, VF>(a, tv, en, sel, chunk_tokens, chunk, seq, hq0, G, hkv, wbuf)
-#define TTKV_QUANT(KF, VF) process_quant<KF, VF, HS>(a, tv, en, sel, chunk_tokens, chunk, n_even, seq, hq0, G, hkv, wbuf)
+#define TTKV_QUANT(KF, VF)                                                                               \
+  process_quant<KF, VF, HS, KF == TTKV_I8_SYM_G32 && offsets_in_lds(KIND, HS)>(a, tv, en, sel, chunk_tokens, chunk, n_even, seq, hq0, G, \
+                                                                               hkv, wbuf)
   switch (combo) {
     case TTKV_F16 * 8 + TTKV_F16: TTKV_ROWS(TTKV_F16, TTKV_F16); break;
     case TTKV_BF16 * 8 + TTKV_BF16: TTKV_ROWS(TTKV_BF16, TTKV_BF16); break;
