@@ -1418,6 +1418,12 @@ __device__ __forceinline__ void process_quant(const FusedArgs &a, const TierView
 // tokens 39.5 us against 37.1, 24 x 21K tokens 104.3 against 102.8; 64 / 4 heads, 16 x 16K tokens 61.0 against 59.5).
 // HS: places for heads (QuantShape).
 enum LaunchKind { FP_ONLY, WITH_INT8, WITH_4BIT, WITH_T128 };
+// Key formats that stay with the vector kernel's head pairs when keys grouped over tokens are in the same launch: those
+// have fp32 weights, where process_rows rounds the weights of the grouped keys to 16 bits.  Error against 64 bits and time of
+// 2 sequences of 8192 tokens of the format and 16384 of grouped keys, pairs and matrix cores: 16 / 2 heads, int8 3.0e-5 in
+// 35.6 us, 1.5e-4 in 16.8; 32 / 2 heads 2.9e-5 in 54.9, 1.7e-4 in 18.4, int4 4.0e-5 in 55.3, 1.7e-4 in 16.8.  Launches that
+// took the matrix cores before there was a faster way for all of them stay there.
+constexpr bool pairs_beside_t128(int k_fmt, int G) { return (k_fmt == TTKV_I8_SYM_G32 && G > 4) || (k_fmt == TTKV_I4_ASYM_G64 && G > 8); }
 constexpr int waves_per_simd(int kind) { return kind == FP_ONLY || kind == WITH_INT8 ? 3 : 2; }
 // Two tiles' rows of queries (8 places), or three workgroups per CU with 16.
 constexpr bool offsets_in_lds(int kind, int hs) { return hs == 8 || (hs == 16 && kind == WITH_INT8); }
@@ -1456,6 +1462,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(waves_per_s
   int chunk = item - item_start;
   const int32_t *sel = resolve_selected(a, tv, en, seq, equal_items, chunk_tokens, chunk);
 
+  constexpr bool K8 = KIND != WITH_T128 || !pairs_beside_t128(TTKV_I8_SYM_G32, HS), K4 = KIND != WITH_T128 || !pairs_beside_t128(TTKV_I4_ASYM_G64, HS);
   const int combo = tv.k_fmt * 8 + tv.v_fmt;
 #define TTKV_ROWS(KF, VF) process_rows<KF, VF>(a, tv, en, sel, chunk_tokens, chunk, seq, hq0, G, hkv, wbuf)
 #define TTKV_QUANT(KF, VF)                                                                               \
@@ -1465,22 +1472,22 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(waves_per_s
     case TTKV_F16 * 8 + TTKV_F16: TTKV_ROWS(TTKV_F16, TTKV_F16); break;
     case TTKV_BF16 * 8 + TTKV_BF16: TTKV_ROWS(TTKV_BF16, TTKV_BF16); break;
     case TTKV_I8_SYM_G32 * 8 + TTKV_I8_SYM_G32:
-      if constexpr (KIND >= WITH_INT8) TTKV_QUANT(TTKV_I8_SYM_G32, TTKV_I8_SYM_G32);
+      if constexpr (KIND >= WITH_INT8 && K8) TTKV_QUANT(TTKV_I8_SYM_G32, TTKV_I8_SYM_G32);
       break;
     case TTKV_I4_ASYM_T128 * 8 + TTKV_I4_ASYM_G64:
       if constexpr (KIND == WITH_T128) TTKV_ROWS(TTKV_I4_ASYM_T128, TTKV_I4_ASYM_G64);
       break;
     case TTKV_I8_SYM_G32 * 8 + TTKV_I4_ASYM_G64:
-      if constexpr (KIND >= WITH_4BIT) TTKV_QUANT(TTKV_I8_SYM_G32, TTKV_I4_ASYM_G64);
+      if constexpr (KIND >= WITH_4BIT && K8) TTKV_QUANT(TTKV_I8_SYM_G32, TTKV_I4_ASYM_G64);
       break;
     case TTKV_I8_SYM_G32 * 8 + TTKV_I4_ASYM_G64_T32:
-      if constexpr (KIND >= WITH_4BIT) TTKV_QUANT(TTKV_I8_SYM_G32, TTKV_I4_ASYM_G64_T32);
+      if constexpr (KIND >= WITH_4BIT && K8) TTKV_QUANT(TTKV_I8_SYM_G32, TTKV_I4_ASYM_G64_T32);
       break;
     case TTKV_I4_ASYM_G64 * 8 + TTKV_I4_ASYM_G64_T32:
-      if constexpr (KIND >= WITH_4BIT) TTKV_QUANT(TTKV_I4_ASYM_G64, TTKV_I4_ASYM_G64_T32);
+      if constexpr (KIND >= WITH_4BIT && K4) TTKV_QUANT(TTKV_I4_ASYM_G64, TTKV_I4_ASYM_G64_T32);
       break;
     default:
-      if constexpr (KIND >= WITH_4BIT) TTKV_QUANT(TTKV_I4_ASYM_G64, TTKV_I4_ASYM_G64);
+      if constexpr (KIND >= WITH_4BIT && K4) TTKV_QUANT(TTKV_I4_ASYM_G64, TTKV_I4_ASYM_G64);
       break;
   }
 #undef TTKV_ROWS
@@ -1536,11 +1543,6 @@ bool attn_mfma_fits(int k_fmt, int v_fmt, int G) {
 bool attn_mfma_four_bit(int k_fmt, int v_fmt) { return !is_fp(k_fmt) && !(k_fmt == TTKV_I8_SYM_G32 && v_fmt == k_fmt); }
 
 namespace {
-// Key formats that stay with the vector kernel's head pairs when keys grouped over tokens are in the same launch: the
-// former score product had no case for them.  This one has, and the pairs are not the faster route any more (2 x 51K
-// tokens, 8 heads per KV head 129 us against 41, 16 heads 134 against 29).
-bool pairs_beside_t128(int k_fmt, int G) { return (k_fmt == TTKV_I8_SYM_G32 && G > 4) || (k_fmt == TTKV_I4_ASYM_G64 && G > 8); }
-
 // What one launch needs: heads per block, quantized tiers, 4-bit ones, keys grouped over tokens.  ok: the kernel takes it.
 struct MfmaShape {
   int heads;
