@@ -143,24 +143,6 @@ __device__ __forceinline__ void touch_arguments(const FusedArgs &a) {
                "s"(a.tv[0].bt), "s"(a.tv[1].bt), "s"(a.tv[2].bt), "s"(a.tv[3].bt), "s"(a.e[0].len), "s"(a.e[5].len),
                "s"(a.e[10].len), "s"(a.chunk[0]), "s"(a.q_fmt));
 }
-// The run that holds an item: start <= item < next run's.
-__device__ __forceinline__ int find_run(const FusedArgs &a, int item) {
-  int seg = 0;
-  if (a.n_entries > 16) {
-#pragma unroll
-    for (int k = 1; k < TTKV_MAX_ENTRIES / 16; ++k) seg += a.coarse[k] <= item;
-  }
-  const int32_t *s = a.start + 16 * seg;
-  int lo = 16 * seg - 1;
-#pragma unroll
-  for (int k = 0; k < 16; ++k) lo += s[k] <= item;
-  return lo;
-}
-// Workgroup -> (item, KV head).
-__device__ __forceinline__ int item_of(const FusedArgs &a, uint32_t base) {
-  if (a.Hkv == 1) return base;
-  return a.hkv_magic ? (int)mul_high(base, a.hkv_magic) : (int)(base / (uint32_t)a.Hkv);
-}
 // A run whose blocks are named by the device-side selection (ids ascending, so only the last can be the tier's
 // partly filled newest block).  Two forms, told apart by the tier's item size in the launch arguments:
 //   fixed items (host tiers): item `chunk` of the run is sub-chunk chunk % ipb of the run's (chunk / ipb)-th

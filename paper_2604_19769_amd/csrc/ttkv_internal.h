@@ -241,6 +241,24 @@ struct FusedArgs {
 static_assert(sizeof(FusedArgs) <= 4096, "kernel arguments are passed by value");
 static_assert(TTKV_MAX_ENTRIES % 16 == 0, "coarse");
 void set_items(FusedArgs &a, int n_entries, int n_items);   // the look-up tables behind `start`
+// The run that holds an item: start <= item < next run's.
+__host__ __device__ inline int find_run(const FusedArgs &a, int item) {
+  int seg = 0;
+  if (a.n_entries > 16) {
+#pragma unroll
+    for (int k = 1; k < TTKV_MAX_ENTRIES / 16; ++k) seg += a.coarse[k] <= item;
+  }
+  const int32_t *s = a.start + 16 * seg;
+  int lo = 16 * seg - 1;
+#pragma unroll
+  for (int k = 0; k < 16; ++k) lo += s[k] <= item;
+  return lo;
+}
+// Workgroup -> (item, KV head).
+__host__ __device__ inline int item_of(const FusedArgs &a, uint32_t base) {
+  if (a.Hkv == 1) return base;
+  return a.hkv_magic ? (int)mul_high(base, a.hkv_magic) : (int)(base / (uint32_t)a.Hkv);
+}
 hipError_t launch_attn(const FusedArgs &a, hipStream_t s, int *n_kernels, int *n_mfma);
 bool attn_supported(int k_fmt, int v_fmt, int G);
 int attn_group_width(int Gtot);
