@@ -137,6 +137,7 @@ constexpr int kSumsLds = kTileRowsLds + 512;   // 16 references, 16 sums of weig
 typedef const __attribute__((address_space(1))) void *gas_ptr;
 typedef __attribute__((address_space(3))) void *las_ptr;
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x4_any __attribute__((ext_vector_type(4), aligned(2)));
 // lane L's 16 (4) bytes land at dst + 16 L (4 L); dst is wave-uniform; OFF is added to both addresses.
 template <int OFF = 0>
 __device__ __forceinline__ void dma16(const uint8_t *src, char *dst) {
@@ -924,10 +925,15 @@ __device__ __forceinline__ void process_quant(const FusedArgs &a, const TierView
   // then copied after them.
   constexpr bool Q_IN_V = HS == 16;
   char *const q_lds = wbuf + (Q_IN_V ? 4096 : kBatchLds);
+  // The copies take addresses of 16-byte alignment; queries that a caller keeps elsewhere (a view into a larger tensor) come
+  // through registers.
+  const bool q_aligned = ((uintptr_t)a.q & 15) == 0;
 #pragma unroll
   for (int i = 0; i < HS / 4; ++i) {
     const int h = min(4 * i + (lane >> 4), Gr - 1);
-    dma16((const uint8_t *)a.q + ((int64_t)seq * a.Hq + hq0 + h) * 256 + n * 16, q_lds + 1024 * i);
+    const uint8_t *const src = (const uint8_t *)a.q + ((int64_t)seq * a.Hq + hq0 + h) * 256 + n * 16;
+    if (q_aligned) dma16(src, q_lds + 1024 * i);
+    else *(u32x4 *)(q_lds + 1024 * i + 16 * lane) = *(const u32x4_any *)src;
   }
   if (tv.in_host) {
     wait_vmcnt<0>();

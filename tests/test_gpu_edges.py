@@ -200,3 +200,28 @@ def test_randomized_layouts_with_channel_major_values(seed):
     run_config(B_, Hq, Hkv, tiers, dtype, None, 12, synth.SEED_BASE + 1200 + seed, lens=lens, n_slots=n_slots,
                check_state_every=6, host_append_direct=bool(seed & 1), host_demote_direct=bool(seed & 2),
                one_call_step=bool(seed % 3))
+
+
+@pytest.mark.parametrize("kfmt,vfmt", [("f16", "f16"), ("i8", "i8"), ("i8", "i4"), ("i4", "i4"), ("i4", "i4c")])
+@pytest.mark.parametrize("Hq,Hkv", [(2, 2), (8, 2), (16, 2), (32, 2)])
+def test_queries_at_any_address(kfmt, vfmt, Hq, Hkv):
+    """Queries that are a contiguous view at any element of a larger tensor: the same bits as from the start of one."""
+    if vfmt == "i4c" and Hq == Hkv:
+        pytest.skip("values packed for the matrix cores need two query heads per KV head")
+    tiers = [dict(k_fmt="f16", v_fmt="f16", capacity=64, block_tokens=64, ring_blocks=3),
+             dict(k_fmt=kfmt, v_fmt=vfmt, capacity=10**9, block_tokens=128, ring_blocks=9)]
+    p = Pair(2, Hq, Hkv, tiers, "f16")
+    try:
+        for b, n in enumerate((63 + 992, 63 + 416)):
+            p.load(b, *synth.kv(synth.SEED_BASE + 60 + b, Hkv, n, "f16"))
+        q = dev(synth.normal(synth.rng(synth.SEED_BASE + 62), (2, Hq, 128), "f16"), "f16")
+        want = [x.clone() for x in p.gpu.decode(q)]
+        for at in (1, 2, 3, 4, 7, 8):
+            big = torch.zeros(q.numel() + 16, dtype=q.dtype, device=q.device)
+            view = big[at:at + q.numel()].view(q.shape)
+            view.copy_(q)
+            got = p.gpu.decode(view)
+            torch.cuda.synchronize()
+            assert all(torch.equal(g, w) for g, w in zip(got, want)), at
+    finally:
+        p.close()
