@@ -35,11 +35,13 @@
 //
 // Bound: the memory system; vector instructions where they are too many.  Quantized loop, 32 / 8 heads, vector
 // instructions per 64 tokens of int4 (32 of int8): 624 -> 280 (337 -> 160) against the form with heads as columns of both
-// products, one rounding of p s and splice constants; one step, us, before -> now: 128K tokens of three formats 42.9 -> 39,
-// 16 ragged sequences of K int4 / V4c 187 -> 178, block-sparse recall 122 -> 118; 64 / 4 heads, K int8 / V int4, 83.7 -> 84
+// products, one rounding of p s and splice constants; one step, us, before -> now: 128K tokens of three formats 42.9 -> 39.2,
+// 16 ragged sequences of K int4 / V4c 187 -> 177, block-sparse recall 125 -> 115; 64 / 4 heads, K int8 / V int4, 84.8 -> 81.7
 // (77 with everything but copies and LDS reads taken out).  Error against 64 bits (2-norm, keys with outlier channels,
-// 4K to 64K tokens): int8 0.9e-4 -> 1.4e-5 to 4e-5, int4 0.95e-4 -> 1e-5.  More heads per KV head than 16 are cut into
-// blocks of 16, one workgroup and one pass over the bytes per block.
+// 4K to 64K tokens): int8 0.9e-4 -> 1.4e-5 to 4.3e-5, int4 1e-4 -> 1e-5 to 2e-5, int4 with scores eight times as large 8e-5 ->
+// 1.9e-5.  One power of two serves a wave's weights: channels whose values are 2^-14 of other channels' keep this error, at
+// 2^-18 it is 1e-4 and at 2^-20 5e-4 (one rounding: 1e-4).  More heads per KV head than 16 are cut into blocks of 16, one
+// workgroup and one pass over the bytes per block.
 #include "ttkv_attn_dev.h"
 
 #include <algorithm>
@@ -99,12 +101,11 @@ constexpr int chan(int s, int i) {
 // A lane's 32 channels of a value row are the 16-byte pieces kg, kg + 4, ... of it (piece x of the lane = bytes
 // [64 x + 16 kg, + 16) of the row), so that every load instruction of a tile reads 64 contiguous bytes per row
 // (measured on a load-only kernel: 6.3 TB/s, against 5.3 TB/s when a lane's pieces are adjacent).  Element j
-// of the lane's slice (j = 4 s + i in unpack order for fp16 / bf16 / int8) is therefore row channel:
+// of the lane's slice (j = 4 s + i in unpack order for fp16 / bf16) is therefore row channel:
 template <int F>
 __device__ __forceinline__ constexpr int slice_channel(int kg, int j) {
-  if (is_i4<F>()) return 32 * kg + j;                                     // one piece of 32 channels
-  if (F == TTKV_I8_SYM_G32) return 64 * (j / 16) + 16 * kg + j % 16;      // two pieces of 16
-  return 32 * (j / 8) + 8 * kg + j % 8;                                   // four pieces of 8
+  if (is_i4<F>()) return 32 * kg + j;     // one piece of 32 channels
+  return 32 * (j / 8) + 8 * kg + j % 8;   // four pieces of 8
 }
 // Key rows with channel groups are sliced so that a 32-deep step stays inside one group: the lane takes 8 bytes of
 // each 32-byte stretch, bytes [32 x + 8 kg, + 8): int8 channels 32 x + 8 kg .. (group x, step x), int4 channels
@@ -128,7 +129,7 @@ __device__ __forceinline__ constexpr int key_channel(int kg, int j) {
 constexpr int kTileRowsLds = 8 * 1024, kMetaLds = 4 * 256, kBatchLds = kTileRowsLds + kMetaLds, kWeightsLds = 2 * 2048;
 constexpr int kTileLds = kBatchLds + kWeightsLds;
 // Behind the four waves' places, int8 keys: the rows' offsets per channel group, [group][kg].  All waves of a workgroup have
-// the same queries and store the same numbers.  (A copy per wave would make three workgroups 40 bytes larger than a CU's
+// the same queries and store the same numbers.  (A copy per wave would make three workgroups 1280 bytes larger than a CU's
 // LDS: it is given out in units of 1280 bytes, and 54272 become 55040.  With two resident, 16 sequences of 2664 fp16 + 8704
 // int8 tokens, 32 / 8 heads, take 85.4 us instead of 79.)
 constexpr int kOffLds = 256;
@@ -765,8 +766,9 @@ template <int KF, int VF, int HS, bool OFF_LDS>
 __device__ __forceinline__ void process_quant(const FusedArgs &a, const TierView &tv, const RunView &en, const int32_t *sel,
                                               int chunk_tokens, int chunk, int n_items, int seq, int hq0, int Gr, int hkv, char *wbuf) {
   // sel, hq0, Gr, wbuf: as process_rows.  n_items: 0, the item is chunk_tokens tokens in a row; else the run's items take
-  // turns at its batches, so that at any time they read one stretch of memory (32 / 8 heads, 128K tokens 40.2 -> 39.3 us,
-  // 64 x 4K tokens 120 -> 118 us).
+  // turns at its batches, so that at any time they read one stretch of memory (8 x 64K tokens of K int8 / V int4, 64 / 4 heads,
+  // 84.2 -> 83.0 us, block-sparse recall 119.5 -> 117.6; in turn over caches of 2.3 GB together, so that each is read cold, 85.5 ->
+  // 83.5 and 121.0 -> 118.9; 128K tokens, ragged and short sequences within 0.5 us either way, cold or not).
   using FK = Fmt<KF>;
   using FV = Fmt<VF>;
   using Q = QuantShape<KF, VF, HS>;
@@ -784,7 +786,7 @@ __device__ __forceinline__ void process_quant(const FusedArgs &a, const TierView
   const int c1 = n_items ? en.len : min(en.len, c0 + chunk_tokens);
 
   // ---- where a batch lies, and its copies into the wave's LDS: K rows at 0, V rows at 4 KiB (row r at r ROWB, its
-  // piece p at 16 (p ^ swz(r))), then the two buffers of meta planes, then the weights.
+  // piece p at 16 (p ^ swz(r))), then the four meta planes, then the weights.
   auto swz = [](int pieces, int r) { return pieces == 4 ? (r >> 2) & 3 : (r >> 1) & 7; };
   // value rows: also different for the rows that the lanes of a transposing read name in different tiles
   auto swzv = [](int pieces, int r) { return pieces == 4 ? ((r >> 2) ^ (r >> 4)) & 3 : ((r >> 1) & 7) ^ ((r >> 3) & 2); };
