@@ -56,6 +56,7 @@ using namespace dev;
 typedef _Float16 h4 __attribute__((ext_vector_type(4)));
 typedef short s4 __attribute__((ext_vector_type(4)));
 typedef float f4 __attribute__((ext_vector_type(4)));
+typedef float f4_any __attribute__((ext_vector_type(4), aligned(4)));
 
 template <bool BF>
 __device__ __forceinline__ f4 mma(uint32_t a0, uint32_t a1, uint32_t b0, uint32_t b1, f4 c) {
@@ -1504,8 +1505,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(waves_per_s
 
   // ---- merge the four waves (each with its own running max) and write the item's partials: four channels per thread, so
   // that 16 heads take two turns of a chain of LDS reads and exponentials, not eight (64 / 4 heads, 4 x 6K tokens 17.9 -> 16.8
-  // us, 64 / 2 heads 82K tokens 38.4 -> 35.8).  Partials are 16-byte stores to addresses of 8-byte alignment, which the
-  // merge reads alike.
+  // us, 64 / 2 heads 82K tokens 38.4 -> 35.8).  Partials are 16-byte stores to addresses of 8-byte alignment (4, if
+  // the caller's workspace is), which the merge reads alike.
   for (int idx = threadIdx.x; idx < G * 32; idx += 256) {
     const int g = idx >> 5, c4 = idx & 31;
     float m[4], l[4];
@@ -1528,7 +1529,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(waves_per_s
       ll = fmaf(l[w], wgt, ll);
     }
     const int64_t prow = ((int64_t)seq * a.Hq + hq0 + g) * a.part_stride + part;
-    *(f4 *)(a.pacc + prow * 128 + c4 * 4) = o;
+    *(f4_any *)(a.pacc + prow * 128 + c4 * 4) = o;
     if (c4 == 0) {
       a.pm[prow] = M * kLn2;  // natural-log units outside the kernel
       a.pl[prow] = ll;
