@@ -958,7 +958,8 @@ __device__ __forceinline__ void process_quant(const FusedArgs &a, const TierView
   }
   if constexpr (Q_IN_V)
     if (!tv.in_host) issue_v(first);
-  float unit = a.scale * kLog2e * (K4 ? 0x1p20f : 0x1p24f);   // a score is its product times this, in the log2 domain
+  // A score is its product times this, in the log2 domain.  Finite for every scale, or a score of zero would be NaN.
+  const float unit = fminf(a.scale * kLog2e * (K4 ? 0x1p20f : 0x1p24f), 3.402823466e38f);
   uint32_t qA[TPC][16];      // row operand of the chain's tiles
   // Int8: minus what the code offset 128 adds to a row's product, per channel group.  OFF_LDS: where these 16 registers would
   // make the loop spill, and a reload from scratch waits for every copy in flight (28 / 4 heads, 2 x 23K tokens 22.0 -> 23.3

@@ -13,7 +13,7 @@ pytestmark = pytest.mark.gpu
 FORMATS = [("i8", "i8"), ("i8", "i4"), ("i4", "i4"), ("i8", "i4c"), ("i4", "i4c")]
 
 
-def run(kfmt, vfmt, q, k, v, mem):
+def run(kfmt, vfmt, q, k, v, mem, scale=None):
     """One KV head, the last 63 tokens of k and v in an fp16 window, the others in one work item of a quantized tier."""
     n = k.shape[1]
     tiers = [dict(k_fmt="f16", v_fmt="f16", capacity=64, block_tokens=64, ring_blocks=3),
@@ -21,6 +21,8 @@ def run(kfmt, vfmt, q, k, v, mem):
     p = Pair(1, q.shape[1], 1, tiers, "f16", host_append_direct=True)
     try:
         B.ttkv_set_split(p.gpu.h, 1)
+        if scale is not None:
+            p.gpu.c.softmax_scale = p.ora.scale = scale
         p.load(0, k, v)
         out, lse = p.gpu.decode(dev(q, "f16"))
         torch.cuda.synchronize()
@@ -85,3 +87,17 @@ def test_small_queries_beside_large_ones(kfmt, vfmt, G, mem):
     # codes are exact, products summed in fp32: 2^-21 of a score's terms (some 100 together) at the most, i.e. 5e-5 of a weight
     assert np.linalg.norm(out[small] - ro[small]) <= 2e-4 * np.linalg.norm(ro[small])
     assert np.abs(lse[small] - rl[small]).max() <= 2e-4
+
+
+@pytest.mark.parametrize("scale", [1e-30, 1e30, 1e37])
+@pytest.mark.parametrize("G", [4, 16])
+@pytest.mark.parametrize("kfmt,vfmt", FORMATS)
+def test_zero_scores_at_any_scale(kfmt, vfmt, G, scale):
+    """Keys of zero have scores of zero whatever the softmax scale: the result is the mean of the values."""
+    n = 416
+    g = synth.rng(synth.SEED_BASE + 990)
+    k, v = np.zeros((1, n + 63, 128), np.float32), synth.normal(g, (1, n + 63, 128), "f16")
+    q = synth.normal(g, (1, G, 128), "f16")
+    out, lse, ro, rl = run(kfmt, vfmt, q, k, v, "device", np.float32(scale))
+    assert_close(out, ro, "out")
+    assert np.abs(lse - np.log(n + 63)).max() <= 1e-5
