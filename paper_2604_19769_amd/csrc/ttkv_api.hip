@@ -1146,10 +1146,15 @@ static ttkv_status decode_impl(Handle *h, const ttkv_cache *c, const void *q, in
     const ttkv_tier &T0 = c->tier[0];
     m.q = q; m.k_new = k_new; m.v_new = v_new;
     m.q_fmt = q_fmt; m.new_fmt = new_fmt;
-    m.Hq = c->n_q_heads; m.Hkv = c->n_kv_heads;
+    m.G = c->n_q_heads / c->n_kv_heads; m.Hkv = c->n_kv_heads;
+    m.g_magic = magic_heads(c->n_q_heads, m.G);
     m.scale = c->softmax_scale;
     m.dst = make_view(T0, make_layout(T0, c->n_kv_heads));
-    for (int b = 0; b < c->batch; ++b) m.new_tok[b] = (int32_t)((T0.start[b] + T0.len[b]) % ring_tokens(T0));
+    for (int b = 0; b < c->batch; ++b) {
+      const int32_t tok = (int32_t)((T0.start[b] + T0.len[b]) % ring_tokens(T0));
+      m.new_block[b] = tok / T0.block_tokens;
+      m.new_row[b] = tok % T0.block_tokens;
+    }
   }
   TTKV_HIP(h, ch.merge(m));
   if (k_new)
@@ -1265,6 +1270,7 @@ ttkv_status ttkv_merge_partials(ttkv_handle hh, const float *m, const float *l, 
   a.rows = rows;
   a.n_parts_row = n_parts_row;
   a.rows_per_seq = 0;
+  a.cnt[0] = n_parts;
   a.out = out;
   a.lse = lse;
   TTKV_HIP(h, launch_merge(a, (hipStream_t)stream));

@@ -440,25 +440,29 @@ __global__ __launch_bounds__(256) void attn_fused_kernel(const FusedArgs a) {
 }
 
 // One workgroup of T threads per row (128 up to 32 parts, else 256: 2048 rows of 5 parts 9.8 us with 256, 7.6 with 128).
-// The kernel is a chain of memory latencies, so everything that does not depend
-// on anything is requested first: 32 lanes take a part's 128 channels in 16 bytes each, T / 32 parts at a time, the first
-// T / 4 parts before anything else (most launches have no more); each part's (m, l) is loaded once, by thread p, and the
-// weights e^(m_p - M) go through LDS.  (One channel per thread and eight parts in flight per half of the workgroup
-// before: 7.9 us at 95 parts per row, now 5.0; 5.8 at 20 parts, now 5.4.)
+// The kernel is a chain of memory latencies, so everything that does not depend on anything is requested first: 32 lanes take
+// a part's 128 channels in 16 bytes each, T / 32 parts at a time, the first T / 4 parts before anything else (most launches
+// have no more), and every wave all parts' (m, l) for itself, a part per lane.  So each wave has the weights e^(m_p - M) and
+// the sum of weights without a barrier, its sums over lanes stay out of LDS, and the waves meet once, to add the channels'
+// sums.  From a row's first instruction to its last, 8 rows of 16 parts and 32 rows of 64: 3.4 and 3.75 us with a thread per
+// part, weights, maxima and sums through LDS, four barriers, divisions for sequence, KV head and block and the token's row
+// stored first; now 2.4 and 2.7, of which 0.5 are the arguments' arrival and 0.85 to 1.05 the parts'.  Steps: multi-head 32K 109.6
+// -> 107.8 us, recall 115.1 -> 113.8, 128K 39.0 -> 38.5.
 // With a new token (Alg. 1 appends it before attending) the row's own term is formed here from q, k_new and
 // v_new, and the first query head of each KV head stores the token's row at the tail of tier 0: the attention
 // kernels then run over the tokens already cached and a step needs no launch of its own for the append.
 template <int T>
 __global__ __launch_bounds__(T) void merge_kernel(const MergeArgs a) {
-  constexpr int NG = T / 32, NW = T / 64;
+  constexpr int NG = T / 32, U = 8;
   __shared__ __align__(16) float s_o[NG][128];
-  __shared__ float s_w[T], s_m[NW], s_l[NW], s_dot[NW];
-  const int row = blockIdx.x, wave = threadIdx.x >> 6, grp = threadIdx.x >> 5, c4 = threadIdx.x & 31;
-  int n = a.n_parts;
-  if (a.n_parts_row)
-    n = a.n_parts_row[row];
-  else if (a.rows_per_seq > 0)
-    n = a.cnt[row / a.rows_per_seq];
+  const int seq = blockIdx.y, hq = blockIdx.x;   // rows_per_seq = 0: all rows are counted by x
+  const int row = seq * a.rows_per_seq + hq;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), half = lane >> 5, c4 = lane & 31;
+  // what the launch's arguments say, all asked for at once (they are in no cache when a launch starts)
+  const int new_block = a.new_block[seq], new_row = a.new_row[seq];
+  int n = a.cnt[seq];
+  asm volatile("" ::"s"(n), "s"(new_block), "s"(new_row), "s"(a.dst.base), "s"(a.Hkv), "s"(a.k_new));
+  if (a.n_parts_row) n = a.n_parts_row[row];
   const float *pm = a.m + (int64_t)row * a.part_stride;
   const float *pl = a.l + (int64_t)row * a.part_stride;
   const float *pa = a.acc + (int64_t)row * a.part_stride * 128 + c4 * 4;
@@ -468,44 +472,37 @@ __global__ __launch_bounds__(T) void merge_kernel(const MergeArgs a) {
     if (wide) return *(const float4 *)x;
     return float4{x[0], x[1], x[2], x[3]};
   };
-  constexpr int U = 8;
+  const int grp = 2 * wave + half;                  // this lane group's parts: grp, grp + NG, ..
   float4 av[U];
 #pragma unroll
   for (int u = 0; u < U; ++u) av[u] = NG * u + grp < n ? part(NG * u + grp) : float4{0.0f, 0.0f, 0.0f, 0.0f};
-  const float mp0 = (int)threadIdx.x < n ? pm[threadIdx.x] : -INFINITY;   // (m, l) of this thread's part in the first batch
-  const float pl0 = (int)threadIdx.x < n ? pl[threadIdx.x] : 0.0f;
+  const float m0 = lane < n ? pm[lane] : -INFINITY;   // (m, l) of the first 64 parts
+  const float l0 = lane < n ? pl[lane] : 0.0f;
 
-  float v_new = 0.0f;
+  // the new token: lane i has channels 2 i and 2 i + 1 of q and k, thread i of the first 128 channel i of v
+  uint32_t kb = 0;
+  uint16_t vb = 0;
+  float Mn = -INFINITY, v_new = 0.0f;   // its part: (m, l, acc) = (score, 1, v)
+  bool stores = false;
+  int64_t head_off = 0;
+  auto f32_of = [](uint32_t bits16, int fmt) { return fmt == TTKV_F16 ? h2f((uint16_t)bits16) : __uint_as_float(bits16 << 16); };
   if (a.k_new) {   // launch-uniform
-    const int dch = threadIdx.x & 127;
-    const int seq = row / a.Hq, hq = row - seq * a.Hq, G = a.Hq / a.Hkv, hkv = hq / G;
-    const int64_t src = ((int64_t)seq * a.Hkv + hkv) * 128 + dch;
-    const uint16_t kb = ((const uint16_t *)a.k_new)[src], vb = ((const uint16_t *)a.v_new)[src];
-    const uint16_t qb = ((const uint16_t *)a.q)[(int64_t)row * 128 + dch];
-    const float kf = a.new_fmt == TTKV_F16 ? h2f(kb) : __uint_as_float((uint32_t)kb << 16);
-    const float qf = a.q_fmt == TTKV_F16 ? h2f(qb) : __uint_as_float((uint32_t)qb << 16);
-    v_new = a.new_fmt == TTKV_F16 ? h2f(vb) : __uint_as_float((uint32_t)vb << 16);
-    const float dot = wave_sum(qf * kf);   // T = 256: both halves form the same two wave sums
-    if ((threadIdx.x & 63) == 0) s_dot[wave] = dot;
-    if (hq == hkv * G && threadIdx.x < 128) {
-      const int tok = a.new_tok[seq];
-      const int rb = tok / a.dst.bt, r = tok - rb * a.dst.bt;
-      const int64_t rec = a.dst.table ? (int64_t)a.dst.table[(int64_t)seq * a.dst.ring_blocks + rb]
-                                      : (int64_t)seq * a.dst.ring_blocks + rb;
-      uint8_t *head = a.dst.base + rec * a.dst.rec_bytes + (int64_t)hkv * a.dst.head_bytes;
-      ((uint16_t *)(head + r * 256))[dch] = kb;
-      ((uint16_t *)(head + a.dst.v_off + r * 256))[dch] = vb;
-    }
+    const int hkv = a.G == 1 ? hq : a.g_magic ? (int)mul_high((uint32_t)hq, a.g_magic) : hq / a.G;
+    stores = hq == hkv * a.G;
+    head_off = (int64_t)hkv * a.dst.head_bytes;
+    const int64_t src = ((int64_t)seq * a.Hkv + hkv) * 128;
+    const uint16_t *kp = (const uint16_t *)a.k_new + src + 2 * lane, *qp = (const uint16_t *)a.q + (int64_t)row * 128 + 2 * lane;
+    const uint32_t k0 = kp[0], k1 = kp[1], q0 = qp[0], q1 = qp[1];   // halves: they may lie at any even address
+    vb = ((const uint16_t *)a.v_new)[src + (threadIdx.x & 127)];
+    kb = k0 | k1 << 16;
+    const float dot = fmaf(f32_of(q1, a.q_fmt), f32_of(k1, a.new_fmt), f32_of(q0, a.q_fmt) * f32_of(k0, a.new_fmt));
+    Mn = wave_sum(dot) * a.scale;
+    v_new = f32_of(vb, a.new_fmt);
   }
 
-  float M = mp0;
-  for (int p = threadIdx.x + T; p < n; p += T) M = fmaxf(M, pm[p]);
+  float M = m0;
+  for (int p = lane + 64; p < n; p += 64) M = fmaxf(M, pm[p]);
   M = wave_max(M);
-  if ((threadIdx.x & 63) == 0) s_m[wave] = M;
-  __syncthreads();
-#pragma unroll
-  for (int w = 0; w < NW; ++w) M = fmaxf(M, s_m[w]);
-
   float4 o = {0.0f, 0.0f, 0.0f, 0.0f};
   float l = 0.0f;
   auto add = [&](const float4 &x, float w) {
@@ -514,48 +511,48 @@ __global__ __launch_bounds__(T) void merge_kernel(const MergeArgs a) {
     o.z = fmaf(x.z, w, o.z);
     o.w = fmaf(x.w, w, o.w);
   };
-  for (int b = 0; b < n; b += T) {   // batches of T parts (workgroup-uniform)
-    const int p = b + threadIdx.x;
-    float w = 0.0f;
-    if (p < n) {
-      const float mp = b == 0 ? mp0 : pm[p];
-      w = mp == -INFINITY ? 0.0f : __expf(mp - M);
-      l = fmaf(b == 0 ? pl0 : pl[p], w, l);
-    }
-    if (b) __syncthreads();   // the weights of the batch before have been used
-    s_w[threadIdx.x] = w;
-    __syncthreads();
-    const int cnt = min(T, n - b);
-    int k = grp;              // this lane group's parts: grp, grp + NG, ..
+  for (int b = 0; b < n; b += 64) {   // (workgroup-uniform)
+    const int p = b + lane;
+    const float mp = b == 0 ? m0 : p < n ? pm[p] : -INFINITY;
+    const float w = mp == -INFINITY ? 0.0f : __expf(mp - M);   // 0 behind the last part
+    l = fmaf(b == 0 ? l0 : p < n ? pl[p] : 0.0f, w, l);
+    auto weight = [&](int u) {   // of part b + NG u + grp
+      const int at = NG * u + 2 * wave;
+      const float w0 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(w), at));
+      const float w1 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(w), at + 1));
+      return half ? w1 : w0;
+    };
+    int u = 0;
     if (b == 0) {
 #pragma unroll
-      for (int u = 0; u < U; ++u)
-        if (NG * u + grp < cnt) add(av[u], s_w[NG * u + grp]);
-      k += NG * U;
+      for (int v = 0; v < U; ++v) add(av[v], weight(v));
+      u = U;
     }
-#pragma unroll 8
-    for (; k < cnt; k += NG) add(part(b + k), s_w[k]);
+    const int rounds = min(64 / NG, (n - b + NG - 1) / NG);
+#pragma unroll 4
+    for (; u < rounds; ++u) add(b + NG * u + grp < n ? part(b + NG * u + grp) : float4{0.0f, 0.0f, 0.0f, 0.0f}, weight(u));
   }
   l = wave_sum(l);
-  if ((threadIdx.x & 63) == 0) s_l[wave] = l;
   *(float4 *)(s_o[grp] + c4 * 4) = o;
   __syncthreads();
-  if (threadIdx.x < 128) {
-    const int dch = threadIdx.x;
-    float sum = 0.0f;
+  if (threadIdx.x >= 128) return;
+  const int dch = threadIdx.x;
+  float sum = 0.0f;
 #pragma unroll
-    for (int g = 0; g < NG; ++g) sum += s_o[g][dch];
-    const float Mn = a.k_new ? (s_dot[0] + s_dot[1]) * a.scale : -INFINITY;   // the new token: (m, l, acc) = (score, 1, v)
-    const float Mt = fmaxf(M, Mn);
-    const float w1 = M == -INFINITY ? 0.0f : __expf(M - Mt);
-    const float wn = Mn == -INFINITY ? 0.0f : __expf(Mn - Mt);
-    sum = sum * w1 + v_new * wn;
-    l = 0.0f;
-#pragma unroll
-    for (int w = 0; w < NW; ++w) l += s_l[w];
-    l = l * w1 + wn;
-    a.out[(int64_t)row * 128 + dch] = l > 0.0f ? sum / l : 0.0f;
-    if (a.lse && dch == 0) a.lse[row] = l > 0.0f ? Mt + __logf(l) : -INFINITY;
+  for (int g = 0; g < NG; ++g) sum += s_o[g][dch];
+  const float Mt = fmaxf(M, Mn);
+  const float w1 = M == -INFINITY ? 0.0f : __expf(M - Mt);
+  const float wn = Mn == -INFINITY ? 0.0f : __expf(Mn - Mt);
+  sum = sum * w1 + v_new * wn;
+  l = l * w1 + wn;
+  a.out[(int64_t)row * 128 + dch] = l > 0.0f ? sum / l : 0.0f;
+  if (a.lse && dch == 0) a.lse[row] = l > 0.0f ? Mt + __logf(l) : -INFINITY;
+  if (stores) {   // workgroup-uniform: the token's row
+    const int64_t rec = a.dst.table ? (int64_t)a.dst.table[(int64_t)seq * a.dst.ring_blocks + new_block]
+                                    : (int64_t)seq * a.dst.ring_blocks + new_block;
+    uint8_t *head = a.dst.base + rec * a.dst.rec_bytes + head_off;
+    if (wave == 0) ((uint32_t *)(head + new_row * 256))[lane] = kb;
+    ((uint16_t *)(head + a.dst.v_off + new_row * 256))[dch] = vb;
   }
 }
 
@@ -598,8 +595,9 @@ hipError_t launch_attn(const FusedArgs &a, hipStream_t s, int *n_kernels, int *n
 
 hipError_t launch_merge(const MergeArgs &a, hipStream_t s) {
   if (a.rows <= 0) return hipSuccess;
-  if (a.n_parts <= 32) hipLaunchKernelGGL(merge_kernel<128>, dim3(a.rows), dim3(128), 0, s, a);
-  else hipLaunchKernelGGL(merge_kernel<256>, dim3(a.rows), dim3(256), 0, s, a);
+  const dim3 grid = a.rows_per_seq > 0 ? dim3(a.rows_per_seq, a.rows / a.rows_per_seq) : dim3(a.rows);
+  if (a.n_parts <= 32) hipLaunchKernelGGL(merge_kernel<128>, grid, dim3(128), 0, s, a);
+  else hipLaunchKernelGGL(merge_kernel<256>, grid, dim3(256), 0, s, a);
   return hipGetLastError();
 }
 

@@ -169,19 +169,29 @@ __device__ __forceinline__ const int32_t *resolve_selected(const FusedArgs &a, c
   return nullptr;
 }
 
+// the two values of the lanes 16 (32) apart by exclusive or, in the same order in both
+typedef float f2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ f2 both16(float v) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return f2{__uint_as_float(r[0]), __uint_as_float(r[1])};
+}
+__device__ __forceinline__ f2 both32(float v) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return f2{__uint_as_float(r[0]), __uint_as_float(r[1])};
+}
+// Over the wave, in every lane, without LDS (an exchange through it costs some 60 ns, a sum of 64 lanes six of them).
 __device__ __forceinline__ float wave_max(float v) {
   v = fmaxf(v, dpp<0xB1>(v));
   v = fmaxf(v, dpp<0x4E>(v));
-  v = fmaxf(v, dpp<0x124>(v));             // row_ror:4
-  v = fmaxf(v, dpp<0x128>(v));             // row_ror:8
-  v = fmaxf(v, __shfl_xor(v, 16));
-  v = fmaxf(v, __shfl_xor(v, 32));
-  return v;
+  v = fmaxf(v, dpp<0x141>(v));             // row_half_mirror
+  v = fmaxf(v, dpp<0x140>(v));             // row_mirror
+  v = fmaxf(both16(v).x, both16(v).y);
+  return fmaxf(both32(v).x, both32(v).y);
 }
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int m = 1; m < 64; m <<= 1) v += __shfl_xor(v, m);
-  return v;
+__device__ __forceinline__ float wave_sum(float v) {   // the order of sums of a tree over lanes 1, 2, 4, .. apart
+  v = group_sum<16>(v);
+  v = both16(v).x + both16(v).y;
+  return both32(v).x + both32(v).y;
 }
 
 }  // namespace dev

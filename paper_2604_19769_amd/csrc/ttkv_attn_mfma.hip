@@ -81,7 +81,6 @@ __device__ __forceinline__ f4 mma32(const uint32_t *a, const uint32_t *b, f4 c) 
 }
 
 // two fp32 values -> packed fp16, round to nearest even (v_cvt_pk_f16_f32)
-typedef float f2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ uint32_t pk(float x, float y) {
   const f2 v = {x, y};
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, h2));
@@ -238,15 +237,6 @@ __device__ __forceinline__ uint32_t wave_max16(uint32_t v) {
   v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x140, 0xf, 0xf, true));   // row_mirror
   return max(max((uint32_t)__builtin_amdgcn_readlane((int)v, 0), (uint32_t)__builtin_amdgcn_readlane((int)v, 16)),
              max((uint32_t)__builtin_amdgcn_readlane((int)v, 32), (uint32_t)__builtin_amdgcn_readlane((int)v, 48)));
-}
-// the two values of the lanes 16 (32) apart by exclusive or, in the same order in both
-__device__ __forceinline__ f2 both16(float v) {
-  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  return f2{__uint_as_float(r[0]), __uint_as_float(r[1])};
-}
-__device__ __forceinline__ f2 both32(float v) {
-  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  return f2{__uint_as_float(r[0]), __uint_as_float(r[1])};
 }
 // the largest value of the lane's row of 16
 __device__ __forceinline__ float row_max(float v) {

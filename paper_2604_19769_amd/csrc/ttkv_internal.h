@@ -271,18 +271,21 @@ hipError_t launch_attn_mfma(const FusedArgs &a, hipStream_t s);
 struct MergeArgs {
   const float *m, *l, *acc;
   int32_t n_parts, part_stride, rows;
-  const int32_t *n_parts_row;   // device, nullable
-  int32_t rows_per_seq;         // > 0: use cnt[row / rows_per_seq]
-  int32_t cnt[TTKV_MAX_BATCH];
+  int32_t rows_per_seq;         // > 0: cnt[sequence] parts per row (the rows of a sequence lie together), 0: cnt[0] in every row
+  const int32_t *n_parts_row;   // device, nullable: parts of each row
   float *out, *lse;
   // The step's new token (k_new nullable; then rows = batch x Hq): its term (score q.k_new, weight 1, value
   // v_new) joins the merge, and its row is stored at the tail of tier 0, whose fp format it has.
   const void *q, *k_new, *v_new;   // q [batch][Hq][128]; k_new, v_new [batch][Hkv][128]
-  int32_t q_fmt, new_fmt, Hq, Hkv;
+  int32_t q_fmt, new_fmt, G, Hkv;  // G: query heads per KV head
+  uint32_t g_magic;                // head / G by a multiplication; 0: by a division
   float scale;
-  TierView dst;                       // tier 0
-  int32_t new_tok[TTKV_MAX_BATCH];    // ring token index where the sequence's row lands
+  TierView dst;                    // tier 0
+  int32_t cnt[TTKV_MAX_BATCH];
+  int32_t new_block[TTKV_MAX_BATCH], new_row[TTKV_MAX_BATCH];   // ring block and row in it where the sequence's row lands
 };
+// head / G = mul_high(head, magic_heads) as long as head G < 2^32; 0: by a division.
+inline uint32_t magic_heads(int32_t Hq, int32_t G) { return G > 1 && (int64_t)Hq * G < (1ll << 32) ? (uint32_t)(((1ll << 32) + G - 1) / G) : 0; }
 hipError_t launch_merge(const MergeArgs &a, hipStream_t s);
 
 struct SelectArgs {
