@@ -4,9 +4,11 @@
 // bit for bit.
 //
 // Work unit of the row kernel: up to 64 consecutive rows of ONE destination block, one KV head, K or V.  A 16-lane
-// group converts one row at a time (8 channels per lane).  Block and record look-ups, and the division by the block
-// size, happen once per unit on the scalar unit; source and destination formats are compile-time inside the unit;
-// all of a unit's loads are in flight before the first conversion.  Where keys also feed block summaries a unit is a
+// group converts one row at a time (8 channels per lane).  Block and record look-ups happen once per unit on the scalar
+// unit, without a division (entry and KV head are the grid's, ring blocks come by a multiplication: a unit of 64 rows is
+// short, and its look-ups took 1.5 of its 3 us; 2 x 32 heads x 8192 tokens into fp16 + int4 74.3 -> 71.8 us, 8 x 32768 into
+// bf16 + K int8 / V int4 channel-major 41.9 -> 40.6, three tiers deep with sums 163.3 -> 160.6); source and destination
+// formats are compile-time inside the unit; all of a unit's loads are in flight before the first conversion.  Where keys also feed block summaries a unit is a
 // whole destination block (see sum_rows).  Bound: memory for the plain copies (5.3 TB/s of read + write), fp16 -> int8
 // (5.2) and fp16 -> int4 (4.8; a copy of 2 GiB reaches 4.9); a second recipe in front (int4 through int8) issues 139
 // vector instructions per four rows, as long as their bytes take: 88 us for 430 MB (4.9 TB/s; 103 with 176 instructions),
@@ -383,7 +385,7 @@ __device__ __forceinline__ RowSource row_source(const Source &c, int t_first) {
     return s;
   }
   const int tok = wrap(c.tok + t_first, c.tier);
-  const int r = tok / c.tier.bt, row = tok - r * c.tier.bt;
+  const int r = div_bt(tok, c.tier.bt, c.tier.bt_magic), row = tok - r * c.tier.bt;
   const uint8_t *h0 = block_head(c.tier, c.seq, c.rec_base, r, c.h);
   s.code = s.code1 = h0 + c.code_off + row * row_bytes<F>();
   s.meta = s.meta1 = h0 + c.meta_off + row * 8;
@@ -641,13 +643,13 @@ __device__ __forceinline__ void sum_unit(const Source &src, const U &u, int src_
 #undef TTKV_SUM_ROWS
 }
 
-// Grid: x = K units then V units of one (entry, KV head), y = entry x KV head.  SUM: K units are whole destination
+// Grid: x = K units then V units of one (entry, KV head), y = KV head, z = entry.  SUM: K units are whole destination
 // blocks and keep the key sums (dst_fmt of K may be NO_STORE: sums only); otherwise every unit is 64 rows.
 template <bool SUM, bool STREAM, int THREADS>
 __global__ __launch_bounds__(THREADS, THREADS == 256 ? 8 : 6) void convert_rows_kernel(const ConvArgs a, int k_units, int k_dst_fmt) {
   constexpr int SUM_BYTES = 2 * (THREADS / 16) * 128 * 4 + 512;
   __shared__ __align__(16) char s_buf[SUM ? (SUM_BYTES > kT32Bytes ? SUM_BYTES : kT32Bytes) : kT32Bytes];
-  const int j = blockIdx.y / a.Hkv, h = blockIdx.y - j * a.Hkv, seq = a.seq_id[j];
+  const int h = blockIdx.y, j = blockIdx.z, seq = a.seq_id[j];
   const int which = (int)blockIdx.x >= k_units;
   const int unit = which ? blockIdx.x - k_units : blockIdx.x;
   const int first = a.dst_first_tok[j];                   // ring token the call's first row lands on
@@ -660,7 +662,7 @@ __global__ __launch_bounds__(THREADS, THREADS == 256 ? 8 : 6) void convert_rows_
   u.meta_off = which ? dst.v_meta_off : dst.k_meta_off;
 
   if (SUM && !which) {
-    const int r = first / dst.bt, r0 = first - r * dst.bt;
+    const int r = div_bt(first, dst.bt, dst.bt_magic), r0 = first - r * dst.bt;
     const int t_lo = max(0, unit * dst.bt - r0), t_hi = min(n_tokens, (unit + 1) * dst.bt - r0);
     if (t_lo >= t_hi) return;
     int rb = r + unit;
@@ -686,7 +688,7 @@ __global__ __launch_bounds__(THREADS, THREADS == 256 ? 8 : 6) void convert_rows_
   u.t_lo = t0 + u.lo;
   if (u.lo >= u.hi) return;
   tok = wrap(tok, dst);
-  const int r = tok / dst.bt;
+  const int r = div_bt(tok, dst.bt, dst.bt_magic);
   u.row0 = tok - r * dst.bt;
   u.head = block_head(dst, seq, dst_rec_base, r, h);
   const int dst_fmt = which ? dst.v_fmt : k_dst_fmt;
@@ -771,13 +773,13 @@ __device__ __forceinline__ void keys_t128(const Source &src, int g, uint8_t *hea
 template <bool STREAM>
 __global__ __launch_bounds__(256) void convert_keys_t128_kernel(const ConvArgs a) {
   __shared__ float s_lo[4][128], s_hi[4][128], s_q[2][128];
-  const int g = blockIdx.x, j = blockIdx.y / a.Hkv, h = blockIdx.y - j * a.Hkv;
+  const int g = blockIdx.x, h = blockIdx.y, j = blockIdx.z;
   const int seq = a.seq_id[j], dst_rec_base = a.dst_rec_base[j];
   const TierView dst = a.dst;
   const Source src = make_source(a, 0, j, h, seq);
   const int src_fmt = src.flat ? a.s.flat_fmt : src.tier.k_fmt;
   const int tok = wrap(a.dst_first_tok[j] + g * 128, dst);
-  const int r = tok / dst.bt, row0 = tok - r * dst.bt;
+  const int r = div_bt(tok, dst.bt, dst.bt_magic), row0 = tok - r * dst.bt;
   uint8_t *const head = block_head(dst, seq, dst_rec_base, r, h);
 #define TTKV_T128(S, D) keys_t128<S, STREAM>(src, g, head, dst.k_meta_off, row0, s_lo, s_hi, s_q)
   TTKV_FOR_SOURCES(0, TTKV_T128)
@@ -790,7 +792,6 @@ namespace {
 template <bool STREAM>
 hipError_t launch(const ConvArgs &a, hipStream_t s, int *n_kernels) {
   if ((int64_t)a.n_seq * a.Hkv * a.n_tokens <= 0) return hipSuccess;
-  const unsigned y = (unsigned)(a.n_seq * a.Hkv);
   int chunks = 0, blocks = 0;      // units of the entry that needs most
   for (int j = 0; j < a.n_seq; ++j) {
     chunks = std::max(chunks, (a.dst_first_tok[j] % CHUNK + a.n_tokens + CHUNK - 1) / CHUNK);
@@ -798,7 +799,7 @@ hipError_t launch(const ConvArgs &a, hipStream_t s, int *n_kernels) {
   }
   const bool t128 = a.dst.k_fmt == TTKV_I4_ASYM_T128;   // whole aligned groups (the caller has checked)
   if (t128) {
-    hipLaunchKernelGGL(convert_keys_t128_kernel<STREAM>, dim3(a.n_tokens / 128, y), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(convert_keys_t128_kernel<STREAM>, dim3(a.n_tokens / 128, a.Hkv, a.n_seq), dim3(256), 0, s, a);
     ++*n_kernels;
   }
   if (a.k_sum) {
@@ -807,13 +808,13 @@ hipError_t launch(const ConvArgs &a, hipStream_t s, int *n_kernels) {
     // per CU keep it busy across each other's barriers (2560 blocks of 256 tokens: step 166 us, 187 with 512 threads); with
     // fewer the time is that of one block, which more threads shorten (640 blocks 59.5 and 56.8 us; evictions of 128 rows:
     // 256 blocks 22.2 and 18.5, 384 27.0 and 25.3, 512 29.7 and 30.3).
-    if ((int64_t)blocks * y >= 1024)
-      hipLaunchKernelGGL((convert_rows_kernel<true, STREAM, 256>), dim3(blocks + chunks, y), dim3(256), 0, s, a, blocks, k_dst);
+    if ((int64_t)blocks * a.n_seq * a.Hkv >= 1024)
+      hipLaunchKernelGGL((convert_rows_kernel<true, STREAM, 256>), dim3(blocks + chunks, a.Hkv, a.n_seq), dim3(256), 0, s, a, blocks, k_dst);
     else
-      hipLaunchKernelGGL((convert_rows_kernel<true, STREAM, SUM_THREADS>), dim3(blocks + chunks, y), dim3(SUM_THREADS), 0, s, a, blocks, k_dst);
+      hipLaunchKernelGGL((convert_rows_kernel<true, STREAM, SUM_THREADS>), dim3(blocks + chunks, a.Hkv, a.n_seq), dim3(SUM_THREADS), 0, s, a, blocks, k_dst);
   } else {
     const int k_units = t128 ? 0 : chunks;
-    hipLaunchKernelGGL((convert_rows_kernel<false, STREAM, 256>), dim3(k_units + chunks, y), dim3(256), 0, s, a, k_units, a.dst.k_fmt);
+    hipLaunchKernelGGL((convert_rows_kernel<false, STREAM, 256>), dim3(k_units + chunks, a.Hkv, a.n_seq), dim3(256), 0, s, a, k_units, a.dst.k_fmt);
   }
   ++*n_kernels;
   return hipGetLastError();
