@@ -219,6 +219,13 @@ size_t ttkv_append_host_workspace_bytes(const ttkv_cache *c, int32_t tier, int32
 ttkv_status ttkv_tier_demote(ttkv_handle h, ttkv_cache *c, int32_t src_tier, int32_t max_blocks, void *workspace,
                              size_t ws_bytes, void *compute, void *copy);
 
+/* The whole eviction cascade (Alg. 1, last lines): what ttkv_tier_demote(h, c, t, 0, ..) does for t = 0 .. n_tiers - 2 in
+ * turn, with the same results, in as few launches as the blocks allow (a block that was in its tier before the cascade
+ * moves on in the same launch that brings the tier its new one).  workspace: that of the boundary into a pinned last tier,
+ * as for ttkv_tier_demote (NULL: stored by the kernels); unused otherwise.  The first boundary that is refused ends the
+ * cascade with its status; those before it have moved their blocks, the others none. */
+ttkv_status ttkv_evict(ttkv_handle h, ttkv_cache *c, void *workspace, size_t ws_bytes, void *compute, void *copy);
+
 /* One decode step of streaming attention (Alg. 1, Sec. 4.3) for every
  * sequence: partial (max, sum-exp, weighted V) over each part of every tier,
  * merged by log-sum-exp.

@@ -47,7 +47,8 @@ class ttkv_stats(C.Structure):
 EXPORTS = [
     "ttkv_create", "ttkv_destroy", "ttkv_get_stats", "ttkv_reset_stats", "ttkv_status_string", "ttkv_record_bytes",
     "ttkv_locate", "ttkv_workspace_bytes", "ttkv_demote_workspace_bytes", "ttkv_append_host_workspace_bytes",
-    "ttkv_count_parts", "ttkv_quantize_append", "ttkv_quantize_append_host", "ttkv_tier_demote", "ttkv_decode_attn",
+    "ttkv_count_parts", "ttkv_quantize_append", "ttkv_quantize_append_host", "ttkv_tier_demote", "ttkv_evict",
+    "ttkv_decode_attn",
     "ttkv_decode_step", "ttkv_decode_step_topk", "ttkv_decode_attn_noalloc",
     "ttkv_merge_partials", "ttkv_select_blocks", "ttkv_set_split", "ttkv_set_table_check",
 ]
@@ -103,6 +104,7 @@ def lib():
         L.ttkv_quantize_append.argtypes = [p, cp, i32, i32, p, p, i32, i64, i32, p]
         L.ttkv_quantize_append_host.argtypes = [p, cp, i32, i32, p, p, i32, i64, i32, p, sz, p]
         L.ttkv_tier_demote.argtypes = [p, cp, i32, i32, p, sz, p, p]
+        L.ttkv_evict.argtypes = [p, cp, p, sz, p, p]
         L.ttkv_decode_attn.argtypes = [p, cp, p, i32, p, p, p, p, i32, p, sz, i32, p, p]
         L.ttkv_decode_attn_noalloc.argtypes = [p, cp, p, i32, p, p, p, p, i32, p]
         L.ttkv_decode_step.argtypes = [p, cp, p, i32, p, p, i32, p, p, p, p, i32, p, sz, i32, p, p]
@@ -215,6 +217,10 @@ def ttkv_quantize_append_host(h, cache, tier, seq, k_src, v_src, src_fmt, n_toke
 def ttkv_tier_demote(h, cache, src_tier, max_blocks, workspace, ws_bytes, compute, copy):
     _check(lib().ttkv_tier_demote(h, C.byref(cache), src_tier, max_blocks, _p(workspace), ws_bytes, _p(compute),
                                   _p(copy)), "ttkv_tier_demote")
+
+
+def ttkv_evict(h, cache, workspace, ws_bytes, compute, copy):
+    _check(lib().ttkv_evict(h, C.byref(cache), _p(workspace), ws_bytes, _p(compute), _p(copy)), "ttkv_evict")
 
 
 def ttkv_decode_attn(h, cache, q, q_fmt, out, lse, sel_blocks, sel_count, sel_stride, workspace, ws_bytes, n_slots,

@@ -81,7 +81,7 @@ class TieredCache:
         self.ws = None
         self.ws_parts = 0
         self.demote_ws = None
-        self._demote_need = None          # per tier: bytes of staging ttkv_tier_demote wants (constant for a cache)
+        self._demote_need = None          # bytes of staging that evictions into a host tier want (constant for a cache)
         self._parts_age = None            # dense steps since the parts per row were last counted (None: never)
         self._until_evict = 0             # steps until some sequence's tier 0 can have filled (0: ask the library)
         self.sel_blocks = self.sel_count = self.sel_scratch = None
@@ -132,13 +132,11 @@ class TieredCache:
     def demote(self, overlap=True):
         """Cascade eviction through all tiers (Alg. 1, last lines)."""
         if self._demote_need is None:
-            self._demote_need = [B.ttkv_demote_workspace_bytes(self.c, t) for t in range(len(self.cfg) - 1)]
-        for t in range(len(self.cfg) - 1):
-            need = 0 if self.host_demote_direct else self._demote_need[t]
-            if need and (self.demote_ws is None or self.demote_ws.numel() < need):
-                self.demote_ws = torch.empty(need, dtype=torch.uint8, device=self.device)
-            B.ttkv_tier_demote(self.h, self.c, t, 0, self.demote_ws if need else None, need, self._compute(),
-                               self._copy(overlap))
+            self._demote_need = max([B.ttkv_demote_workspace_bytes(self.c, t) for t in range(len(self.cfg) - 1)], default=0)
+        need = 0 if self.host_demote_direct else self._demote_need
+        if need and (self.demote_ws is None or self.demote_ws.numel() < need):
+            self.demote_ws = torch.empty(need, dtype=torch.uint8, device=self.device)
+        B.ttkv_evict(self.h, self.c, self.demote_ws if need else None, need, self._compute(), self._copy(overlap))
 
     def _workspace(self, parts):
         if self.ws is None or parts > self.ws_parts or self.ws_slots != self.n_slots:

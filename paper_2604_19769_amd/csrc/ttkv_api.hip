@@ -816,110 +816,194 @@ ttkv_status ttkv_quantize_append_host(ttkv_handle hh, ttkv_cache *c, int32_t tie
                      workspace, ws_bytes, (hipStream_t)stream, true);
 }
 
-ttkv_status ttkv_tier_demote(ttkv_handle hh, ttkv_cache *c, int32_t src_tier, int32_t max_blocks, void *workspace,
-                             size_t ws_bytes, void *compute_, void *copy_) {
-  Handle *h = reinterpret_cast<Handle *>(hh);
-  if (!h) return TTKV_ERR_INVALID_ARG;
-  ttkv_status st = validate_cache(c, h->check_tables);
-  if (st != TTKV_OK) return st;
-  if (src_tier < 0 || src_tier + 1 >= c->n_tiers) return TTKV_ERR_INVALID_ARG;
-  ttkv_tier &S = c->tier[src_tier];
-  ttkv_tier &D = c->tier[src_tier + 1];
+}  // extern "C"
+
+// One tier boundary of an eviction (Alg. 1, last lines): the blocks that tier src gives to tier src + 1.
+namespace {
+struct Demotion {
+  int src;
+  Layout LS, LD;
+  bool to_host;       // through staging records and copies
+  bool host_direct;   // the kernels store into the pinned records (ordered on the compute stream like a device destination)
+  int touched;        // staging records per sequence
+  int nmove[TTKV_MAX_BATCH], rounds;   // blocks per sequence; the most of any
+};
+// Checks a boundary and counts its blocks; nothing is enqueued or changed.
+ttkv_status plan_demotion(const ttkv_cache *c, int32_t src_tier, int32_t max_blocks, void *workspace, size_t ws_bytes, Demotion &d) {
+  const ttkv_tier &S = c->tier[src_tier], &D = c->tier[src_tier + 1];
   if (S.mem != TTKV_MEM_DEVICE) return TTKV_ERR_UNSUPPORTED;
   if (is_fp(D.k_fmt) && D.k_fmt != S.k_fmt) return TTKV_ERR_UNSUPPORTED;
   if (is_fp(D.v_fmt) && D.v_fmt != S.v_fmt) return TTKV_ERR_UNSUPPORTED;
   if (D.k_fmt == TTKV_I4_ASYM_T128 && S.block_tokens % 128) return TTKV_ERR_UNSUPPORTED;   // whole token groups arrive
-  hipStream_t compute = (hipStream_t)compute_, copy = (hipStream_t)copy_;
-  const Layout LS = make_layout(S, c->n_kv_heads), LD = make_layout(D, c->n_kv_heads);
-  // host destination with a workspace: staging records + copies; without one the kernels store into the pinned
-  // records themselves (ordered on `compute` like a device destination)
-  const bool to_host = D.mem == TTKV_MEM_HOST_PINNED && workspace != nullptr;
-  const bool host_direct = D.mem == TTKV_MEM_HOST_PINNED && workspace == nullptr;
-  if (host_direct && D.block_table && !D.block_table_dev) return TTKV_ERR_INVALID_ARG;   // the kernels look the records up
-
-  // how many blocks each sequence moves; check every ring before touching anything
-  int nmove[TTKV_MAX_BATCH], rounds = 0;
+  d.src = src_tier;
+  d.LS = make_layout(S, c->n_kv_heads);
+  d.LD = make_layout(D, c->n_kv_heads);
+  d.to_host = D.mem == TTKV_MEM_HOST_PINNED && workspace != nullptr;
+  d.host_direct = D.mem == TTKV_MEM_HOST_PINNED && workspace == nullptr;
+  if (d.host_direct && D.block_table && !D.block_table_dev) return TTKV_ERR_INVALID_ARG;   // the kernels look the records up
+  d.rounds = 0;
   for (int b = 0; b < c->batch; ++b) {
     int64_t len = S.len[b];
     int n = 0;
     while (len >= S.capacity_tokens && (max_blocks <= 0 || n < max_blocks)) {
-      if (len < LS.bt) return TTKV_ERR_CAPACITY;
-      len -= LS.bt;
+      if (len < d.LS.bt) return TTKV_ERR_CAPACITY;
+      len -= d.LS.bt;
       ++n;
     }
-    nmove[b] = n;
-    rounds = std::max(rounds, n);
-    if (D.len[b] + (int64_t)n * LS.bt > ring_tokens(D)) return TTKV_ERR_CAPACITY;
+    d.nmove[b] = n;
+    d.rounds = std::max(d.rounds, n);
+    if (D.len[b] + (int64_t)n * d.LS.bt > ring_tokens(D)) return TTKV_ERR_CAPACITY;
   }
-  if (rounds == 0) return TTKV_OK;
-  const int touched = LS.bt / LD.bt + 2;
-  if (to_host && ws_bytes < (size_t)c->batch * touched * LD.rec_bytes) return TTKV_ERR_WORKSPACE;
-  if (to_host && (st = ensure_events(h)) != TTKV_OK) return st;
-
-  for (int round = 0; round < rounds; ++round) {
-    ConvArgs a{};
-    a.s.from_tier = 1;
-    a.s.src = make_view(S, LS);
-    a.Hkv = c->n_kv_heads;
-    a.n_tokens = LS.bt;
-    a.n_via = 0;
-    a.dst = to_host ? make_slot_view(D, LD, workspace, touched) : make_view(D, LD);
-    for (int b = 0; b < c->batch; ++b) {
-      if (round >= nmove[b]) continue;
-      const int j = a.n_seq++;
-      a.seq_id[j] = b;
-      a.s.src_first_tok[j] = (int32_t)(S.start[b] % ring_tokens(S));
-      a.s.src_rec_base[j] = (int32_t)((int64_t)b * S.ring_blocks);
-      const int64_t o = D.start[b] + D.len[b];  // ordinal of the first row written
-      if (to_host) {
-        a.dst_rec_base[j] = j * touched;
-        a.dst_first_tok[j] = (int32_t)(o % LD.bt);
-      } else {
-        a.dst_rec_base[j] = (int32_t)((int64_t)b * D.ring_blocks);
-        a.dst_first_tok[j] = (int32_t)(o % ring_tokens(D));
-      }
+  d.touched = d.LS.bt / d.LD.bt + 2;
+  if (d.rounds && d.to_host && ws_bytes < (size_t)c->batch * d.touched * d.LD.rec_bytes) return TTKV_ERR_WORKSPACE;
+  return TTKV_OK;
+}
+// The conversion of each moving sequence's oldest block (turn `round` of those that move several).
+void demotion_args(const ttkv_cache *c, const Demotion &d, int round, void *workspace, ConvArgs &a) {
+  const ttkv_tier &S = c->tier[d.src], &D = c->tier[d.src + 1];
+  a.s.from_tier = 1;
+  a.s.src = make_view(S, d.LS);
+  a.Hkv = c->n_kv_heads;
+  a.n_tokens = d.LS.bt;
+  a.dst = d.to_host ? make_slot_view(D, d.LD, workspace, d.touched) : make_view(D, d.LD);
+  for (int b = 0; b < c->batch; ++b) {
+    if (round >= d.nmove[b]) continue;
+    const int j = a.n_seq++;
+    a.seq_id[j] = b;
+    a.s.src_first_tok[j] = (int32_t)(S.start[b] % ring_tokens(S));
+    a.s.src_rec_base[j] = (int32_t)((int64_t)b * S.ring_blocks);
+    const int64_t o = D.start[b] + D.len[b];  // ordinal of the first row written
+    if (d.to_host) {
+      a.dst_rec_base[j] = j * d.touched;
+      a.dst_first_tok[j] = (int32_t)(o % d.LD.bt);
+    } else {
+      a.dst_rec_base[j] = (int32_t)((int64_t)b * D.ring_blocks);
+      a.dst_first_tok[j] = (int32_t)(o % ring_tokens(D));
     }
+  }
+  fill_summary(a, c, d.src + 1);
+}
+// A block of every sequence of `a` has moved (blocks = 1), or has not after all (-1).
+void move_blocks(Handle *h, ttkv_cache *c, const Demotion &d, const ConvArgs &a, int blocks) {
+  ttkv_tier &S = c->tier[d.src], &D = c->tier[d.src + 1];
+  for (int j = 0; j < a.n_seq; ++j) {
+    const int b = a.seq_id[j];
+    S.start[b] += blocks * d.LS.bt;
+    S.len[b] -= blocks * d.LS.bt;
+    D.len[b] += blocks * d.LS.bt;
+  }
+  h->stats.demotions += (uint64_t)(int64_t)(blocks * a.n_seq);
+}
+ttkv_status run_demotion(Handle *h, ttkv_cache *c, const Demotion &d, void *workspace, hipStream_t compute, hipStream_t copy) {
+  if (d.rounds == 0) return TTKV_OK;
+  ttkv_status st;
+  if (d.to_host && (st = ensure_events(h)) != TTKV_OK) return st;
+  ttkv_tier &D = c->tier[d.src + 1];
+  const Layout &LS = d.LS, &LD = d.LD;
+  for (int round = 0; round < d.rounds; ++round) {
+    ConvArgs a{};
+    demotion_args(c, d, round, workspace, a);
     int nk = 0;
-    fill_summary(a, c, src_tier + 1);
     TTKV_HIP(h, launch_convert(a, compute, &nk));
     h->stats.kernels += nk;
 
-    if (to_host) {
+    if (d.to_host) {
       TTKV_HIP(h, hipEventRecord(h->fence2, compute));
       TTKV_HIP(h, hipStreamWaitEvent(copy, h->fence2, 0));
-    }
-    for (int j = 0; j < a.n_seq; ++j) {
-      const int b = a.seq_id[j];
-      if (to_host) {
+      for (int j = 0; j < a.n_seq; ++j) {
+        const int b = a.seq_id[j];
         const int64_t o0 = D.start[b] + D.len[b];
         for (int64_t id = o0 / LD.bt; id <= (o0 + LS.bt - 1) / LD.bt; ++id) {
           const int lo = (int)std::max<int64_t>(o0 - id * LD.bt, 0);
           const int hi = (int)std::min<int64_t>(o0 + LS.bt - id * LD.bt, LD.bt);
           uint8_t *host_rec = (uint8_t *)D.data + record_of(D, b, id % D.ring_blocks) * LD.rec_bytes;
-          const uint8_t *dev_rec = (const uint8_t *)workspace + ((int64_t)j * touched + (id - o0 / LD.bt)) * LD.rec_bytes;
+          const uint8_t *dev_rec = (const uint8_t *)workspace + ((int64_t)j * d.touched + (id - o0 / LD.bt)) * LD.rec_bytes;
           st = copy_rows_to_host(h, LD, c->n_kv_heads, host_rec, dev_rec, lo, hi, copy);
           if (st != TTKV_OK) return st;
         }
       }
-      if (host_direct) h->stats.d2h_bytes += (uint64_t)LS.bt * (LD.kc + LD.km + LD.vc + LD.vm) * c->n_kv_heads;
-      S.start[b] += LS.bt;
-      S.len[b] -= LS.bt;
-      D.len[b] += LS.bt;
-      h->stats.demotions += 1;
     }
-    if (to_host && round + 1 < rounds) {
+    if (d.host_direct) h->stats.d2h_bytes += (uint64_t)a.n_seq * LS.bt * (LD.kc + LD.km + LD.vc + LD.vm) * c->n_kv_heads;
+    move_blocks(h, c, d, a, 1);
+    if (d.to_host && round + 1 < d.rounds) {
       // the staging records are reused by the next round: wait for the copies
       TTKV_HIP(h, hipEventRecord(h->fence2, copy));
       TTKV_HIP(h, hipStreamWaitEvent(compute, h->fence2, 0));
     }
   }
-  if (to_host) {
+  if (d.to_host) {
     // later compute work (and the next step's fetches on `copy`) must see the host records complete;
     // `copy` is ordered by itself, `compute` is released by this event
     TTKV_HIP(h, hipEventRecord(h->fence2, copy));
     TTKV_HIP(h, hipStreamWaitEvent(compute, h->fence2, 0));
   }
   return TTKV_OK;
+}
+}  // namespace
+
+extern "C" {
+
+ttkv_status ttkv_tier_demote(ttkv_handle hh, ttkv_cache *c, int32_t src_tier, int32_t max_blocks, void *workspace,
+                             size_t ws_bytes, void *compute, void *copy) {
+  Handle *h = reinterpret_cast<Handle *>(hh);
+  if (!h) return TTKV_ERR_INVALID_ARG;
+  ttkv_status st = validate_cache(c, h->check_tables);
+  if (st != TTKV_OK) return st;
+  if (src_tier < 0 || src_tier + 1 >= c->n_tiers) return TTKV_ERR_INVALID_ARG;
+  Demotion d;
+  st = plan_demotion(c, src_tier, max_blocks, workspace, ws_bytes, d);
+  return st != TTKV_OK ? st : run_demotion(h, c, d, workspace, (hipStream_t)compute, (hipStream_t)copy);
+}
+
+ttkv_status ttkv_evict(ttkv_handle hh, ttkv_cache *c, void *workspace, size_t ws_bytes, void *compute_, void *copy_) {
+  Handle *h = reinterpret_cast<Handle *>(hh);
+  if (!h) return TTKV_ERR_INVALID_ARG;
+  ttkv_status st = validate_cache(c, h->check_tables);
+  if (st != TTKV_OK) return st;
+  hipStream_t compute = (hipStream_t)compute_, copy = (hipStream_t)copy_;
+  // A boundary whose blocks do not depend on what the one before it moves waits for that one's launch and goes with it.
+  Demotion d[2];
+  ConvArgs args[2];
+  bool holds = false;        // d[0]'s blocks are counted as moved, their conversion (args[0]) is not enqueued yet
+  auto enqueue = [&](bool pair) -> ttkv_status {   // what is held, and args[1] with it
+    if (!holds) return TTKV_OK;
+    holds = false;
+    int nk = 0;
+    const hipError_t e = pair ? launch_convert_pair(args[0], args[1], compute, &nk) : launch_convert(args[0], compute, &nk);
+    if (e != hipSuccess) move_blocks(h, c, d[0], args[0], -1);
+    TTKV_HIP(h, e);
+    h->stats.kernels += nk;
+    return TTKV_OK;
+  };
+  for (int t = 0; t + 1 < c->n_tiers; ++t) {
+    Demotion &now = d[holds];
+    const bool host = c->tier[t + 1].mem == TTKV_MEM_HOST_PINNED;
+    st = plan_demotion(c, t, 0, host ? workspace : nullptr, ws_bytes, now);
+    if (st != TTKV_OK) {
+      const ttkv_status before = enqueue(false);
+      return before != TTKV_OK ? before : st;
+    }
+    if (now.rounds == 0) continue;
+    bool alone = now.rounds > 1 || host || (!holds && t + 2 == c->n_tiers);
+    if (holds && d[0].src + 1 == t)   // every block that moves on was in the tier before the other ones arrived
+      for (int b = 0; b < c->batch; ++b) alone |= now.nmove[b] && c->tier[t].len[b] - d[0].nmove[b] * d[0].LS.bt < now.LS.bt;
+    if (alone) {
+      if ((st = enqueue(false)) != TTKV_OK) return st;
+      if ((st = run_demotion(h, c, now, workspace, compute, copy)) != TTKV_OK) return st;
+      continue;
+    }
+    ConvArgs &a = args[holds];
+    a = ConvArgs{};
+    demotion_args(c, now, 0, nullptr, a);
+    if (!holds) {
+      holds = true;
+      move_blocks(h, c, now, a, 1);
+    } else {
+      if ((st = enqueue(true)) != TTKV_OK) return st;
+      move_blocks(h, c, now, a, 1);
+    }
+  }
+  return enqueue(false);
 }
 
 // The stream operations of one attention call -- the copy/compute chain of streaming attention (Sec. 4.3) -- behind

@@ -192,6 +192,8 @@ struct ConvArgs {
   float inv_bt;
 };
 hipError_t launch_convert(const ConvArgs &a, hipStream_t s, int *n_kernels);
+// Two conversions of which neither reads what the other writes, in one launch where that pays; else one after the other.
+hipError_t launch_convert_pair(const ConvArgs &a, const ConvArgs &b, hipStream_t s, int *n_kernels);
 
 // One launch of the fused attention kernel: up to TTKV_MAX_ENTRIES runs of tokens,
 // each belonging to one (tier, sequence), all passed by value (no per-step upload).  16 bytes per run, so that one

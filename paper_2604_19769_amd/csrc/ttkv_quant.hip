@@ -645,11 +645,12 @@ __device__ __forceinline__ void sum_unit(const Source &src, const U &u, int src_
 
 // Grid: x = K units then V units of one (entry, KV head), y = KV head, z = entry.  SUM: K units are whole destination
 // blocks and keep the key sums (dst_fmt of K may be NO_STORE: sums only); otherwise every unit is 64 rows.
+// With SUM a conversion that keeps no sums (beside one that does) has units of 64 rows for K and V.
 template <bool SUM, bool STREAM, int THREADS>
-__global__ __launch_bounds__(THREADS, THREADS == 256 ? 8 : 6) void convert_rows_kernel(const ConvArgs a, int k_units, int k_dst_fmt) {
+__device__ __forceinline__ void convert_rows(const ConvArgs &a, int k_units, int k_dst_fmt, bool sums, int j) {
   constexpr int SUM_BYTES = 2 * (THREADS / 16) * 128 * 4 + 512;
   __shared__ __align__(16) char s_buf[SUM ? (SUM_BYTES > kT32Bytes ? SUM_BYTES : kT32Bytes) : kT32Bytes];
-  const int h = blockIdx.y, j = blockIdx.z, seq = a.seq_id[j];
+  const int h = blockIdx.y, seq = a.seq_id[j];
   const int which = (int)blockIdx.x >= k_units;
   const int unit = which ? blockIdx.x - k_units : blockIdx.x;
   const int first = a.dst_first_tok[j];                   // ring token the call's first row lands on
@@ -661,7 +662,7 @@ __global__ __launch_bounds__(THREADS, THREADS == 256 ? 8 : 6) void convert_rows_
   u.code_off = which ? dst.v_off : 0;
   u.meta_off = which ? dst.v_meta_off : dst.k_meta_off;
 
-  if (SUM && !which) {
+  if (SUM && !which && sums) {
     const int r = div_bt(first, dst.bt, dst.bt_magic), r0 = first - r * dst.bt;
     const int t_lo = max(0, unit * dst.bt - r0), t_hi = min(n_tokens, (unit + 1) * dst.bt - r0);
     if (t_lo >= t_hi) return;
@@ -704,6 +705,24 @@ __global__ __launch_bounds__(THREADS, THREADS == 256 ? 8 : 6) void convert_rows_
   }
 #undef TTKV_ROW_UNIT
   if (dst_fmt == TTKV_I4_ASYM_G64_T32) store_t32<THREADS>(u, s_t32);
+}
+template <bool SUM, bool STREAM, int THREADS>
+__global__ __launch_bounds__(THREADS, THREADS == 256 ? 8 : 6) void convert_rows_kernel(const ConvArgs a, int k_units, int k_dst_fmt) {
+  convert_rows<SUM, STREAM, THREADS>(a, k_units, k_dst_fmt, true, blockIdx.z);
+}
+
+// Two conversions side by side (two boundaries of an eviction): the entries of the second follow those of the first.
+struct ConvPair {
+  ConvArgs a[2];
+  int32_t k_units[2], units[2];   // K units, K and V units
+  int32_t n_first;                // entries of the first one
+};
+template <bool SUM, int THREADS>
+__global__ __launch_bounds__(THREADS, THREADS == 256 ? 8 : 6) void convert_pair_kernel(const ConvPair c) {
+  const int i = (int)blockIdx.z >= c.n_first;
+  const ConvArgs &a = c.a[i];
+  if ((int)blockIdx.x >= c.units[i]) return;
+  convert_rows<SUM, true, THREADS>(a, c.k_units[i], a.dst.k_fmt, a.k_sum != nullptr, (int)blockIdx.z - (i ? c.n_first : 0));
 }
 
 // Keys of a tier whose int4 groups run over 128 consecutive tokens of one channel (Q_4bit's arithmetic with the
@@ -789,14 +808,22 @@ __global__ __launch_bounds__(256) void convert_keys_t128_kernel(const ConvArgs a
 }  // namespace
 
 namespace {
+// How a conversion is cut: units of the entry that needs most.
+struct Units {
+  int chunks, blocks;   // of 64 rows; whole destination blocks
+};
+Units units_of(const ConvArgs &a) {
+  Units u{0, 0};
+  for (int j = 0; j < a.n_seq; ++j) {
+    u.chunks = std::max(u.chunks, (a.dst_first_tok[j] % CHUNK + a.n_tokens + CHUNK - 1) / CHUNK);
+    u.blocks = std::max(u.blocks, (a.dst_first_tok[j] % a.dst.bt + a.n_tokens + a.dst.bt - 1) / a.dst.bt);
+  }
+  return u;
+}
 template <bool STREAM>
 hipError_t launch(const ConvArgs &a, hipStream_t s, int *n_kernels) {
   if ((int64_t)a.n_seq * a.Hkv * a.n_tokens <= 0) return hipSuccess;
-  int chunks = 0, blocks = 0;      // units of the entry that needs most
-  for (int j = 0; j < a.n_seq; ++j) {
-    chunks = std::max(chunks, (a.dst_first_tok[j] % CHUNK + a.n_tokens + CHUNK - 1) / CHUNK);
-    blocks = std::max(blocks, (a.dst_first_tok[j] % a.dst.bt + a.n_tokens + a.dst.bt - 1) / a.dst.bt);
-  }
+  const Units u = units_of(a);
   const bool t128 = a.dst.k_fmt == TTKV_I4_ASYM_T128;   // whole aligned groups (the caller has checked)
   if (t128) {
     hipLaunchKernelGGL(convert_keys_t128_kernel<STREAM>, dim3(a.n_tokens / 128, a.Hkv, a.n_seq), dim3(256), 0, s, a);
@@ -808,13 +835,13 @@ hipError_t launch(const ConvArgs &a, hipStream_t s, int *n_kernels) {
     // per CU keep it busy across each other's barriers (2560 blocks of 256 tokens: step 166 us, 187 with 512 threads); with
     // fewer the time is that of one block, which more threads shorten (640 blocks 59.5 and 56.8 us; evictions of 128 rows:
     // 256 blocks 22.2 and 18.5, 384 27.0 and 25.3, 512 29.7 and 30.3).
-    if ((int64_t)blocks * a.n_seq * a.Hkv >= 1024)
-      hipLaunchKernelGGL((convert_rows_kernel<true, STREAM, 256>), dim3(blocks + chunks, a.Hkv, a.n_seq), dim3(256), 0, s, a, blocks, k_dst);
+    if ((int64_t)u.blocks * a.n_seq * a.Hkv >= 1024)
+      hipLaunchKernelGGL((convert_rows_kernel<true, STREAM, 256>), dim3(u.blocks + u.chunks, a.Hkv, a.n_seq), dim3(256), 0, s, a, u.blocks, k_dst);
     else
-      hipLaunchKernelGGL((convert_rows_kernel<true, STREAM, SUM_THREADS>), dim3(blocks + chunks, a.Hkv, a.n_seq), dim3(SUM_THREADS), 0, s, a, blocks, k_dst);
+      hipLaunchKernelGGL((convert_rows_kernel<true, STREAM, SUM_THREADS>), dim3(u.blocks + u.chunks, a.Hkv, a.n_seq), dim3(SUM_THREADS), 0, s, a, u.blocks, k_dst);
   } else {
-    const int k_units = t128 ? 0 : chunks;
-    hipLaunchKernelGGL((convert_rows_kernel<false, STREAM, 256>), dim3(k_units + chunks, a.Hkv, a.n_seq), dim3(256), 0, s, a, k_units, a.dst.k_fmt);
+    const int k_units = t128 ? 0 : u.chunks;
+    hipLaunchKernelGGL((convert_rows_kernel<false, STREAM, 256>), dim3(k_units + u.chunks, a.Hkv, a.n_seq), dim3(256), 0, s, a, k_units, a.dst.k_fmt);
   }
   ++*n_kernels;
   return hipGetLastError();
@@ -824,6 +851,35 @@ hipError_t launch(const ConvArgs &a, hipStream_t s, int *n_kernels) {
 // Converts the rows and, where the destination keeps block summaries (a.k_sum), their key sums.
 hipError_t launch_convert(const ConvArgs &a, hipStream_t s, int *n_kernels) {
   return a.to_host ? launch<false>(a, s, n_kernels) : launch<true>(a, s, n_kernels);
+}
+
+// One launch takes as long as the slower of the two, where two launches take their sum and the gap between them (16 x 8 KV heads,
+// 128 rows of fp16 into int8 and of int8 into int4 with sums, 16.4 -> 12.8 us; without sums 39 x 16 heads 27.2 -> 23.1, 39 x 2
+// heads 14.4 -> 8.4).  With sums all its workgroups have 512 threads and 33 KB of LDS, three on a CU, which units without
+// sums do not need: up to 1024 workgroups, one round and a third, it pays (60 x 2 heads, 960 of them, 16.1 -> 12.8), beyond it
+// does not (24 x 8 heads, 1536: 15.2 -> 18.0; 56 x 16 heads 45.7 -> 65.7; with 256 threads 16.8 and 46.6).
+hipError_t launch_convert_pair(const ConvArgs &a, const ConvArgs &b, hipStream_t s, int *n_kernels) {
+  const bool turned = b.k_sum && !a.k_sum;   // the one with sums first: its workgroups take longest
+  ConvPair c{{turned ? b : a, turned ? a : b}, {}, {}, turned ? b.n_seq : a.n_seq};
+  bool apart = a.to_host || b.to_host;
+  for (int i = 0; i < 2; ++i) {
+    const Units u = units_of(c.a[i]);
+    c.k_units[i] = c.a[i].k_sum ? u.blocks : u.chunks;
+    c.units[i] = c.k_units[i] + u.chunks;
+    apart |= c.a[i].dst.k_fmt == TTKV_I4_ASYM_T128;
+  }
+  const dim3 grid(std::max(c.units[0], c.units[1]), a.Hkv, a.n_seq + b.n_seq);   // (one cache: as many KV heads in both)
+  const bool sums = a.k_sum || b.k_sum;
+  if (apart || (sums && (int64_t)grid.x * grid.y * grid.z > 1024)) {
+    const hipError_t e = launch_convert(a, s, n_kernels);
+    return e != hipSuccess ? e : launch_convert(b, s, n_kernels);
+  }
+  if (sums)
+    hipLaunchKernelGGL((convert_pair_kernel<true, SUM_THREADS>), grid, dim3(SUM_THREADS), 0, s, c);
+  else
+    hipLaunchKernelGGL((convert_pair_kernel<false, 256>), grid, dim3(256), 0, s, c);
+  ++*n_kernels;
+  return hipGetLastError();
 }
 
 }  // namespace ttkv
