@@ -28,8 +28,10 @@
 //   holds head c of tokens 4 kg .. 4 kg + 3 and the softmax is per column.  V rows like K's (int4 ones dequantized in packed
 //   fp16); a product with the identity matrix brings the tile from [token][channel] to [channel][token]: the fp32 result
 //   (exact) has lane (c, kg) holding channel-row c for tokens 4 kg .. 4 kg + 3, the A layout.  Two 16-token tiles feed
-//   one 32-deep product.  The zero points and scales ride along as a 4-channel V.  P is rounded to fp16 once and that
-//   rounded value is used for the row sum as well.
+//   one 32-deep product.  The zero points and scales ride along as a 4-channel V.  P meets V with 22 bits here too, as an
+//   fp16 number and its remainder, eight products per 32 tokens that cost no time beside the memory's (steps of fp16 alone,
+//   1 x 30K to 64 x 2K tokens, within 1 % either way); error against 64 bits, 2 x 8192 tokens: fp16 9.0e-5 -> 5e-7, bf16 9.1e-5
+//   -> 5e-7, 64 sequences of 1003 fp16 + up to 3072 int8 tokens 4.3e-5 -> 6e-6.
 //   Keys grouped over 128 tokens per channel have no channel groups; the token group's scales fold into the q operand,
 //   carried as fp16 rounded product + exact remainder (two products per step), rebuilt for every 64 tokens in flight.
 //
@@ -348,6 +350,10 @@ __device__ __forceinline__ void process_rows(const FusedArgs &a, const TierView 
 #pragma unroll
   for (int s = 0; s < 8; ++s) acc[s] = zero4;
   float m = -INFINITY, l = 0.0f, mcs = INFINITY;   // a token's weight: exp2(score cs + mcs)
+  // The weights carry 2^14: rounded to fp16 they keep their 11 bits down to 2^-28 of the largest one instead of 2^-14 (fp16's
+  // subnormals), so that the error does not grow with the tokens of an item, among which the largest weight is found.  As for
+  // the quantized tiers a reference beyond 4 million carries none, and f - mcs, the reference of the result, is exact.
+  float f = 0.0f;
   Splice sp;
   sp.init();
 
@@ -457,21 +463,23 @@ __device__ __forceinline__ void process_rows(const FusedArgs &a, const TierView 
     mt = fmaxf(mt, __shfl_xor(mt, 16));
     mt = fmaxf(mt, __shfl_xor(mt, 32));
     if (__any(mt > m)) {
-      const float mn = fmaxf(m, mt), alpha = __builtin_amdgcn_exp2f((m - mn) * cs);
-      mcs = -(mn * cs);
+#pragma clang fp contract(off)
+      const float mn = fmaxf(m, mt), r = mn * cs, was = f;
+      f = fabsf(r) < 4194304.0f ? 14.0f : 0.0f;
+      mcs = f - r;
+      const float alpha = __builtin_amdgcn_exp2f((m - mn) * cs + (f - was));
       l *= alpha;
       accz *= alpha;
 #pragma unroll
       for (int s = 0; s < 8; ++s) acc[s] *= alpha;
       m = mn;
     }
-    const h2 ones = {(_Float16)1.0f, (_Float16)1.0f};
 
     // ---- weighted V, two 16-token tiles per 32-deep product
     before_v();
 #pragma unroll
     for (int tp = 0; tp < NT; tp += 2) {
-      uint32_t pB[4];          // softmax weights of the pair, rounded to fp16: the B operand
+      uint32_t pB[4], pR[4];   // softmax weights of the pair, rounded to fp16, and their remainders: the B operands
       uint32_t vr[2][16];
 #pragma unroll
       for (int u = 0; u < 2; ++u) {
@@ -479,10 +487,13 @@ __device__ __forceinline__ void process_rows(const FusedArgs &a, const TierView 
         float p[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) p[i] = __builtin_amdgcn_exp2f(fmaf(S[tt][i], cs, mcs));
-        pB[2 * u] = pk(p[0], p[1]);
-        pB[2 * u + 1] = pk(p[2], p[3]);
-        l = __builtin_amdgcn_fdot2(as_h2(pB[2 * u]), ones, l, false);       // the row sum uses the rounded weights
-        l = __builtin_amdgcn_fdot2(as_h2(pB[2 * u + 1]), ones, l, false);
+        l += (p[0] + p[1]) + (p[2] + p[3]);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          const uint32_t w = pk(p[2 * i], p[2 * i + 1]);
+          pB[2 * u + i] = w;
+          pR[2 * u + i] = pk(p[2 * i] - half0(w), p[2 * i + 1] - half1(w));
+        }
 
 #pragma unroll
         for (int x = 0; x < NLV; ++x) unpack16<VF>(t.vw[tt][x], vr[u] + x * (16 / NLV), sp);
@@ -502,6 +513,7 @@ __device__ __forceinline__ void process_rows(const FusedArgs &a, const TierView 
         const f4 d0 = mma<VBF>(vr[0][2 * s], vr[0][2 * s + 1], id0, id1, zero4);
         const f4 d1 = mma<VBF>(vr[1][2 * s], vr[1][2 * s + 1], id0, id1, zero4);
         const uint32_t A[4] = {pk(d0[0], d0[1]), pk(d0[2], d0[3]), pk(d1[0], d1[1]), pk(d1[2], d1[3])};
+        acc[s] = mma32<false>(A, pR, acc[s]);
         acc[s] = mma32<false>(A, pB, acc[s]);
       }
       if constexpr (VF == TTKV_I4_ASYM_G64) {
@@ -510,6 +522,7 @@ __device__ __forceinline__ void process_rows(const FusedArgs &a, const TierView 
         const f4 d0 = mma<false>(t.vmeta[tp].x, t.vmeta[tp].y, id0, id1, zero4);
         const f4 d1 = mma<false>(t.vmeta[tp + 1].x, t.vmeta[tp + 1].y, id0, id1, zero4);
         const uint32_t A[4] = {pk(d0[0], d0[1]), pk(d0[2], d0[3]), pk(d1[0], d1[1]), pk(d1[2], d1[3])};
+        accz = mma32<false>(A, pR, accz);
         accz = mma32<false>(A, pB, accz);
       }
     }
@@ -607,15 +620,16 @@ __device__ __forceinline__ void process_rows(const FusedArgs &a, const TierView 
     z = (kg >> 1) ? fmaf(8.0f, accz[2], accz[3]) : fmaf(8.0f, accz[0], accz[1]);
   float (*w_acc)[128] = (float (*)[128])wbuf;   // [head][channel]; the wave's last batch has been consumed
   if (n < Gr) {
+    const float unscale = f == 0.0f ? 1.0f : 0x1p-14f;
 #pragma unroll
     for (int s = 0; s < 8; ++s)
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        w_acc[n][slice_channel<VF>(kg, chan<VF>(s, i))] = acc[s][i] + z;
+        w_acc[n][slice_channel<VF>(kg, chan<VF>(s, i))] = (acc[s][i] + z) * unscale;
       }
     if (kg == 0) {
-      ((float *)(wbuf + kSumsLds))[n] = m * cs;
-      ((float *)(wbuf + kSumsLds))[16 + n] = l;
+      ((float *)(wbuf + kSumsLds))[n] = f - mcs;
+      ((float *)(wbuf + kSumsLds))[16 + n] = l * unscale;
     }
   }
 }
@@ -1419,9 +1433,9 @@ __device__ __forceinline__ void process_quant(const FusedArgs &a, const TierView
 // HS: places for heads (QuantShape).
 enum LaunchKind { FP_ONLY, WITH_INT8, WITH_4BIT, WITH_T128 };
 // Key formats that stay with the vector kernel's head pairs when keys grouped over tokens are in the same launch: those
-// have fp32 weights, where process_rows rounds the weights of the grouped keys to 16 bits.  Error against 64 bits and time of
-// 2 sequences of 8192 tokens of the format and 16384 of grouped keys, pairs and matrix cores: 16 / 2 heads, int8 3.0e-5 in
-// 35.6 us, 1.5e-4 in 16.8; 32 / 2 heads 2.9e-5 in 54.9, 1.7e-4 in 18.4, int4 4.0e-5 in 55.3, 1.7e-4 in 16.8.  Launches that
+// have fp32 values, where process_rows rounds code x scale of the values beside grouped keys to 16 bits.  Error against 64
+// bits and time of 2 sequences of 8192 tokens of the format and 16384 of grouped keys, pairs and matrix cores: 16 / 2 heads, int8
+// 3.7e-5 in 32.4 us, 1.4e-4 in 15.1; 32 / 2 heads 3.8e-5 in 51.9, 1.3e-4 in 16.9, int4 4.0e-5 in 52.0, 1.9e-4 in 16.5.  Launches that
 // took the matrix cores before there was a faster way for all of them stay there.
 constexpr bool pairs_beside_t128(int k_fmt, int G) { return (k_fmt == TTKV_I8_SYM_G32 && G > 4) || (k_fmt == TTKV_I4_ASYM_G64 && G > 8); }
 constexpr int waves_per_simd(int kind) { return kind == FP_ONLY || kind == WITH_INT8 ? 3 : 2; }
