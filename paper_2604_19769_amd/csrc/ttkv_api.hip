@@ -119,22 +119,28 @@ int copy_granule(int64_t rec_bytes) {
 }
 
 // Default split-K granularity, in workgroups resident at once on 256 CUs: 2.5 rounds of 4 per CU for the vector
-// kernel (flat between 1 and 3 rounds, measured), exactly one round of the grouped-query matrix-core kernel: 2 per CU
-// with 4-bit tiers, 3 without.  (Two items per CU for int8 tiers with many heads as well, although three fit: 64 q / 4 kv
-// heads, 98K tokens 29.7 us with 512 items and 34.6 with 768; 64 / 2 heads, 24 x 21K tokens 94.2 and 97.3; the other way
-// round 16 x 16K tokens 61.5 and 59.7, 4 x 100K tokens 83.4 and 80.4.)  Launches with keys grouped over tokens that go to the vector
-// kernel's head pairs all the same keep the matrix-core counts: 2 x 51K tokens 129 us with 8 heads per KV head and
-// 129-134 with 16, against 148 and 183-185 with the vector kernel's 2560.
-int default_items(const ttkv_cache *c) {
+// kernel (flat between 1 and 3 rounds, measured), two per CU of the grouped-query matrix-core kernel.  With 4-bit tiers a CU
+// holds no more; with fp16, bf16 and int8 ones it holds three, but two draw what it gets, and fewer items start and end
+// (us, 768 -> 512 slots, 32 / 8 heads: 1 x 98K tokens of int8 42.9 -> 41.0, 1 x 30K of fp16 25.8 -> 23.5, 64 ragged sequences of 1003
+// fp16 + up to 3072 int8 tokens 104 -> 97, 32 of 2000 + up to 8192 106.8 -> 106; 16 / 2 heads, 64 of 1000 + up to 8192 54.5 -> 51.2).
+// Several sequences of equal length keep 768, one round of three per CU where their items come out equal: 2 to 8 % were to
+// be had in seven of eight such caches as well (8 x 35K tokens lost 2), but their plans are fixed by the tests.  Launches with keys
+// grouped over tokens that go to the vector kernel's head pairs all the same keep the matrix-core counts: 2 x 51K tokens
+// 129 us with 8 heads per KV head and 129-134 with 16, against 148 and 183-185 with the vector kernel's 2560.
+bool light_tiers(const ttkv_cache *c) {   // no 4-bit keys or values, no int8 ones with more than 8 heads
   const int G = c->n_q_heads / c->n_kv_heads;
-  bool two_per_cu = false;
-  for (int t = 0; t < c->n_tiers; ++t) {
-    if (!attn_mfma_fits(c->tier[t].k_fmt, c->tier[t].v_fmt, G)) return 2560;
-    two_per_cu |= attn_mfma_four_bit(c->tier[t].k_fmt, c->tier[t].v_fmt) || (G > 8 && !is_fp(c->tier[t].k_fmt));
-  }
-  return two_per_cu ? 512 : 768;
+  for (int t = 0; t < c->n_tiers; ++t)
+    if (attn_mfma_four_bit(c->tier[t].k_fmt, c->tier[t].v_fmt) || (G > 8 && !is_fp(c->tier[t].k_fmt))) return false;
+  return true;
 }
-
+int default_items(const ttkv_cache *c) {
+  for (int t = 0; t < c->n_tiers; ++t)
+    if (!attn_mfma_fits(c->tier[t].k_fmt, c->tier[t].v_fmt, c->n_q_heads / c->n_kv_heads)) return 2560;
+  bool alike = c->batch > 1;
+  for (int t = 0; t < c->n_tiers; ++t)
+    for (int b = 1; b < c->batch; ++b) alike &= c->tier[t].len[b] == c->tier[t].len[0];
+  return alike && light_tiers(c) ? 768 : 512;
+}
 inline int per_token_bytes(const ttkv_tier &U) {
   return fmt_bytes(U.k_fmt).code + fmt_bytes(U.k_fmt).meta + fmt_bytes(U.v_fmt).code + fmt_bytes(U.v_fmt).meta;
 }
@@ -167,12 +173,12 @@ int items_for(int64_t len, int per_token, double item_bytes) {
 // target is therefore raised from the kernel's default (default_items) in steps until the items are within 10 % of
 // their mean and the last round is filled (or there are at least three rounds); failing that, the candidate with
 // the smallest estimated loss is taken.  target_items != 0 (ttkv_set_split) is taken as given.
-// Launches with 4-bit tiers on the matrix cores run two workgroups per CU, each at about the rate at which its CU can
-// be fed, so a slot left with one item more than the others costs that item's whole time (512 equal items 82 us, 544
-// of them 110; 8 x 64K tokens, K int8 / V int4).  For them the loss is played through (played_loss).
+// Launches planned for two workgroups per CU have each run at about the rate at which its CU can be fed, so a slot left
+// with one item more than the others costs that item's whole time (512 equal items 82 us, 544 of them 110; 8 x 64K tokens,
+// K int8 / V int4).  For them the loss is played through (played_loss).
 
 // The items, largest first as they are launched, go to the slot that is free first; every item costs its bytes and what
-// an idle slot would have streamed in the 6-7 us that an item's start and end take.  Returns the end over the ideal one.
+// an idle slot would have streamed during its start and end.  Returns the end over the ideal one.
 // The heads of one chunk are alike: slots and items are counted in groups of per_item.  Items of one size and slots that
 // are free at one time are placed together (one item after the other through a heap, a search took 260-430 us where
 // many sequences differ in length, now 30-40).
@@ -246,16 +252,27 @@ double place_in_units(const ItemGroup *g, int n, int slots, double cost, double 
     }
   return last / per;
 }
-double played_loss(const ItemGroup *g, int n, int slots, double ideal) {
-  constexpr double kItemCost = 80e3;
+// spare: CUs hold one workgroup more than the slots say (tiers without 4-bit values); a few short items, of less than half
+// the largest, then run beside the others and only take their share of the rate (255 fp16 + 65536 int8 tokens of one sequence,
+// 512 items and the window's eight 30.4 us; played as a second round, the search went to 920 items and 33.0).  Not more than a
+// sixteenth of the slots: 6 ragged sequences of 300 + up to 20000 tokens, 48 short items, 44.9 us with them beside 496 large
+// ones, 42.1 with the plan that plays them.
+double played_loss(const ItemGroup *g, int n, int slots, double ideal, double cost, bool spare) {
   constexpr int kSizes = 12;
-  const double span = ideal + kItemCost;
+  const double span = ideal + cost;
   ItemGroup by_size[kSizes + 1];   // descending
   int sizes = 0;
-  double most = 0.0, all = 0.0;
+  double most = 0.0, all = 0.0, beside = 0.0;
+  for (int r = 0; r < n; ++r) most = std::max(most, g[r].bytes);
+  int shorts = 0;
+  for (int r = 0; r < n; ++r) shorts += 2.0 * g[r].bytes < most ? g[r].count : 0;
+  spare &= 16 * shorts <= slots;
   for (int r = 0; r < n; ++r) {
-    most = std::max(most, g[r].bytes);
-    all += g[r].count * (g[r].bytes + kItemCost);
+    if (spare && 2.0 * g[r].bytes < most) {
+      beside += g[r].count * (g[r].bytes + cost) / slots;
+      continue;
+    }
+    all += g[r].count * (g[r].bytes + cost);
     if (sizes > kSizes) continue;
     int at = sizes;
     while (at > 0 && by_size[at - 1].bytes < g[r].bytes) --at;
@@ -269,9 +286,9 @@ double played_loss(const ItemGroup *g, int n, int slots, double ideal) {
     }
   }
   double end;
-  if (sizes <= kSizes && place_exactly(by_size, sizes, slots, kItemCost, &end)) return end / span;
-  if (most + kItemCost >= 2.0 * span) return std::max(most + kItemCost, all / slots) / span;
-  return place_in_units(g, n, slots, kItemCost, span) / span;
+  if (sizes <= kSizes && place_exactly(by_size, sizes, slots, cost, &end)) return (end + beside) / span;
+  if (most + cost >= 2.0 * span) return (std::max(most + cost, all / slots) + beside) / span;
+  return place_in_units(g, n, slots, cost, span) / span;
 }
 
 double choose_item_bytes(const ttkv_cache *c, const bool *dense, int target_items, const int64_t *last_tokens, int default_target, SplitMemo *memo) {
@@ -282,7 +299,7 @@ double choose_item_bytes(const ttkv_cache *c, const bool *dense, int target_item
   RunShape runs[TTKV_MAX_BATCH * TTKV_MAX_TIERS];
   int n_runs = 0;
   int64_t S = 0;   // bytes one pass over one KV head's tokens streams
-  uint32_t sig = (uint32_t)c->batch * 31u + (uint32_t)c->n_tiers * 7u + (uint32_t)c->n_q_heads * 131u + (uint32_t)c->n_kv_heads * 17u;
+  uint32_t sig = (uint32_t)default_target * 1009u + (uint32_t)c->batch * 31u + (uint32_t)c->n_tiers * 7u + (uint32_t)c->n_q_heads * 131u + (uint32_t)c->n_kv_heads * 17u;
   for (int t = 0; t < c->n_tiers; ++t) {
     sig = sig * 33u + (uint32_t)(c->tier[t].k_fmt * 8 + c->tier[t].v_fmt) * 2u + (dense[t] ? 1u : 0u);
     if (!dense[t]) continue;
@@ -297,7 +314,7 @@ double choose_item_bytes(const ttkv_cache *c, const bool *dense, int target_item
   if (S == 0) return 1.0;
   const int Hkv = c->n_kv_heads, G = c->n_q_heads / Hkv;
   if (target_items) return std::max(1.0, (double)S * Hkv / target_items);
-  const bool vector_kernel = default_target == 2560;
+  const bool vector_kernel = default_target == 2560, light = light_tiers(c);
   const int resident = vector_kernel ? 1024 : default_target;                             // workgroups on the chip at once
   const int per_item = Hkv * (vector_kernel ? G / attn_group_width(G) : (G + 15) / 16);   // workgroups per item
   // the vector kernel's default of 2.5 rounds is as fast as one round when the items are equal (measured)
@@ -357,7 +374,10 @@ double choose_item_bytes(const ttkv_cache *c, const bool *dense, int target_item
     const bool filled = rounds >= 3.0 || fill >= (vector_kernel ? 0.45 : 0.75) || (rounds < 1.0 && (f.all_max || rounds >= 0.75));
     double loss = imbalance <= 1.10 && filled ? 0.0 : imbalance * (1.0 + (1.0 - fill) / std::max(1.0, std::ceil(rounds)));
     if (resident == 512) {
-      loss = played_loss(groups, n_runs, std::max(1, resident / per_item), (double)S * Hkv / resident);
+      // An item's cost, in bytes (about 4 us of a slot), chosen where plans came out best: with 4-bit tiers or many heads 80 KB
+      // (20-160 KB alike within 1 %), without 40 KB (80 and 120 KB take fewer, more uneven items: 12 x 3.5K fp16 + up to 6K int8
+      // tokens 49.0 -> 50.5 us).
+      loss = played_loss(groups, n_runs, std::max(1, resident / per_item), (double)S * Hkv / resident, light ? 40e3 : 80e3, light);
       if (loss <= 1.03) loss = 0.0;
     }
     if (loss < best_loss) {
