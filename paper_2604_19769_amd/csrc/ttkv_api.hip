@@ -1397,6 +1397,8 @@ static ttkv_status enqueue_select(Handle *h, const ttkv_cache *c, const void *q,
   a.ring_blocks = (int32_t)T.ring_blocks;
   a.Hq = c->n_q_heads;
   a.Hkv = c->n_kv_heads;
+  a.G = c->n_q_heads / c->n_kv_heads;
+  a.g_magic = magic_heads(a.Hq, a.G);
   a.k = std::min(k, sel_stride);
   a.sel_stride = sel_stride;
   a.n_seq = c->batch;

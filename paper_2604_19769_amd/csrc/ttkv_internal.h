@@ -296,6 +296,8 @@ struct SelectArgs {
   const uint16_t *k_summary;
   const int32_t *table;          // device block table of the last tier or nullptr
   int32_t ring_blocks, Hq, Hkv, k, sel_stride, n_seq;
+  int32_t G;                     // query heads per KV head
+  uint32_t g_magic;              // head / G by a multiplication; 0: by a division
   int32_t rec_base[TTKV_MAX_BATCH];
   int32_t first_block[TTKV_MAX_BATCH];   // ring index of the oldest live block
   int64_t first_block_id[TTKV_MAX_BATCH];  // its block id (Eq. 1)

@@ -1,0 +1,60 @@
+"""Block selection over numbers of live blocks at the edges of the two ranking kernels (up to 256 blocks ranks are counted, beyond
+it a radix select), of waves and of four; ties, NaN and both zeros; numbers of query heads that are no powers of two.  Scores,
+and so the selection, are defined bit for bit."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2604_19769_amd.cache import TierConfig, TieredCache
+
+pytestmark = pytest.mark.gpu
+
+
+def phi(q, mean, G):
+    """Per head a chain of fused multiply-adds over the channels in ascending order, then the heads in ascending order: in
+    float64 with one rounding per step (a product of two halves is exact in 32 bits, so the step rounds once)."""
+    s = np.zeros((mean.shape[0], q.shape[0]), np.float32)
+    m = np.repeat(mean, G, axis=1).astype(np.float64)
+    for d in range(128):
+        s = (s.astype(np.float64) + q[None, :, d].astype(np.float64) * m[:, :, d]).astype(np.float32)
+    out = np.zeros(mean.shape[0], np.float32)
+    for h in range(q.shape[0]):
+        out = out + s[:, h]
+    return out
+
+
+@pytest.mark.parametrize("n", [1, 3, 4, 63, 64, 65, 127, 255, 256, 257, 700, 1024])
+@pytest.mark.parametrize("heads", [(8, 2), (14, 2), (5, 5), (72, 8)])
+@pytest.mark.parametrize("kind", ["ordinary", "ties", "special"])
+def test_ids_at_every_number_of_blocks(n, heads, kind):
+    Hq, Hkv = heads
+    g = np.random.default_rng(n + Hq)
+    mean = g.standard_normal((2 * n, Hkv, 128)).astype(np.float16)
+    if kind == "ties":
+        mean = mean[g.integers(0, max(1, n // 5), 2 * n)]
+    if kind == "special":
+        mean[::3] = 0.0
+        mean[1::7] = -0.0
+        mean[2::5, 0, 5] = np.nan
+        mean[4::11, 0, 9] = np.inf
+    q = g.standard_normal((2, Hq, 128)).astype(np.float16)
+    c = TieredCache(2, Hq, Hkv, [TierConfig("f16", "f16", 10**9, 64, 2), TierConfig("i8", "i8", 10**9, 64, n, paged_seed=3, summary=True)])
+    try:
+        lens = [64 * n, max(1, 64 * n - 64 * (n // 3) - 5)]
+        c.len[1][:] = lens
+        c.start[1][:] = [64 * 5 * n, 64 * (n - 1)]                     # rings that have moved on
+        c.kmu.view(2 * n, Hkv, 128).copy_(torch.from_numpy(mean).cuda())
+        for k in sorted({1, max(1, n // 2), n, n + 3}):
+            blocks, count = c.select(torch.from_numpy(q).cuda(), k)
+            for b in range(2):
+                first, end = int(c.start[1][b]) // 64, (int(c.start[1][b]) + lens[b] + 63) // 64
+                with np.errstate(all="ignore"):
+                    s = phi(q[b], mean[[c.table[1][b][i % n] for i in range(first, end)]], Hq // Hkv)
+                s[np.isnan(s)] = -np.inf
+                s[s == 0] = 0.0
+                want = np.sort(np.argsort(-s, kind="stable")[:k]) + first
+                assert int(count[b]) == len(want)
+                assert np.array_equal(blocks[b, :len(want)].numpy(), want), (k, b)
+    finally:
+        c.close()
+
