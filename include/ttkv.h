@@ -287,8 +287,8 @@ ttkv_status ttkv_decode_step(ttkv_handle h, ttkv_cache *c, const void *q, int32_
  * fp16/bf16 device tier of format new_fmt (UNSUPPORTED otherwise).
  *   sel_scratch [device] as for ttkv_select_blocks; it holds the ids until the call's kernels have run.
  *   sel_blocks_out [pinned] [batch][sel_stride], sel_count_out [pinned] [batch], or both NULL: copies of the
- *   chosen ids and counts for the caller's information, enqueued behind the attention; valid once `stream`
- *   has drained.
+ *   chosen ids and counts for the caller's information, stored by the attention launch or enqueued behind it;
+ *   the counts' first ids of each row are valid once `stream` has drained.
  * Same results as ttkv_select_blocks + ttkv_decode_step with its lists.  Enqueues on `stream` only and does
  * not block. */
 ttkv_status ttkv_decode_step_topk(ttkv_handle h, ttkv_cache *c, const void *q, int32_t q_fmt, const void *k_new,

@@ -1146,6 +1146,8 @@ static ttkv_status decode_impl(Handle *h, const ttkv_cache *c, const void *q, in
     const ttkv_tier &T = c->tier[c->n_tiers - 1];
     a.sel_ids = ds->ids;
     a.sel_stride = ds->stride;
+    a.host_ids = ds->host_ids;
+    a.host_count = ds->host_count;
     for (int b = 0; b < c->batch; ++b) {
       const int64_t live_end = T.start[b] + T.len[b];
       a.sel_last_ntok[b] = T.len[b] ? (int32_t)(live_end - (live_end - 1) / T.block_tokens * T.block_tokens) : 0;
@@ -1443,6 +1445,16 @@ ttkv_status ttkv_select_blocks(ttkv_handle hh, const ttkv_cache *c, const void *
   return TTKV_OK;
 }
 
+// Where kernels find page-locked host memory; null: they cannot (pageable memory, or no answer).
+static void *device_address(const void *host) {
+  hipPointerAttribute_t at{};
+  if (hipPointerGetAttributes(&at, host) != hipSuccess) {
+    (void)hipGetLastError();   // "not known to HIP" is no error of this call's
+    return nullptr;
+  }
+  return at.type == hipMemoryTypeHost ? at.devicePointer : nullptr;
+}
+
 ttkv_status ttkv_decode_step_topk(ttkv_handle hh, ttkv_cache *c, const void *q, int32_t q_fmt, const void *k_new,
                                   const void *v_new, int32_t new_fmt, float *out, float *lse, int32_t k,
                                   int32_t *sel_blocks_out, int32_t *sel_count_out, int32_t sel_stride, void *sel_scratch,
@@ -1469,18 +1481,24 @@ ttkv_status ttkv_decode_step_topk(ttkv_handle hh, ttkv_cache *c, const void *q, 
   }
   hipStream_t stream = (hipStream_t)stream_;
   // everything the attention call checks before it enqueues, first: nothing is enqueued on a refusal
-  DevSel probe{nullptr, k, sel_stride};
+  DevSel probe{nullptr, k, sel_stride, nullptr, nullptr};
   st = decode_impl(h, c, q, q_fmt, out, lse, nullptr, nullptr, 0, workspace, ws_bytes, 0, stream_, stream_, k_new, v_new, new_fmt,
                    true, &probe);
   if (st != TTKV_OK) return st;
   int32_t *sel_out = nullptr;
   st = enqueue_select(h, c, q, q_fmt, k, sel_stride, sel_scratch, sel_scratch_bytes, stream, &sel_out);
   if (st != TTKV_OK) return st;
-  const DevSel ds{sel_out + c->batch, k, sel_stride};
+  // The caller's copies of ids and counts: stored by the attention launch where its kernels can reach them (page-locked memory)
+  // and every sequence has a block in it, else copied behind it.
+  int32_t *host_ids = sel_blocks_out ? (int32_t *)device_address(sel_blocks_out) : nullptr;
+  int32_t *host_count = host_ids ? (int32_t *)device_address(sel_count_out) : nullptr;
+  bool stored = host_count && k > 0;
+  for (int b = 0; b < c->batch; ++b) stored &= TL.len[b] > 0;
+  const DevSel ds{sel_out + c->batch, k, sel_stride, stored ? host_ids : nullptr, host_count};
   st = decode_impl(h, c, q, q_fmt, out, lse, nullptr, nullptr, 0, workspace, ws_bytes, 0, stream_, stream_, k_new, v_new,
                    new_fmt, false, &ds);
   if (st != TTKV_OK) return st;
-  if (sel_blocks_out) {   // for the caller's information, behind the attention; valid once `stream` has drained
+  if (sel_blocks_out && !stored) {   // for the caller's information, behind the attention; valid once `stream` has drained
     TTKV_HIP(h, hipMemcpyAsync(sel_count_out, sel_out, (size_t)c->batch * sizeof(int32_t), hipMemcpyDeviceToHost, stream));
     TTKV_HIP(h, hipMemcpyAsync(sel_blocks_out, sel_out + c->batch, (size_t)c->batch * sel_stride * sizeof(int32_t),
                                hipMemcpyDeviceToHost, stream));

@@ -392,6 +392,7 @@ __global__ __launch_bounds__(256) void attn_fused_kernel(const FusedArgs a) {
   if (equal_items) chunk_tokens = even_chunk(en.len, (lo + 1 < a.n_entries ? a.start[lo + 1] : a.n_items) - item_start);
   const int part = en.part_base + item - item_start;   // this item's partial
   int chunk = item - item_start;
+  if ((en.flags & kEntrySelected) && a.host_ids && chunk == 0 && hq0 == 0) report_selected(a, tv, en, seq, equal_items);
   const int32_t *sel = resolve_selected(a, tv, en, seq, equal_items, chunk_tokens, chunk);
 
   const int combo = tv.k_fmt * 8 + tv.v_fmt;

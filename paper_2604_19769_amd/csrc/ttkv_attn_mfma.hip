@@ -1474,6 +1474,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(waves_per_s
   if (equal_items) chunk_tokens = even_chunk(en.len, n_even);
   const int part = en.part_base + item - item_start;   // this item's partial
   int chunk = item - item_start;
+  if ((en.flags & kEntrySelected) && a.host_ids && chunk == 0 && hq0 == 0) report_selected(a, tv, en, seq, equal_items);
   const int32_t *sel = resolve_selected(a, tv, en, seq, equal_items, chunk_tokens, chunk);
 
   constexpr bool K8 = KIND != WITH_T128 || !pairs_beside_t128(TTKV_I8_SYM_G32, HS), K4 = KIND != WITH_T128 || !pairs_beside_t128(TTKV_I4_ASYM_G64, HS);

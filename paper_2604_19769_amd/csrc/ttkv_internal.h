@@ -91,6 +91,7 @@ struct Run {
 struct DevSel {
   const int32_t *ids;
   int32_t k, stride;
+  int32_t *host_ids, *host_count;   // nullable: where the attention launch stores them for the caller
 };
 // One staged copy: consecutive pool records of a host tier brought into a slot.
 struct Fetch {
@@ -239,6 +240,7 @@ struct FusedArgs {
   Entry e[TTKV_MAX_ENTRIES];
   const int32_t *sel_ids;                    // device: block ids (Eq. 1) chosen by the top-k kernel [batch][sel_stride], for selected runs
   int32_t sel_last_ntok[TTKV_MAX_BATCH];     // live tokens in the newest block of the selected tier, per sequence
+  int32_t *host_ids, *host_count;            // nullable: the caller's copies of them in pinned memory ([batch][sel_stride], [batch])
 };
 static_assert(sizeof(FusedArgs) <= 4096, "kernel arguments are passed by value");
 static_assert(TTKV_MAX_ENTRIES % 16 == 0, "coarse");

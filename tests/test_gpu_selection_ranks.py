@@ -1,10 +1,13 @@
 """Block selection over numbers of live blocks at the edges of the two ranking kernels (up to 256 blocks ranks are counted, beyond
 it a radix select), of waves and of four; ties, NaN and both zeros; numbers of query heads that are no powers of two.  Scores,
-and so the selection, are defined bit for bit."""
+and so the selection, are defined bit for bit; the ids reach the caller's memory whether it is page-locked or not."""
+import ctypes as C
+
 import numpy as np
 import pytest
 import torch
 
+from paper_2604_19769_amd import binding as B
 from paper_2604_19769_amd.cache import TierConfig, TieredCache
 
 pytestmark = pytest.mark.gpu
@@ -58,3 +61,30 @@ def test_ids_at_every_number_of_blocks(n, heads, kind):
     finally:
         c.close()
 
+
+@pytest.mark.parametrize("pinned", [True, False])
+@pytest.mark.parametrize("heads", [(8, 2), (4, 4), (40, 2)])      # matrix cores, vector kernel, blocks of heads
+@pytest.mark.parametrize("lens", [(128 * 9, 128 * 4), (128 * 9, 0)])
+def test_ids_reach_the_callers_memory(heads, lens, pinned):
+    g = torch.Generator(device="cuda:0").manual_seed(5)
+    c = TieredCache(2, *heads, [TierConfig("f16", "f16", 10**9, 64, 8), TierConfig("i8", "i8", 10**9, 128, 10, summary=True)])
+    try:
+        for b in range(2):
+            for t, n in ((1, lens[b]), (0, 70)):
+                if n:
+                    k, v = (torch.randn(heads[1], n, 128, generator=g, device="cuda:0").half() for _ in range(2))
+                    c.append(t, k, v, seq=b)
+        q = torch.randn(2, heads[0], 128, generator=g, device="cuda:0").half()
+        kn, vn = (torch.randn(2, heads[1], 1, 128, generator=g, device="cuda:0").half() for _ in range(2))
+        k = 6
+        blocks, count = c.select(q, k)
+        want = [blocks[b, :int(count[b])].tolist() for b in range(2)]
+        assert [len(w) for w in want] == [min(k, n // 128) for n in lens]
+        c.sel_blocks = torch.full((2, k), -7, dtype=torch.int32, pin_memory=pinned)
+        c.sel_count = torch.full((2,), -7, dtype=torch.int32, pin_memory=pinned)
+        for _ in range(3):
+            c.step(q, kn, vn, select_k=k)
+            torch.cuda.synchronize()
+            assert [c.sel_blocks[b, :int(c.sel_count[b])].tolist() for b in range(2)] == want
+    finally:
+        c.close()
