@@ -136,12 +136,8 @@ def _check(status, what):
 
 
 def _p(x):
-    """Pointer of a torch tensor / int / None."""
-    if x is None:
-        return None
-    if isinstance(x, int):
-        return C.c_void_p(x)
-    return C.c_void_p(x.data_ptr())
+    """Pointer of a torch tensor / int / None, as ctypes takes it for a void* argument."""
+    return x if x is None or isinstance(x, int) else x.data_ptr()
 
 
 def ttkv_create():

@@ -23,6 +23,11 @@ class TierConfig:
     summary: bool = False      # keep mean-key summaries (block identification)
 
 
+_Q_FMT = {torch.float16: B.F16, torch.bfloat16: B.BF16}
+_SRC_FMT = {torch.float16: B.F16, torch.bfloat16: B.BF16, torch.float32: B.F32}
+# The current stream's handle without a torch.cuda.Stream object around it (2 us of a step's 14 on the host).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
 _SECTION_BYTES = {"f16": (256, 0), "bf16": (256, 0), "i8": (128, 8), "i4": (64, 8), "i4t": (64, 4), "i4c": (64, 8)}
 
 
@@ -96,7 +101,9 @@ class TieredCache:
 
     # ------------------------------------------------------------------ streams
     def _compute(self):
-        return torch.cuda.current_stream(self.device).cuda_stream
+        if _raw_stream is None or self.device.index is None:
+            return torch.cuda.current_stream(self.device).cuda_stream
+        return _raw_stream(self.device.index)
 
     def _copy(self, overlap=True):
         return self.copy_stream.cuda_stream if overlap else self._compute()
@@ -113,7 +120,7 @@ class TieredCache:
 
     def append(self, tier, k, v, seq=-1, through_tiers=False):
         """k, v: device tensors [B][Hkv][n][128] (seq=-1) or [Hkv][n][128], f16 / bf16 / f32."""
-        fmt = {torch.float16: B.F16, torch.bfloat16: B.BF16, torch.float32: B.F32}[k.dtype]
+        fmt = _SRC_FMT[k.dtype]
         assert k.is_contiguous() and v.is_contiguous() and k.shape == v.shape and k.dtype == v.dtype
         n = k.shape[-2]
         self._parts_age = None            # lengths jump: count the parts again at the next step
@@ -150,8 +157,8 @@ class TieredCache:
     def decode(self, q, selected=None, overlap=True, new=None):
         """q [B][Hq][128] f16/bf16 on the device.  selected: None or (sel_blocks, sel_count) pinned int32 tensors.
         new: None, or (k_new, v_new) [B][Hkv][1][128] of the step's token, appended to tier 0 by the same call."""
-        q_fmt = {torch.float16: B.F16, torch.bfloat16: B.BF16}[q.dtype]
-        assert q.is_contiguous() and tuple(q.shape) == (self.B, self.Hq, 128)
+        q_fmt = _Q_FMT[q.dtype]
+        assert q.is_contiguous() and q.shape == (self.B, self.Hq, 128)
         sb = sc = None
         stride = 0
         if selected is not None:
@@ -176,9 +183,9 @@ class TieredCache:
             self._parts_age = 0 if (selected is None and new is not None) else None
         if new is not None:
             k_new, v_new = new
-            fmt = {torch.float16: B.F16, torch.bfloat16: B.BF16}[k_new.dtype]
+            fmt = _Q_FMT[k_new.dtype]
             assert k_new.is_contiguous() and v_new.is_contiguous() and k_new.dtype == v_new.dtype
-            assert tuple(k_new.shape) == tuple(v_new.shape) == (self.B, self.Hkv, 1, 128)
+            assert k_new.shape == v_new.shape == (self.B, self.Hkv, 1, 128)
             try:
                 B.ttkv_decode_step(self.h, self.c, q, q_fmt, k_new, v_new, fmt, self.out, self.lse, sb, sc, stride, ws, ws.numel(),
                                    self.n_slots, self._compute(), self._copy(overlap))
@@ -193,7 +200,7 @@ class TieredCache:
         return self.out, self.lse
 
     def select(self, q, k):
-        q_fmt = {torch.float16: B.F16, torch.bfloat16: B.BF16}[q.dtype]
+        q_fmt = _Q_FMT[q.dtype]
         stride = self._select_buffers(k)
         B.ttkv_select_blocks(self.h, self.c, q, q_fmt, k, self.sel_blocks, self.sel_count, stride, self.sel_scratch,
                              self.sel_scratch.numel(), self._compute())
@@ -209,10 +216,10 @@ class TieredCache:
 
     def step_topk(self, q, k_new, v_new, k):
         """append -> identify + top-k + attend with the chosen ids left on the device (no host round trip)."""
-        q_fmt = {torch.float16: B.F16, torch.bfloat16: B.BF16}[q.dtype]
-        fmt = {torch.float16: B.F16, torch.bfloat16: B.BF16}[k_new.dtype]
+        q_fmt = _Q_FMT[q.dtype]
+        fmt = _Q_FMT[k_new.dtype]
         assert q.is_contiguous() and k_new.is_contiguous() and v_new.is_contiguous()
-        assert tuple(k_new.shape) == tuple(v_new.shape) == (self.B, self.Hkv, 1, 128)
+        assert k_new.shape == v_new.shape == (self.B, self.Hkv, 1, 128)
         stride = self._select_buffers(k)
         # The split of a selection is planned inside the call, which refuses a workspace that is too small for it before
         # anything is enqueued: the workspace is sized once from a dense plan's parts and grows when it is refused (no
