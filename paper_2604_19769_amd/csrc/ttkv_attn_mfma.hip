@@ -28,7 +28,7 @@
 //   holds head c of tokens 4 kg .. 4 kg + 3 and the softmax is per column.  V rows like K's (int4 ones dequantized in packed
 //   fp16); a product with the identity matrix brings the tile from [token][channel] to [channel][token]: the fp32 result
 //   (exact) has lane (c, kg) holding channel-row c for tokens 4 kg .. 4 kg + 3, the A layout.  Two 16-token tiles feed
-//   one 32-deep product.  The zero points and scales ride along as a 4-channel V.  P meets V with 22 bits here too, as an
+//   one 32-deep product.  The zero points and scales ride along as a 4-channel V.  P meets an fp16 / bf16 V with 22 bits, as an
 //   fp16 number and its remainder, eight products per 32 tokens that cost no time beside the memory's (steps of fp16 alone,
 //   1 x 30K to 64 x 2K tokens, within 1 % either way); error against 64 bits, 2 x 8192 tokens: fp16 9.0e-5 -> 5e-7, bf16 9.1e-5
 //   -> 5e-7, 64 sequences of 1003 fp16 + up to 3072 int8 tokens 4.3e-5 -> 6e-6.
@@ -291,6 +291,9 @@ __device__ __forceinline__ void process_rows(const FusedArgs &a, const TierView 
   constexpr bool VQ = n_groups<VF>() > 1;
   constexpr bool KT = KF == TTKV_I4_ASYM_T128;   // keys grouped over 128 tokens per channel: the scales fold into q
   constexpr bool KBF = KF == TTKV_BF16, VBF = VF == TTKV_BF16;
+  // Weights with their remainders; not beside grouped keys, whose values are rounded as they are dequantized: nothing would be
+  // gained (1.9e-4 either way), and that loop is bound by its instructions (3-4 % slower).
+  constexpr bool REST = !VQ;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n = lane & 15, kg = lane >> 4;
@@ -465,9 +468,9 @@ __device__ __forceinline__ void process_rows(const FusedArgs &a, const TierView 
     if (__any(mt > m)) {
 #pragma clang fp contract(off)
       const float mn = fmaxf(m, mt), r = mn * cs, was = f;
-      f = fabsf(r) < 4194304.0f ? 14.0f : 0.0f;
+      if constexpr (REST) f = fabsf(r) < 4194304.0f ? 14.0f : 0.0f;
       mcs = f - r;
-      const float alpha = __builtin_amdgcn_exp2f((m - mn) * cs + (f - was));
+      const float alpha = __builtin_amdgcn_exp2f(REST ? (m - mn) * cs + (f - was) : (m - mn) * cs);
       l *= alpha;
       accz *= alpha;
 #pragma unroll
@@ -487,12 +490,13 @@ __device__ __forceinline__ void process_rows(const FusedArgs &a, const TierView 
         float p[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) p[i] = __builtin_amdgcn_exp2f(fmaf(S[tt][i], cs, mcs));
-        l += (p[0] + p[1]) + (p[2] + p[3]);
+        if constexpr (REST) l += (p[0] + p[1]) + (p[2] + p[3]);
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
           const uint32_t w = pk(p[2 * i], p[2 * i + 1]);
           pB[2 * u + i] = w;
-          pR[2 * u + i] = pk(p[2 * i] - half0(w), p[2 * i + 1] - half1(w));
+          if constexpr (REST) pR[2 * u + i] = pk(p[2 * i] - half0(w), p[2 * i + 1] - half1(w));
+          else l = __builtin_amdgcn_fdot2(as_h2(w), h2{(_Float16)1.0f, (_Float16)1.0f}, l, false);   // the sum of the rounded weights
         }
 
 #pragma unroll
@@ -513,7 +517,7 @@ __device__ __forceinline__ void process_rows(const FusedArgs &a, const TierView 
         const f4 d0 = mma<VBF>(vr[0][2 * s], vr[0][2 * s + 1], id0, id1, zero4);
         const f4 d1 = mma<VBF>(vr[1][2 * s], vr[1][2 * s + 1], id0, id1, zero4);
         const uint32_t A[4] = {pk(d0[0], d0[1]), pk(d0[2], d0[3]), pk(d1[0], d1[1]), pk(d1[2], d1[3])};
-        acc[s] = mma32<false>(A, pR, acc[s]);
+        if constexpr (REST) acc[s] = mma32<false>(A, pR, acc[s]);
         acc[s] = mma32<false>(A, pB, acc[s]);
       }
       if constexpr (VF == TTKV_I4_ASYM_G64) {
@@ -522,7 +526,6 @@ __device__ __forceinline__ void process_rows(const FusedArgs &a, const TierView 
         const f4 d0 = mma<false>(t.vmeta[tp].x, t.vmeta[tp].y, id0, id1, zero4);
         const f4 d1 = mma<false>(t.vmeta[tp + 1].x, t.vmeta[tp + 1].y, id0, id1, zero4);
         const uint32_t A[4] = {pk(d0[0], d0[1]), pk(d0[2], d0[3]), pk(d1[0], d1[1]), pk(d1[2], d1[3])};
-        accz = mma32<false>(A, pR, accz);
         accz = mma32<false>(A, pB, accz);
       }
     }
@@ -620,7 +623,7 @@ __device__ __forceinline__ void process_rows(const FusedArgs &a, const TierView 
     z = (kg >> 1) ? fmaf(8.0f, accz[2], accz[3]) : fmaf(8.0f, accz[0], accz[1]);
   float (*w_acc)[128] = (float (*)[128])wbuf;   // [head][channel]; the wave's last batch has been consumed
   if (n < Gr) {
-    const float unscale = f == 0.0f ? 1.0f : 0x1p-14f;
+    const float unscale = !REST || f == 0.0f ? 1.0f : 0x1p-14f;
 #pragma unroll
     for (int s = 0; s < 8; ++s)
 #pragma unroll
@@ -1433,10 +1436,11 @@ __device__ __forceinline__ void process_quant(const FusedArgs &a, const TierView
 // HS: places for heads (QuantShape).
 enum LaunchKind { FP_ONLY, WITH_INT8, WITH_4BIT, WITH_T128 };
 // Key formats that stay with the vector kernel's head pairs when keys grouped over tokens are in the same launch: those
-// have fp32 values, where process_rows rounds code x scale of the values beside grouped keys to 16 bits.  Error against 64
-// bits and time of 2 sequences of 8192 tokens of the format and 16384 of grouped keys, pairs and matrix cores: 16 / 2 heads, int8
-// 3.7e-5 in 32.4 us, 1.4e-4 in 15.1; 32 / 2 heads 3.8e-5 in 51.9, 1.3e-4 in 16.9, int4 4.0e-5 in 52.0, 1.9e-4 in 16.5.  Launches that
-// took the matrix cores before there was a faster way for all of them stay there.
+// have fp32 weights, where process_rows rounds the weights of the grouped keys, and the values beside them, to 16 bits.  Error
+// against 64 bits and time of 2 sequences of 8192 tokens of the format and 16384 of grouped keys, pairs and matrix cores: 16 / 2
+// heads, int8 3.0e-5 in 35.6 us, 1.5e-4 in 16.8; 32 / 2 heads 2.9e-5 in 54.9, 1.7e-4 in 18.4, int4 4.0e-5 in 55.3, 1.7e-4 in 16.8
+// (with 22-bit weights still 1.3e-4 to 1.9e-4).  Launches that took the matrix cores before there was a faster way for all of
+// them stay there.
 constexpr bool pairs_beside_t128(int k_fmt, int G) { return (k_fmt == TTKV_I8_SYM_G32 && G > 4) || (k_fmt == TTKV_I4_ASYM_G64 && G > 8); }
 constexpr int waves_per_simd(int kind) { return kind == FP_ONLY || kind == WITH_INT8 ? 3 : 2; }
 // Two tiles' rows of queries (8 places), or three workgroups per CU with 16.
