@@ -154,10 +154,16 @@ int even_items(int len, int want) {
     n = n2;
   }
 }
+// The shortest items worth having: 256 tokens.  A launch of the matrix-core kernel that takes only some of the CUs (`few`) ends
+// a batch earlier with items of one batch for each of a workgroup's four waves, 128 tokens (64 x 4 with int4 keys): 2 x (500 fp16 +
+// 2048 int8) tokens, 16 / 4 heads, 160 items 11.0 -> 10.3 us, 1 x 4096 fp16, 32 / 8 heads, 256 items 11.2 -> 10.1.  Beyond one
+// workgroup per CU it is the other way round (1 x 12K fp16, 16 / 4 heads, 192 -> 376 items 11.4 -> 12.8; 12K of K8/V4 11.7 -> 14.6).
+int finest_item(const ttkv_tier &T, bool few) { return few && (is_fp(T.k_fmt) || T.k_fmt == TTKV_I8_SYM_G32) ? 128 : 256; }
+constexpr int kFewItems = 256;
 // Items for a run of `len` tokens of `per_token` bytes when an item should stream about item_bytes: at most 8192
-// tokens each, and no more items than 256-token ones would give.
-int items_for(int64_t len, int per_token, double item_bytes) {
-  const int64_t lo = (len + 8191) / 8192, hi = (len + 255) / 256;
+// tokens each, and no more items than ones of `finest` tokens would give.
+int items_for(int64_t len, int per_token, double item_bytes, int finest) {
+  const int64_t lo = (len + 8191) / 8192, hi = (len + finest - 1) / finest;
   const int64_t want = (int64_t)((double)len * per_token / item_bytes + 0.5);
   return even_items((int)len, (int)std::max(lo, std::min(hi, want)));
 }
@@ -291,11 +297,11 @@ double played_loss(const ItemGroup *g, int n, int slots, double ideal, double co
   return place_in_units(g, n, slots, cost, span) / span;
 }
 
-double choose_item_bytes(const ttkv_cache *c, const bool *dense, int target_items, const int64_t *last_tokens, int default_target, SplitMemo *memo) {
+double choose_item_bytes(const ttkv_cache *c, const bool *dense, int target_items, const int64_t *last_tokens, int default_target, bool few, SplitMemo *memo) {
   // default_target: default_items
   // last_tokens: null, or the tokens of the last tier that are attended, per sequence (its selected blocks)
   // The runs, gathered once: length and bytes per token (at most batch x tiers of them).
-  struct RunShape { int32_t len, per_token, finest; };
+  struct RunShape { int32_t len, per_token, finest, most; };   // tokens, bytes per token, tokens of the shortest item, items then
   RunShape runs[TTKV_MAX_BATCH * TTKV_MAX_TIERS];
   int n_runs = 0;
   int64_t S = 0;   // bytes one pass over one KV head's tokens streams
@@ -303,11 +309,11 @@ double choose_item_bytes(const ttkv_cache *c, const bool *dense, int target_item
   for (int t = 0; t < c->n_tiers; ++t) {
     sig = sig * 33u + (uint32_t)(c->tier[t].k_fmt * 8 + c->tier[t].v_fmt) * 2u + (dense[t] ? 1u : 0u);
     if (!dense[t]) continue;
-    const int pt = per_token_bytes(c->tier[t]);
+    const int pt = per_token_bytes(c->tier[t]), finest = finest_item(c->tier[t], few);
     for (int b = 0; b < c->batch; ++b) {
       const int64_t len = last_tokens && t == c->n_tiers - 1 ? last_tokens[b] : c->tier[t].len[b];
       if (len == 0) continue;
-      runs[n_runs++] = RunShape{(int32_t)len, pt, (int32_t)((len + 255) / 256)};
+      runs[n_runs++] = RunShape{(int32_t)len, pt, finest, (int32_t)((len + finest - 1) / finest)};
       S += len * pt;
     }
   }
@@ -337,13 +343,13 @@ double choose_item_bytes(const ttkv_cache *c, const bool *dense, int target_item
       f.largest = f.sum_b = f.sum_b2 = f.n_big = 0.0;
       f.all_max = true;
       for (int r = 0; r < n_runs; ++r) {
-        count[r] = items_for(runs[r].len, runs[r].per_token, f.b);
+        count[r] = items_for(runs[r].len, runs[r].per_token, f.b, runs[r].finest);
         item[r] = (double)even_chunk(runs[r].len, count[r]) * runs[r].per_token;
         groups[r] = ItemGroup{item[r], count[r]};
         f.sum_b += count[r] * item[r];
         f.sum_b2 += count[r] * item[r] * item[r];
         f.largest = std::max(f.largest, item[r]);
-        f.all_max &= count[r] >= runs[r].finest;
+        f.all_max &= count[r] >= runs[r].most;
       }
       bool all_min = true;   // every run in one item already: larger items change nothing
       for (int r = 0; r < n_runs; ++r) {
@@ -412,12 +418,21 @@ void build_plan(const ttkv_cache *c, const int32_t *sel_blocks, const int32_t *s
       sel_tokens[b] = std::max<int64_t>(0, std::min<int64_t>(std::min(ds->k, ds->stride), live)) * T.block_tokens;
     }
   P->resident_items = default_items(c);
-  const double item_bytes = choose_item_bytes(c, P->even, target_items, ds ? sel_tokens : nullptr, P->resident_items, &P->memo[ds != nullptr]);
+  const int heads = (c->n_q_heads / c->n_kv_heads + 15) / 16 * c->n_kv_heads;   // workgroups of an item on the matrix cores
+  int64_t shortest = 0;
+  for (int t = 0; t < c->n_tiers && shortest * heads <= kFewItems; ++t)
+    for (int b = 0; b < c->batch; ++b) {
+      const int finest = finest_item(c->tier[t], true);
+      shortest += ((ds && t == last ? sel_tokens[b] : c->tier[t].len[b]) + finest - 1) / finest;
+    }
+  const bool few = P->resident_items != 2560 && !target_items && shortest * heads <= kFewItems;
+  const double item_bytes = choose_item_bytes(c, P->even, target_items, ds ? sel_tokens : nullptr, P->resident_items, few, &P->memo[ds != nullptr]);
   for (int t = 0; t < c->n_tiers; ++t) {
     const ttkv_tier &T = c->tier[t];
     const Layout L = make_layout(T, c->n_kv_heads);
     const bool sparse = sel_blocks && t == last;
     const bool host = T.mem == TTKV_MEM_HOST_PINNED;
+    const int finest = finest_item(T, few);
     // host rows read in place: few large sequential items keep the PCIe read stream efficient (measured); staged
     // slots: 256-token items for parallelism; tiers in HBM, dense or selected on the device: equal items per run (0)
     P->chunk[t] = (host && !staged) ? 2048 : (host || sparse) ? 256 : 0;
@@ -447,7 +462,7 @@ void build_plan(const ttkv_cache *c, const int32_t *sel_blocks, const int32_t *s
         r.len = host ? count : count * L.bt;     // blocks in fixed items, or their tokens as one run in equal items
         r.selected = true;
         r.part_base = P->parts[b];
-        r.n_chunks = host ? count * ipb : items_for((int64_t)count * L.bt, per_token_bytes(T), item_bytes);
+        r.n_chunks = host ? count * ipb : items_for((int64_t)count * L.bt, per_token_bytes(T), item_bytes, finest);
         P->parts[b] += r.n_chunks;
         P->runs.push_back(r);
       }
@@ -462,7 +477,7 @@ void build_plan(const ttkv_cache *c, const int32_t *sel_blocks, const int32_t *s
         r.len = (int32_t)T.len[b];
         r.no_table = false;
         r.part_base = P->parts[b];
-        r.n_chunks = P->even[t] ? items_for(T.len[b], per_token_bytes(T), item_bytes) : (int)((T.len[b] + chunk - 1) / chunk);
+        r.n_chunks = P->even[t] ? items_for(T.len[b], per_token_bytes(T), item_bytes, finest) : (int)((T.len[b] + chunk - 1) / chunk);
         P->parts[b] += r.n_chunks;
         P->runs.push_back(r);
       }

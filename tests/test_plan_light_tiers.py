@@ -35,3 +35,21 @@ def test_unequal_lengths_change_the_plan_and_back():
         assert 1 + int(many.max()) // 8192 <= B.ttkv_count_parts(h, c) <= 1 + -(-int(many.max()) // 256)
     finally:
         B.ttkv_destroy(h)
+
+
+@pytest.mark.parametrize("heads,tiers,parts", [
+    ((8, 2), [("f16", "f16", 64, 507), ("i8", "i8", 64, 3584)], 4 + 28),             # 64 workgroups: items of 128 tokens
+    ((32, 8), [("f16", "f16", 128, 4096)], 32),                                      # 256: one per CU, the most
+    ((32, 8), [("f16", "f16", 128, 4097)], 17),                                      # 33 items would be 264
+    ((8, 2), [("f16", "f16", 128, 300), ("i4", "i4", 128, 1024)], 3 + 4),            # int4 keys: 256 tokens are a batch per wave
+    ((4, 4), [("f16", "f16", 128, 512)], 2),                                         # the vector kernel
+])
+def test_launches_that_leave_cus_idle_are_cut_finer(heads, tiers, parts):
+    c = plan_cache(1, *heads, tiers)
+    h = B.ttkv_create()
+    try:
+        assert B.ttkv_count_parts(h, c) == parts
+        B.ttkv_set_split(h, 1 << 20)
+        assert B.ttkv_count_parts(h, c) == sum(-(-t[3] // 256) for t in tiers)
+    finally:
+        B.ttkv_destroy(h)
