@@ -137,7 +137,7 @@ __device__ __forceinline__ void process(const FusedArgs &a, const TierView &tv, 
     if (tok0 >= ring_tokens) tok0 -= ring_tokens;
     int rb = div_bt(tok0, tv.bt, tv.bt_magic);
     const int row0 = tok0 - rb * tv.bt;
-    if (sel) rb = sel[rb] % tv.ring_blocks;
+    if (sel) rb = ring_of_id(sel[rb], en, tv);
     const int64_t rec = tv.table ? (int64_t)tv.table[(int64_t)seq * tv.ring_blocks + rb] : (int64_t)en.rec_base + rb;
     const uint8_t *head = tv.base + rec * tv.rec_bytes + (int64_t)hkv * tv.head_bytes;
     // wave-uniform section bases of the tile + per-lane 32-bit offsets: the loads below can

@@ -122,7 +122,14 @@ struct RunView {
   int rec_base;    // record of ring block 0 (no block table) or the run's first pool record
   int first_tok;   // ring token index of the run's first token, 0 for runs that name records; selected: newest block id
   int len;
+  int id_base;     // of a run of selected blocks: the multiple of the ring's blocks below the newest id
 };
+// Ring block of a selected id, which is less than a ring older than the newest one (a remainder is worked out on the vector
+// unit, some 30 instructions for every batch of a wave).
+__device__ __forceinline__ int ring_of_id(int id, const RunView &en, const TierView &tv) {
+  const int rb = id - en.id_base;
+  return rb < 0 ? rb + tv.ring_blocks : rb;
+}
 __device__ __forceinline__ RunView run_view(const FusedArgs &a, int i) {
   const Entry e = a.e[i];
   RunView r;
@@ -134,6 +141,7 @@ __device__ __forceinline__ RunView run_view(const FusedArgs &a, int i) {
   r.rec_base = direct ? e.at : r.seq * a.tv[r.tier].ring_blocks;
   r.first_tok = direct ? 0 : e.at;
   r.len = e.len;
+  r.id_base = 0;
   return r;
 }
 // Asks for what the look-up of an item reads, all at once and before anything is worked out: a launch's arguments are in no
@@ -165,6 +173,7 @@ __device__ __forceinline__ const int32_t *resolve_selected(const FusedArgs &a, c
   const int32_t *ids = a.sel_ids + seq * a.sel_stride;
   if (equal_items) {
     if (ids[en.len / tv.bt - 1] == en.first_tok) en.len -= tv.bt - a.sel_last_ntok[seq];
+    en.id_base = __builtin_amdgcn_readfirstlane(en.first_tok - en.first_tok % tv.ring_blocks);
     en.first_tok = 0;
     return ids;
   }

@@ -268,8 +268,7 @@ __device__ __forceinline__ Place place_of(const TierView &tv, const RunView &en,
 }
 __device__ __forceinline__ const uint8_t *head_at(const TierView &tv, const RunView &en, const int32_t *sel, int seq, int hkv, int block) {
   int rb = block;
-  // (a remainder is worked out on the vector unit; without the read all addresses behind it stay there)
-  if (sel) rb = __builtin_amdgcn_readfirstlane(((const_i32)(uintptr_t)sel)[rb] % tv.ring_blocks);
+  if (sel) rb = ring_of_id(((const_i32)(uintptr_t)sel)[rb], en, tv);
   const int64_t rec = tv.table ? (int64_t)((const_i32)(uintptr_t)tv.table)[(int64_t)seq * tv.ring_blocks + rb]
                                : (int64_t)en.rec_base + rb;
   return tv.base + rec * tv.rec_bytes + (int64_t)hkv * tv.head_bytes;
