@@ -432,10 +432,13 @@ struct Unit {
   int lo, hi, t_lo;
 };
 
+// A thread's number inside its unit (workgroups of SUM_THREADS may take two units side by side).
+template <int THREADS>
+__device__ __forceinline__ int unit_thread() { return threadIdx.x & (THREADS - 1); }
 template <int SRC, int THREADS, int ROWS, typename U>
 __device__ __forceinline__ void load_unit(const Source &c, const U &u, Raw (&raw)[ROWS * 16 / THREADS]) {
   const RowSource s = row_source<SRC>(c, u.t_lo);
-  const int l16 = threadIdx.x & 15, r = threadIdx.x >> 4;
+  const int t = unit_thread<THREADS>(), l16 = t & 15, r = t >> 4;
   if (u.lo == 0 && u.hi == ROWS && s.split >= ROWS) {   // every row live and in one block: one base, constant offsets
 #pragma unroll
     for (int p = 0; p < ROWS * 16 / THREADS; ++p) {
@@ -504,10 +507,10 @@ __device__ __forceinline__ void keep_values(float (*s_x)[128], int i, int l16, c
 template <int SRC, int DST, int THREADS, int ROWS, bool SUM, typename U>
 __device__ __forceinline__ void convert_unit(const Source &c, const U &u, const Raw (&raw)[ROWS * 16 / THREADS],
                                              float (*s_x)[128], uint32_t *s_t32) {
-  const int l16 = threadIdx.x & 15;
+  const int t = unit_thread<THREADS>(), l16 = t & 15;
 #pragma unroll
   for (int p = 0; p < ROWS * 16 / THREADS; ++p) {
-    const int i = p * (THREADS / 16) + (threadIdx.x >> 4);
+    const int i = p * (THREADS / 16) + (t >> 4);
     constexpr bool COPY = SRC == DST && (DST == TTKV_F16 || DST == TTKV_BF16);
     if (COPY && !SUM && c.n_via == 0) {   // bytes as they are
       if (i >= u.lo && i < u.hi) st_row<U::STREAM>(u.head + u.code_off + (u.row0 + i) * 256 + l16 * 16, raw[p].a);
@@ -536,11 +539,13 @@ __device__ __forceinline__ void convert_unit(const Source &c, const U &u, const 
 // nibbles by masks, then bytes by v_perm, 32 operations for 8 words instead of 24 per word gathered one by one -- and
 // the words meet in LDS in the group's order, pieces permuted inside eights to spread them over the banks.
 template <int THREADS, typename U>
-__device__ __forceinline__ void store_t32(const U &u, uint32_t *s_t32) {
+__device__ __forceinline__ void store_t32(const U &u, uint32_t *s_t32) {   // (a unit without live rows takes part in the barriers)
+  const int t = unit_thread<THREADS>();
+  const bool live = u.lo < u.hi;
   uint4 *const s_out = (uint4 *)(s_t32 + CHUNK * kT32Stride);
   __syncthreads();
-  if (threadIdx.x < 128) {
-    const int g = threadIdx.x >> 6, kg = (threadIdx.x >> 4) & 3, cw = threadIdx.x & 15;
+  if (live && t < 128) {
+    const int g = t >> 6, kg = (t >> 4) & 3, cw = t & 15;
     const int kTok[8] = {0, 2, 16, 18, 1, 3, 17, 19};
     uint32_t in[8], even[4], odd[4];
 #pragma unroll
@@ -555,16 +560,16 @@ __device__ __forceinline__ void store_t32(const U &u, uint32_t *s_t32) {
     auto turned = [&](const uint32_t (&m)[4], int odd_channel) {
       const uint32_t lo01 = __builtin_amdgcn_perm(m[1], m[0], 0x05010400u), lo23 = __builtin_amdgcn_perm(m[3], m[2], 0x05010400u);
       const uint32_t hi01 = __builtin_amdgcn_perm(m[1], m[0], 0x07030602u), hi23 = __builtin_amdgcn_perm(m[3], m[2], 0x07030602u);
-      const uint32_t t[4] = {__builtin_amdgcn_perm(lo23, lo01, 0x05040100u), __builtin_amdgcn_perm(lo23, lo01, 0x07060302u),
+      const uint32_t turned4[4] = {__builtin_amdgcn_perm(lo23, lo01, 0x05040100u), __builtin_amdgcn_perm(lo23, lo01, 0x07060302u),
                              __builtin_amdgcn_perm(hi23, hi01, 0x05040100u), __builtin_amdgcn_perm(hi23, hi01, 0x07060302u)};
 #pragma unroll
-      for (int k = 0; k < 4; ++k) out[4 * ((base + 2 * k + odd_channel) ^ turn) + w] = t[k];
+      for (int k = 0; k < 4; ++k) out[4 * ((base + 2 * k + odd_channel) ^ turn) + w] = turned4[k];
     };
     turned(even, 0);
     turned(odd, 1);
   }
   __syncthreads();
-  for (int idx = threadIdx.x; idx < 256; idx += THREADS) {
+  for (int idx = t; idx < 256; idx += THREADS) {
     const int g = idx >> 7, p = idx & 127, turn = 2 * ((p >> 4) & 3) + (p >> 6);
     if (g * 32 >= u.lo && g * 32 < u.hi) st_row<U::STREAM>(u.head + u.code_off + (u.row0 + g * 32) * 64 + p * 16, s_out[g * 128 + (p ^ turn)]);
   }
@@ -645,14 +650,16 @@ __device__ __forceinline__ void sum_unit(const Source &src, const U &u, int src_
 
 // Grid: x = K units then V units of one (entry, KV head), y = KV head, z = entry.  SUM: K units are whole destination
 // blocks and keep the key sums (dst_fmt of K may be NO_STORE: sums only); otherwise every unit is 64 rows.
-// With SUM a conversion that keeps no sums (beside one that does) has units of 64 rows for K and V.
-template <bool SUM, bool STREAM, int THREADS>
+// With SUM a conversion that keeps no sums (beside one that does) has units of 64 rows for K and V.  UT: threads of such a
+// unit; a workgroup takes THREADS / UT of them.
+template <bool SUM, bool STREAM, int THREADS, int UT>
 __device__ __forceinline__ void convert_rows(const ConvArgs &a, int k_units, int k_dst_fmt, bool sums, int j) {
   constexpr int SUM_BYTES = 2 * (THREADS / 16) * 128 * 4 + 512;
-  __shared__ __align__(16) char s_buf[SUM ? (SUM_BYTES > kT32Bytes ? SUM_BYTES : kT32Bytes) : kT32Bytes];
+  constexpr int PER = THREADS / UT;
+  __shared__ __align__(16) char s_buf[SUM && SUM_BYTES > PER * kT32Bytes ? SUM_BYTES : PER * kT32Bytes];
   const int h = blockIdx.y, seq = a.seq_id[j];
   const int which = (int)blockIdx.x >= k_units;
-  const int unit = which ? blockIdx.x - k_units : blockIdx.x;
+  int unit = which ? blockIdx.x - k_units : blockIdx.x;
   const int first = a.dst_first_tok[j];                   // ring token the call's first row lands on
   const int dst_rec_base = a.dst_rec_base[j], n_tokens = a.n_tokens;
   const TierView dst = a.dst;
@@ -682,20 +689,25 @@ __device__ __forceinline__ void convert_rows(const ConvArgs &a, int k_units, int
     return;
   }
 
+  const int side = PER > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x / UT) : 0;
+  unit = unit * PER + side;
   int tok = first / CHUNK * CHUNK + unit * CHUNK;         // ring token of the unit's row 0
   const int t0 = tok - first;                             // its token of the call (the first unit may start before it)
   u.lo = max(0, -t0);
   u.hi = min(CHUNK, n_tokens - t0);
   u.t_lo = t0 + u.lo;
-  if (u.lo >= u.hi) return;
+  const int dst_fmt = which ? dst.v_fmt : k_dst_fmt;
+  if (u.lo >= u.hi) {
+    if (PER > 1 && dst_fmt == TTKV_I4_ASYM_G64_T32) store_t32<UT>(u, nullptr);   // barriers beside a unit with rows
+    return;
+  }
   tok = wrap(tok, dst);
   const int r = div_bt(tok, dst.bt, dst.bt_magic);
   u.row0 = tok - r * dst.bt;
   u.head = block_head(dst, seq, dst_rec_base, r, h);
-  const int dst_fmt = which ? dst.v_fmt : k_dst_fmt;
-  uint32_t *const s_t32 = (uint32_t *)s_buf;
-  Raw raw[CHUNK * 16 / THREADS];
-#define TTKV_ROW_UNIT(S, D) load_unit<S, THREADS, CHUNK>(src, u, raw), convert_unit<S, D, THREADS, CHUNK, false>(src, u, raw, nullptr, s_t32)
+  uint32_t *const s_t32 = (uint32_t *)(s_buf + side * kT32Bytes);
+  Raw raw[CHUNK * 16 / UT];
+#define TTKV_ROW_UNIT(S, D) load_unit<S, UT, CHUNK>(src, u, raw), convert_unit<S, D, UT, CHUNK, false>(src, u, raw, nullptr, s_t32)
   switch (dst_fmt) {
     case TTKV_F16: TTKV_ROW_UNIT(TTKV_F16, TTKV_F16); break;
     case TTKV_BF16: TTKV_ROW_UNIT(TTKV_BF16, TTKV_BF16); break;
@@ -704,17 +716,17 @@ __device__ __forceinline__ void convert_rows(const ConvArgs &a, int k_units, int
     default: TTKV_FOR_SOURCES(TTKV_I4_ASYM_G64, TTKV_ROW_UNIT) break;
   }
 #undef TTKV_ROW_UNIT
-  if (dst_fmt == TTKV_I4_ASYM_G64_T32) store_t32<THREADS>(u, s_t32);
+  if (dst_fmt == TTKV_I4_ASYM_G64_T32) store_t32<UT>(u, s_t32);
 }
 template <bool SUM, bool STREAM, int THREADS>
 __global__ __launch_bounds__(THREADS, THREADS == 256 ? 8 : 6) void convert_rows_kernel(const ConvArgs a, int k_units, int k_dst_fmt) {
-  convert_rows<SUM, STREAM, THREADS>(a, k_units, k_dst_fmt, true, blockIdx.z);
+  convert_rows<SUM, STREAM, THREADS, THREADS>(a, k_units, k_dst_fmt, true, blockIdx.z);
 }
 
 // Two conversions side by side (two boundaries of an eviction): the entries of the second follow those of the first.
 struct ConvPair {
   ConvArgs a[2];
-  int32_t k_units[2], units[2];   // K units, K and V units
+  int32_t k_units[2], units[2];   // workgroups of K, of K and V
   int32_t n_first;                // entries of the first one
 };
 template <bool SUM, int THREADS>
@@ -722,7 +734,7 @@ __global__ __launch_bounds__(THREADS, THREADS == 256 ? 8 : 6) void convert_pair_
   const int i = (int)blockIdx.z >= c.n_first;
   const ConvArgs &a = c.a[i];
   if ((int)blockIdx.x >= c.units[i]) return;
-  convert_rows<SUM, true, THREADS>(a, c.k_units[i], a.dst.k_fmt, a.k_sum != nullptr, (int)blockIdx.z - (i ? c.n_first : 0));
+  convert_rows<SUM, true, THREADS, 256>(a, c.k_units[i], a.dst.k_fmt, a.k_sum != nullptr, (int)blockIdx.z - (i ? c.n_first : 0));
 }
 
 // Keys of a tier whose int4 groups run over 128 consecutive tokens of one channel (Q_4bit's arithmetic with the
@@ -853,24 +865,25 @@ hipError_t launch_convert(const ConvArgs &a, hipStream_t s, int *n_kernels) {
   return a.to_host ? launch<false>(a, s, n_kernels) : launch<true>(a, s, n_kernels);
 }
 
-// One launch takes as long as the slower of the two, where two launches take their sum and the gap between them (16 x 8 KV heads,
-// 128 rows of fp16 into int8 and of int8 into int4 with sums, 16.4 -> 12.8 us; without sums 39 x 16 heads 27.2 -> 23.1, 39 x 2
-// heads 14.4 -> 8.4).  With sums all its workgroups have 512 threads and 33 KB of LDS, three on a CU, which units without
-// sums do not need: up to 1024 workgroups, one round and a third, it pays (60 x 2 heads, 960 of them, 16.1 -> 12.8), beyond it
-// does not (24 x 8 heads, 1536: 15.2 -> 18.0; 56 x 16 heads 45.7 -> 65.7; with 256 threads 16.8 and 46.6).
+// One launch takes as long as the slower of the two, where two launches take their sum and the gap between them: 39 x 16 heads,
+// 128 rows of fp16 into int8 and of int8 into int4, 27.2 -> 23.1 us, 39 x 2 heads 14.4 -> 8.4.  With sums all its workgroups
+// have the 512 threads and 33 KB of LDS of those that add, three on a CU; they take two 64-row units, or 16 x 8 heads were 1024
+// of them for 768 places: two launches 15.8, with one unit 12.6, with two 9.1 (24 x 8 heads 14.3, 18.0, 11.4; 56 x 16 heads 43.0,
+// 65.7, 39.0; 40 x 32 heads 55.6 and 53.2).  64 x 32 heads, 2048 summed blocks, are faster apart, with 256 threads each (78.8, 81.2).
 hipError_t launch_convert_pair(const ConvArgs &a, const ConvArgs &b, hipStream_t s, int *n_kernels) {
   const bool turned = b.k_sum && !a.k_sum;   // the one with sums first: its workgroups take longest
   ConvPair c{{turned ? b : a, turned ? a : b}, {}, {}, turned ? b.n_seq : a.n_seq};
+  const bool sums = a.k_sum || b.k_sum;
   bool apart = a.to_host || b.to_host;
   for (int i = 0; i < 2; ++i) {
     const Units u = units_of(c.a[i]);
-    c.k_units[i] = c.a[i].k_sum ? u.blocks : u.chunks;
-    c.units[i] = c.k_units[i] + u.chunks;
-    apart |= c.a[i].dst.k_fmt == TTKV_I4_ASYM_T128;
+    const int groups = sums ? (u.chunks + SUM_THREADS / 256 - 1) / (SUM_THREADS / 256) : u.chunks;   // of 64-row units
+    c.k_units[i] = c.a[i].k_sum ? u.blocks : groups;
+    c.units[i] = c.k_units[i] + groups;
+    apart |= c.a[i].dst.k_fmt == TTKV_I4_ASYM_T128 || (c.a[i].k_sum && (int64_t)u.blocks * c.a[i].n_seq * c.a[i].Hkv > 1536);
   }
   const dim3 grid(std::max(c.units[0], c.units[1]), a.Hkv, a.n_seq + b.n_seq);   // (one cache: as many KV heads in both)
-  const bool sums = a.k_sum || b.k_sum;
-  if (apart || (sums && (int64_t)grid.x * grid.y * grid.z > 1024)) {
+  if (apart) {
     const hipError_t e = launch_convert(a, s, n_kernels);
     return e != hipSuccess ? e : launch_convert(b, s, n_kernels);
   }

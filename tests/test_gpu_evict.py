@@ -80,3 +80,25 @@ def test_a_refused_boundary_ends_the_cascade():
         assert [int(x) for x in c.len[0]] == [64] * 3 and [int(x) for x in c.len[1]] == [192] * 3 and int(c.len[2][0]) == 64
     finally:
         c.close()
+
+
+@pytest.mark.parametrize("tokens", [64, 192])      # one unit of 64 rows, and three: workgroups of two units, one of them alone
+@pytest.mark.parametrize("last", [("i4", "i4"), ("i8", "i4c")])
+def test_units_side_by_side(tokens, last):
+    """Blocks whose 64-row units do not pair up, rows that start inside a unit, sums beside conversions without them."""
+    tiers = [(F16, tokens, tokens), (I8, tokens, 2 * tokens), (last, 64, 10**9)]
+    held = [[tokens, tokens + 1, tokens], [tokens, 2 * tokens - 1, 2 * tokens + 32], [32, 64, 96]]
+    one, many = (filled(tiers, held, True, False, (6, 3)) for _ in range(2))
+    try:
+        one.demote()
+        s = torch.cuda.current_stream().cuda_stream
+        for t in range(2):
+            B.ttkv_tier_demote(many.h, many.c, t, 0, None, 0, s, s)
+        torch.cuda.synchronize()
+        assert one.stats()["demotions"] == many.stats()["demotions"] >= 6
+        for t in range(3):
+            assert np.array_equal(one.len[t], many.len[t]) and torch.equal(one.pool[t], many.pool[t]), t
+        assert torch.equal(one.ksum, many.ksum) and torch.equal(one.kmu.view(torch.int16), many.kmu.view(torch.int16))
+    finally:
+        one.close()
+        many.close()
