@@ -273,7 +273,7 @@ ttkv_status ttkv_decode_attn_noalloc(ttkv_handle h, const ttkv_cache *c, const v
  * cached, and the merge kernel adds the new token's own term (score q.k_new, weight 1, value v_new)
  * and stores its row.  Any other first tier: the two calls, one after the other.  CAPACITY if tier
  * 0's ring has no room; nothing is enqueued and no length changes when a status other than OK or
- * HIP is returned.  Eviction (ttkv_tier_demote) stays the caller's next call. */
+ * HIP is returned.  Eviction (ttkv_evict) stays the caller's next call. */
 ttkv_status ttkv_decode_step(ttkv_handle h, ttkv_cache *c, const void *q, int32_t q_fmt, const void *k_new,
                              const void *v_new, int32_t new_fmt, float *out, float *lse, const int32_t *sel_blocks,
                              const int32_t *sel_count, int32_t sel_stride, void *workspace, size_t ws_bytes,

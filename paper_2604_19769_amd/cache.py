@@ -165,7 +165,7 @@ class TieredCache:
             sb, sc = selected
             stride = sb.shape[1]
         # Parts per row: counted by the library.  A dense decode step adds one token per sequence, i.e. at most one
-        # part per tier every 256 steps, and the workspace is sized with 16 parts to spare: inside step() the count is
+        # part per tier every 128 steps, and the workspace is sized with 16 parts to spare: inside step() the count is
         # therefore refreshed only every 64 steps (the library still checks the workspace on every call).
         if selected is None and new is not None and self.ws is not None and self._parts_age is not None and self._parts_age < 64 \
                 and self.ws_slots == self.n_slots:
@@ -223,7 +223,7 @@ class TieredCache:
         stride = self._select_buffers(k)
         # The split of a selection is planned inside the call, which refuses a workspace that is too small for it before
         # anything is enqueued: the workspace is sized once from a dense plan's parts and grows when it is refused (no
-        # run is cut finer than into items of 256 tokens, which bounds it).
+        # run is cut finer than into items of 128 tokens, which bounds it).
         self._parts_age = None
         if self.ws is None or self.ws_slots != self.n_slots:
             self.len[0] += 1
