@@ -15,8 +15,6 @@ namespace ttkv {
 
 namespace {
 
-constexpr int SCORE_WAVES = 4;   // score_kernel: one wave64 per live block, four blocks per workgroup
-
 template <bool BF16>
 __device__ __forceinline__ float q2f(uint32_t bits16) {
   if (BF16) return __uint_as_float(bits16 << 16);
@@ -40,11 +38,12 @@ __device__ __forceinline__ float chain8(const uint4 qq, const uint4 mm, float s)
 // then the lanes' results are added in head order (every lane forms the same sum; lane by lane from scalar registers: a
 // loop of exchanges through LDS, each waited for, was a third of the kernel).  Blocks are independent, so the
 // launch spreads over the chip and its latency is one block's: the loads of 2 KiB of mean keys and a 128-deep chain.
-template <bool BF16>
-__global__ __launch_bounds__(SCORE_WAVES * 64) void score_kernel(const SelectArgs a) {
+// WAVES: blocks of a workgroup (launch_select).
+template <bool BF16, int WAVES>
+__global__ __launch_bounds__(WAVES * 64) void score_kernel(const SelectArgs a) {
   const int b = blockIdx.y;
   const int lane = threadIdx.x & 63;
-  const int i = blockIdx.x * SCORE_WAVES + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int i = blockIdx.x * WAVES + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n = a.n_blocks[b], first = a.first_block[b], rec_base = a.rec_base[b];
   asm volatile("" ::"s"(n), "s"(first), "s"(rec_base), "s"(a.q), "s"(a.Hq), "s"(a.g_magic));   // all asked for at once
   if (i >= n) return;                                 // whole waves leave together
@@ -200,12 +199,25 @@ __global__ __launch_bounds__(1024) void topk_kernel(const SelectArgs a) {
 
 }  // namespace
 
-hipError_t launch_select(const SelectArgs &a, hipStream_t s) {
-  const dim3 grid((a.max_blocks + SCORE_WAVES - 1) / SCORE_WAVES, a.n_seq);
+namespace {
+template <int WAVES>
+void launch_scores(const SelectArgs &a, hipStream_t s) {
+  const dim3 grid((a.max_blocks + WAVES - 1) / WAVES, a.n_seq);
   if (a.q_fmt == TTKV_BF16)
-    hipLaunchKernelGGL(score_kernel<true>, grid, dim3(SCORE_WAVES * 64), 0, s, a);
+    hipLaunchKernelGGL((score_kernel<true, WAVES>), grid, dim3(WAVES * 64), 0, s, a);
   else
-    hipLaunchKernelGGL(score_kernel<false>, grid, dim3(SCORE_WAVES * 64), 0, s, a);
+    hipLaunchKernelGGL((score_kernel<false, WAVES>), grid, dim3(WAVES * 64), 0, s, a);
+}
+}  // namespace
+
+hipError_t launch_select(const SelectArgs &a, hipStream_t s) {
+  // A block's loads name 32 rows of queries at a time, each a line of its own to the CU's L1, so waves on one CU wait for each
+  // other: with up to four per CU, a workgroup each spreads them over all CUs (recall steps, four -> one: 4 x 96 blocks
+  // 107.7 -> 106.8 us, small ones 19.7 -> 18.4, 22.2 -> 21.0, 29.3 -> 28.2).  With more, every CU is busy
+  // either way, and fewer workgroups start sooner (8 x 768 blocks 42.9 us, one wave each 43.2; 16 x 128 of 96 heads 40.6
+  // and 41.1).
+  if ((int64_t)a.max_blocks * a.n_seq <= 1024) launch_scores<1>(a, s);
+  else launch_scores<4>(a, s);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const int waves = (a.max_blocks + 63) / 64;

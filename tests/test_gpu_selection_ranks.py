@@ -1,5 +1,5 @@
 """Block selection over numbers of live blocks at the edges of the two ranking kernels (up to 256 blocks ranks are counted, beyond
-it a radix select), of waves and of four; ties, NaN and both zeros; numbers of query heads that are no powers of two.  Scores,
+it a radix select) and the two forms of the scoring launch (up to 1024 blocks of all sequences together, and more), of waves and of four; ties, NaN and both zeros; numbers of query heads that are no powers of two.  Scores,
 and so the selection, are defined bit for bit; the ids reach the caller's memory whether it is page-locked or not."""
 import ctypes as C
 
@@ -26,7 +26,7 @@ def phi(q, mean, G):
     return out
 
 
-@pytest.mark.parametrize("n", [1, 3, 4, 63, 64, 65, 127, 255, 256, 257, 700, 1024])
+@pytest.mark.parametrize("n", [1, 3, 4, 63, 64, 65, 127, 255, 256, 257, 512, 513, 700, 1024])
 @pytest.mark.parametrize("heads", [(8, 2), (14, 2), (5, 5), (72, 8)])
 @pytest.mark.parametrize("kind", ["ordinary", "ties", "special"])
 def test_ids_at_every_number_of_blocks(n, heads, kind):
