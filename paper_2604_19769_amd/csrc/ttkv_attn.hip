@@ -440,7 +440,9 @@ __global__ __launch_bounds__(256) void attn_fused_kernel(const FusedArgs a) {
   }
 }
 
-// One workgroup of T threads per row (128 up to 32 parts, else 256: 2048 rows of 5 parts 9.8 us with 256, 7.6 with 128).
+// One workgroup of T threads per row: 128 up to 32 parts (2048 rows of 5 parts 9.8 us with 256, 7.6 with 128), 256 up to 64, beyond
+// that 1024, whose first loads are 256 parts where 256 threads go round after round (32 rows of 254 parts, launch of 65K fp16
+// tokens: step 28.8 -> 20.2 us; 64 rows of 128 parts 30.8 -> 28.1; 32 rows of 111 parts beside a host tier -1).
 // The kernel is a chain of memory latencies, so everything that does not depend on anything is requested first: 32 lanes take
 // a part's 128 channels in 16 bytes each, T / 32 parts at a time, the first T / 4 parts before anything else (most launches
 // have no more), and every wave all parts' (m, l) for itself, a part per lane.  So each wave has the weights e^(m_p - M) and
@@ -454,7 +456,8 @@ __global__ __launch_bounds__(256) void attn_fused_kernel(const FusedArgs a) {
 // kernels then run over the tokens already cached and a step needs no launch of its own for the append.
 template <int T>
 __global__ __launch_bounds__(T) void merge_kernel(const MergeArgs a) {
-  constexpr int NG = T / 32, U = 8;
+  constexpr int NG = T / 32, U = 8, R = 64 / NG;   // lane groups; parts of a group asked for first; its parts of 64
+  constexpr int CH = U > R ? U / R : 1;             // times 64 parts whose (m, l) are asked for first
   __shared__ __align__(16) float s_o[NG][128];
   const int seq = blockIdx.y, hq = blockIdx.x;   // rows_per_seq = 0: all rows are counted by x
   const int row = seq * a.rows_per_seq + hq;
@@ -477,8 +480,12 @@ __global__ __launch_bounds__(T) void merge_kernel(const MergeArgs a) {
   float4 av[U];
 #pragma unroll
   for (int u = 0; u < U; ++u) av[u] = NG * u + grp < n ? part(NG * u + grp) : float4{0.0f, 0.0f, 0.0f, 0.0f};
-  const float m0 = lane < n ? pm[lane] : -INFINITY;   // (m, l) of the first 64 parts
-  const float l0 = lane < n ? pl[lane] : 0.0f;
+  float m0[CH], l0[CH];
+#pragma unroll
+  for (int k = 0; k < CH; ++k) {
+    m0[k] = 64 * k + lane < n ? pm[64 * k + lane] : -INFINITY;
+    l0[k] = 64 * k + lane < n ? pl[64 * k + lane] : 0.0f;
+  }
 
   // the new token: lane i has channels 2 i and 2 i + 1 of q and k, thread i of the first 128 channel i of v
   uint32_t kb = 0;
@@ -501,8 +508,10 @@ __global__ __launch_bounds__(T) void merge_kernel(const MergeArgs a) {
     v_new = f32_of(vb, a.new_fmt);
   }
 
-  float M = m0;
-  for (int p = lane + 64; p < n; p += 64) M = fmaxf(M, pm[p]);
+  float M = m0[0];
+#pragma unroll
+  for (int k = 1; k < CH; ++k) M = fmaxf(M, m0[k]);
+  for (int p = lane + 64 * CH; p < n; p += 64) M = fmaxf(M, pm[p]);
   M = wave_max(M);
   float4 o = {0.0f, 0.0f, 0.0f, 0.0f};
   float l = 0.0f;
@@ -512,26 +521,28 @@ __global__ __launch_bounds__(T) void merge_kernel(const MergeArgs a) {
     o.z = fmaf(x.z, w, o.z);
     o.w = fmaf(x.w, w, o.w);
   };
-  for (int b = 0; b < n; b += 64) {   // (workgroup-uniform)
-    const int p = b + lane;
-    const float mp = b == 0 ? m0 : p < n ? pm[p] : -INFINITY;
+  // 64 parts from b on, weights in the lanes; `done` of a lane group's rounds are in registers, from av[at] on
+  auto chunk = [&](int b, float mp, float lp, int at, int done) __attribute__((always_inline)) {
     const float w = mp == -INFINITY ? 0.0f : __expf(mp - M);   // 0 behind the last part
-    l = fmaf(b == 0 ? l0 : p < n ? pl[p] : 0.0f, w, l);
+    l = fmaf(lp, w, l);
     auto weight = [&](int u) {   // of part b + NG u + grp
-      const int at = NG * u + 2 * wave;
-      const float w0 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(w), at));
-      const float w1 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(w), at + 1));
+      const int p = NG * u + 2 * wave;
+      const float w0 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(w), p));
+      const float w1 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(w), p + 1));
       return half ? w1 : w0;
     };
-    int u = 0;
-    if (b == 0) {
 #pragma unroll
-      for (int v = 0; v < U; ++v) add(av[v], weight(v));
-      u = U;
-    }
-    const int rounds = min(64 / NG, (n - b + NG - 1) / NG);
+    for (int u = 0; u < done; ++u) add(av[at + u], weight(u));
+    const int rounds = min(R, (n - b + NG - 1) / NG);
 #pragma unroll 4
-    for (; u < rounds; ++u) add(b + NG * u + grp < n ? part(b + NG * u + grp) : float4{0.0f, 0.0f, 0.0f, 0.0f}, weight(u));
+    for (int u = done; u < rounds; ++u) add(b + NG * u + grp < n ? part(b + NG * u + grp) : float4{0.0f, 0.0f, 0.0f, 0.0f}, weight(u));
+  };
+#pragma unroll
+  for (int k = 0; k < CH; ++k)
+    if (64 * k < n) chunk(64 * k, m0[k], l0[k], k * R, U < R ? U : R);   // (workgroup-uniform)
+  for (int b = 64 * CH; b < n; b += 64) {
+    const int p = b + lane;
+    chunk(b, p < n ? pm[p] : -INFINITY, p < n ? pl[p] : 0.0f, 0, 0);
   }
   l = wave_sum(l);
   *(float4 *)(s_o[grp] + c4 * 4) = o;
@@ -598,7 +609,8 @@ hipError_t launch_merge(const MergeArgs &a, hipStream_t s) {
   if (a.rows <= 0) return hipSuccess;
   const dim3 grid = a.rows_per_seq > 0 ? dim3(a.rows_per_seq, a.rows / a.rows_per_seq) : dim3(a.rows);
   if (a.n_parts <= 32) hipLaunchKernelGGL(merge_kernel<128>, grid, dim3(128), 0, s, a);
-  else hipLaunchKernelGGL(merge_kernel<256>, grid, dim3(256), 0, s, a);
+  else if (a.n_parts <= 64) hipLaunchKernelGGL(merge_kernel<256>, grid, dim3(256), 0, s, a);
+  else hipLaunchKernelGGL(merge_kernel<1024>, grid, dim3(1024), 0, s, a);
   return hipGetLastError();
 }
 

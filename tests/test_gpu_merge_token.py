@@ -1,4 +1,4 @@
-"""The merge with the step's new token: parts below and above a lane's one and the first batch of 64, numbers of query heads
+"""The merge with the step's new token: parts below and above a lane's one and the first batches of 64 and 256, numbers of query heads
 that are and are not powers of two, and queries, keys and values that start at any even address."""
 import numpy as np
 import pytest
@@ -19,7 +19,7 @@ def shifted(t):
 
 
 @pytest.mark.parametrize("Hq,Hkv", [(1, 1), (3, 3), (6, 2), (14, 2), (40, 2)])
-@pytest.mark.parametrize("tokens", [1, 2047, 9000, 20000])      # 1, 8, 36 and 80 parts (256 tokens each)
+@pytest.mark.parametrize("tokens", [1, 2047, 9000, 20000, 66000])      # 1, 8, 36, 80 and 258 parts (256 tokens each)
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
 def test_new_token_joins_any_number_of_parts(Hq, Hkv, tokens, dtype):
     p = Pair(2, Hq, Hkv, [dict(k_fmt=dtype, v_fmt=dtype, capacity=10**9, block_tokens=64, ring_blocks=tokens // 64 + 2)], dtype)
