@@ -305,7 +305,7 @@ double choose_item_bytes(const ttkv_cache *c, const bool *dense, int target_item
   RunShape runs[TTKV_MAX_BATCH * TTKV_MAX_TIERS];
   int n_runs = 0;
   int64_t S = 0;   // bytes one pass over one KV head's tokens streams
-  uint32_t sig = (uint32_t)default_target * 1009u + (uint32_t)c->batch * 31u + (uint32_t)c->n_tiers * 7u + (uint32_t)c->n_q_heads * 131u + (uint32_t)c->n_kv_heads * 17u;
+  uint32_t sig = (uint32_t)default_target * 1009u + (few ? 7919u : 0u) + (uint32_t)c->batch * 31u + (uint32_t)c->n_tiers * 7u + (uint32_t)c->n_q_heads * 131u + (uint32_t)c->n_kv_heads * 17u;
   for (int t = 0; t < c->n_tiers; ++t) {
     sig = sig * 33u + (uint32_t)(c->tier[t].k_fmt * 8 + c->tier[t].v_fmt) * 2u + (dense[t] ? 1u : 0u);
     if (!dense[t]) continue;

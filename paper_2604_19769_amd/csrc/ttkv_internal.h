@@ -108,7 +108,7 @@ struct Fetch {
 // What the search for the split-K item size settled on, kept while the cache keeps its shape.
 struct SplitMemo {
   bool valid;
-  uint32_t sig;      // tiers, formats, head counts, batch
+  uint32_t sig;      // tiers, formats, head counts, batch, slots and shortest items planned with
   int n_runs;
   int step;          // index into the table of rounds
   int64_t bytes;     // bytes of one pass over one KV head when it was chosen
