@@ -158,7 +158,10 @@ ttkv_status ttkv_locate(const ttkv_cache *c, int32_t b, int64_t pos, int32_t *ti
  * else use ttkv_demote_workspace_bytes). */
 size_t ttkv_workspace_bytes(const ttkv_cache *c, int32_t max_parts, int32_t n_slots);
 size_t ttkv_demote_workspace_bytes(const ttkv_cache *c, int32_t src_tier);
-/* Parts per (sequence, query head) ttkv_decode_attn would use right now with this n_slots. */
+/* Parts per (sequence, query head) ttkv_decode_attn would use right now with this n_slots.  Not monotonic in the lengths:
+ * a launch of up to 256 workgroups takes items of 128 tokens where the workspace holds their partials, 256-token ones
+ * where it does not, so a cache one token longer may count half the parts; and the default split (ttkv_set_split) goes to
+ * finer items at some lengths than at longer ones.  A workspace for several lengths covers the largest count among them. */
 int32_t ttkv_count_parts(ttkv_handle h, const ttkv_cache *c, const int32_t *sel_blocks, const int32_t *sel_count,
                          int32_t sel_stride, int32_t n_slots);
 /* Split-K granularity (how many terms Alg. 1's sum over blocks is cut into; the result is the same up to fp32
@@ -167,9 +170,10 @@ int32_t ttkv_count_parts(ttkv_handle h, const ttkv_cache *c, const int32_t *sel_
  * (tier, sequence) run is cut into items of equal size (multiples of 64 tokens, 256 to 8192).
  * 0 restores the default: chosen per call from the lengths -- the number of rounds of resident
  * workgroups that suits the kernel the cache's formats and head counts select, raised in steps
- * until the items of all runs are within 10 % of each other and the last round is filled; where two
- * workgroups per CU run (2 or more heads per KV head and 4-bit tiers, or more than 8 and int8), until the
- * items placed one after the other, largest first, end within 3 % of an even split.
+ * until the items of all runs are within 10 % of each other and the last round is filled; where it is planned
+ * for two workgroups per CU (2 or more heads per KV head, except several sequences of equal lengths in fp16,
+ * bf16 and, up to 8 heads, int8 keys without 4-bit values), until the items placed one after the other, largest
+ * first, end within 3 % of an even split.  Launches of up to 256 workgroups: items down to 128 tokens.
  * More items: better balance over 256 CUs, more partials. */
 ttkv_status ttkv_set_split(ttkv_handle h, int32_t target_items);
 /* Paged tiers (Eq. (1): the index maps a block to where it is stored): by default every call that takes the handle

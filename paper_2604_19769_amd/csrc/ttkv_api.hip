@@ -399,8 +399,9 @@ double choose_item_bytes(const ttkv_cache *c, const bool *dense, int target_item
 
 // staged: host tiers are copied block by block into staging slots (one kernel per
 // copy); otherwise the fused kernel reads them in place.
+// may_be_few: items of 128 tokens where the launch leaves CUs idle (finest_item); false: none shorter than 256.
 void build_plan(const ttkv_cache *c, const int32_t *sel_blocks, const int32_t *sel_count, int32_t sel_stride, bool staged,
-                int target_items, Plan *P, const DevSel *ds = nullptr) {
+                int target_items, Plan *P, const DevSel *ds = nullptr, bool may_be_few = true) {
   P->status = TTKV_OK;
   P->slot_bytes = 0;
   P->max_parts = 0;
@@ -425,7 +426,8 @@ void build_plan(const ttkv_cache *c, const int32_t *sel_blocks, const int32_t *s
       const int finest = finest_item(c->tier[t], true);
       shortest += ((ds && t == last ? sel_tokens[b] : c->tier[t].len[b]) + finest - 1) / finest;
     }
-  const bool few = P->resident_items != 2560 && !target_items && shortest * heads <= kFewItems;
+  const bool few = may_be_few && P->resident_items != 2560 && !target_items && shortest * heads <= kFewItems;
+  P->few = few;
   const double item_bytes = choose_item_bytes(c, P->even, target_items, ds ? sel_tokens : nullptr, P->resident_items, few, &P->memo[ds != nullptr]);
   for (int t = 0; t < c->n_tiers; ++t) {
     const ttkv_tier &T = c->tier[t];
@@ -1122,6 +1124,9 @@ static ttkv_status decode_impl(Handle *h, const ttkv_cache *c, const void *q, in
   const size_t mis = (256 - ((uintptr_t)workspace & 255)) & 255;
   if (ws_bytes < mis + slots_bytes) return TTKV_ERR_WORKSPACE;
   const int64_t stride = (int64_t)((ws_bytes - mis - slots_bytes) / (rows * 130 * sizeof(float)));
+  // Items of 128 tokens are twice as many partials.  A cache one token longer may be beyond them, so a workspace sized for
+  // the longer one holds the plan of 256-token items and not always this one.
+  if (P.few && P.max_parts > stride) build_plan(c, sel_blocks, sel_count, sel_stride, staged, 0, &P, ds, false);
   if (fixed_ws && h->target_items == 0)
     for (int target = P.resident_items; P.max_parts > stride && target > 0; target /= 2)
       build_plan(c, sel_blocks, sel_count, sel_stride, staged, target, &P, ds);

@@ -123,6 +123,7 @@ struct Plan {
   int parts[TTKV_MAX_BATCH];
   int max_parts;
   int resident_items;   // the kernel's default split (default_items)
+  bool few;             // some runs may be in items of 128 tokens (finest_item)
   size_t slot_bytes;
   ttkv_status status;
 };
