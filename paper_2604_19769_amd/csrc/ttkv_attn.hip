@@ -440,14 +440,17 @@ __global__ __launch_bounds__(256) void attn_fused_kernel(const FusedArgs a) {
   }
 }
 
-// One workgroup of T threads per row: 128 up to 32 parts (2048 rows of 5 parts 9.8 us with 256, 7.6 with 128), 256 up to 64, beyond
-// that 1024, whose first loads are 256 parts where 256 threads go round after round (32 rows of 254 parts, launch of 65K fp16
-// tokens: step 28.8 -> 20.2 us; 64 rows of 128 parts 30.8 -> 28.1; 32 rows of 111 parts beside a host tier -1).
+// One workgroup of T threads per row: 128 up to 32 parts (2048 rows of 5 parts 9.8 us with 256, 7.6 with 128), 256 up to 64,
+// whose loads are 64 parts at a time; beyond, 1024 with 256 parts at a time for up to a row per CU (in a step, behind the
+// launch that wrote the partials: 16 rows of 130 parts 30.3 -> 29.7 us, 64 of 128 36.8 -> 36.3) and from 192 parts on (us of a merge
+// of rows x parts, 256 and 1024 threads: 32 x 256 5.6 and 4.6, 256 x 400 11.3 and 10.4, 4096 x 400 145 and 139).  Many rows of
+// fewer parts keep the chip busy either way and pay for threads without a part: 512 x 65 4.4 and 4.7, 1024 x 65 6.5 and
+// 8.1, 4096 x 80 26.2 and 29.9, 2048 x 128 20.6 and 21.7.
 // The kernel is a chain of memory latencies, so everything that does not depend on anything is requested first: 32 lanes take
 // a part's 128 channels in 16 bytes each, T / 32 parts at a time, the first T / 4 parts before anything else (most launches
-// have no more), and every wave all parts' (m, l) for itself, a part per lane.  So each wave has the weights e^(m_p - M) and
-// the sum of weights without a barrier, its sums over lanes stay out of LDS, and the waves meet once, to add the channels'
-// sums.  From a row's first instruction to its last, 8 rows of 16 parts and 32 rows of 64: 3.4 and 3.75 us with a thread per
+// have no more; further ones as many at a time: one by one 256 x 256 10.8 us with 256 threads, now 6.4), and every wave all
+// parts' (m, l) for itself, a part per lane.  So each wave has the weights e^(m_p - M) and the sum of weights without a
+// barrier, its sums over lanes stay out of LDS, and the waves meet once, to add the channels' sums.  From a row's first instruction to its last, 8 rows of 16 parts and 32 rows of 64: 3.4 and 3.75 us with a thread per
 // part, weights, maxima and sums through LDS, four barriers, divisions for sequence, KV head and block and the token's row
 // stored first; now 2.4 and 2.7, of which 0.5 are the arguments' arrival and 0.85 to 1.05 the parts'.  Steps: multi-head 32K 109.6
 // -> 107.8 us, recall 115.1 -> 113.8, 128K 39.0 -> 38.5.
@@ -478,14 +481,17 @@ __global__ __launch_bounds__(T) void merge_kernel(const MergeArgs a) {
   };
   const int grp = 2 * wave + half;                  // this lane group's parts: grp, grp + NG, ..
   float4 av[U];
-#pragma unroll
-  for (int u = 0; u < U; ++u) av[u] = NG * u + grp < n ? part(NG * u + grp) : float4{0.0f, 0.0f, 0.0f, 0.0f};
   float m0[CH], l0[CH];
+  auto request = [&](int b) __attribute__((always_inline)) {   // the 64 CH parts from b on, or a group's first U of them
 #pragma unroll
-  for (int k = 0; k < CH; ++k) {
-    m0[k] = 64 * k + lane < n ? pm[64 * k + lane] : -INFINITY;
-    l0[k] = 64 * k + lane < n ? pl[64 * k + lane] : 0.0f;
-  }
+    for (int u = 0; u < U; ++u) av[u] = b + NG * u + grp < n ? part(b + NG * u + grp) : float4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int k = 0; k < CH; ++k) {
+      m0[k] = b + 64 * k + lane < n ? pm[b + 64 * k + lane] : -INFINITY;
+      l0[k] = b + 64 * k + lane < n ? pl[b + 64 * k + lane] : 0.0f;
+    }
+  };
+  request(0);
 
   // the new token: lane i has channels 2 i and 2 i + 1 of q and k, thread i of the first 128 channel i of v
   uint32_t kb = 0;
@@ -537,12 +543,11 @@ __global__ __launch_bounds__(T) void merge_kernel(const MergeArgs a) {
 #pragma unroll 4
     for (int u = done; u < rounds; ++u) add(b + NG * u + grp < n ? part(b + NG * u + grp) : float4{0.0f, 0.0f, 0.0f, 0.0f}, weight(u));
   };
+  for (int b = 0; b < n; b += 64 * CH) {
+    if (b) request(b);
 #pragma unroll
-  for (int k = 0; k < CH; ++k)
-    if (64 * k < n) chunk(64 * k, m0[k], l0[k], k * R, U < R ? U : R);   // (workgroup-uniform)
-  for (int b = 64 * CH; b < n; b += 64) {
-    const int p = b + lane;
-    chunk(b, p < n ? pm[p] : -INFINITY, p < n ? pl[p] : 0.0f, 0, 0);
+    for (int k = 0; k < CH; ++k)
+      if (b + 64 * k < n) chunk(b + 64 * k, m0[k], l0[k], k * R, U < R ? U : R);   // (workgroup-uniform)
   }
   l = wave_sum(l);
   *(float4 *)(s_o[grp] + c4 * 4) = o;
@@ -608,9 +613,11 @@ hipError_t launch_attn(const FusedArgs &a, hipStream_t s, int *n_kernels, int *n
 hipError_t launch_merge(const MergeArgs &a, hipStream_t s) {
   if (a.rows <= 0) return hipSuccess;
   const dim3 grid = a.rows_per_seq > 0 ? dim3(a.rows_per_seq, a.rows / a.rows_per_seq) : dim3(a.rows);
-  if (a.n_parts <= 32) hipLaunchKernelGGL(merge_kernel<128>, grid, dim3(128), 0, s, a);
-  else if (a.n_parts <= 64) hipLaunchKernelGGL(merge_kernel<256>, grid, dim3(256), 0, s, a);
-  else hipLaunchKernelGGL(merge_kernel<1024>, grid, dim3(1024), 0, s, a);
+  switch (merge_threads(a.n_parts, a.rows)) {
+    case 128: hipLaunchKernelGGL(merge_kernel<128>, grid, dim3(128), 0, s, a); break;
+    case 256: hipLaunchKernelGGL(merge_kernel<256>, grid, dim3(256), 0, s, a); break;
+    default: hipLaunchKernelGGL(merge_kernel<1024>, grid, dim3(1024), 0, s, a); break;
+  }
   return hipGetLastError();
 }
 

@@ -291,6 +291,12 @@ struct MergeArgs {
 };
 // head / G = mul_high(head, magic_heads) as long as head G < 2^32; 0: by a division.
 inline uint32_t magic_heads(int32_t Hq, int32_t G) { return G > 1 && (int64_t)Hq * G < (1ll << 32) ? (uint32_t)(((1ll << 32) + G - 1) / G) : 0; }
+// Threads per row of the merge (merge_kernel); a launch holds fewer than 2^32 threads.
+inline int merge_threads(int32_t n_parts, int32_t rows) {
+  if (n_parts <= 32) return 128;
+  if (n_parts <= 64 || rows >= 1 << 22) return 256;
+  return n_parts < 192 && rows > 256 ? 256 : 1024;
+}
 hipError_t launch_merge(const MergeArgs &a, hipStream_t s);
 
 struct SelectArgs {

@@ -97,4 +97,14 @@ static int runs() {
   return 0;
 }
 
-int main() { return divisions() || heads() || runs(); }
+// the merge's threads per row: whole waves, and a launch of fewer than 2^32 threads as far as 256 of them allow
+static int merges() {
+  for (int parts : {0, 1, 32, 33, 64, 65, 191, 192, 256, 1 << 20})
+    for (int rows : {1, 256, 257, (1 << 22) - 1, 1 << 22, (1 << 24) - 1}) {
+      const int t = merge_threads(parts, rows);
+      if ((t != 128 && t != 256 && t != 1024) || (uint64_t)t * (uint64_t)rows >> 32) return fail("merge_threads", parts, rows, t);
+    }
+  return 0;
+}
+
+int main() { return divisions() || heads() || runs() || merges(); }
