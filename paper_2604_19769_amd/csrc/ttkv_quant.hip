@@ -697,25 +697,26 @@ __device__ __forceinline__ void convert_rows(const ConvArgs &a, int k_units, int
   u.hi = min(CHUNK, n_tokens - t0);
   u.t_lo = t0 + u.lo;
   const int dst_fmt = which ? dst.v_fmt : k_dst_fmt;
-  if (u.lo >= u.hi) {
-    if (PER > 1 && dst_fmt == TTKV_I4_ASYM_G64_T32) store_t32<UT>(u, nullptr);   // barriers beside a unit with rows
-    return;
-  }
-  tok = wrap(tok, dst);
-  const int r = div_bt(tok, dst.bt, dst.bt_magic);
-  u.row0 = tok - r * dst.bt;
-  u.head = block_head(dst, seq, dst_rec_base, r, h);
+  // A unit without rows leaves; beside another one whose values meet in LDS it takes part in the workgroup's barriers.
+  const bool live = u.lo < u.hi;
+  if (!live && (PER == 1 || dst_fmt != TTKV_I4_ASYM_G64_T32)) return;
   uint32_t *const s_t32 = (uint32_t *)(s_buf + side * kT32Bytes);
-  Raw raw[CHUNK * 16 / UT];
+  if (live) {
+    tok = wrap(tok, dst);
+    const int r = div_bt(tok, dst.bt, dst.bt_magic);
+    u.row0 = tok - r * dst.bt;
+    u.head = block_head(dst, seq, dst_rec_base, r, h);
+    Raw raw[CHUNK * 16 / UT];
 #define TTKV_ROW_UNIT(S, D) load_unit<S, UT, CHUNK>(src, u, raw), convert_unit<S, D, UT, CHUNK, false>(src, u, raw, nullptr, s_t32)
-  switch (dst_fmt) {
-    case TTKV_F16: TTKV_ROW_UNIT(TTKV_F16, TTKV_F16); break;
-    case TTKV_BF16: TTKV_ROW_UNIT(TTKV_BF16, TTKV_BF16); break;
-    case TTKV_I8_SYM_G32: TTKV_FOR_SOURCES(TTKV_I8_SYM_G32, TTKV_ROW_UNIT) break;
-    case TTKV_I4_ASYM_G64_T32: TTKV_FOR_SOURCES(TTKV_I4_ASYM_G64_T32, TTKV_ROW_UNIT) break;
-    default: TTKV_FOR_SOURCES(TTKV_I4_ASYM_G64, TTKV_ROW_UNIT) break;
-  }
+    switch (dst_fmt) {
+      case TTKV_F16: TTKV_ROW_UNIT(TTKV_F16, TTKV_F16); break;
+      case TTKV_BF16: TTKV_ROW_UNIT(TTKV_BF16, TTKV_BF16); break;
+      case TTKV_I8_SYM_G32: TTKV_FOR_SOURCES(TTKV_I8_SYM_G32, TTKV_ROW_UNIT) break;
+      case TTKV_I4_ASYM_G64_T32: TTKV_FOR_SOURCES(TTKV_I4_ASYM_G64_T32, TTKV_ROW_UNIT) break;
+      default: TTKV_FOR_SOURCES(TTKV_I4_ASYM_G64, TTKV_ROW_UNIT) break;
+    }
 #undef TTKV_ROW_UNIT
+  }
   if (dst_fmt == TTKV_I4_ASYM_G64_T32) store_t32<UT>(u, s_t32);
 }
 template <bool SUM, bool STREAM, int THREADS>
