@@ -151,6 +151,14 @@ __device__ __forceinline__ void touch_arguments(const FusedArgs &a) {
                "s"(a.tv[0].bt), "s"(a.tv[1].bt), "s"(a.tv[2].bt), "s"(a.tv[3].bt), "s"(a.e[0].len), "s"(a.e[5].len),
                "s"(a.e[10].len), "s"(a.chunk[0]), "s"(a.q_fmt));
 }
+// The first workgroup of a run of selected blocks also stores their ids and number to the caller's pinned memory: the
+// stores cross PCIe while the launch streams (two copies behind it took 2-3 us of the stream; stored by the ranking kernel,
+// whose end waits for them, as much).
+__device__ __forceinline__ void report_selected(const FusedArgs &a, const TierView &tv, const RunView &en, int seq, bool equal_items) {
+  const int n = equal_items ? en.len / tv.bt : en.len;
+  for (int i = threadIdx.x; i < n; i += blockDim.x) a.host_ids[seq * a.sel_stride + i] = a.sel_ids[seq * a.sel_stride + i];
+  if (threadIdx.x == 0) a.host_count[seq] = n;
+}
 // A run whose blocks are named by the device-side selection (ids ascending, so only the last can be the tier's
 // partly filled newest block).  Two forms, told apart by the tier's item size in the launch arguments:
 //   fixed items (host tiers): item `chunk` of the run is sub-chunk chunk % ipb of the run's (chunk / ipb)-th
@@ -159,14 +167,6 @@ __device__ __forceinline__ void touch_arguments(const FusedArgs &a) {
 //     run; token i of it lies in block ids[i / bt], which the tile address look-up follows (`sel`), so an item may
 //     span several blocks and small blocks cost no more than large ones.
 // Either way everything after this sees an ordinary run.  Returns the run's id list for the second form.
-// The run's first workgroup also stores the ids and their number to the caller's pinned memory: the stores cross PCIe while
-// the launch streams (two copies behind it took 2-3 us of the stream; stored by the ranking kernel, whose end waits for them,
-// as much).
-__device__ __forceinline__ void report_selected(const FusedArgs &a, const TierView &tv, const RunView &en, int seq, bool equal_items) {
-  const int n = equal_items ? en.len / tv.bt : en.len;
-  for (int i = threadIdx.x; i < n; i += blockDim.x) a.host_ids[seq * a.sel_stride + i] = a.sel_ids[seq * a.sel_stride + i];
-  if (threadIdx.x == 0) a.host_count[seq] = n;
-}
 __device__ __forceinline__ const int32_t *resolve_selected(const FusedArgs &a, const TierView &tv, RunView &en, int seq,
                                                            bool equal_items, int chunk_tokens, int &chunk) {
   if (!(en.flags & kEntrySelected)) return nullptr;
