@@ -85,7 +85,9 @@ class TieredCache:
         self.copy_stream = torch.cuda.Stream(device=self.device)
         self.ws = None
         self.ws_parts = 0
-        # parts per row of a launch of up to 256 workgroups, the most that the library cuts into items of 128 tokens
+        # Parts per row of a launch of up to 256 workgroups, the most that the library cuts into items of 128 tokens where the
+        # workspace holds their partials.  Every workspace does: one token more than such a launch takes, or all blocks
+        # where only some are selected, counts fewer parts.
         self._few_parts = max(0, 256 // max(1, n_kv_heads * -(-n_q_heads // (16 * n_kv_heads))) - (batch - 1))
         self.demote_ws = None
         self._demote_need = None          # bytes of staging that evictions into a host tier want (constant for a cache)
@@ -149,24 +151,12 @@ class TieredCache:
 
     def _workspace(self, parts):
         if self.ws is None or parts > self.ws_parts or self.ws_slots != self.n_slots:
-            parts = max(parts + 16, int(parts * 1.25))
+            parts = max(parts + 16, int(parts * 1.25), self._few_parts)
             need = B.ttkv_workspace_bytes(self.c, parts, self.n_slots)
             assert need > 0
             self.ws = torch.empty(need, dtype=torch.uint8, device=self.device)
             self.ws_parts, self.ws_slots = parts, self.n_slots
         return self.ws
-
-    def _count_parts(self, appends, sb=None, sc=None, stride=0, n_slots=0):
-        """Parts per row of a call that attends the cache as it is or, where it appends a token, with that token counted
-        or not (the library does either), -1 if either is refused: a longer cache may have fewer parts.  The lengths as
-        they are come last, so that the step plans from what the library remembers of them."""
-        parts = 0
-        if appends:
-            self.len[0] += 1
-            parts = B.ttkv_count_parts(self.h, self.c, sb, sc, stride, n_slots)
-            self.len[0] -= 1
-        now = B.ttkv_count_parts(self.h, self.c, sb, sc, stride, n_slots)
-        return max(parts, now) if min(parts, now) >= 0 else -1
 
     def decode(self, q, selected=None, overlap=True, new=None):
         """q [B][Hq][128] f16/bf16 on the device.  selected: None or (sel_blocks, sel_count) pinned int32 tensors.
@@ -186,7 +176,11 @@ class TieredCache:
             self._parts_age += 1
             ws = self.ws
         else:
-            parts = self._count_parts(new is not None, sb, sc, stride, self.n_slots)
+            if new is not None:
+                self.len[0] += 1            # size the workspace for the lengths the attention may see
+            parts = B.ttkv_count_parts(self.h, self.c, sb, sc, stride, self.n_slots)
+            if new is not None:
+                self.len[0] -= 1
             if parts < 0:
                 raise B.TTKVError(B.ERR_INVALID_ARG, "ttkv_count_parts")
             ws = self._workspace(max(parts, 1))
@@ -233,11 +227,13 @@ class TieredCache:
         stride = self._select_buffers(k)
         # The split of a selection is planned inside the call, which refuses a workspace that is too small for it before
         # anything is enqueued: the workspace is sized once from a dense plan's parts and grows when it is refused (no
-        # run is cut finer than into items of 128 tokens, which bounds it).  Items of 128 tokens are taken only where the
-        # workspace holds their partials, so there is room for them from the first call on.
+        # run is cut finer than into items of 128 tokens, which bounds it).
         self._parts_age = None
-        if self.ws is None or self.ws_slots != self.n_slots or self.ws_parts < self._few_parts:
-            self._workspace(max(self._count_parts(True), self._few_parts, 1))
+        if self.ws is None or self.ws_slots != self.n_slots:
+            self.len[0] += 1
+            parts = B.ttkv_count_parts(self.h, self.c, None, None, 0, 0)
+            self.len[0] -= 1
+            self._workspace(max(parts, 1))
         while True:
             try:
                 B.ttkv_decode_step_topk(self.h, self.c, q, q_fmt, k_new, v_new, fmt, self.out, self.lse, k, self.sel_blocks,

@@ -63,7 +63,7 @@ def test_the_same_result_in_a_workspace_for_the_longer_cache():
 
 
 def test_a_selection_of_few_blocks_keeps_short_items():
-    """A workspace sized by a dense step of 256-token items grows for a selection that takes 128-token ones."""
+    """A workspace made for a dense step of 256-token items holds the 128-token ones of a selection."""
     c = zeros_cache(1, 8, 2, [F + (300,), I8 + (65536,)], True)
     try:
         z = torch.zeros(1, 2, 1, 128, dtype=torch.float16, device="cuda:0")
