@@ -5,6 +5,7 @@ import pytest
 import torch
 
 from paper_2604_19769_amd import binding as B
+from test_gpu_workspaces import zeros_cache
 
 pytestmark = pytest.mark.gpu
 
@@ -39,3 +40,32 @@ def test_rows_of_unequal_parts_against_float64(n_parts, rows):
     got = lse.cpu().numpy()
     assert np.all(np.isneginf(got[cnt == 0]))
     assert np.max(np.abs(got[cnt > 0] - np.log(den[cnt > 0]))) <= 1e-5
+
+
+def test_a_token_joins_many_parts_of_many_rows():
+    """320 rows of 79 parts take 256 threads each: the same step as with 16 parts a row, up to the rounding of
+    sums of 20000 terms in fp32 (the weights are exact to 22 bits), and the same row stored."""
+    c = zeros_cache(8, 40, 2, [("f16", "f16", 128, 20000)], False)
+    try:
+        g = torch.Generator(device="cuda:0").manual_seed(21)
+        c.len[0][:] = 0
+        k, v = (torch.randn(8, 2, 20000, 128, generator=g, device="cuda:0").half() for _ in range(2))
+        c.append(0, k, v)
+        q = torch.randn(8, 40, 128, generator=g, device="cuda:0").half()
+        kn, vn = (torch.randn(8, 2, 1, 128, generator=g, device="cuda:0").half() for _ in range(2))
+        B.ttkv_set_split(c.h, 256)
+        ref, ref_lse = (x.clone() for x in c.decode(q, new=(kn, vn)))
+        row = c.dump_tier(0, 5)
+        assert B.ttkv_count_parts(c.h, c.c) <= 32          # 128 threads a row
+        c.len[0] -= 1
+        B.ttkv_set_split(c.h, 1 << 16)
+        assert B.ttkv_count_parts(c.h, c.c) == 79
+        c._parts_age = None
+        out, lse = c.decode(q, new=(kn, vn))
+        torch.cuda.synchronize()
+        assert float((out - ref).abs().max()) <= 1e-5 * float(ref.abs().max())
+        assert torch.allclose(lse, ref_lse, atol=1e-5)
+        again = c.dump_tier(0, 5)
+        assert np.array_equal(row["k"], again["k"]) and np.array_equal(row["v"], again["v"])
+    finally:
+        c.close()
