@@ -310,7 +310,7 @@ def plan_cache(batch, Hq, Hkv, tiers):
 def test_split_plan_equal_items_and_whole_rounds():
     """The split-K plan (how Alg. 1's sum over blocks is cut; host arithmetic only): one long run per tier and
     sequence keeps the kernel's default number of workgroups; many short runs get finer, equal items instead of one
-    unequal item per run; a forced target is taken as given; no item is shorter than 256 or longer than 8192 tokens."""
+    unequal item per run; a forced target is taken as given; items of launches that fill the chip have 256 to 8192 tokens."""
     h = B.ttkv_create()
     try:
         # batch 4, 32 q / 8 kv heads, 256-token window + one long int8 tier: one round of 768 workgroups = 24 items per run
