@@ -6,10 +6,10 @@
 // Work unit of the row kernel: up to 64 consecutive rows of ONE destination block, one KV head, K or V.  A 16-lane
 // group converts one row at a time (8 channels per lane).  Block and record look-ups happen once per unit on the scalar
 // unit, without a division (entry and KV head are the grid's, ring blocks come by a multiplication: a unit of 64 rows is
-// short, and its look-ups took 1.5 of its 3 us; 2 x 32 heads x 8192 tokens into fp16 + int4 74.3 -> 71.8 us, 8 x 32768 into
-// bf16 + K int8 / V int4 channel-major 41.9 -> 40.6, three tiers deep with sums 163.3 -> 160.6); source and destination
-// formats are compile-time inside the unit; all of a unit's loads are in flight before the first conversion.  Where keys also feed block summaries a unit is a
-// whole destination block (see sum_rows).  Bound: memory for the plain copies (5.3 TB/s of read + write), fp16 -> int8
+// short, and its look-ups took 1.5 of its 3 us; 2 x 32 heads x 8192 tokens into fp16 + int4 75.6 -> 73.2 us, 8 x 32768 into
+// bf16 + K int8 / V int4 channel-major 43.3 -> 42.1, three tiers deep with sums 162.0 -> 158.7); source and destination
+// formats are compile-time inside the unit; all of a unit's loads are in flight before the first conversion.  Where keys
+// also feed block summaries a unit is a whole destination block (see sum_rows).  Bound: memory for the plain copies (5.3 TB/s of read + write), fp16 -> int8
 // (5.2) and fp16 -> int4 (4.8; a copy of 2 GiB reaches 4.9); a second recipe in front (int4 through int8) issues 139
 // vector instructions per four rows, as long as their bytes take: 88 us for 430 MB (4.9 TB/s; 103 with 176 instructions),
 // with key sums about 100 (153).  The one generic body before -- a 64-bit address and a division by the block
